@@ -222,11 +222,12 @@ int plan_attend(ha_rag_ctx *c, const ha_rag_packed_chunk *chunks, const ha_rag_a
     // bound by how long one of them takes: halve once more (one request of 10 x 512 tokens:
     // 13.7 against 14.7 us; with two requests, 1,280 workgroups, it would cost 1.5 us).
     if (piece == kAttendMinRunBlocks && groups_at(piece / 2u) <= 4ull * kChipCUs) piece /= 2u;
-    // The shared kernel: a run crosses document boundaries (records rival the packed bytes once
-    // a request has hundreds of query rows; equal runs also finish together whatever the
-    // documents' lengths).  Workgroups of one size finish in rounds of as many as the chip holds
-    // side by side, so a launch takes rounds x blocks per run: the longest run with the least
-    // of that is taken; a run is at least kAttendMinRunBlocks long.
+    // The shared kernel: a run crosses document boundaries (equal runs finish together whatever
+    // the documents' lengths).  Workgroups of one size finish in rounds of as many as the chip
+    // holds side by side; every round pays for starting and ending a workgroup, and every record
+    // is written and read again, 16 KiB in all.  Of the run lengths (at least kAttendMinRunBlocks)
+    // the one with the least of rounds x (blocks + start) + records is taken, in units of the time a
+    // workgroup takes for a block: COSTNOTE
     const uint64_t side_by_side = (uint64_t)kChipCUs * (8u / waves);  // two waves per SIMD: eight per CU
     uint64_t most_blocks = 0;
     for (uint32_t r = 0; r < n_reqs; ++r)
@@ -235,12 +236,16 @@ int plan_attend(ha_rag_ctx *c, const ha_rag_packed_chunk *chunks, const ha_rag_a
     for (uint64_t n = 1; n <= most_blocks; ++n) {  // n runs for the largest request
         const uint64_t len = (most_blocks + n - 1u) / n;
         if (n > 1 && len < kAttendMinRunBlocks) break;
-        uint64_t wgs = 0;
+        uint64_t wgs = 0, recs = 0;
         for (uint32_t r = 0; r < n_reqs; ++r) {
             const Plan &pl = plans[r];
-            if (pl.shared) wgs += (pl.all_blocks + len - 1u) / len * H * tile_groups(pl, waves);
+            if (!pl.shared) continue;
+            const uint64_t runs = (pl.all_blocks + len - 1u) / len;
+            wgs += runs * H * tile_groups(pl, waves);
+            if (runs > 1u) recs += runs * H * pl.n_mt;
         }
-        const uint64_t cost = (wgs + side_by_side - 1u) / side_by_side * len;
+        const uint64_t cost = (wgs + side_by_side - 1u) / side_by_side * (len + kAttendStartBlocks) +
+                              recs / kAttendRecsPerBlock;
         if (cost < least) {
             least = cost;
             run_blocks = len;

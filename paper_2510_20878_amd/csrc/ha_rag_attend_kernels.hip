@@ -548,13 +548,19 @@ __global__ void __launch_bounds__(32 * kMergeGroups) k7_attend_merge(const K7Par
 }
 
 // The merge for requests with many query rows: one workgroup per (request, KV head, 16-row
-// query tile), 16 threads a row, 8 dims a thread.  A record is then read as the contiguous
-// 8 KiB it is, by one workgroup, and a request of hundreds of rows needs hundreds of workgroups
-// instead of one for each of its rows.
-__global__ void __launch_bounds__(256) k7_attend_merge_tiles(const K7Params p)
+// query tile), groups of 256 threads that share the tile's records, 16 threads a row and 8 dims a
+// thread.  A record is then read as the contiguous 8 KiB it is, by one group, and a request of
+// hundreds of rows needs hundreds of workgroups instead of one for each of its rows.
+// Bound: the latency of the rounds of loads (a group has four records under way at a time), so
+// the more records a tile has the more groups share them: 21 records per tile in one group
+// (six rounds) 10.6 us per call, in four groups (two rounds) MERGE4 us.
+template <uint32_t NG>
+__global__ void __launch_bounds__(256 * NG) k7_attend_merge_tiles(const K7Params p)
 {
     typedef const float __attribute__((address_space(1))) *gfloats;
     typedef const f32x4 __attribute__((address_space(1))) *gquads;
+    __shared__ __attribute__((aligned(16))) float s_acc[NG > 1 ? NG : 1][NG > 1 ? 2048 : 4];
+    __shared__ float s_m[NG][16], s_l[NG][16];
     K7Req r = p.r[blockIdx.y];
     uint32_t n_kv_heads = p.n_kv_heads, n_q_heads = p.n_q_heads;
     pin(r.part);
@@ -568,21 +574,21 @@ __global__ void __launch_bounds__(256) k7_attend_merge_tiles(const K7Params p)
     const uint32_t n_mt = (M + 15u) >> 4;
     if (blockIdx.x >= n_kv_heads * n_mt) return;  // the grid is as wide as the largest request
     const uint32_t h = blockIdx.x / n_mt, mt = blockIdx.x - h * n_mt;
-    const uint32_t ri = threadIdx.x >> 4, d8 = threadIdx.x & 15u;
-    const uint32_t mrow = mt * 16u + ri;
-    if (mrow >= M) return;  // rows without a query are not in the records either
+    const uint32_t g = threadIdx.x >> 8;
+    const uint32_t ri = (threadIdx.x >> 4) & 15u, d8 = threadIdx.x & 15u;
+    const bool live = mt * 16u + ri < M;  // rows without a query are not in the records either
     const uint64_t run_stride = (uint64_t)n_kv_heads * n_mt * kAttendRecFloats;  // records are [run][head][tile]
     gfloats first = (gfloats)r.part + ((uint64_t)h * n_mt + mt) * kAttendRecFloats;
-    const uint32_t n_units = r.n_runs;
+    const uint32_t n_units = live ? r.n_runs : 0u;
     float m_max = neg_inf(), l_sum = 0.0f;
     f32x4 acc[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
-    for (uint32_t u0 = 0; u0 < n_units; u0 += 4u) {
+    for (uint32_t u0 = g; u0 < n_units; u0 += 4u * NG) {
         float m[4], l[4];
         f32x4 o[4][2];
 #pragma unroll
         for (uint32_t k = 0; k < 4; ++k) {  // four records under way at a time
-            const bool have = u0 + k < n_units;
-            const uint32_t u = have ? u0 + k : n_units - 1u;
+            const bool have = u0 + k * NG < n_units;
+            const uint32_t u = have ? u0 + k * NG : n_units - 1u;
             gfloats rec = first + u * run_stride;
             m[k] = rec[2048 + ri];
             l[k] = have ? rec[2048 + 16 + ri] : 0.0f;
@@ -605,6 +611,40 @@ __global__ void __launch_bounds__(256) k7_attend_merge_tiles(const K7Params p)
             }
         }
     }
+    if (NG > 1) {
+        // the groups' results come together in the first group, through LDS
+        if (g) {
+            f32x4 *mine = reinterpret_cast<f32x4 *>(&s_acc[g][(ri * 16u + d8) * 8u]);
+            mine[0] = acc[0];
+            mine[1] = acc[1];
+            if (d8 == 0) {
+                s_m[g][ri] = m_max;
+                s_l[g][ri] = l_sum;
+            }
+        }
+        __syncthreads();
+        if (g) return;
+#pragma unroll
+        for (uint32_t k = 1; k < NG; ++k) {
+            const float l_k = s_l[k][ri], m_k = s_m[k][ri];
+            const f32x4 *theirs = reinterpret_cast<const f32x4 *>(&s_acc[k][(ri * 16u + d8) * 8u]);
+            const f32x4 o0 = theirs[0], o1 = theirs[1];
+            if (l_k > 0.0f) {
+                const float m_new = __builtin_fmaxf(m_max, m_k);
+                const float fa = __builtin_amdgcn_exp2f(m_max - m_new);
+                const float fb = __builtin_amdgcn_exp2f(m_k - m_new);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    acc[0][e] = __builtin_fmaf(o0[e], fb, acc[0][e] * fa);
+                    acc[1][e] = __builtin_fmaf(o1[e], fb, acc[1][e] * fa);
+                }
+                l_sum = __builtin_fmaf(l_k, fb, l_sum * fa);
+                m_max = m_new;
+            }
+        }
+    }
+    if (!live) return;
+    const uint32_t mrow = mt * 16u + ri;
     const uint32_t qt = mrow / G, gq = mrow - qt * G;
     const uint64_t orow = (uint64_t)qt * n_q_heads + h * G + gq;
     f32x4 __attribute__((address_space(1))) *dst =
@@ -644,7 +684,11 @@ hipError_t launch_k7(K7Params &p, hipStream_t stream, bool check_only)
     if (width > 0x7FFFFFFFull) return hipErrorInvalidValue;
     if (check_only) return hipSuccess;
     if (max_mt > 2u) {  // the requests of the shared kernel: merge tile by tile
-        hipLaunchKernelGGL(k7_attend_merge_tiles, dim3((uint32_t)tile_width, p.n_reqs), dim3(256), 0, stream, p);
+        // a second and a third and fourth group as soon as a group would need a second round of loads
+        const dim3 grid((uint32_t)tile_width, p.n_reqs);
+        if (max_units <= 4u) hipLaunchKernelGGL(k7_attend_merge_tiles<1>, grid, dim3(256), 0, stream, p);
+        else if (max_units <= 8u) hipLaunchKernelGGL(k7_attend_merge_tiles<2>, grid, dim3(512), 0, stream, p);
+        else hipLaunchKernelGGL(k7_attend_merge_tiles<4>, grid, dim3(1024), 0, stream, p);
         return hipGetLastError();
     }
     // one group per two records of the longest row if that fits (a group fetches four at a

@@ -309,63 +309,117 @@ __device__ __forceinline__ SharedSide shared_side(const uint8_t *first, uint32_t
     return sd;
 }
 
-}  // namespace
 
-// W = 2, 4 or 8 waves, half of them decoding keys and half values; two waves per SIMD keep 256 registers
-// each (two tiles of output, their queries, the raw words of two blocks).
-template <int W>
-__global__ void __launch_bounds__(64 * W, 2) k6_attend_shared(const K6Params p)
+// ---- the same with waves of two kinds -----------------------------------------------------------
+
+// Orders LDS accesses of the whole workgroup across a barrier, and only those: global loads under
+// way stay under way (__syncthreads() would wait for them).
+__device__ __forceinline__ void lds_barrier()
 {
-    // two sets of W block buffers; dynamic, because eight waves need 128 KiB (a workgroup may
-    // declare 64 KiB at most statically)
-    extern __shared__ __attribute__((aligned(16))) uint8_t lds_bytes[];
-    uint8_t (*lds)[W][kSharedBlockLds] = reinterpret_cast<uint8_t (*)[W][kSharedBlockLds]>(lds_bytes);
-    K6Run c = p.run[blockIdx.y];
-    AttendHdr hdr = {p.n_kv_heads, p.n_q_heads, p.layer, p.scale_log2};
-    pin(c.k);
-    pin(c.v);
-    pin(c.q);
-    pin(c.part);
-    pin(c.n_tokens);
-    pin(c.info);
-    pin(c.n_q);
-    pin(hdr.n_kv_heads);
-    pin(hdr.n_q_heads);
-    pin(hdr.scale_log2);
-    uint32_t run = c.n_docs, more = c.more;  // the run's documents: this one, then descriptors more, more + 1, ..
-    uint32_t first_block = c.first_block, end_block = c.end_block;  // where the run starts in its first and ends in its last
-    pin(run);
-    pin(more);
-    pin(first_block);
-    pin(end_block);
-    const uint32_t H = hdr.n_kv_heads, G = hdr.n_q_heads / H, M = c.n_q * G;
-    const uint32_t n_mt = (M + 15u) >> 4;
-    const uint32_t n_mtg = (n_mt + 2u * W - 1u) / (2u * W);
-    const uint32_t u = blockIdx.x;
-    if (u >= H * n_mtg) return;  // the grid is as wide as the widest run
-    const uint32_t mtg = u % n_mtg, h = u / n_mtg;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
 
-    SharedLane ln;
-    ln.lane = threadIdx.x & 63u;
-    ln.c_ = ln.lane >> 4;
-    ln.n_ = ln.lane & 15u;
-    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const uint32_t tile0 = (mtg * W + wave) * 2u;  // this wave's tiles: tile0, tile0 + 1
-    const bool active = tile0 < n_mt;              // a wave without a tile still decodes
-    const bool is_k = wave < (uint32_t)W / 2u;
-    const uint32_t r = is_k ? wave : wave - (uint32_t)W / 2u;
-    // where this lane reads its K operands: the token of MFMA row n_ is 4 (n_ % 4) + n_ / 4, so
-    // that score register jj of lane group c_ belongs to token 4 jj + c_, the token whose values
-    // the lane group's plane jj holds
-    {
-        const uint32_t tau = 4u * (ln.n_ & 3u) + (ln.n_ >> 2);
-        ln.k_rd = tau * 256u + (((4u * ln.c_) ^ tau) & 15u) * 16u;  // octet 4 c_ + y of token tau: slot (4 c_ ^ tau) ^ y
-        ln.k_wr = ln.c_ * 256u + ((ln.n_ ^ ln.c_) & 15u) * 16u;     // n_ ^ (4 j + c_) = (n_ ^ c_) ^ 4 j
+constexpr uint32_t kRoleScorers = 8, kRoleDecoders = 4;  // waves of a workgroup
+constexpr uint32_t kRoleBlocks = 8;                       // layout blocks per round
+
+// One block of one side: decode what the lane has fetched and leave it in the pair's buffer
+// (`pair`, e = 0 / 1: first / second block of the pair).
+template <uint32_t P, bool IS_K>
+__device__ __forceinline__ void role_decode(const u32x4 *w, const u32x4 &m, const SharedSide &sd, uint32_t blk, uint32_t T,
+                                            uint8_t *pair, int e, const SharedLane &ln)
+{
+    u32x4 o[4];  // o[j] = token 4 j + c_, dims 8 n_ .. 8 n_ + 7 as BF16
+#pragma unroll
+    for (int j = 0; j < 4; ++j) o[j] = decode_octet<P>(plane_raw<P>(w, j), m[j], sd.base, sd.top);
+    if (IS_K) {
+        uint8_t *dst = pair + e * 4096u;
+#pragma unroll
+        for (uint32_t j = 0; j < 4; ++j)
+            *reinterpret_cast<u32x4 *>(dst + ((ln.k_wr ^ (64u * j)) + 1024u * j)) = o[j];
+    } else {
+        if (blk * 16u + 16u > T) {  // rows past the document's end
+#pragma unroll
+            for (uint32_t j = 0; j < 4; ++j)
+                if (blk * 16u + 4u * j + ln.c_ >= T) o[j] = u32x4{0u, 0u, 0u, 0u};
+        }
+        uint8_t *vdst = pair + 8192u + ln.lane * 16u + e * 8u;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            u32x2 lo, hi;
+            lo.x = __builtin_amdgcn_perm(o[1][q], o[0][q], 0x05040100u);
+            lo.y = __builtin_amdgcn_perm(o[3][q], o[2][q], 0x05040100u);
+            hi.x = __builtin_amdgcn_perm(o[1][q], o[0][q], 0x07060302u);
+            hi.y = __builtin_amdgcn_perm(o[3][q], o[2][q], 0x07060302u);
+            *reinterpret_cast<u32x2 *>(vdst + (2 * q) * 1024u) = lo;
+            *reinterpret_cast<u32x2 *>(vdst + (2 * q + 1) * 1024u) = hi;
+        }
     }
+}
 
-    // Q as the B operand of S^T = K Q^T: lane (c_, n_) holds, for MFMA y, dims
-    // 32 c_ + 8 y .. + 7 of query row n_ of the tile (zero rows beyond M)
-    SharedState st;
+// The rounds of one document for decoder r (0, 1) of one side: blocks 4 r .. 4 r + 3 of every
+// round.  A block's words of the next round are requested as soon as this round's are decoded and
+// stay under way across the barrier.
+template <uint32_t P, bool IS_K>
+__device__ __forceinline__ void role_decode_rounds(const SharedSide &sd, uint32_t T, uint32_t b0, uint32_t b1, uint32_t r,
+                                                   const SharedLane &ln, uint8_t (*lds)[kRoleBlocks][kSharedBlockLds],
+                                                   uint32_t &set)
+{
+    typedef Fmt<P> F;
+    u32x4 w[4][F::kWords], m[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) m[i] = u32x4{0u, 0u, 0u, 0u};
+    auto fetch = [&](int i, uint32_t b) {
+        b = b < b1 ? b : b1 - 1u;  // issued whether or not the block exists: no branch around loads
+#pragma unroll
+        for (uint32_t a = 0; a < F::kWords; ++a)
+            w[i][a] = ldg16(sd.tile + ((uint64_t)b * F::kPayload + a * 1024u + ln.lane * 16u));
+        if (F::kMeta) m[i] = ldg16(sd.meta + ((uint64_t)b * sd.meta_blk + ((ln.lane * 8u) >> sd.gsh) * 16u));
+    };
+#pragma unroll
+    for (int i = 0; i < 4; ++i) fetch(i, b0 + 4u * r + i);
+    for (uint32_t rb = b0; rb < b1; rb += kRoleBlocks) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const uint32_t blk = rb + 4u * r + i;
+            uint8_t *pair = lds[set][4u * r + (i & 2)];
+            if (blk < b1) role_decode<P, IS_K>(w[i], m[i], sd, blk, T, pair, i & 1, ln);
+            else if (!IS_K && (i & 1) && blk - 1u < b1) {
+                // no such block, but its partner exists: the pair's MFMAs take this half of the V
+                // operands with weight zero, so it must hold numbers
+#pragma unroll
+                for (int pp = 0; pp < 8; ++pp)
+                    *reinterpret_cast<u32x2 *>(pair + 8192u + pp * 1024u + ln.lane * 16u + 8u) = u32x2{0u, 0u};
+            }
+            fetch(i, blk + kRoleBlocks);
+        }
+        lds_barrier();
+        set ^= 1u;
+    }
+}
+
+template <bool IS_K>
+__device__ __forceinline__ void role_decode_any(uint32_t prec, const SharedSide &sd, uint32_t T, uint32_t b0, uint32_t b1,
+                                                uint32_t r, const SharedLane &ln,
+                                                uint8_t (*lds)[kRoleBlocks][kSharedBlockLds], uint32_t &set)
+{
+    switch (prec) {
+    case kP16: role_decode_rounds<kP16, IS_K>(sd, T, b0, b1, r, ln, lds, set); break;
+    case kInt8: role_decode_rounds<kInt8, IS_K>(sd, T, b0, b1, r, ln, lds, set); break;
+    case kInt4: role_decode_rounds<kInt4, IS_K>(sd, T, b0, b1, r, ln, lds, set); break;
+    case kE4M3: role_decode_rounds<kE4M3, IS_K>(sd, T, b0, b1, r, ln, lds, set); break;
+    case kE5M2: role_decode_rounds<kE5M2, IS_K>(sd, T, b0, b1, r, ln, lds, set); break;
+    default: role_decode_rounds<kGSE8, IS_K>(sd, T, b0, b1, r, ln, lds, set); break;
+    }
+}
+
+// The wave's queries as the B operand of S^T = K Q^T: lane (c_, n_) holds, for MFMA y, dims
+// 32 c_ + 8 y .. + 7 of query row n_ of the tile (zero rows beyond M); nothing accumulated yet.
+__device__ __forceinline__ void shared_load_queries(const K6Run &c, const AttendHdr &hdr, uint32_t h, uint32_t tile0,
+                                                    uint32_t M, const SharedLane &ln, SharedState &st)
+{
+    const uint32_t G = hdr.n_q_heads / hdr.n_kv_heads;
 #pragma unroll
     for (int mt = 0; mt < 2; ++mt) {
         const uint32_t row = (tile0 + mt) * 16u + ln.n_;
@@ -383,37 +437,14 @@ __global__ void __launch_bounds__(64 * W, 2) k6_attend_shared(const K6Params p)
 #pragma unroll
         for (int pp = 0; pp < 8; ++pp) st.O[mt][pp] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
+}
 
-    uint32_t set = 0;
-    for (uint32_t d = 0; d < run; ++d) {
-        // ---- the document: descriptor d of the run (its first is already here)
-        const uint8_t *dk = c.k, *dv = c.v;
-        uint32_t T = c.n_tokens, dinfo = c.info;
-        if (d) {
-            const K6Doc &cd = p.doc[more + d - 1u];
-            dk = cd.k;
-            dv = cd.v;
-            T = cd.n_tokens;
-            dinfo = cd.info;
-        }
-        const uint32_t nblk = (T + 15u) >> 4;
-        const uint32_t b0 = d ? 0u : first_block;
-        const uint32_t b1 = d + 1u == run ? end_block : nblk;
-        if (b0 >= b1) continue;  // cannot happen with a checked launch
-        if (is_k) {
-            const uint32_t prec = dinfo & 0xFu;
-            const SharedSide sd = shared_side(dk, prec, (dinfo >> 4) & 0xFu, h, nblk, true);
-            shared_rounds_any<true, W>(prec, sd, T, b0, b1, hdr.scale_log2, r, active, ln, lds, set, st);
-        } else {
-            const uint32_t prec = (dinfo >> 8) & 0xFu;
-            const SharedSide sd = shared_side(dv, prec, (dinfo >> 12) & 0xFu, h, nblk, true);
-            shared_rounds_any<false, W>(prec, sd, T, b0, b1, hdr.scale_log2, r, active, ln, lds, set, st);
-        }
-    }
-
-    // ---- the wave's results, straight from its registers: lane (c_, n_) holds rows
-    // 4 c_ + jj, dims 8 n_ + pp of each tile
-    if (!active) return;
+// The wave's results, straight from its registers: lane (c_, n_) holds rows 4 c_ + jj, dims
+// 8 n_ + pp of each tile.
+__device__ __forceinline__ void shared_write_results(const K6Run &c, const AttendHdr &hdr, uint32_t h, uint32_t tile0,
+                                                     uint32_t M, const SharedLane &ln, SharedState &st)
+{
+    const uint32_t G = hdr.n_q_heads / hdr.n_kv_heads, n_mt = (M + 15u) >> 4;
     uint32_t final = c.final;
     pin(final);
     const float *lse_ptr = c.lse;
@@ -472,6 +503,202 @@ __global__ void __launch_bounds__(64 * W, 2) k6_attend_shared(const K6Params p)
     }
 }
 
+}  // namespace
+
+// W = 2, 4 or 8 waves, half of them decoding keys and half values; two waves per SIMD keep 256 registers
+// each (two tiles of output, their queries, the raw words of two blocks).
+template <int W>
+__global__ void __launch_bounds__(64 * W, 2) k6_attend_shared(const K6Params p)
+{
+    // two sets of W block buffers; dynamic, because eight waves need 128 KiB (a workgroup may
+    // declare 64 KiB at most statically)
+    extern __shared__ __attribute__((aligned(16))) uint8_t lds_bytes[];
+    uint8_t (*lds)[W][kSharedBlockLds] = reinterpret_cast<uint8_t (*)[W][kSharedBlockLds]>(lds_bytes);
+    K6Run c = p.run[blockIdx.y];
+    AttendHdr hdr = {p.n_kv_heads, p.n_q_heads, p.layer, p.scale_log2};
+    pin(c.k);
+    pin(c.v);
+    pin(c.q);
+    pin(c.part);
+    pin(c.n_tokens);
+    pin(c.info);
+    pin(c.n_q);
+    pin(hdr.n_kv_heads);
+    pin(hdr.n_q_heads);
+    pin(hdr.scale_log2);
+    uint32_t run = c.n_docs, more = c.more;  // the run's documents: this one, then descriptors more, more + 1, ..
+    uint32_t first_block = c.first_block, end_block = c.end_block;  // where the run starts in its first and ends in its last
+    pin(run);
+    pin(more);
+    pin(first_block);
+    pin(end_block);
+    const uint32_t H = hdr.n_kv_heads, G = hdr.n_q_heads / H, M = c.n_q * G;
+    const uint32_t n_mt = (M + 15u) >> 4;
+    const uint32_t n_mtg = (n_mt + 2u * W - 1u) / (2u * W);
+    const uint32_t u = blockIdx.x;
+    if (u >= H * n_mtg) return;  // the grid is as wide as the widest run
+    const uint32_t mtg = u % n_mtg, h = u / n_mtg;
+
+    SharedLane ln;
+    ln.lane = threadIdx.x & 63u;
+    ln.c_ = ln.lane >> 4;
+    ln.n_ = ln.lane & 15u;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t tile0 = (mtg * W + wave) * 2u;  // this wave's tiles: tile0, tile0 + 1
+    const bool active = tile0 < n_mt;              // a wave without a tile still decodes
+    const bool is_k = wave < (uint32_t)W / 2u;
+    const uint32_t r = is_k ? wave : wave - (uint32_t)W / 2u;
+    // where this lane reads its K operands: the token of MFMA row n_ is 4 (n_ % 4) + n_ / 4, so
+    // that score register jj of lane group c_ belongs to token 4 jj + c_, the token whose values
+    // the lane group's plane jj holds
+    {
+        const uint32_t tau = 4u * (ln.n_ & 3u) + (ln.n_ >> 2);
+        ln.k_rd = tau * 256u + (((4u * ln.c_) ^ tau) & 15u) * 16u;  // octet 4 c_ + y of token tau: slot (4 c_ ^ tau) ^ y
+        ln.k_wr = ln.c_ * 256u + ((ln.n_ ^ ln.c_) & 15u) * 16u;     // n_ ^ (4 j + c_) = (n_ ^ c_) ^ 4 j
+    }
+
+    SharedState st;
+    shared_load_queries(c, hdr, h, tile0, M, ln, st);
+
+    uint32_t set = 0;
+    for (uint32_t d = 0; d < run; ++d) {
+        // ---- the document: descriptor d of the run (its first is already here)
+        const uint8_t *dk = c.k, *dv = c.v;
+        uint32_t T = c.n_tokens, dinfo = c.info;
+        if (d) {
+            const K6Doc &cd = p.doc[more + d - 1u];
+            dk = cd.k;
+            dv = cd.v;
+            T = cd.n_tokens;
+            dinfo = cd.info;
+        }
+        const uint32_t nblk = (T + 15u) >> 4;
+        const uint32_t b0 = d ? 0u : first_block;
+        const uint32_t b1 = d + 1u == run ? end_block : nblk;
+        if (b0 >= b1) continue;  // cannot happen with a checked launch
+        if (is_k) {
+            const uint32_t prec = dinfo & 0xFu;
+            const SharedSide sd = shared_side(dk, prec, (dinfo >> 4) & 0xFu, h, nblk, true);
+            shared_rounds_any<true, W>(prec, sd, T, b0, b1, hdr.scale_log2, r, active, ln, lds, set, st);
+        } else {
+            const uint32_t prec = (dinfo >> 8) & 0xFu;
+            const SharedSide sd = shared_side(dv, prec, (dinfo >> 12) & 0xFu, h, nblk, true);
+            shared_rounds_any<false, W>(prec, sd, T, b0, b1, hdr.scale_log2, r, active, ln, lds, set, st);
+        }
+    }
+
+    // ---- the wave's results, straight from its registers: lane (c_, n_) holds rows
+    // 4 c_ + jj, dims 8 n_ + pp of each tile
+    if (!active) return;
+    shared_write_results(c, hdr, h, tile0, M, ln, st);
+}
+
+// Eight waves score, two query tiles each (up to 256 query rows a workgroup), four decode: two the
+// keys and two the values of a round of eight blocks, for the round after the one that is being
+// scored.  One barrier per round, for LDS only.  Three waves per SIMD (168 registers): two scorers,
+// whose registers hold no raw words, and a decoder that fills their gaps.
+__global__ void __launch_bounds__(64 * (kRoleScorers + kRoleDecoders), 3) k6_attend_roles(const K6Params p)
+{
+    extern __shared__ __attribute__((aligned(16))) uint8_t lds_bytes[];
+    uint8_t (*lds)[kRoleBlocks][kSharedBlockLds] = reinterpret_cast<uint8_t (*)[kRoleBlocks][kSharedBlockLds]>(lds_bytes);
+    K6Run c = p.run[blockIdx.y];
+    AttendHdr hdr = {p.n_kv_heads, p.n_q_heads, p.layer, p.scale_log2};
+    pin(c.k);
+    pin(c.v);
+    pin(c.q);
+    pin(c.part);
+    pin(c.n_tokens);
+    pin(c.info);
+    pin(c.n_q);
+    pin(hdr.n_kv_heads);
+    pin(hdr.n_q_heads);
+    pin(hdr.scale_log2);
+    uint32_t run = c.n_docs, more = c.more;  // the run's documents: this one, then descriptors more, more + 1, ..
+    uint32_t first_block = c.first_block, end_block = c.end_block;
+    pin(run);
+    pin(more);
+    pin(first_block);
+    pin(end_block);
+    const uint32_t H = hdr.n_kv_heads, G = hdr.n_q_heads / H, M = c.n_q * G;
+    const uint32_t n_mt = (M + 15u) >> 4;
+    const uint32_t n_mtg = (n_mt + 2u * kRoleScorers - 1u) / (2u * kRoleScorers);
+    const uint32_t u = blockIdx.x;
+    if (u >= H * n_mtg) return;  // the grid is as wide as the widest run
+    const uint32_t mtg = u % n_mtg, h = u / n_mtg;
+
+    SharedLane ln;
+    ln.lane = threadIdx.x & 63u;
+    ln.c_ = ln.lane >> 4;
+    ln.n_ = ln.lane & 15u;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    {
+        const uint32_t tau = 4u * (ln.n_ & 3u) + (ln.n_ >> 2);
+        ln.k_rd = tau * 256u + (((4u * ln.c_) ^ tau) & 15u) * 16u;  // as in k6_attend_shared
+        ln.k_wr = ln.c_ * 256u + ((ln.n_ ^ ln.c_) & 15u) * 16u;
+    }
+    uint32_t set = 0;
+
+    if (wave >= kRoleScorers) {
+        const uint32_t dec = wave - kRoleScorers;
+        const bool is_k = dec < kRoleDecoders / 2u;
+        const uint32_t r = dec & 1u;
+        for (uint32_t d = 0; d < run; ++d) {
+            const uint8_t *dp = is_k ? c.k : c.v;
+            uint32_t T = c.n_tokens, dinfo = c.info;
+            if (d) {
+                const K6Doc &cd = p.doc[more + d - 1u];
+                dp = is_k ? cd.k : cd.v;
+                T = cd.n_tokens;
+                dinfo = cd.info;
+            }
+            const uint32_t nblk = (T + 15u) >> 4;
+            const uint32_t b0 = d ? 0u : first_block;
+            const uint32_t b1 = d + 1u == run ? end_block : nblk;
+            if (b0 >= b1) continue;  // cannot happen with a checked launch
+            const uint32_t info = is_k ? dinfo : dinfo >> 8;
+            const uint32_t prec = info & 0xFu;
+            const SharedSide sd = shared_side(dp, prec, (info >> 4) & 0xFu, h, nblk, true);
+            if (is_k) role_decode_any<true>(prec, sd, T, b0, b1, r, ln, lds, set);
+            else role_decode_any<false>(prec, sd, T, b0, b1, r, ln, lds, set);
+        }
+        return;
+    }
+
+    const uint32_t tile0 = (mtg * kRoleScorers + wave) * 2u;  // this wave's tiles: tile0, tile0 + 1
+    const bool active = tile0 < n_mt;
+    SharedState st;
+    shared_load_queries(c, hdr, h, tile0, M, ln, st);
+    for (uint32_t d = 0; d < run; ++d) {
+        const uint32_t T = d ? p.doc[more + d - 1u].n_tokens : c.n_tokens;
+        const uint32_t nblk = (T + 15u) >> 4;
+        const uint32_t b0 = d ? 0u : first_block;
+        const uint32_t b1 = d + 1u == run ? end_block : nblk;
+        if (b0 >= b1) continue;
+        const uint32_t end = b1 * 16u < T ? b1 * 16u : T;  // the first token that does not count
+        for (uint32_t rb = b0; rb < b1; rb += kRoleBlocks) {
+            lds_barrier();
+            if (active) {
+                const uint32_t nb = b1 - rb < kRoleBlocks ? b1 - rb : kRoleBlocks;
+                const uint8_t *base = lds[set][0];
+#pragma unroll 1
+                for (uint32_t pr = 0; 2u * pr < nb; ++pr) {
+                    const uint8_t *pair = base + pr * (2u * kSharedBlockLds);
+                    f32x4 S[2][2];
+                    bf16x8 P8[2];
+                    shared_qk_pair(pair, ln, st, S);
+                    mfma_result_wait();
+                    shared_softmax_pair(S, rb + 2u * pr, end, hdr.scale_log2, ln, st, P8);
+                    shared_pv_pair(pair + 8192u, ln, st, P8);
+                }
+            }
+            set ^= 1u;
+        }
+        mfma_result_wait();
+    }
+    if (!active) return;
+    shared_write_results(c, hdr, h, tile0, M, ln, st);
+}
+
 // The eight-wave build takes 128 KiB of LDS per workgroup; more than 64 KiB has to be asked for
 // once per device.  Called when a context is created on the device (not from inside a launch
 // that a caller may be capturing into a graph) and, as a fallback, before the first such launch.
@@ -483,8 +710,8 @@ hipError_t prepare_k6_shared()
     if (e != hipSuccess) return e;
     if (dev < 0 || dev >= 64) return hipErrorInvalidDevice;
     if (asked.load(std::memory_order_acquire) >> dev & 1u) return hipSuccess;
-    e = hipFuncSetAttribute(reinterpret_cast<const void *>(k6_attend_shared<8>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)(2u * 8u * kSharedBlockLds));
+    e = hipFuncSetAttribute(reinterpret_cast<const void *>(k6_attend_roles),
+                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)(2u * kRoleBlocks * kSharedBlockLds));
     if (e != hipSuccess) return e;
     asked.fetch_or(1ull << dev, std::memory_order_release);
     return hipSuccess;
@@ -509,7 +736,7 @@ hipError_t launch_k6_shared(K6Params &p, uint32_t waves, hipStream_t stream, boo
     else {
         e = prepare_k6_shared();  // done at ha_rag_create; a no-op from then on
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL((k6_attend_shared<8>), grid, dim3(512), lds_bytes, stream, p);
+        hipLaunchKernelGGL(k6_attend_roles, grid, dim3(64 * (kRoleScorers + kRoleDecoders)), lds_bytes, stream, p);
     }
     return hipGetLastError();
 }

@@ -112,6 +112,10 @@ constexpr uint32_t kAttendMinRunBlocks = 8;    // a workgroup takes at least thi
                                                // half as many in a call of very few workgroups),
 constexpr uint32_t kAttendMaxRunBlocks = 128;  // and a piece of one document is at most this long (a power of two)
 constexpr uint32_t kAttendTargetGroups = 2048; // pieces are halved while a launch has fewer workgroups
+// run lengths of the shared kernel, in units of the time one of its workgroups takes for a block
+// (0.65 us with eight waves): starting and ending a workgroup costs as much as this many blocks,
+constexpr uint32_t kAttendStartBlocks = 10;
+constexpr uint32_t kAttendRecsPerBlock = 160;  // and this many records are written and merged in that time
 constexpr uint32_t kChipCUs = 256;            // compute units of the one GPU this library is built for
 constexpr uint32_t kAttendWaves = 2;          // waves of a workgroup; they interleave its blocks
 // Descriptors travel in the kernel argument buffer (36 KiB; launches with arguments of up to
