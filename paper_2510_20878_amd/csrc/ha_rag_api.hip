@@ -98,7 +98,7 @@ int ha_rag_create(const ha_rag_config *cfg, ha_rag_ctx **out)
             c->copy_streams.push_back(s);
         }
         // the library's set-up on this device: where its static scratch array lives here, and
-        // the LDS allowance of the eight-wave attention kernel
+        // the LDS allowance of the many-rows attention kernel with eight scoring waves
         hipError_t pe = hipSuccess;
         if (attend_static_scratch(nullptr, &g_create_err) != HA_RAG_OK ||
             (pe = ha_rag::prepare_k6_shared()) != hipSuccess) {

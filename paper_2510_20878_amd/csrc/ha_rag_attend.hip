@@ -110,6 +110,78 @@ uint32_t count_runs(const Plan &pl, const Doc *docs)
     return n;
 }
 
+// Cuts every request into runs (plans[r].shared says by which kernel's rule) and lays the workspace
+// out.  Returns its size in binary32 words.
+uint64_t lay_out_runs(Plan *plans, uint32_t n_reqs, const Doc *docs, uint32_t H, uint32_t waves)
+{
+    uint64_t total = 0;
+    // A workgroup takes a run of its request's blocks and writes one record per query tile for
+    // it.  Requests of at most two query tiles: a run is a piece of one document, as long as
+    // possible (every workgroup pays for fetching the queries and for writing a record), but
+    // short enough that the launch fills the chip a few times over, since the hardware then
+    // evens out what documents of different formats and lengths take.
+    auto groups_at = [&](uint32_t piece) {  // workgroups of the one/two-tile kernel with pieces this long
+        uint64_t groups = 0;
+        for (uint32_t r = 0; r < n_reqs; ++r) {
+            const Plan &pl = plans[r];
+            if (pl.shared) continue;
+            uint64_t runs = 0;
+            for (uint32_t i = 0; i < pl.n_docs; ++i)
+                runs += ((docs[pl.first_doc + i].n_tokens + 15u) / 16u + piece - 1u) / piece;
+            groups += runs * H * tile_groups(pl, waves);
+        }
+        return groups;
+    };
+    uint32_t piece = kAttendMaxRunBlocks;
+    while (piece > kAttendMinRunBlocks && groups_at(piece) < kAttendTargetGroups) piece >>= 1;
+    // A call of so few workgroups that even twice as many run side by side (four per CU) is
+    // bound by how long one of them takes: halve once more (one request of 10 x 512 tokens:
+    // 13.7 against 14.7 us; with two requests, 1,280 workgroups, it would cost 1.5 us).
+    if (piece == kAttendMinRunBlocks && groups_at(piece / 2u) <= 4ull * kChipCUs) piece /= 2u;
+    // The shared kernel: a run crosses document boundaries (equal runs finish together whatever
+    // the documents' lengths).  Workgroups of one size finish in rounds of as many as the chip
+    // holds side by side; every round pays for starting and ending a workgroup, and every record
+    // is written and read again, 16 KiB in all.  Of the run lengths (at least kAttendMinRunBlocks)
+    // the one with the least of rounds x (blocks + start) + records is taken, in units of the time a
+    // workgroup takes for a block with its neighbours: 0.57 us with eight scoring waves, 0.9 with
+    // four, 1.2 with two; a record costs the chip about 2 ns.  Without the last two terms three
+    // requests of 96 to 201 query tokens took runs of 8 blocks, 0.9 GB of records: 460 us and
+    // 210 us of merge per layer, against 220 and 9 with two runs per request.
+    const uint64_t side_by_side = (uint64_t)kChipCUs * (8u / waves);  // two waves per SIMD: eight per CU
+    uint64_t most_blocks = 0;
+    for (uint32_t r = 0; r < n_reqs; ++r)
+        if (plans[r].shared && plans[r].all_blocks > most_blocks) most_blocks = plans[r].all_blocks;
+    const uint64_t recs_per_block = waves == 8u ? 280u : waves == 4u ? 450u : 600u;
+    uint64_t run_blocks = most_blocks, least = ~0ull;
+    for (uint64_t n = 1; n <= most_blocks; ++n) {  // n runs for the largest request
+        const uint64_t len = (most_blocks + n - 1u) / n;
+        if (n > 1 && len < kAttendMinRunBlocks) break;
+        uint64_t wgs = 0, recs = 0;
+        for (uint32_t r = 0; r < n_reqs; ++r) {
+            const Plan &pl = plans[r];
+            if (!pl.shared) continue;
+            const uint64_t runs = (pl.all_blocks + len - 1u) / len;
+            wgs += runs * H * tile_groups(pl, waves);
+            if (runs > 1u) recs += runs * H * pl.n_mt;
+        }
+        const uint64_t cost = (wgs + side_by_side - 1u) / side_by_side * (len + kAttendStartBlocks) + recs / recs_per_block;
+        if (cost < least) {
+            least = cost;
+            run_blocks = len;
+        }
+        if (wgs >= 64u * side_by_side) break;  // finer than this gains nothing
+    }
+    for (uint32_t r = 0; r < n_reqs; ++r) {
+        Plan &pl = plans[r];
+        pl.run_blocks = !pl.shared ? piece : run_blocks > 0xFFFFFFFFull ? 0xFFFFFFFFu : (uint32_t)(run_blocks ? run_blocks : 1u);
+        pl.n_runs = count_runs(pl, docs + pl.first_doc);
+        pl.final = pl.shared && pl.n_runs == 1u;  // no record, no merge
+        pl.part_floats = total;
+        if (!pl.final) total += (uint64_t)pl.n_runs * H * pl.n_mt * kAttendRecFloats;
+    }
+    return total;
+}
+
 // Checks everything and lays the workspace out.  *floats = workspace size in binary32 words.
 // plans: n_reqs entries; docs, open_k, open_v: filled here, ENOSPC if one of them is too small
 // (never with lists as long as the call's chunk list).
@@ -123,7 +195,7 @@ int plan_attend(ha_rag_ctx *c, const ha_rag_packed_chunk *chunks, const ha_rag_a
     const uint32_t L = c->cfg.n_layers, H = c->cfg.n_kv_heads;
     if (n_q_heads == 0 || n_q_heads % H || n_q_heads / H > 64) return HA_RAG_EINVAL;
     const uint32_t G = n_q_heads / H;
-    uint64_t total = 0, n_chunks = 0;
+    uint64_t n_chunks = 0;
     docs->clear();
     // open_k / open_v: documents still waiting for their values / keys
     for (uint32_t r = 0; r < n_reqs; ++r) {
@@ -188,77 +260,34 @@ int plan_attend(ha_rag_ctx *c, const ha_rag_packed_chunk *chunks, const ha_rag_a
         n_chunks += rq.n_chunks;
     }
     // The shared kernel runs with as many waves (two tiles each) as the call's largest request
-    // has use for: 2, 4 or 8.
+    // has use for: 2 or 4, or the eight scoring waves of k6_attend_roles.
     uint32_t most_mt = 0;
-    for (uint32_t r = 0; r < n_reqs; ++r)
-        if (plans[r].shared && plans[r].n_mt > most_mt) most_mt = plans[r].n_mt;
-    const uint32_t waves = most_mt > 8u ? 8u : most_mt > 4u ? 4u : 2u;
-    *shared_waves = waves;
-    // A workgroup takes a run of its request's blocks and writes one record per query tile for
-    // it.  Requests of at most two query tiles: a run is a piece of one document, as long as
-    // possible (every workgroup pays for fetching the queries and for writing a record), but
-    // short enough that the launch fills the chip a few times over, since the hardware then
-    // evens out what documents of different formats and lengths take.
     for (uint32_t r = 0; r < n_reqs; ++r) {
         Plan &pl = plans[r];
+        if (pl.shared && pl.n_mt > most_mt) most_mt = pl.n_mt;
         pl.all_blocks = 0;
         for (uint32_t i = 0; i < pl.n_docs; ++i) pl.all_blocks += ((*docs)[pl.first_doc + i].n_tokens + 15u) / 16u;
     }
-    auto groups_at = [&](uint32_t piece) {  // workgroups of the one/two-tile kernel with pieces this long
-        uint64_t groups = 0;
-        for (uint32_t r = 0; r < n_reqs; ++r) {
-            const Plan &pl = plans[r];
-            if (pl.shared) continue;
-            uint64_t runs = 0;
-            for (uint32_t i = 0; i < pl.n_docs; ++i)
-                runs += (((*docs)[pl.first_doc + i].n_tokens + 15u) / 16u + piece - 1u) / piece;
-            groups += runs * H * tile_groups(pl, waves);
+    const uint32_t waves = most_mt > 8u ? 8u : most_mt > 4u ? 4u : 2u;
+    *shared_waves = waves;
+    uint64_t total = lay_out_runs(plans, n_reqs, docs->data, H, waves);
+    // A call that needs the two-wave shared kernel anyway takes its requests of two query tiles there
+    // as well: a block costs that kernel what it costs the other one (103 against 100 us per
+    // call of 32 requests), and one launch fills the chip where two in a row do not (12 requests of
+    // 6 to 16 query tokens: 48 against 63 us per layer).  Not if the partial results then took
+    // more workspace.
+    if (most_mt && waves == 2u) {
+        uint32_t moved = 0;
+        for (uint32_t r = 0; r < n_reqs; ++r)
+            if (plans[r].n_mt == 2u) plans[r].shared = moved = 1u;
+        if (moved) {
+            const uint64_t together = lay_out_runs(plans, n_reqs, docs->data, H, waves);
+            if (together <= total) total = together;
+            else {
+                for (uint32_t r = 0; r < n_reqs; ++r) plans[r].shared = plans[r].n_mt > 2u;
+                total = lay_out_runs(plans, n_reqs, docs->data, H, waves);
+            }
         }
-        return groups;
-    };
-    uint32_t piece = kAttendMaxRunBlocks;
-    while (piece > kAttendMinRunBlocks && groups_at(piece) < kAttendTargetGroups) piece >>= 1;
-    // A call of so few workgroups that even twice as many run side by side (four per CU) is
-    // bound by how long one of them takes: halve once more (one request of 10 x 512 tokens:
-    // 13.7 against 14.7 us; with two requests, 1,280 workgroups, it would cost 1.5 us).
-    if (piece == kAttendMinRunBlocks && groups_at(piece / 2u) <= 4ull * kChipCUs) piece /= 2u;
-    // The shared kernel: a run crosses document boundaries (equal runs finish together whatever
-    // the documents' lengths).  Workgroups of one size finish in rounds of as many as the chip
-    // holds side by side; every round pays for starting and ending a workgroup, and every record
-    // is written and read again, 16 KiB in all.  Of the run lengths (at least kAttendMinRunBlocks)
-    // the one with the least of rounds x (blocks + start) + records is taken, in units of the time a
-    // workgroup takes for a block: COSTNOTE
-    const uint64_t side_by_side = (uint64_t)kChipCUs * (8u / waves);  // two waves per SIMD: eight per CU
-    uint64_t most_blocks = 0;
-    for (uint32_t r = 0; r < n_reqs; ++r)
-        if (plans[r].shared && plans[r].all_blocks > most_blocks) most_blocks = plans[r].all_blocks;
-    uint64_t run_blocks = most_blocks, least = ~0ull;
-    for (uint64_t n = 1; n <= most_blocks; ++n) {  // n runs for the largest request
-        const uint64_t len = (most_blocks + n - 1u) / n;
-        if (n > 1 && len < kAttendMinRunBlocks) break;
-        uint64_t wgs = 0, recs = 0;
-        for (uint32_t r = 0; r < n_reqs; ++r) {
-            const Plan &pl = plans[r];
-            if (!pl.shared) continue;
-            const uint64_t runs = (pl.all_blocks + len - 1u) / len;
-            wgs += runs * H * tile_groups(pl, waves);
-            if (runs > 1u) recs += runs * H * pl.n_mt;
-        }
-        const uint64_t cost = (wgs + side_by_side - 1u) / side_by_side * (len + kAttendStartBlocks) +
-                              recs / kAttendRecsPerBlock;
-        if (cost < least) {
-            least = cost;
-            run_blocks = len;
-        }
-        if (wgs >= 64u * side_by_side) break;  // finer than this gains nothing
-    }
-    for (uint32_t r = 0; r < n_reqs; ++r) {
-        Plan &pl = plans[r];
-        pl.run_blocks = !pl.shared ? piece : run_blocks > 0xFFFFFFFFull ? 0xFFFFFFFFu : (uint32_t)(run_blocks ? run_blocks : 1u);
-        pl.n_runs = count_runs(pl, docs->data + pl.first_doc);
-        pl.final = pl.shared && pl.n_runs == 1u;  // no record, no merge
-        pl.part_floats = total;
-        if (!pl.final) total += (uint64_t)pl.n_runs * H * pl.n_mt * kAttendRecFloats;
     }
     if (total * 4ull > (1ull << 40)) return HA_RAG_EINVAL;
     *floats = total;

@@ -43,7 +43,7 @@ struct AttendLds {
 template <uint32_t KP, uint32_t VP, int MTW, bool NARROW>
 __device__ __forceinline__ void attend_unit(const AttendHdr &p, const K6Run &c,
                                             uint32_t h, uint32_t mtg, uint8_t *lds_all,
-                                            float (*sm)[MTW * 16], float (*sl)[MTW * 16])
+                                            float (*sm)[MTW * 16], float (*sl)[2][MTW * 16])
 {
     typedef Fmt<KP> FK;
     typedef Fmt<VP> FV;
@@ -95,12 +95,12 @@ __device__ __forceinline__ void attend_unit(const AttendHdr &p, const K6Run &c,
         }
     }
 
-    float m_run[MTW], l_run[MTW];
+    float m_run[MTW], l_run[MTW], r_run[MTW];
     f32x4 O[MTW][8];
 #pragma unroll
     for (int mt = 0; mt < MTW; ++mt) {
         m_run[mt] = neg_inf();
-        l_run[mt] = 0.0f;
+        l_run[mt] = r_run[mt] = 0.0f;
 #pragma unroll
         for (int pp = 0; pp < 8; ++pp) O[mt][pp] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
@@ -178,9 +178,10 @@ __device__ __forceinline__ void attend_unit(const AttendHdr &p, const K6Run &c,
             // which bounds every weight by 2^kLazyMaxSlack.  After the first blocks that almost
             // never happens, and a block costs one comparison instead of the reduction.
             if (__any(mx > m_run[mt] + kLazyMaxSlack)) {
-                const float m_new = __builtin_fmaxf(m_run[mt], max_over_lane_groups(mx));
+                const float m_new = __builtin_fmaxf(m_run[mt], max_over_lane_groups(mx) + kLazyMaxLift);
                 const float alpha = __builtin_amdgcn_exp2f(m_run[mt] - m_new);  // 0 at the first block
                 l_run[mt] *= alpha;
+                r_run[mt] *= alpha;
                 m_run[mt] = m_new;
 #pragma unroll
                 for (int jj = 0; jj < 4; ++jj) {
@@ -195,6 +196,7 @@ __device__ __forceinline__ void attend_unit(const AttendHdr &p, const K6Run &c,
                 pr[jj] = __builtin_amdgcn_exp2f(__builtin_fmaf(S[jj], p.scale_log2, -m_run[mt]));
             l_run[mt] += (pr[0] + pr[1]) + (pr[2] + pr[3]);
             const u32x2 pk = {pack_bf16(pr[0], pr[1]), pack_bf16(pr[2], pr[3])};
+            r_run[mt] = add_weights(pk.y, add_weights(pk.x, r_run[mt]));
             pa[mt] = __builtin_bit_cast(s16x4, pk);
         }
 
@@ -259,12 +261,15 @@ blocks_done:
     // threads bring them to one maximum per row, add them up and write the record
 #pragma unroll
     for (int mt = 0; mt < MTW; ++mt) {
-        float l_tot = l_run[mt];
+        float l_tot = l_run[mt], r_tot = r_run[mt];
         l_tot += __shfl_xor(l_tot, 16);
+        r_tot += __shfl_xor(r_tot, 16);
         l_tot += __shfl_xor(l_tot, 32);
+        r_tot += __shfl_xor(r_tot, 32);
         if (c_ == 0) {
             sm[wave][mt * 16 + n_] = m_run[mt];
-            sl[wave][mt * 16 + n_] = l_tot;
+            sl[wave][0][mt * 16 + n_] = l_tot;
+            sl[wave][1][mt * 16 + n_] = r_tot;
         }
     }
     float *acc = reinterpret_cast<float *>(lds_all);  // [wave][16 rows][128]
@@ -289,13 +294,17 @@ blocks_done:
 #pragma unroll
             for (uint32_t w = 1; w < kAttendWaves; ++w) m_all = __builtin_fmaxf(m_all, sm[w][row]);
             f32x4 sum = {0.f, 0.f, 0.f, 0.f};
+            float l_all = 0.0f, r_all = 0.0f;
 #pragma unroll
             for (uint32_t w = 0; w < kAttendWaves; ++w) {
                 // a wave that had no block has m = -inf and l = 0: nothing to add
-                const float f = sl[w][row] > 0.0f ? __builtin_amdgcn_exp2f(sm[w][row] - m_all) : 0.0f;
+                const float l_w = sl[w][0][row], f = l_w > 0.0f ? __builtin_amdgcn_exp2f(sm[w][row] - m_all) : 0.0f;
                 sum += reinterpret_cast<const f32x4 *>(acc + w * 2048u)[i] * f;
+                l_all = __builtin_fmaf(l_w, f, l_all);
+                r_all = __builtin_fmaf(sl[w][1][row], f, r_all);
             }
-            ((f32x4 __attribute__((address_space(1))) *)rec)[i] = sum;
+            // the merge divides by the record's unrounded sum
+            ((f32x4 __attribute__((address_space(1))) *)rec)[i] = sum * (r_all > 0.0f ? l_all / r_all : 0.0f);
         }
         if (threadIdx.x < 16u) {
             const uint32_t row = mt * 16u + threadIdx.x;
@@ -305,7 +314,7 @@ blocks_done:
             float l_all = 0.0f;
 #pragma unroll
             for (uint32_t w = 0; w < kAttendWaves; ++w)
-                if (sl[w][row] > 0.0f) l_all += sl[w][row] * __builtin_amdgcn_exp2f(sm[w][row] - m_all);
+                if (sl[w][0][row] > 0.0f) l_all += sl[w][0][row] * __builtin_amdgcn_exp2f(sm[w][row] - m_all);
             rec[2048 + threadIdx.x] = m_all;
             rec[2048 + 16 + threadIdx.x] = l_all;
         }
@@ -318,7 +327,7 @@ blocks_done:
 template <uint32_t KP, uint32_t VP, int MTW, bool NARROW>
 __device__ __forceinline__ void attend_pair(const AttendHdr &hdr, const K6Run &c, uint32_t h,
                                             uint32_t mtg, uint8_t *lds, float (*sm)[MTW * 16],
-                                            float (*sl)[MTW * 16])
+                                            float (*sl)[2][MTW * 16])
 {
     if constexpr (!(NARROW && (KP == kP16 || VP == kP16)))
         attend_unit<KP, VP, MTW, NARROW>(hdr, c, h, mtg, lds, sm, sl);
@@ -327,7 +336,7 @@ __device__ __forceinline__ void attend_pair(const AttendHdr &hdr, const K6Run &c
 template <uint32_t KP, int MTW, bool NARROW>
 __device__ __forceinline__ void attend_values(const AttendHdr &hdr, const K6Run &c, uint32_t h,
                                               uint32_t mtg, uint8_t *lds, float (*sm)[MTW * 16],
-                                              float (*sl)[MTW * 16])
+                                              float (*sl)[2][MTW * 16])
 {
     switch ((c.info >> 8) & 0xFu) {
     case kP16: attend_pair<KP, kP16, MTW, NARROW>(hdr, c, h, mtg, lds, sm, sl); break;
@@ -348,7 +357,7 @@ template <int MTW, bool NARROW>
 __global__ void __launch_bounds__(64 * kAttendWaves, NARROW ? 3 : 2) k6_attend_partial(const K6Params p)
 {
     __shared__ __attribute__((aligned(16))) uint8_t lds[AttendLds<MTW>::kBytes];
-    __shared__ float sm[kAttendWaves][MTW * 16], sl[kAttendWaves][MTW * 16];
+    __shared__ float sm[kAttendWaves][MTW * 16], sl[kAttendWaves][2][MTW * 16];  // reference; sums of the weights (unrounded, rounded)
     // the whole descriptor and the header at once, before anything depends on a part of them
     K6Run c = p.run[blockIdx.y];
     AttendHdr hdr = {p.n_kv_heads, p.n_q_heads, p.layer, p.scale_log2};
@@ -551,9 +560,8 @@ __global__ void __launch_bounds__(32 * kMergeGroups) k7_attend_merge(const K7Par
 // query tile), groups of 256 threads that share the tile's records, 16 threads a row and 8 dims a
 // thread.  A record is then read as the contiguous 8 KiB it is, by one group, and a request of
 // hundreds of rows needs hundreds of workgroups instead of one for each of its rows.
-// Bound: the latency of the rounds of loads (a group has four records under way at a time), so
-// the more records a tile has the more groups share them: 21 records per tile in one group
-// (six rounds) 10.6 us per call, in four groups (two rounds) MERGE4 us.
+// Bound: the records' bytes in a batch (44 MB in 10.3 us), the latency of the rounds of loads in a
+// small launch (a group has four records under way at a time), where four groups share them.
 template <uint32_t NG>
 __global__ void __launch_bounds__(256 * NG) k7_attend_merge_tiles(const K7Params p)
 {
@@ -684,10 +692,12 @@ hipError_t launch_k7(K7Params &p, hipStream_t stream, bool check_only)
     if (width > 0x7FFFFFFFull) return hipErrorInvalidValue;
     if (check_only) return hipSuccess;
     if (max_mt > 2u) {  // the requests of the shared kernel: merge tile by tile
-        // a second and a third and fourth group as soon as a group would need a second round of loads
+        // More groups where a group would need several rounds of loads and the launch is small enough
+        // for that to show (384 workgroups); with 1,936, most of them without a tile of their
+        // own, the large workgroups cost 0.7 us instead.
         const dim3 grid((uint32_t)tile_width, p.n_reqs);
-        if (max_units <= 4u) hipLaunchKernelGGL(k7_attend_merge_tiles<1>, grid, dim3(256), 0, stream, p);
-        else if (max_units <= 8u) hipLaunchKernelGGL(k7_attend_merge_tiles<2>, grid, dim3(512), 0, stream, p);
+        const bool small = tile_width * p.n_reqs <= 2u * kChipCUs;
+        if (max_units <= 4u || !small) hipLaunchKernelGGL(k7_attend_merge_tiles<1>, grid, dim3(256), 0, stream, p);
         else hipLaunchKernelGGL(k7_attend_merge_tiles<4>, grid, dim3(1024), 0, stream, p);
         return hipGetLastError();
     }

@@ -2,7 +2,7 @@
 // wave can keep (more than two 16-row tiles: the question's prefill of Sec. 2.1, tens of query
 // tokens times the query heads of a KV head).
 //
-//  k6_attend_shared<W>   one workgroup of W waves (2, 4 or 8) per (run of blocks across a request's
+//  k6_attend_shared<W>   one workgroup of W waves (2 or 4) per (run of blocks across a request's
 //      documents in list order, KV head, group of 2 W query tiles).  Every wave owns two query
 //      tiles for the whole run: their queries, reference maxima, sums and output rows stay in its
 //      registers.  The layout blocks are taken W at a time: half the waves decode the keys and
@@ -13,6 +13,9 @@
 //      between two sets of LDS buffers, so one barrier per round is enough: a wave that writes
 //      round r + 1 has passed barrier r, which every wave reaches only after it has read all of
 //      round r - 1.
+//  k6_attend_roles       the same for requests of more than eight tiles, with waves of two kinds:
+//      eight that score (two tiles each, so 256 query rows) and four that decode the next round
+//      meanwhile.  Described at the kernel.
 //
 // Block geometry as for k6_attend_partial: lane (c = lane / 16, n = lane % 16) of the wave that
 // reads a block holds, in plane j, token 4 j + c, dims 8 n .. 8 n + 7.
@@ -23,7 +26,8 @@
 //   K: the score MFMA wants, per lane, 8 dims of the token of its column; the decoding wave
 //      stores octet o of token t at 16-byte slot (o ^ t) of row t (256 bytes a row), which
 //      both its own stores and the readers' loads reach without bank conflicts.
-// A pair's buffer is 16 KiB: K of its first block, K of its second block, V of both.
+// A pair's buffer is 16 KiB: K of its first block, K of its second block, V of both (the layout of
+// k6_attend_roles differs in the rows of K: kRoleKeyRow).
 #include "ha_rag_attend_dev.h"
 #include <atomic>
 
@@ -33,9 +37,11 @@ namespace {
 
 constexpr uint32_t kSharedBlockLds = 8192;  // LDS per block: K operands 4 KiB, V operands 4 KiB (laid out per pair)
 
+
 struct SharedState {  // a wave's two query tiles
     bf16x8 qb[2][4];
     float m_run[2], l_run[2];
+    float r_run[2];  // the sum of the weights as they multiply V (add_weights); l_run: before rounding
     f32x4 O[2][8];
 };
 
@@ -57,6 +63,15 @@ __device__ __forceinline__ uint32_t fresh(uint32_t v)
 {
     asm volatile("" : "+v"(v));
     return v;
+}
+
+// the eight weights of a pair
+__device__ __forceinline__ float add_weights8(const bf16x8 &w, float sum)
+{
+    const u32x4 pk = __builtin_bit_cast(u32x4, w);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) sum = add_weights(pk[i], sum);
+    return sum;
 }
 
 // Two blocks (a pair) against the wave's two tiles, in three steps: S^T = K Q^T of both blocks
@@ -99,9 +114,8 @@ __device__ __forceinline__ void shared_qk_pair(const uint8_t *pair, const Shared
 __device__ __forceinline__ void shared_softmax_pair(f32x4 (&S)[2][2], uint32_t b, uint32_t end, float scale_log2,
                                                     const SharedLane &ln, SharedState &st, bf16x8 (&P8)[2])
 {
-    const uint32_t c_ = ln.c_;
     if (b * 16u + 32u > end) {  // a ragged last block, or a last block without a partner
-        const uint32_t tok = b * 16u + fresh(c_);  // computed only here
+        const uint32_t tok = b * 16u + (fresh(ln.lane) >> 4);  // computed only here
 #pragma unroll
         for (int e = 0; e < 2; ++e)
 #pragma unroll
@@ -125,10 +139,12 @@ __device__ __forceinline__ void shared_softmax_pair(f32x4 (&S)[2][2], uint32_t b
     if (__any(mx[0] > st.m_run[0] + kLazyMaxSlack || mx[1] > st.m_run[1] + kLazyMaxSlack)) {
 #pragma unroll
         for (int mt = 0; mt < 2; ++mt) {
-            const float m_new = __builtin_fmaxf(st.m_run[mt], max_over_lane_groups(mx[mt]));
+            const float m_new = __builtin_fmaxf(st.m_run[mt], max_over_lane_groups(mx[mt]) + kLazyMaxLift);
             const float alpha = __builtin_amdgcn_exp2f(st.m_run[mt] - m_new);  // 0 at the first block, 1 if nothing moved
             st.l_run[mt] *= alpha;
+            st.r_run[mt] *= alpha;
             st.m_run[mt] = m_new;
+            const uint32_t c_ = fresh(ln.lane) >> 4;
 #pragma unroll
             for (int jj = 0; jj < 4; ++jj) {
                 const float ar = __shfl(alpha, (int)(4u * c_ + jj));  // factor of output row 4 c_ + jj
@@ -149,6 +165,7 @@ __device__ __forceinline__ void shared_softmax_pair(f32x4 (&S)[2][2], uint32_t b
         const u32x4 pk = {pack_bf16(pr[0][0], pr[0][1]), pack_bf16(pr[0][2], pr[0][3]),
                           pack_bf16(pr[1][0], pr[1][1]), pack_bf16(pr[1][2], pr[1][3])};
         P8[mt] = __builtin_bit_cast(bf16x8, pk);
+        st.r_run[mt] = add_weights8(P8[mt], st.r_run[mt]);
     }
 }
 
@@ -323,39 +340,49 @@ __device__ __forceinline__ void lds_barrier()
 
 constexpr uint32_t kRoleScorers = 8, kRoleDecoders = 4;  // waves of a workgroup
 constexpr uint32_t kRoleBlocks = 8;                       // layout blocks per round
+// LDS of a pair of blocks: the keys of each block as 16 rows of 256 bytes, 16 bytes apart so that
+// the lanes of a column reach different banks with constant offsets (an exclusive-or of row and
+// octet does the same, but costs an instruction per access), then the values of both.
+constexpr uint32_t kRoleKeyRow = 272, kRoleKeys = 16 * kRoleKeyRow, kRolePair = 2 * kRoleKeys + 8192;
+constexpr uint32_t kRoleSet = kRoleBlocks / 2 * kRolePair;  // 66 KiB; two sets
+
+struct RoleLane {
+    uint32_t lane, c_, n_;  // MFMA coordinates: lane group, lane column
+    uint32_t key;           // a scorer: where its K operands start in a block; a decoder: where plane 0 goes
+};
 
 // One block of one side: decode what the lane has fetched and leave it in the pair's buffer
 // (`pair`, e = 0 / 1: first / second block of the pair).
 template <uint32_t P, bool IS_K>
 __device__ __forceinline__ void role_decode(const u32x4 *w, const u32x4 &m, const SharedSide &sd, uint32_t blk, uint32_t T,
-                                            uint8_t *pair, int e, const SharedLane &ln)
+                                            uint8_t *pair, int e, const RoleLane &ln)
 {
-    u32x4 o[4];  // o[j] = token 4 j + c_, dims 8 n_ .. 8 n_ + 7 as BF16
-#pragma unroll
-    for (int j = 0; j < 4; ++j) o[j] = decode_octet<P>(plane_raw<P>(w, j), m[j], sd.base, sd.top);
     if (IS_K) {
-        uint8_t *dst = pair + e * 4096u;
+        uint8_t *dst = pair + e * kRoleKeys + ln.key;  // token 4 j + c_, octet n_
 #pragma unroll
         for (uint32_t j = 0; j < 4; ++j)
-            *reinterpret_cast<u32x4 *>(dst + ((ln.k_wr ^ (64u * j)) + 1024u * j)) = o[j];
-    } else {
-        if (blk * 16u + 16u > T) {  // rows past the document's end
+            *reinterpret_cast<u32x4 *>(dst + j * (4u * kRoleKeyRow)) =
+                decode_octet<P>(plane_raw<P>(w, j), m[j], sd.base, sd.top);
+        return;
+    }
+    // Operand pp of P V: value pp of the octet of each of the lane's four tokens; the pair's
+    // second block fills the second half of the lane's 16 bytes.
+    uint32_t t01[8], t23[8];  // value pp of tokens 4 * 0 + c_ and 4 * 1 + c_, of 4 * 2 + c_ and 4 * 3 + c_
+    decode_octets_by_token<P>(plane_raw<P>(w, 0), plane_raw<P>(w, 1), m[0], m[1], sd.base, sd.top, t01);
+    decode_octets_by_token<P>(plane_raw<P>(w, 2), plane_raw<P>(w, 3), m[2], m[3], sd.base, sd.top, t23);
+    if (blk * 16u + 16u > T) {  // rows past the document's end
+        uint32_t keep[4];
 #pragma unroll
-            for (uint32_t j = 0; j < 4; ++j)
-                if (blk * 16u + 4u * j + ln.c_ >= T) o[j] = u32x4{0u, 0u, 0u, 0u};
-        }
-        uint8_t *vdst = pair + 8192u + ln.lane * 16u + e * 8u;
+        for (uint32_t j = 0; j < 4; ++j) keep[j] = blk * 16u + 4u * j + ln.c_ < T ? 0xFFFFu : 0u;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            u32x2 lo, hi;
-            lo.x = __builtin_amdgcn_perm(o[1][q], o[0][q], 0x05040100u);
-            lo.y = __builtin_amdgcn_perm(o[3][q], o[2][q], 0x05040100u);
-            hi.x = __builtin_amdgcn_perm(o[1][q], o[0][q], 0x07060302u);
-            hi.y = __builtin_amdgcn_perm(o[3][q], o[2][q], 0x07060302u);
-            *reinterpret_cast<u32x2 *>(vdst + (2 * q) * 1024u) = lo;
-            *reinterpret_cast<u32x2 *>(vdst + (2 * q + 1) * 1024u) = hi;
+        for (int pp = 0; pp < 8; ++pp) {
+            t01[pp] &= keep[0] | (keep[1] << 16);
+            t23[pp] &= keep[2] | (keep[3] << 16);
         }
     }
+    uint8_t *vdst = pair + 2u * kRoleKeys + ln.lane * 16u + e * 8u;
+#pragma unroll
+    for (int pp = 0; pp < 8; ++pp) *reinterpret_cast<u32x2 *>(vdst + pp * 1024u) = u32x2{t01[pp], t23[pp]};
 }
 
 // The rounds of one document for decoder r (0, 1) of one side: blocks 4 r .. 4 r + 3 of every
@@ -363,35 +390,33 @@ __device__ __forceinline__ void role_decode(const u32x4 *w, const u32x4 &m, cons
 // stay under way across the barrier.
 template <uint32_t P, bool IS_K>
 __device__ __forceinline__ void role_decode_rounds(const SharedSide &sd, uint32_t T, uint32_t b0, uint32_t b1, uint32_t r,
-                                                   const SharedLane &ln, uint8_t (*lds)[kRoleBlocks][kSharedBlockLds],
-                                                   uint32_t &set)
+                                                   const RoleLane &ln, uint8_t *lds, uint32_t &set)
 {
     typedef Fmt<P> F;
     u32x4 w[4][F::kWords], m[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) m[i] = u32x4{0u, 0u, 0u, 0u};
+    // Issued whether or not the block exists (a block past the end is replaced by the last one), in
+    // the order the blocks are decoded in, here and in the loop: only then does a wait for one
+    // block leave the others' loads under way.
     auto fetch = [&](int i, uint32_t b) {
-        b = b < b1 ? b : b1 - 1u;  // issued whether or not the block exists: no branch around loads
+        b = b < b1 ? b : b1 - 1u;
 #pragma unroll
         for (uint32_t a = 0; a < F::kWords; ++a)
             w[i][a] = ldg16(sd.tile + ((uint64_t)b * F::kPayload + a * 1024u + ln.lane * 16u));
         if (F::kMeta) m[i] = ldg16(sd.meta + ((uint64_t)b * sd.meta_blk + ((ln.lane * 8u) >> sd.gsh) * 16u));
+        __builtin_amdgcn_sched_barrier(0);
     };
 #pragma unroll
     for (int i = 0; i < 4; ++i) fetch(i, b0 + 4u * r + i);
     for (uint32_t rb = b0; rb < b1; rb += kRoleBlocks) {
+        // Blocks past the end are decoded like the others: the keys' scores are replaced, and the
+        // values, which the MFMAs take with weight zero, are numbers (zeros: all their tokens lie
+        // behind the document's, or run's, last).
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const uint32_t blk = rb + 4u * r + i;
-            uint8_t *pair = lds[set][4u * r + (i & 2)];
-            if (blk < b1) role_decode<P, IS_K>(w[i], m[i], sd, blk, T, pair, i & 1, ln);
-            else if (!IS_K && (i & 1) && blk - 1u < b1) {
-                // no such block, but its partner exists: the pair's MFMAs take this half of the V
-                // operands with weight zero, so it must hold numbers
-#pragma unroll
-                for (int pp = 0; pp < 8; ++pp)
-                    *reinterpret_cast<u32x2 *>(pair + 8192u + pp * 1024u + ln.lane * 16u + 8u) = u32x2{0u, 0u};
-            }
+            role_decode<P, IS_K>(w[i], m[i], sd, blk, T, lds + set * kRoleSet + (2u * r + i / 2) * kRolePair, i & 1, ln);
             fetch(i, blk + kRoleBlocks);
         }
         lds_barrier();
@@ -401,8 +426,7 @@ __device__ __forceinline__ void role_decode_rounds(const SharedSide &sd, uint32_
 
 template <bool IS_K>
 __device__ __forceinline__ void role_decode_any(uint32_t prec, const SharedSide &sd, uint32_t T, uint32_t b0, uint32_t b1,
-                                                uint32_t r, const SharedLane &ln,
-                                                uint8_t (*lds)[kRoleBlocks][kSharedBlockLds], uint32_t &set)
+                                                uint32_t r, const RoleLane &ln, uint8_t *lds, uint32_t &set)
 {
     switch (prec) {
     case kP16: role_decode_rounds<kP16, IS_K>(sd, T, b0, b1, r, ln, lds, set); break;
@@ -417,23 +441,23 @@ __device__ __forceinline__ void role_decode_any(uint32_t prec, const SharedSide 
 // The wave's queries as the B operand of S^T = K Q^T: lane (c_, n_) holds, for MFMA y, dims
 // 32 c_ + 8 y .. + 7 of query row n_ of the tile (zero rows beyond M); nothing accumulated yet.
 __device__ __forceinline__ void shared_load_queries(const K6Run &c, const AttendHdr &hdr, uint32_t h, uint32_t tile0,
-                                                    uint32_t M, const SharedLane &ln, SharedState &st)
+                                                    uint32_t M, uint32_t c_, uint32_t n_, SharedState &st)
 {
     const uint32_t G = hdr.n_q_heads / hdr.n_kv_heads;
 #pragma unroll
     for (int mt = 0; mt < 2; ++mt) {
-        const uint32_t row = (tile0 + mt) * 16u + ln.n_;
+        const uint32_t row = (tile0 + mt) * 16u + n_;
         u32x4 z = {0u, 0u, 0u, 0u};
 #pragma unroll
         for (int y = 0; y < 4; ++y) st.qb[mt][y] = __builtin_bit_cast(bf16x8, z);
         if (row < M) {
             const uint32_t qt = row / G, gq = row - qt * G;
-            gbytes qp = (gbytes)c.q + ((uint64_t)(qt * hdr.n_q_heads + h * G + gq) * 128u + 32u * ln.c_) * 2u;
+            gbytes qp = (gbytes)c.q + ((uint64_t)(qt * hdr.n_q_heads + h * G + gq) * 128u + 32u * c_) * 2u;
 #pragma unroll
             for (int y = 0; y < 4; ++y) st.qb[mt][y] = __builtin_bit_cast(bf16x8, ldg16(qp + 16 * y));
         }
         st.m_run[mt] = neg_inf();
-        st.l_run[mt] = 0.0f;
+        st.l_run[mt] = st.r_run[mt] = 0.0f;
 #pragma unroll
         for (int pp = 0; pp < 8; ++pp) st.O[mt][pp] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
@@ -442,7 +466,7 @@ __device__ __forceinline__ void shared_load_queries(const K6Run &c, const Attend
 // The wave's results, straight from its registers: lane (c_, n_) holds rows 4 c_ + jj, dims
 // 8 n_ + pp of each tile.
 __device__ __forceinline__ void shared_write_results(const K6Run &c, const AttendHdr &hdr, uint32_t h, uint32_t tile0,
-                                                     uint32_t M, const SharedLane &ln, SharedState &st)
+                                                     uint32_t M, uint32_t c_, uint32_t n_, SharedState &st)
 {
     const uint32_t G = hdr.n_q_heads / hdr.n_kv_heads, n_mt = (M + 15u) >> 4;
     uint32_t final = c.final;
@@ -453,9 +477,11 @@ __device__ __forceinline__ void shared_write_results(const K6Run &c, const Atten
     for (int mt = 0; mt < 2; ++mt) {
         const uint32_t tile = tile0 + mt;
         if (tile >= n_mt) continue;
-        float l_tot = st.l_run[mt];
+        float l_tot = st.l_run[mt], r_tot = st.r_run[mt];
         l_tot += __shfl_xor(l_tot, 16);
+        r_tot += __shfl_xor(r_tot, 16);
         l_tot += __shfl_xor(l_tot, 32);
+        r_tot += __shfl_xor(r_tot, 32);
         if (final) {
             // The run is everything the request attends to: what the merge would do with its one
             // record is done here.  l_tot of row n_ is in every lane of column n_; the rows this
@@ -463,23 +489,23 @@ __device__ __forceinline__ void shared_write_results(const K6Run &c, const Atten
             gfloats out = (gfloats)c.part;
 #pragma unroll
             for (uint32_t jj = 0; jj < 4; ++jj) {
-                const uint32_t row = 4u * ln.c_ + jj, mrow = tile * 16u + row;
-                const float l_row = __shfl(l_tot, (int)row);
+                const uint32_t row = 4u * c_ + jj, mrow = tile * 16u + row;
+                const float r_row = __shfl(r_tot, (int)row);
                 if (mrow >= M) continue;
                 const uint32_t qt = mrow / G, gq = mrow - qt * G;
                 f32x4 __attribute__((address_space(1))) *dst = (f32x4 __attribute__((address_space(1))) *)(
-                    out + ((uint64_t)qt * hdr.n_q_heads + h * G + gq) * 128u + 8u * ln.n_);
+                    out + ((uint64_t)qt * hdr.n_q_heads + h * G + gq) * 128u + 8u * n_);
                 f32x4 w0, w1;
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
-                    w0[e] = l_row > 0.0f ? st.O[mt][e][jj] / l_row : 0.0f;
-                    w1[e] = l_row > 0.0f ? st.O[mt][4 + e][jj] / l_row : 0.0f;
+                    w0[e] = r_row > 0.0f ? st.O[mt][e][jj] / r_row : 0.0f;
+                    w1[e] = r_row > 0.0f ? st.O[mt][4 + e][jj] / r_row : 0.0f;
                 }
                 dst[0] = w0;
                 dst[1] = w1;
             }
-            const uint32_t mrow = tile * 16u + ln.n_;
-            if (ln.c_ == 0 && lse_ptr && mrow < M) {
+            const uint32_t mrow = tile * 16u + n_;
+            if (c_ == 0 && lse_ptr && mrow < M) {
                 const uint32_t qt = mrow / G, gq = mrow - qt * G;
                 ((gfloats)lse_ptr)[(uint64_t)qt * hdr.n_q_heads + h * G + gq] =
                     l_tot > 0.0f ? (st.m_run[mt] + __builtin_log2f(l_tot)) * 0.69314718055994531f : neg_inf();
@@ -489,29 +515,152 @@ __device__ __forceinline__ void shared_write_results(const K6Run &c, const Atten
         gfloats rec = (gfloats)c.part + ((uint64_t)h * n_mt + tile) * kAttendRecFloats;
 #pragma unroll
         for (uint32_t jj = 0; jj < 4; ++jj) {
-            const uint32_t row = 4u * ln.c_ + jj;
+            const uint32_t row = 4u * c_ + jj;
+            const float fit = __shfl(r_tot > 0.0f ? l_tot / r_tot : 0.0f, (int)row);  // the merge divides by l
             if (tile * 16u + row >= M) continue;  // no query in this row: the merge never reads it
             f32x4 __attribute__((address_space(1))) *dst =
-                (f32x4 __attribute__((address_space(1))) *)(rec + row * 128u + 8u * ln.n_);
-            dst[0] = f32x4{st.O[mt][0][jj], st.O[mt][1][jj], st.O[mt][2][jj], st.O[mt][3][jj]};
-            dst[1] = f32x4{st.O[mt][4][jj], st.O[mt][5][jj], st.O[mt][6][jj], st.O[mt][7][jj]};
+                (f32x4 __attribute__((address_space(1))) *)(rec + row * 128u + 8u * n_);
+            dst[0] = f32x4{st.O[mt][0][jj], st.O[mt][1][jj], st.O[mt][2][jj], st.O[mt][3][jj]} * fit;
+            dst[1] = f32x4{st.O[mt][4][jj], st.O[mt][5][jj], st.O[mt][6][jj], st.O[mt][7][jj]} * fit;
         }
-        if (ln.c_ == 0) {
-            rec[2048 + ln.n_] = st.m_run[mt];
-            rec[2048 + 16 + ln.n_] = l_tot;
+        if (c_ == 0) {
+            rec[2048 + n_] = st.m_run[mt];
+            rec[2048 + 16 + n_] = l_tot;
+        }
+    }
+}
+
+// How large the sum of a lane's eight weights of a pair and tile may get before the row's reference
+// maximum is brought up to date: no weight exceeds 2^kLazyMaxSlack.
+constexpr float kRoleMaxSum = 256.0f;
+// A reference that any score exceeds.  Finite: a masked score (-inf) minus it is still -inf.
+constexpr float kRoleNoRef = -1.0e30f;
+constexpr int kRoleEarlyV = 6;  // V operands read before the softmax; the last two would not fit the registers
+
+// The weights of one tile and pair relative to the row's reference, and their sum in this lane.
+__device__ __forceinline__ float role_weights(const f32x4 &s0, const f32x4 &s1, float scale_log2, float ref, bf16x8 &P8)
+{
+    float pr[8];
+#pragma unroll
+    for (int jj = 0; jj < 4; ++jj) {
+        pr[jj] = __builtin_amdgcn_exp2f(__builtin_fmaf(s0[jj], scale_log2, -ref));
+        pr[4 + jj] = __builtin_amdgcn_exp2f(__builtin_fmaf(s1[jj], scale_log2, -ref));
+    }
+    const u32x4 pk = {pack_bf16(pr[0], pr[1]), pack_bf16(pr[2], pr[3]), pack_bf16(pr[4], pr[5]), pack_bf16(pr[6], pr[7])};
+    P8 = __builtin_bit_cast(bf16x8, pk);
+    return ((pr[0] + pr[1]) + (pr[2] + pr[3])) + ((pr[4] + pr[5]) + (pr[6] + pr[7]));
+}
+
+// A round of a scorer: its two tiles against `nb` blocks, two (a pair) at a time.  The LDS reads are
+// issued ahead of what hides them: the keys of a pair's first block before the P V MFMAs of the
+// pair before, those of the second before the first's MFMAs, the values before the softmax.
+// The reference maximum is looked at after the fact: weights are formed with the reference there
+// is, and only if their sum says that one of them may be too large (or there is no reference yet)
+// the row maxima are taken, what is accumulated is rescaled and the weights are formed again.
+// That saves the maxima of every pair, a fifth of the softmax's instructions.
+__device__ __forceinline__ void role_score_round(const uint8_t *base, uint32_t rb, uint32_t nb, uint32_t end,
+                                                 float scale_log2, const RoleLane &ln, SharedState &st)
+{
+    u32x4 ka0[4], ka1[4];
+    const uint8_t *key = base + ln.key;
+#pragma unroll
+    for (uint32_t y = 0; y < 4; ++y) ka0[y] = *reinterpret_cast<const u32x4 *>(key + 16u * y);
+#pragma unroll 1
+    for (uint32_t pr = 0; 2u * pr < nb; ++pr) {
+        f32x4 S[2][2];
+        bf16x8 P8[2];
+#pragma unroll
+        for (int e = 0; e < 2; ++e)
+#pragma unroll
+            for (int mt = 0; mt < 2; ++mt) S[e][mt] = f32x4{0.f, 0.f, 0.f, 0.f};
+        key = base + pr * kRolePair + fresh(ln.key);
+#pragma unroll
+        for (uint32_t y = 0; y < 4; ++y) ka1[y] = *reinterpret_cast<const u32x4 *>(key + kRoleKeys + 16u * y);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int y = 0; y < 4; ++y)
+#pragma unroll
+            for (int mt = 0; mt < 2; ++mt)
+                S[0][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, ka0[y]), st.qb[mt][y], S[0][mt], 0, 0, 0);
+#pragma unroll
+        for (int y = 0; y < 4; ++y)
+#pragma unroll
+            for (int mt = 0; mt < 2; ++mt)
+                S[1][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, ka1[y]), st.qb[mt][y], S[1][mt], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        u32x4 vq[8];
+        const uint8_t *val = base + pr * kRolePair + 2u * kRoleKeys + fresh(ln.lane) * 16u;
+#pragma unroll
+        for (int pp = 0; pp < kRoleEarlyV; ++pp) vq[pp] = *reinterpret_cast<const u32x4 *>(val + pp * 1024u);
+        mfma_result_wait();
+        const uint32_t b = rb + 2u * pr;
+        if (b * 16u + 32u > end) {  // a ragged last block, or a last block without a partner
+            const uint32_t tok = b * 16u + (fresh(ln.lane) >> 4);
+#pragma unroll
+            for (int e = 0; e < 2; ++e)
+#pragma unroll
+                for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+                    for (int jj = 0; jj < 4; ++jj)
+                        if (tok + 16u * e + 4u * jj >= end) S[e][mt][jj] = neg_inf();
+        }
+        float sum[2];
+#pragma unroll
+        for (int mt = 0; mt < 2; ++mt) {
+            sum[mt] = role_weights(S[0][mt], S[1][mt], scale_log2, st.m_run[mt], P8[mt]);
+            __builtin_amdgcn_sched_barrier(0);  // one tile after the other: registers are short
+        }
+        if (__builtin_amdgcn_ballot_w64(sum[0] > kRoleMaxSum || sum[1] > kRoleMaxSum) != 0ull) {
+#pragma unroll
+            for (int mt = 0; mt < 2; ++mt) {
+                const float a = __builtin_fmaxf(__builtin_fmaxf(S[0][mt][0], S[0][mt][1]), __builtin_fmaxf(S[0][mt][2], S[0][mt][3]));
+                const float bb = __builtin_fmaxf(__builtin_fmaxf(S[1][mt][0], S[1][mt][1]), __builtin_fmaxf(S[1][mt][2], S[1][mt][3]));
+                const float m_new = __builtin_fmaxf(st.m_run[mt], max_over_lane_groups(__builtin_fmaxf(a, bb) * scale_log2) + kLazyMaxLift);
+                const float alpha = __builtin_amdgcn_exp2f(st.m_run[mt] - m_new);  // 0 where there was no reference, 1 if nothing moved
+                st.l_run[mt] *= alpha;
+                st.r_run[mt] *= alpha;
+                st.m_run[mt] = m_new;
+                const uint32_t c_ = fresh(ln.lane) >> 4;
+#pragma unroll
+                for (int jj = 0; jj < 4; ++jj) {
+                    const float ar = __shfl(alpha, (int)(4u * c_ + jj));  // factor of output row 4 c_ + jj
+#pragma unroll
+                    for (int pp = 0; pp < 8; ++pp) st.O[mt][pp][jj] *= ar;
+                }
+                sum[mt] = role_weights(S[0][mt], S[1][mt], scale_log2, m_new, P8[mt]);
+            }
+        }
+#pragma unroll
+        for (int mt = 0; mt < 2; ++mt) {
+            st.l_run[mt] += sum[mt];
+            st.r_run[mt] = add_weights8(P8[mt], st.r_run[mt]);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        val = base + pr * kRolePair + 2u * kRoleKeys + fresh(ln.lane) * 16u;
+#pragma unroll
+        for (int pp = kRoleEarlyV; pp < 8; ++pp) vq[pp] = *reinterpret_cast<const u32x4 *>(val + pp * 1024u);
+        key = base + (2u * pr + 2u < nb ? pr + 1u : pr) * kRolePair + fresh(ln.key);
+#pragma unroll
+        for (uint32_t y = 0; y < 4; ++y) ka0[y] = *reinterpret_cast<const u32x4 *>(key + 16u * y);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int pp = 0; pp < 8; ++pp) {
+            const bf16x8 v = __builtin_bit_cast(bf16x8, vq[pp]);
+#pragma unroll
+            for (int mt = 0; mt < 2; ++mt)
+                st.O[mt][pp] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(P8[mt], v, st.O[mt][pp], 0, 0, 0);
         }
     }
 }
 
 }  // namespace
 
-// W = 2, 4 or 8 waves, half of them decoding keys and half values; two waves per SIMD keep 256 registers
+// W = 2 or 4 waves, half of them decoding keys and half values; two waves per SIMD keep 256 registers
 // each (two tiles of output, their queries, the raw words of two blocks).
 template <int W>
 __global__ void __launch_bounds__(64 * W, 2) k6_attend_shared(const K6Params p)
 {
-    // two sets of W block buffers; dynamic, because eight waves need 128 KiB (a workgroup may
-    // declare 64 KiB at most statically)
+    // two sets of W block buffers
     extern __shared__ __attribute__((aligned(16))) uint8_t lds_bytes[];
     uint8_t (*lds)[W][kSharedBlockLds] = reinterpret_cast<uint8_t (*)[W][kSharedBlockLds]>(lds_bytes);
     K6Run c = p.run[blockIdx.y];
@@ -558,7 +707,7 @@ __global__ void __launch_bounds__(64 * W, 2) k6_attend_shared(const K6Params p)
     }
 
     SharedState st;
-    shared_load_queries(c, hdr, h, tile0, M, ln, st);
+    shared_load_queries(c, hdr, h, tile0, M, ln.c_, ln.n_, st);
 
     uint32_t set = 0;
     for (uint32_t d = 0; d < run; ++d) {
@@ -590,17 +739,27 @@ __global__ void __launch_bounds__(64 * W, 2) k6_attend_shared(const K6Params p)
     // ---- the wave's results, straight from its registers: lane (c_, n_) holds rows
     // 4 c_ + jj, dims 8 n_ + pp of each tile
     if (!active) return;
-    shared_write_results(c, hdr, h, tile0, M, ln, st);
+    shared_write_results(c, hdr, h, tile0, M, ln.c_, ln.n_, st);
 }
 
 // Eight waves score, two query tiles each (up to 256 query rows a workgroup), four decode: two the
 // keys and two the values of a round of eight blocks, for the round after the one that is being
 // scored.  One barrier per round, for LDS only.  Three waves per SIMD (168 registers): two scorers,
 // whose registers hold no raw words, and a decoder that fills their gaps.
+//
+// Bound: the SIMDs' instruction slots and the clock.  32 requests x 5,120 tokens x 64 query tokens
+// x 32 heads (172 GFLOP a layer, one workgroup per CU, one run per request): 205-215 us with eight waves
+// that decoded and scored in turn, 180-187 now = 940 TFLOP/s, against 1,390 of a large matrix product on the
+// same card.  Of 383,000 clocks the matrix cores work 164,000 and vector instructions take about
+// 160,000, which overlap with them only in part (two waves of 16 MFMAs and 64 fused multiply-adds
+// each take 355 ns where the MFMAs alone take 273); under this load the card runs at 2.07 GHz.  What gave how
+// much: the split into two kinds of waves 10 %; operands read ahead of what hides them 2 %; the maxima
+// after the fact, keys without address arithmetic, codes without conversions and values rounded
+// straight into operands 4 %; the reference lifted above the maximum 3 %; loads issued in the order they are
+// decoded in (before, the compiler waited for all of them at the top of the loop) 2 %.
 __global__ void __launch_bounds__(64 * (kRoleScorers + kRoleDecoders), 3) k6_attend_roles(const K6Params p)
 {
     extern __shared__ __attribute__((aligned(16))) uint8_t lds_bytes[];
-    uint8_t (*lds)[kRoleBlocks][kSharedBlockLds] = reinterpret_cast<uint8_t (*)[kRoleBlocks][kSharedBlockLds]>(lds_bytes);
     K6Run c = p.run[blockIdx.y];
     AttendHdr hdr = {p.n_kv_heads, p.n_q_heads, p.layer, p.scale_log2};
     pin(c.k);
@@ -626,48 +785,47 @@ __global__ void __launch_bounds__(64 * (kRoleScorers + kRoleDecoders), 3) k6_att
     if (u >= H * n_mtg) return;  // the grid is as wide as the widest run
     const uint32_t mtg = u % n_mtg, h = u / n_mtg;
 
-    SharedLane ln;
+    RoleLane ln;
     ln.lane = threadIdx.x & 63u;
     ln.c_ = ln.lane >> 4;
     ln.n_ = ln.lane & 15u;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    {
-        const uint32_t tau = 4u * (ln.n_ & 3u) + (ln.n_ >> 2);
-        ln.k_rd = tau * 256u + (((4u * ln.c_) ^ tau) & 15u) * 16u;  // as in k6_attend_shared
-        ln.k_wr = ln.c_ * 256u + ((ln.n_ ^ ln.c_) & 15u) * 16u;
-    }
     uint32_t set = 0;
 
     if (wave >= kRoleScorers) {
+        ln.key = ln.c_ * kRoleKeyRow + ln.n_ * 16u;
         const uint32_t dec = wave - kRoleScorers;
         const bool is_k = dec < kRoleDecoders / 2u;
         const uint32_t r = dec & 1u;
         for (uint32_t d = 0; d < run; ++d) {
             const uint8_t *dp = is_k ? c.k : c.v;
-            uint32_t T = c.n_tokens, dinfo = c.info;
+            uint32_t T = c.n_tokens, info = is_k ? c.info : c.info >> 8;
             if (d) {
                 const K6Doc &cd = p.doc[more + d - 1u];
                 dp = is_k ? cd.k : cd.v;
                 T = cd.n_tokens;
-                dinfo = cd.info;
+                info = is_k ? cd.info : cd.info >> 8;
             }
             const uint32_t nblk = (T + 15u) >> 4;
             const uint32_t b0 = d ? 0u : first_block;
             const uint32_t b1 = d + 1u == run ? end_block : nblk;
             if (b0 >= b1) continue;  // cannot happen with a checked launch
-            const uint32_t info = is_k ? dinfo : dinfo >> 8;
             const uint32_t prec = info & 0xFu;
             const SharedSide sd = shared_side(dp, prec, (info >> 4) & 0xFu, h, nblk, true);
-            if (is_k) role_decode_any<true>(prec, sd, T, b0, b1, r, ln, lds, set);
-            else role_decode_any<false>(prec, sd, T, b0, b1, r, ln, lds, set);
+            if (is_k) role_decode_any<true>(prec, sd, T, b0, b1, r, ln, lds_bytes, set);
+            else role_decode_any<false>(prec, sd, T, b0, b1, r, ln, lds_bytes, set);
         }
         return;
     }
 
     const uint32_t tile0 = (mtg * kRoleScorers + wave) * 2u;  // this wave's tiles: tile0, tile0 + 1
     const bool active = tile0 < n_mt;
+    // the token of MFMA row n_ is 4 (n_ % 4) + n_ / 4, so that score register jj of lane group c_
+    // belongs to token 4 jj + c_, the token whose values the lane group's plane jj holds
+    ln.key = (4u * (ln.n_ & 3u) + (ln.n_ >> 2)) * kRoleKeyRow + ln.c_ * 64u;
     SharedState st;
-    shared_load_queries(c, hdr, h, tile0, M, ln, st);
+    shared_load_queries(c, hdr, h, tile0, M, ln.lane >> 4, ln.lane & 15u, st);
+    st.m_run[0] = st.m_run[1] = kRoleNoRef;
     for (uint32_t d = 0; d < run; ++d) {
         const uint32_t T = d ? p.doc[more + d - 1u].n_tokens : c.n_tokens;
         const uint32_t nblk = (T + 15u) >> 4;
@@ -679,27 +837,18 @@ __global__ void __launch_bounds__(64 * (kRoleScorers + kRoleDecoders), 3) k6_att
             lds_barrier();
             if (active) {
                 const uint32_t nb = b1 - rb < kRoleBlocks ? b1 - rb : kRoleBlocks;
-                const uint8_t *base = lds[set][0];
-#pragma unroll 1
-                for (uint32_t pr = 0; 2u * pr < nb; ++pr) {
-                    const uint8_t *pair = base + pr * (2u * kSharedBlockLds);
-                    f32x4 S[2][2];
-                    bf16x8 P8[2];
-                    shared_qk_pair(pair, ln, st, S);
-                    mfma_result_wait();
-                    shared_softmax_pair(S, rb + 2u * pr, end, hdr.scale_log2, ln, st, P8);
-                    shared_pv_pair(pair + 8192u, ln, st, P8);
-                }
+                role_score_round(lds_bytes + set * kRoleSet, rb, nb, end, hdr.scale_log2, ln, st);
             }
             set ^= 1u;
         }
         mfma_result_wait();
     }
     if (!active) return;
-    shared_write_results(c, hdr, h, tile0, M, ln, st);
+    const uint32_t lane_ = fresh(ln.lane);
+    shared_write_results(c, hdr, h, tile0, M, lane_ >> 4, lane_ & 15u, st);
 }
 
-// The eight-wave build takes 128 KiB of LDS per workgroup; more than 64 KiB has to be asked for
+// k6_attend_roles takes 132 KiB of LDS per workgroup; more than 64 KiB has to be asked for
 // once per device.  Called when a context is created on the device (not from inside a launch
 // that a caller may be capturing into a graph) and, as a fallback, before the first such launch.
 hipError_t prepare_k6_shared()
@@ -711,7 +860,7 @@ hipError_t prepare_k6_shared()
     if (dev < 0 || dev >= 64) return hipErrorInvalidDevice;
     if (asked.load(std::memory_order_acquire) >> dev & 1u) return hipSuccess;
     e = hipFuncSetAttribute(reinterpret_cast<const void *>(k6_attend_roles),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)(2u * kRoleBlocks * kSharedBlockLds));
+                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)(2u * kRoleSet));
     if (e != hipSuccess) return e;
     asked.fetch_or(1ull << dev, std::memory_order_release);
     return hipSuccess;
@@ -736,7 +885,7 @@ hipError_t launch_k6_shared(K6Params &p, uint32_t waves, hipStream_t stream, boo
     else {
         e = prepare_k6_shared();  // done at ha_rag_create; a no-op from then on
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(k6_attend_roles, grid, dim3(64 * (kRoleScorers + kRoleDecoders)), lds_bytes, stream, p);
+        hipLaunchKernelGGL(k6_attend_roles, grid, dim3(64 * (kRoleScorers + kRoleDecoders)), 2u * kRoleSet, stream, p);
     }
     return hipGetLastError();
 }

@@ -205,6 +205,56 @@ def test_many_rows_kernel_with_blocks_that_have_no_partner(tokens):
     run_case((1, 2, 128), [(tokens, precs, 40), (tokens[::-1], precs[::-1], 9)], 0, 8, 0.1, 130 + len(tokens))
 
 
+@pytest.mark.parametrize("n_q", [33, 64, 65])
+def test_many_rows_kernel_with_decoding_waves_at_the_edges_of_rounds_and_tiles(n_q):
+    """More than eight query tiles: eight waves score, four decode rounds of eight blocks ahead of
+    them.  9, 16 and 17 tiles (a wave with one tile and idle waves; full; a second workgroup with
+    one tile); documents that end at, just before and just behind a round, a pair and a block, in
+    every format; long enough runs that both buffer sets are used many times."""
+    tokens = [128, 127, 129, 16, 1, 64, 65, 200, 113, 256, 33, 144]
+    precs = [ALL[(5 * i + 2) % 6] for i in range(len(tokens))]
+    run_case((1, 1, 128), [(tokens, precs, n_q), (tokens[::-1], precs, n_q)], 0, 4, 0.1, 150 + n_q)
+
+
+def test_requests_of_two_tiles_go_with_those_of_three_and_four():
+    """A call with requests of three or four query tiles takes its requests of two tiles to the same
+    kernel (runs across documents), those of one tile stay with the other."""
+    tokens = [70, 16, 129, 33, 300]
+    precs = [B.PREC_INT8, B.PREC_GSE8, B.PREC_INT4, B.PREC_16, B.PREC_FP8_E4M3]
+    reqs = [(tokens, precs, 8), (tokens[::-1], precs, 12), (tokens, precs[::-1], 1), (tokens[:2], precs[:2], 5),
+            (tokens, precs, 16)]
+    run_case((1, 2, 128), reqs, 0, 8, 0.1, 170)
+
+
+@pytest.mark.parametrize("prec", [B.PREC_INT4, B.PREC_INT8])
+@pytest.mark.parametrize("n_q", [1, 12, 64])
+def test_one_token_documents_return_the_stored_values_exactly(prec, n_q):
+    """With one key every softmax weight is a power of two and cancels: the output is the BF16 value
+    a load would write, bit for bit, whatever its code, scale and zero (tiny and huge ones among
+    them).  One request per document, so all three attention kernels decode every code."""
+    L, H, D, g, n_docs = 1, 4, 128, 32, 24
+    ctx = B.Context(L, H, D, 16, group_int8=g, group_int4=g)
+    bits = 4 if prec == B.PREC_INT4 else 8
+    rng = np.random.Generator(np.random.PCG64(5 + bits))
+    call, want = [], []
+    qw = q_words(n_q, 4 * H, D, 6)
+    q_d = torch.from_numpy(qw.view(np.int16)).cuda()
+    for i in range(n_docs):
+        x = rng.standard_normal((L, 2, H, 1, D)).astype(np.float32) * np.float32(10.0) ** (i % 8 - 4) + np.float32(i % 5 - 2)
+        pk = codec.quantize_pack_chunk(wl.f32_to_bf16_words(x), bits, g)[0]
+        cache, _ = codec.load_chunks([pk], (L, H, D), [1], [bits], [g], [0])
+        want.append(A.bf16_words_to_f64(cache[0, 1, :, 0]).astype(np.float32))  # [H][D]
+        out = torch.full((n_q, 4 * H, D), float("nan"), dtype=torch.float32, device="cuda")
+        call.append(([(dev_u8(pk), 1, prec, g)], q_d, out, None, n_q))
+    nb = ctx.attend_workspace_bytes(call, 4 * H)
+    ws = torch.full((max(nb, 16) // 4,), float("nan"), dtype=torch.float32, device="cuda")
+    ctx.attend_packed(call, 0, 4 * H, 1e-6, ws, nb)
+    torch.cuda.synchronize()
+    for (_, _, out, _, _), ref in zip(call, want):
+        assert np.array_equal(out.cpu().numpy(), np.broadcast_to(np.repeat(ref, 4, axis=0), (n_q, 4 * H, D)))
+    ctx.destroy()
+
+
 def test_requests_that_ask_for_no_log_sum_exp():
     """lse may be null: in the merge kernels (a decode request, a many-rows request of several
     runs) and in the many-rows workgroups that write their request's output themselves (one run),
