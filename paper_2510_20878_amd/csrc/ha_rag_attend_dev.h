@@ -211,4 +211,17 @@ __device__ __forceinline__ float max_over_lane_groups(float x)
     return __builtin_fmaxf(__builtin_bit_cast(float, t0), __builtin_bit_cast(float, t1));
 }
 
+// the sum over the same four lanes, in every lane, the same way
+__device__ __forceinline__ float sum_over_lane_groups(float x)
+{
+    typedef unsigned u2 __attribute__((ext_vector_type(2)));
+    const unsigned xi = __builtin_bit_cast(unsigned, x);
+    const u2 r = __builtin_amdgcn_permlane16_swap(xi, xi, false, false);
+    const unsigned r0 = r.x, r1 = r.y;
+    const unsigned yi = __builtin_bit_cast(unsigned, __builtin_bit_cast(float, r0) + __builtin_bit_cast(float, r1));
+    const u2 t = __builtin_amdgcn_permlane32_swap(yi, yi, false, false);
+    const unsigned t0 = t.x, t1 = t.y;
+    return __builtin_bit_cast(float, t0) + __builtin_bit_cast(float, t1);
+}
+
 }  // namespace ha_rag

@@ -261,11 +261,7 @@ blocks_done:
     // threads bring them to one maximum per row, add them up and write the record
 #pragma unroll
     for (int mt = 0; mt < MTW; ++mt) {
-        float l_tot = l_run[mt], r_tot = r_run[mt];
-        l_tot += __shfl_xor(l_tot, 16);
-        r_tot += __shfl_xor(r_tot, 16);
-        l_tot += __shfl_xor(l_tot, 32);
-        r_tot += __shfl_xor(r_tot, 32);
+        const float l_tot = sum_over_lane_groups(l_run[mt]), r_tot = sum_over_lane_groups(r_run[mt]);
         if (c_ == 0) {
             sm[wave][mt * 16 + n_] = m_run[mt];
             sl[wave][0][mt * 16 + n_] = l_tot;
@@ -692,12 +688,12 @@ hipError_t launch_k7(K7Params &p, hipStream_t stream, bool check_only)
     if (width > 0x7FFFFFFFull) return hipErrorInvalidValue;
     if (check_only) return hipSuccess;
     if (max_mt > 2u) {  // the requests of the shared kernel: merge tile by tile
-        // More groups where a group would need several rounds of loads and the launch is small enough
-        // for that to show (384 workgroups); with 1,936, most of them without a tile of their
-        // own, the large workgroups cost 0.7 us instead.
+        // Four groups where one would need more than four rounds of loads, in a launch small enough
+        // for that to show.  Large workgroups start more slowly: 5 records a tile in 256 workgroups
+        // took 2 us more with four groups, 1,936 workgroups (most without a tile) 0.7 us.
         const dim3 grid((uint32_t)tile_width, p.n_reqs);
-        const bool small = tile_width * p.n_reqs <= 2u * kChipCUs;
-        if (max_units <= 4u || !small) hipLaunchKernelGGL(k7_attend_merge_tiles<1>, grid, dim3(256), 0, stream, p);
+        if (max_units <= 16u || tile_width * p.n_reqs > 2u * kChipCUs)
+            hipLaunchKernelGGL(k7_attend_merge_tiles<1>, grid, dim3(256), 0, stream, p);
         else hipLaunchKernelGGL(k7_attend_merge_tiles<4>, grid, dim3(1024), 0, stream, p);
         return hipGetLastError();
     }

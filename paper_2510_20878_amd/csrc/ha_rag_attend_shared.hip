@@ -477,11 +477,7 @@ __device__ __forceinline__ void shared_write_results(const K6Run &c, const Atten
     for (int mt = 0; mt < 2; ++mt) {
         const uint32_t tile = tile0 + mt;
         if (tile >= n_mt) continue;
-        float l_tot = st.l_run[mt], r_tot = st.r_run[mt];
-        l_tot += __shfl_xor(l_tot, 16);
-        r_tot += __shfl_xor(r_tot, 16);
-        l_tot += __shfl_xor(l_tot, 32);
-        r_tot += __shfl_xor(r_tot, 32);
+        const float l_tot = sum_over_lane_groups(st.l_run[mt]), r_tot = sum_over_lane_groups(st.r_run[mt]);
         if (final) {
             // The run is everything the request attends to: what the merge would do with its one
             // record is done here.  l_tot of row n_ is in every lane of column n_; the rows this
