@@ -11,6 +11,7 @@
 // reads 16-byte word i of a 1024-byte run and writes 16-byte word i of four
 // 1024-byte runs: every memory instruction of a wave covers one contiguous KiB.
 #include <algorithm>
+#include <type_traits>
 
 #include "ha_rag_kernels.h"
 #include "ha_rag_decode.h"
@@ -403,6 +404,9 @@ __device__ __forceinline__ void group_minmax(float &mn, float &mx)
     }
 }
 
+// Packed bytes are stored nontemporally (here and in the other packing kernels): nothing reads them
+// soon, and written through the caches they pushed out what was still to be read.  Ten 512-token chunks
+// of the 8B shape by class: int8 54 -> 48 us (6.3 TB/s), int4 75.9 -> 70.8 (6.0), 16-bit 43.2 -> 41.4 (6.5).
 template <int BITS, int GSH>
 __global__ void __launch_bounds__(256) k2_quantize_pack(const K2Params p)
 {
@@ -505,15 +509,15 @@ __global__ void __launch_bounds__(256) k2_quantize_pack(const K2Params p)
         }
     }
     if (BITS == 4) {
-        st16<false>(pay + (uint64_t)blk * pay_blk + lane * 16u,
+        st16<true>(pay + (uint64_t)blk * pay_blk + lane * 16u,
                     u32x4{code_lo[0], code_lo[1], code_lo[2], code_lo[3]});
     } else {
         uint8_t *o = pay + (uint64_t)blk * pay_blk + lane * 16u;
-        st16<false>(o, u32x4{code_lo[0], code_hi[0], code_lo[1], code_hi[1]});
-        st16<false>(o + 1024, u32x4{code_lo[2], code_hi[2], code_lo[3], code_hi[3]});
+        st16<true>(o, u32x4{code_lo[0], code_hi[0], code_lo[1], code_hi[1]});
+        st16<true>(o + 1024, u32x4{code_lo[2], code_hi[2], code_lo[3], code_hi[3]});
     }
     if ((lane & (lanes_per_group - 1)) == 0) {  // first lane of each group
-        st16<false>(meta + (uint64_t)blk * meta_blk + ((lane * 8u) >> GSH) * 16u, mrow);
+        st16<true>(meta + (uint64_t)blk * meta_blk + ((lane * 8u) >> GSH) * 16u, mrow);
         if (saturated != nullptr && n_sat) atomicAdd(saturated, n_sat);
     }
 }
@@ -533,7 +537,7 @@ __global__ void __launch_bounds__(64) k2_pack16(const K2Params p)
     const uint32_t e = pl * 512u + threadIdx.x * 8u;
     u32x4 w = u32x4{0, 0, 0, 0};
     if (e < n_e) w = ld16s<true>(src + ((uint64_t)tile * n_e + e) * 2u);
-    st16<false>(dst + ((uint64_t)tile * planes_per_tile * 512u + e) * 2u, w);
+    st16<true>(dst + ((uint64_t)tile * planes_per_tile * 512u + e) * 2u, w);
 }
 
 // FP8 tags: every element is rounded on its own (nearest, ties to even, by the hardware
@@ -581,8 +585,8 @@ __global__ void __launch_bounds__(256) k2_pack_fp8(const K2Params p)
         }
     }
     uint8_t *o = dst + (uint64_t)tile * nblk * 2048u + (uint64_t)blk * 2048u + lane * 16u;
-    st16<false>(o, u32x4{code[0][0], code[0][1], code[1][0], code[1][1]});
-    st16<false>(o + 1024, u32x4{code[2][0], code[2][1], code[3][0], code[3][1]});
+    st16<true>(o, u32x4{code[0][0], code[0][1], code[1][0], code[1][1]});
+    st16<true>(o + 1024, u32x4{code[2][0], code[2][1], code[3][0], code[3][1]});
 }
 
 // GSE-8: one workgroup of up to 16 waves per tile (a tile is the unit that shares an exponent
@@ -598,38 +602,82 @@ __device__ __forceinline__ u16x2 splat16(uint32_t v)
     return u16x2{(uint16_t)v, (uint16_t)v};
 }
 
-// the two codes of one dword of BF16 words, one per 16-bit half (code in the low byte).
-// lo: biased e_lo; lo7: e_lo + 2 + 5 and hi5: e_hi + 5, the shared exponents with the shift's
-// constant folded in
-__device__ __forceinline__ uint32_t gse8_encode_pair(uint32_t r, u16x2 lo, u16x2 lo7, u16x2 hi5)
+// What the encoding of a tile needs, the same in both halves: lo = biased e_lo; lo7 = e_lo + 2 + 5
+// and hi5 = e_hi + 5, the shared exponents with the shift's constant folded in; and constants, kept
+// in vector registers so that masking and setting a bit is one instruction.
+struct Gse8Enc {
+    u16x2 lo, lo7, hi5;
+    uint32_t low7, lead;
+};
+
+// Index and field (no sign) of the two BF16 words of a dword, one code per 16-bit half.
+// FEW_LOW: no exponent the tile shares lies near the bottom of the format (biased e_lo >= 4), so
+// zeros and subnormals, whose leading one is not there, are shifted out whether or not it is set.
+template <bool FEW_LOW>
+__device__ __forceinline__ u16x2 gse8_encode_pair(uint32_t r, const Gse8Enc &c)
 {
     const uint32_t magw = r & 0x7FFF7FFFu;
     const u16x2 mag = __builtin_bit_cast(u16x2, magw);
-    const u16x2 eb = __builtin_elementwise_max(mag >> splat16(7), splat16(1));  // subnormal: 1
-    const u16x2 rel = __builtin_elementwise_sub_sat(eb, lo);                    // exponent above e_lo
-    const u16x2 k = (rel * splat16(171)) >> splat16(9);                         // rel / 3, rel < 254
+    u16x2 eb = mag >> splat16(7);
+    if (!FEW_LOW) eb = __builtin_elementwise_max(eb, splat16(1));               // subnormal: 1
+    const u16x2 rel = __builtin_elementwise_sub_sat(eb, c.lo);                  // exponent above e_lo, at most 47
+    const u16x2 k = (rel * splat16(43)) >> splat16(7);                          // rel / 3
     // G + 5, G the k-th shared exponent min(e_lo + 2 + 3k, e_hi)
-    const u16x2 g5 = __builtin_elementwise_min(k * splat16(3) + lo7, hi5);
+    const u16x2 g5 = __builtin_elementwise_min(k * splat16(3) + c.lo7, c.hi5);
     // significand with its leading one (none for subnormals) as an 8-bit integer: |x| =
     // sig / 128 * 2^(eb - 127), so floor(|x| * 2^(2 - G)) = sig >> (G - eb + 5); G >= eb always.
-    // min(mag, low seven bits | 0x80) is that integer: a normal value is at least 0x80
-    const u16x2 sig = __builtin_elementwise_min(mag, __builtin_bit_cast(u16x2, (magw & 0x007F007Fu) | 0x00800080u));
+    u16x2 sig = __builtin_bit_cast(u16x2, (magw & c.low7) | c.lead);
+    // min(mag, that) is that integer also without a leading one: a normal value is at least 0x80
+    if (!FEW_LOW) sig = __builtin_elementwise_min(mag, sig);
     const u16x2 sh = __builtin_elementwise_min(g5 - eb, splat16(15));
-    const u16x2 field = sig >> sh;                                               // 0..7
-    // a zero field is stored with index 0
-    // (0 - min(field, 1)) is all ones in a half with a nonzero field, else zero
-    const uint32_t keep = __builtin_bit_cast(uint32_t, (u16x2)(splat16(0) - __builtin_elementwise_min(field, splat16(1))));
-    const uint32_t k8 = __builtin_bit_cast(uint32_t, (u16x2)(k << splat16(3)));
-    return ((k8 & keep) | __builtin_bit_cast(uint32_t, field)) | ((r >> 8) & 0x00800080u);
+    // A zero field is stored with index 0, and has it: in an unclipped group the shift is 5, 6 or 7,
+    // which leaves a field of at least 1, so a zero field means an exponent at or below e_lo.
+    return k * splat16(8) + (sig >> sh);
 }
 
+// the four codes of two dwords, signs included (bit 7 of each from bit 15 of its word)
+template <bool FEW_LOW>
+__device__ __forceinline__ uint32_t gse8_encode_quad(uint32_t r0, uint32_t r1, const Gse8Enc &c)
+{
+    const uint32_t c01 = __builtin_bit_cast(uint32_t, gse8_encode_pair<FEW_LOW>(r0, c));
+    const uint32_t c23 = __builtin_bit_cast(uint32_t, gse8_encode_pair<FEW_LOW>(r1, c));
+    return (__builtin_amdgcn_perm(r1, r0, 0x07050301u) & 0x80808080u) | __builtin_amdgcn_perm(c23, c01, 0x06040200u);
+}
+
+// the larger of each half, over the lanes of a wave (every lane gets it)
+template <int CTRL>
+__device__ __forceinline__ uint32_t pk_max_dpp(uint32_t v)
+{
+    const uint32_t o = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, true);
+    return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(u16x2, v), __builtin_bit_cast(u16x2, o)));
+}
+__device__ __forceinline__ uint32_t pk_max_wave(uint32_t v)
+{
+    v = pk_max_dpp<0xB1>(v);   // lane ^ 1
+    v = pk_max_dpp<0x4E>(v);   // lane ^ 2
+    v = pk_max_dpp<0x141>(v);  // the other four of each eight
+    v = pk_max_dpp<0x140>(v);  // the other eight of each row of sixteen
+#pragma unroll
+    for (int o = 16; o <= 32; o <<= 1) {
+        const uint32_t x = (uint32_t)__shfl_xor((int)v, o);
+        v = __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(u16x2, v), __builtin_bit_cast(u16x2, x)));
+    }
+    return v;
+}
+
+// Bound: memory once the encoding is 15 packed instructions per two values (it was 26: the index of
+// a zero field needs no masking, the signs of four codes are merged at once, and constants sit
+// in registers).  Seven ragged chunks of 2,351 tokens in all (462 MB read and written): 122 -> 99 us; with
+// loads and stores that bypass the caches, 86 us = 5.4 TB/s.  Eight or four waves per tile with more
+// blocks each measured the same.
+//
 // HELD: blocks of the tile that every wave keeps in registers between the two passes (the
 // tile is then read once); 0: the tile is longer than 16 waves can hold and pass 2 reads it
 // again.
 template <int HELD>
 __global__ void __launch_bounds__(1024) k2_pack_gse8(const K2Params p)
 {
-    __shared__ uint32_t s_lo[16], s_hi[16];
+    __shared__ uint32_t s_range[16];
     const K2Chunk c = p.c[blockIdx.y];
     const uint8_t *__restrict__ src = c.src;
     uint8_t *__restrict__ dst = c.dst;
@@ -650,7 +698,7 @@ __global__ void __launch_bounds__(1024) k2_pack_gse8(const K2Params p)
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             const uint32_t ej = e + j * 512;
-            planes[j] = ld16(in + (uint64_t)(ej < n_e ? ej : 0u) * 2u);
+            planes[j] = ld16s<(HELD > 0)>(in + (uint64_t)(ej < n_e ? ej : 0u) * 2u);  // read once, unless the tile is read twice
         }
     };
     // The range follows from the largest magnitude and the smallest nonzero one (the exponent
@@ -683,33 +731,29 @@ __global__ void __launch_bounds__(1024) k2_pack_gse8(const K2Params p)
             range_block(held[0]);
         }
     }
-    // magnitudes -> biased exponents (a subnormal counts as 1; no nonzero value: 0xFFFF)
+    // both extremes as maxima, one in each half: the complement of the smallest nonzero magnitude - 1,
+    // and the largest magnitude
     const uint32_t lo_pair = __builtin_bit_cast(uint32_t, lo2), hi_pair = __builtin_bit_cast(uint32_t, hi2);
-    const uint32_t min_m1 = (lo_pair & 0xFFFFu) < (lo_pair >> 16) ? (lo_pair & 0xFFFFu) : (lo_pair >> 16);
-    const uint32_t max_m = (hi_pair & 0xFFFFu) > (hi_pair >> 16) ? (hi_pair & 0xFFFFu) : (hi_pair >> 16);
+    const uint32_t min_own = (lo_pair & 0xFFFFu) < (lo_pair >> 16) ? (lo_pair & 0xFFFFu) : (lo_pair >> 16);
+    const uint32_t max_own = (hi_pair & 0xFFFFu) > (hi_pair >> 16) ? (hi_pair & 0xFFFFu) : (hi_pair >> 16);
+    uint32_t range = pk_max_wave((min_own ^ 0xFFFFu) | (max_own << 16));
+    if (lane == 0) s_range[wave] = range;
+    __syncthreads();
+    range = s_range[0];
+    for (uint32_t w = 1; w < n_waves; ++w)
+        range = __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(u16x2, range), __builtin_bit_cast(u16x2, s_range[w])));
+    const uint32_t min_m1 = __builtin_amdgcn_readfirstlane((range & 0xFFFFu) ^ 0xFFFFu);
+    const uint32_t max_m = __builtin_amdgcn_readfirstlane(range >> 16);
+    // magnitudes -> biased exponents (a subnormal counts as 1; no nonzero value: 0xFFFF)
     uint32_t lo = min_m1 == 0xFFFFu ? 0xFFFFu : ((min_m1 + 1u) >> 7 ? (min_m1 + 1u) >> 7 : 1u);
     uint32_t hi = max_m >> 7 ? max_m >> 7 : 1u;
-    for (int o = 32; o >= 1; o >>= 1) {
-        const uint32_t l2 = (uint32_t)__shfl_xor((int)lo, o), h2 = (uint32_t)__shfl_xor((int)hi, o);
-        lo = l2 < lo ? l2 : lo;
-        hi = h2 > hi ? h2 : hi;
-    }
-    if (lane == 0) {
-        s_lo[wave] = lo;
-        s_hi[wave] = hi;
-    }
-    __syncthreads();
-    lo = s_lo[0];
-    hi = s_hi[0];
-    for (uint32_t w = 1; w < n_waves; ++w) {
-        lo = s_lo[w] < lo ? s_lo[w] : lo;
-        hi = s_hi[w] > hi ? s_hi[w] : hi;
-    }
     if (lo > hi) lo = hi = 127;          // all zero: range (e_lo, e_hi) = (0, 0)
     if (lo + 47 < hi) lo = hi - 47;      // 16 shared exponents, 3 apart, reach 48 binades
 
-    const u16x2 vlo = splat16(lo), vlo2 = splat16(lo + 7u), vhi = splat16(hi + 5u);
-    auto encode_block = [&](uint32_t blk, const u32x4 *planes) {
+    Gse8Enc enc = {splat16(lo), splat16(lo + 7u), splat16(hi + 5u), 0x007F007Fu, 0x00800080u};
+    asm("" : "+v"(enc.low7), "+v"(enc.lead));
+    auto encode_block = [&](auto few_low, uint32_t blk, const u32x4 *planes) {
+        constexpr bool kFewLow = decltype(few_low)::value;
         const uint32_t e = blk * kBlockElems + lane * 8;
         uint32_t code[4][2];
 #pragma unroll
@@ -718,28 +762,31 @@ __global__ void __launch_bounds__(1024) k2_pack_gse8(const K2Params p)
             const bool live = e + j * 512 < n_e;  // the padding behind the tile's end is zero bytes
 #pragma unroll
             for (int d = 0; d < 2; ++d) {  // four elements -> one dword of codes
-                const uint32_t c01 = gse8_encode_pair(raw[2 * d], vlo, vlo2, vhi);
-                const uint32_t c23 = gse8_encode_pair(raw[2 * d + 1], vlo, vlo2, vhi);
-                code[j][d] = live ? __builtin_amdgcn_perm(c23, c01, 0x06040200u) : 0u;  // low bytes of the halves
+                const uint32_t quad = gse8_encode_quad<kFewLow>(raw[2 * d], raw[2 * d + 1], enc);
+                code[j][d] = live ? quad : 0u;
             }
         }
         uint8_t *o = rec + (uint64_t)blk * 2048u + lane * 16u;
-        st16<false>(o, u32x4{code[0][0], code[0][1], code[1][0], code[1][1]});
-        st16<false>(o + 1024, u32x4{code[2][0], code[2][1], code[3][0], code[3][1]});
+        st16<true>(o, u32x4{code[0][0], code[0][1], code[1][0], code[1][1]});
+        st16<true>(o + 1024, u32x4{code[2][0], code[2][1], code[3][0], code[3][1]});
     };
-    if (HELD > 0) {
+    auto encode_all = [&](auto few_low) {
+        if (HELD > 0) {
 #pragma unroll
-        for (int i = 0; i < kHold; ++i)
-            if (wave + i * n_waves < nblk) encode_block(wave + i * n_waves, held[i]);
-    } else {
-        for (uint32_t blk = wave; blk < nblk; blk += n_waves) {
-            load_block(blk, held[0]);
-            encode_block(blk, held[0]);
+            for (int i = 0; i < kHold; ++i)
+                if (wave + i * n_waves < nblk) encode_block(few_low, wave + i * n_waves, held[i]);
+        } else {
+            for (uint32_t blk = wave; blk < nblk; blk += n_waves) {
+                load_block(blk, held[0]);
+                encode_block(few_low, blk, held[0]);
+            }
         }
-    }
+    };
+    if (lo >= 4u) encode_all(std::true_type{});
+    else encode_all(std::false_type{});
     if (threadIdx.x == 0) {
         const uint32_t e_lo = (lo - 127u) & 0xFFu, e_hi = (hi - 127u) & 0xFFu;
-        st16<false>(rec + (uint64_t)nblk * 2048u, u32x4{e_lo | (e_hi << 8), 0, 0, 0});
+        st16<true>(rec + (uint64_t)nblk * 2048u, u32x4{e_lo | (e_hi << 8), 0, 0, 0});
     }
 }
 

@@ -405,6 +405,17 @@ def test_gse8_every_finite_bf16_value_in_tiles_of_different_ranges():
     _gse_roundtrip(src, 512)
 
 
+@pytest.mark.parametrize("lo_e", [1, 2, 3, 4, 5, 6])
+def test_gse8_tiles_whose_exponents_begin_at_the_bottom_of_the_format(lo_e):
+    """Tiles of biased exponents lo_e .. lo_e + width with zeros of both signs among them: the encoder
+    takes a shorter path from lo_e = 4 on, where a value without a leading one is shifted out anyway."""
+    words = np.arange(65536, dtype=np.uint32).astype(np.uint16)
+    e = (words >> 7) & 0xFF
+    tiles = [np.where((e >= lo_e) & (e <= lo_e + width), words, words & 0x8000).astype(np.uint16)
+             for width in (0, 1, 2, 3, 5, 47, 60, 100)]
+    _gse_roundtrip(np.stack(tiles).reshape(2, 2, 2, 512, 128), 512)
+
+
 @pytest.mark.parametrize("shape", [(2, 2, 64, 128), (1, 2, 128, 100), (1, 1, 128, 1), (2, 1, 96, 40),
                                    (1, 2, 128, 272)])
 def test_gse8_shapes(shape):
