@@ -43,7 +43,8 @@ struct AttendLds {
 template <uint32_t KP, uint32_t VP, int MTW, bool NARROW>
 __device__ __forceinline__ void attend_unit(const AttendHdr &p, const K6Run &c,
                                             uint32_t h, uint32_t mtg, uint8_t *lds_all,
-                                            float (*sm)[MTW * 16], float (*sl)[2][MTW * 16])
+                                            float (*sm)[MTW * 16], float (*sl)[2][MTW * 16],
+                                            float (*sf)[MTW * 16])
 {
     typedef Fmt<KP> FK;
     typedef Fmt<VP> FV;
@@ -128,6 +129,9 @@ __device__ __forceinline__ void attend_unit(const AttendHdr &p, const K6Run &c,
         if (FK::kMeta)
             r.km = *(const uint32_t __attribute__((address_space(1))) *)(kmeta + ((uint64_t)b * kmeta_blk + 4u * k_entry));
         if (FV::kMeta) r.vm = ldg16(vmeta + ((uint64_t)b * vmeta_blk + ((lane * 8u) >> vgsh) * 16u));
+        // Blocks are requested in the order they are worked on, before the loop as in it: the compiler
+        // turned the first ones round, and then waited at the top of the loop for all of them.
+        __builtin_amdgcn_sched_barrier(0);
     };
 
     // the waves of the workgroup take the blocks of the run in turn; each wave fetches its
@@ -278,41 +282,40 @@ blocks_done:
             dst[0] = f32x4{O[mt][0][jj], O[mt][1][jj], O[mt][2][jj], O[mt][3][jj]};
             dst[1] = f32x4{O[mt][4][jj], O[mt][5][jj], O[mt][6][jj], O[mt][7][jj]};
         }
-        __syncthreads();
         const uint32_t mtile = mtg * MTW + mt;
-        if (mtile >= n_mt) continue;
         gfloats rec = rec0 + (uint64_t)mtile * kAttendRecFloats;
-#pragma unroll
-        for (uint32_t k = 0; k < 512u / (64u * kAttendWaves); ++k) {  // 512 16-byte words of output per tile
-            const uint32_t i = threadIdx.x + 64u * kAttendWaves * k, row = mt * 16u + (i >> 5);
-            if (mtile * 16u + (i >> 5) >= M) continue;  // no query in this row: the merge never reads it
-            float m_all = sm[0][row];
-#pragma unroll
-            for (uint32_t w = 1; w < kAttendWaves; ++w) m_all = __builtin_fmaxf(m_all, sm[w][row]);
-            f32x4 sum = {0.f, 0.f, 0.f, 0.f};
-            float l_all = 0.0f, r_all = 0.0f;
-#pragma unroll
-            for (uint32_t w = 0; w < kAttendWaves; ++w) {
-                // a wave that had no block has m = -inf and l = 0: nothing to add
-                const float l_w = sl[w][0][row], f = l_w > 0.0f ? __builtin_amdgcn_exp2f(sm[w][row] - m_all) : 0.0f;
-                sum += reinterpret_cast<const f32x4 *>(acc + w * 2048u)[i] * f;
-                l_all = __builtin_fmaf(l_w, f, l_all);
-                r_all = __builtin_fmaf(sl[w][1][row], f, r_all);
-            }
-            // the merge divides by the record's unrounded sum
-            ((f32x4 __attribute__((address_space(1))) *)rec)[i] = sum * (r_all > 0.0f ? l_all / r_all : 0.0f);
-        }
-        if (threadIdx.x < 16u) {
+        if (threadIdx.x < 16u) {  // one thread a row: the waves' factors, and the row's maximum and sum
             const uint32_t row = mt * 16u + threadIdx.x;
             float m_all = sm[0][row];
 #pragma unroll
             for (uint32_t w = 1; w < kAttendWaves; ++w) m_all = __builtin_fmaxf(m_all, sm[w][row]);
-            float l_all = 0.0f;
+            float l_all = 0.0f, r_all = 0.0f, f[kAttendWaves];
 #pragma unroll
-            for (uint32_t w = 0; w < kAttendWaves; ++w)
-                if (sl[w][0][row] > 0.0f) l_all += sl[w][0][row] * __builtin_amdgcn_exp2f(sm[w][row] - m_all);
-            rec[2048 + threadIdx.x] = m_all;
-            rec[2048 + 16 + threadIdx.x] = l_all;
+            for (uint32_t w = 0; w < kAttendWaves; ++w) {
+                // a wave that had no block has m = -inf and l = 0: nothing to add
+                f[w] = sl[w][0][row] > 0.0f ? __builtin_amdgcn_exp2f(sm[w][row] - m_all) : 0.0f;
+                l_all = __builtin_fmaf(sl[w][0][row], f[w], l_all);
+                r_all = __builtin_fmaf(sl[w][1][row], f[w], r_all);
+            }
+            // the merge divides by the record's unrounded sum
+            const float fit = r_all > 0.0f ? l_all / r_all : 0.0f;
+#pragma unroll
+            for (uint32_t w = 0; w < kAttendWaves; ++w) sf[w][row] = f[w] * fit;
+            if (mtile < n_mt) {
+                rec[2048 + threadIdx.x] = m_all;
+                rec[2048 + 16 + threadIdx.x] = l_all;
+            }
+        }
+        __syncthreads();
+        if (mtile >= n_mt) continue;
+#pragma unroll
+        for (uint32_t k = 0; k < 512u / (64u * kAttendWaves); ++k) {  // 512 16-byte words of output per tile
+            const uint32_t i = threadIdx.x + 64u * kAttendWaves * k, row = mt * 16u + (i >> 5);
+            if (mtile * 16u + (i >> 5) >= M) continue;  // no query in this row: the merge never reads it
+            f32x4 sum = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (uint32_t w = 0; w < kAttendWaves; ++w) sum += reinterpret_cast<const f32x4 *>(acc + w * 2048u)[i] * sf[w][row];
+            ((f32x4 __attribute__((address_space(1))) *)rec)[i] = sum;
         }
     }
 }
@@ -323,24 +326,24 @@ blocks_done:
 template <uint32_t KP, uint32_t VP, int MTW, bool NARROW>
 __device__ __forceinline__ void attend_pair(const AttendHdr &hdr, const K6Run &c, uint32_t h,
                                             uint32_t mtg, uint8_t *lds, float (*sm)[MTW * 16],
-                                            float (*sl)[2][MTW * 16])
+                                            float (*sl)[2][MTW * 16], float (*sf)[MTW * 16])
 {
     if constexpr (!(NARROW && (KP == kP16 || VP == kP16)))
-        attend_unit<KP, VP, MTW, NARROW>(hdr, c, h, mtg, lds, sm, sl);
+        attend_unit<KP, VP, MTW, NARROW>(hdr, c, h, mtg, lds, sm, sl, sf);
 }
 
 template <uint32_t KP, int MTW, bool NARROW>
 __device__ __forceinline__ void attend_values(const AttendHdr &hdr, const K6Run &c, uint32_t h,
                                               uint32_t mtg, uint8_t *lds, float (*sm)[MTW * 16],
-                                              float (*sl)[2][MTW * 16])
+                                              float (*sl)[2][MTW * 16], float (*sf)[MTW * 16])
 {
     switch ((c.info >> 8) & 0xFu) {
-    case kP16: attend_pair<KP, kP16, MTW, NARROW>(hdr, c, h, mtg, lds, sm, sl); break;
-    case kInt8: attend_pair<KP, kInt8, MTW, NARROW>(hdr, c, h, mtg, lds, sm, sl); break;
-    case kInt4: attend_pair<KP, kInt4, MTW, NARROW>(hdr, c, h, mtg, lds, sm, sl); break;
-    case kE4M3: attend_pair<KP, kE4M3, MTW, NARROW>(hdr, c, h, mtg, lds, sm, sl); break;
-    case kE5M2: attend_pair<KP, kE5M2, MTW, NARROW>(hdr, c, h, mtg, lds, sm, sl); break;
-    default: attend_pair<KP, kGSE8, MTW, NARROW>(hdr, c, h, mtg, lds, sm, sl); break;
+    case kP16: attend_pair<KP, kP16, MTW, NARROW>(hdr, c, h, mtg, lds, sm, sl, sf); break;
+    case kInt8: attend_pair<KP, kInt8, MTW, NARROW>(hdr, c, h, mtg, lds, sm, sl, sf); break;
+    case kInt4: attend_pair<KP, kInt4, MTW, NARROW>(hdr, c, h, mtg, lds, sm, sl, sf); break;
+    case kE4M3: attend_pair<KP, kE4M3, MTW, NARROW>(hdr, c, h, mtg, lds, sm, sl, sf); break;
+    case kE5M2: attend_pair<KP, kE5M2, MTW, NARROW>(hdr, c, h, mtg, lds, sm, sl, sf); break;
+    default: attend_pair<KP, kGSE8, MTW, NARROW>(hdr, c, h, mtg, lds, sm, sl, sf); break;
     }
 }
 
@@ -354,6 +357,7 @@ __global__ void __launch_bounds__(64 * kAttendWaves, NARROW ? 3 : 2) k6_attend_p
 {
     __shared__ __attribute__((aligned(16))) uint8_t lds[AttendLds<MTW>::kBytes];
     __shared__ float sm[kAttendWaves][MTW * 16], sl[kAttendWaves][2][MTW * 16];  // reference; sums of the weights (unrounded, rounded)
+    __shared__ float sf[kAttendWaves][MTW * 16];                                 // what a wave's output rows are multiplied by
     // the whole descriptor and the header at once, before anything depends on a part of them
     K6Run c = p.run[blockIdx.y];
     AttendHdr hdr = {p.n_kv_heads, p.n_q_heads, p.layer, p.scale_log2};
@@ -378,12 +382,12 @@ __global__ void __launch_bounds__(64 * kAttendWaves, NARROW ? 3 : 2) k6_attend_p
     const uint32_t mtg = u % n_mtg;
     const uint32_t h = u / n_mtg;
     switch (c.info & 0xFu) {
-    case kP16: attend_values<kP16, MTW, NARROW>(hdr, c, h, mtg, lds, sm, sl); break;
-    case kInt8: attend_values<kInt8, MTW, NARROW>(hdr, c, h, mtg, lds, sm, sl); break;
-    case kInt4: attend_values<kInt4, MTW, NARROW>(hdr, c, h, mtg, lds, sm, sl); break;
-    case kE4M3: attend_values<kE4M3, MTW, NARROW>(hdr, c, h, mtg, lds, sm, sl); break;
-    case kE5M2: attend_values<kE5M2, MTW, NARROW>(hdr, c, h, mtg, lds, sm, sl); break;
-    default: attend_values<kGSE8, MTW, NARROW>(hdr, c, h, mtg, lds, sm, sl); break;
+    case kP16: attend_values<kP16, MTW, NARROW>(hdr, c, h, mtg, lds, sm, sl, sf); break;
+    case kInt8: attend_values<kInt8, MTW, NARROW>(hdr, c, h, mtg, lds, sm, sl, sf); break;
+    case kInt4: attend_values<kInt4, MTW, NARROW>(hdr, c, h, mtg, lds, sm, sl, sf); break;
+    case kE4M3: attend_values<kE4M3, MTW, NARROW>(hdr, c, h, mtg, lds, sm, sl, sf); break;
+    case kE5M2: attend_values<kE5M2, MTW, NARROW>(hdr, c, h, mtg, lds, sm, sl, sf); break;
+    default: attend_values<kGSE8, MTW, NARROW>(hdr, c, h, mtg, lds, sm, sl, sf); break;
     }
 }
 
