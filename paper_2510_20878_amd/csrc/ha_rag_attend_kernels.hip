@@ -466,10 +466,12 @@ hipError_t launch_k6(K6Params &p, hipStream_t stream, bool check_only)
 // ---------------------------------------------------------------------------
 constexpr uint32_t kMergeGroups = 32;  // at most: 1024 threads
 
-__global__ void __launch_bounds__(32 * kMergeGroups) k7_attend_merge(const K7Params p)
+// MAXG: groups the build has LDS and an unrolled end for; U: records a group has under way at a time.
+template <uint32_t MAXG, uint32_t U>
+__global__ void __launch_bounds__(32 * MAXG) k7_attend_merge(const K7Params p)
 {
-    __shared__ __attribute__((aligned(16))) float s_acc[kMergeGroups][128];
-    __shared__ float s_m[kMergeGroups], s_l[kMergeGroups];
+    __shared__ __attribute__((aligned(16))) float s_acc[MAXG][128];
+    __shared__ float s_m[MAXG], s_l[MAXG];
     // grid: x = row of the request (the grid is as wide as the largest), y = request; the
     // descriptor is fetched at once
     K7Req r = p.r[blockIdx.y];
@@ -492,17 +494,17 @@ __global__ void __launch_bounds__(32 * kMergeGroups) k7_attend_merge(const K7Par
     const uint64_t run_stride = (uint64_t)n_kv_heads * n_mt * kAttendRecFloats;  // records are [run][head][tile]
     const float *first = r.part + ((uint64_t)h * n_mt + mt) * kAttendRecFloats;
 
-    // Group g takes records g, g + n_g, ..., four at a time: their maxima, sums and this
+    // Group g takes records g, g + n_g, ..., U at a time: their maxima, sums and this
     // thread's four dims are fetched together (every thread of a group reads the same m and l:
     // broadcast loads), then folded into a running maximum like the blocks inside a record were.
     const uint32_t n_units = r.n_runs;
     float m_max = neg_inf(), l_sum = 0.0f;
     f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
-    for (uint32_t u0 = g; u0 < n_units; u0 += 4u * n_g) {
-        float m[4], l[4];
-        f32x4 o[4];
+    for (uint32_t u0 = g; u0 < n_units; u0 += U * n_g) {
+        float m[U], l[U];
+        f32x4 o[U];
 #pragma unroll
-        for (uint32_t k = 0; k < 4; ++k) {
+        for (uint32_t k = 0; k < U; ++k) {
             const bool have = u0 + k * n_g < n_units;
             const uint32_t u = have ? u0 + k * n_g : n_units - 1u;
             const float *rec = first + u * run_stride;
@@ -511,7 +513,7 @@ __global__ void __launch_bounds__(32 * kMergeGroups) k7_attend_merge(const K7Par
             o[k] = *reinterpret_cast<const f32x4 *>(rec + ri * 128u + 4u * d4);
         }
 #pragma unroll
-        for (uint32_t k = 0; k < 4; ++k) {
+        for (uint32_t k = 0; k < U; ++k) {
             if (l[k] > 0.0f) {  // the same for the whole group; an empty record holds no output rows
                 const float m_new = __builtin_fmaxf(m_max, m[k]);
                 const float fa = __builtin_amdgcn_exp2f(m_max - m_new);  // 0 at the first record
@@ -532,19 +534,19 @@ __global__ void __launch_bounds__(32 * kMergeGroups) k7_attend_merge(const K7Par
     const uint32_t d = threadIdx.x;
     if (d >= 128u) return;
     // every group's maximum and sum at once (no branch between the LDS reads), then the weights
-    float gm[kMergeGroups], gl[kMergeGroups];
+    float gm[MAXG], gl[MAXG];
 #pragma unroll
-    for (uint32_t i = 0; i < kMergeGroups; ++i) {
+    for (uint32_t i = 0; i < MAXG; ++i) {
         gm[i] = s_m[i];
         gl[i] = i < n_g ? s_l[i] : 0.0f;  // what lies beyond the launch's groups was never written
     }
     m_max = neg_inf();
 #pragma unroll
-    for (uint32_t i = 0; i < kMergeGroups; ++i) m_max = gl[i] > 0.0f ? __builtin_fmaxf(m_max, gm[i]) : m_max;
+    for (uint32_t i = 0; i < MAXG; ++i) m_max = gl[i] > 0.0f ? __builtin_fmaxf(m_max, gm[i]) : m_max;
     float out = 0.0f;
     l_sum = 0.0f;
 #pragma unroll
-    for (uint32_t i = 0; i < kMergeGroups; ++i) {
+    for (uint32_t i = 0; i < MAXG; ++i) {
         const float a = s_acc[i][d];
         const float w = __builtin_amdgcn_exp2f(gm[i] - m_max);
         out = gl[i] > 0.0f ? __builtin_fmaf(a, w, out) : out;
@@ -701,12 +703,20 @@ hipError_t launch_k7(K7Params &p, hipStream_t stream, bool check_only)
         else hipLaunchKernelGGL(k7_attend_merge_tiles<4>, grid, dim3(1024), 0, stream, p);
         return hipGetLastError();
     }
-    // one group per two records of the longest row if that fits (a group fetches four at a
-    // time), in whole waves, at least the 128 threads that write the row
-    const uint64_t want = (max_units + 1u) / 2u;
+    // Bound: the launch, one round of loads and the end that brings the groups together, which grows
+    // with the groups.  Up to 32 records one group per two of them (a group has four under way); more
+    // records: eight under way per group and as few groups as that allows.  In whole waves, at least the
+    // 128 threads that write the row, and a build whose end is no longer than it has to be: a batch's 10
+    // records a row 5.4 -> 4.3 us (it went over 32 groups at the end), one request's 80 records 4.7 (32 groups) -> 4.1.
+    const bool many = max_units > 32u;
+    const uint64_t want = many ? (max_units + 7u) / 8u : (max_units + 1u) / 2u;
     uint32_t groups = want < 4u ? 4u : want > kMergeGroups ? kMergeGroups : (uint32_t)want;
     groups = (groups + 1u) & ~1u;
-    hipLaunchKernelGGL(k7_attend_merge, dim3((uint32_t)width, p.n_reqs), dim3(32 * groups), 0, stream, p);
+    const dim3 grid((uint32_t)width, p.n_reqs), block(32 * groups);
+    if (many && groups <= 16u) hipLaunchKernelGGL((k7_attend_merge<16, 8>), grid, block, 0, stream, p);
+    else if (many) hipLaunchKernelGGL((k7_attend_merge<kMergeGroups, 8>), grid, block, 0, stream, p);
+    else if (groups <= 8u) hipLaunchKernelGGL((k7_attend_merge<8, 4>), grid, block, 0, stream, p);
+    else hipLaunchKernelGGL((k7_attend_merge<16, 4>), grid, block, 0, stream, p);
     return hipGetLastError();
 }
 

@@ -146,6 +146,16 @@ def test_many_long_chunks_take_long_pieces():
     run_case((1, 8, 128), reqs, 0, 16, 0.09, 45)
 
 
+@pytest.mark.parametrize("n_docs", [15, 16, 17, 31, 32, 33, 40, 128, 129, 256, 257])
+def test_merge_at_the_edges_of_its_builds(n_docs):
+    """One record per document (documents of one block): 16 / 17 and 32 / 33 records change the
+    build (groups of the end, records under way), 128 / 129 and 256 / 257 fill the larger builds'
+    groups once and begin a second round."""
+    tokens = [1 + (7 * i) % 16 for i in range(n_docs)]
+    precs = [ALL[(i * 5 + 1) % 6] for i in range(n_docs)]
+    run_case((1, 1, 128), [(tokens, precs, 2)], 0, 4, 0.11, 400 + n_docs)
+
+
 @pytest.mark.parametrize("n_docs", [1, 3, 8, 9, 63, 64, 65, 150, 300])
 def test_merge_of_one_request_with_few_and_with_many_records(n_docs):
     """The merge kernel shares a row's records between groups of threads (launch_k7): one record,
