@@ -352,9 +352,10 @@ struct RoleLane {
 };
 
 // One block of one side: decode what the lane has fetched and leave it in the pair's buffer
-// (`pair`, e = 0 / 1: first / second block of the pair).
+// (`pair`, e = 0 / 1: first / second block of the pair).  `end` = the first token that does not
+// count: the document's end, or that of the run's last block; values from there on are zeros.
 template <uint32_t P, bool IS_K>
-__device__ __forceinline__ void role_decode(const u32x4 *w, const u32x4 &m, const SharedSide &sd, uint32_t blk, uint32_t T,
+__device__ __forceinline__ void role_decode(const u32x4 *w, const u32x4 &m, const SharedSide &sd, uint32_t blk, uint32_t end,
                                             uint8_t *pair, int e, const RoleLane &ln)
 {
     if (IS_K) {
@@ -370,10 +371,10 @@ __device__ __forceinline__ void role_decode(const u32x4 *w, const u32x4 &m, cons
     uint32_t t01[8], t23[8];  // value pp of tokens 4 * 0 + c_ and 4 * 1 + c_, of 4 * 2 + c_ and 4 * 3 + c_
     decode_octets_by_token<P>(plane_raw<P>(w, 0), plane_raw<P>(w, 1), m[0], m[1], sd.base, sd.top, t01);
     decode_octets_by_token<P>(plane_raw<P>(w, 2), plane_raw<P>(w, 3), m[2], m[3], sd.base, sd.top, t23);
-    if (blk * 16u + 16u > T) {  // rows past the document's end
+    if (blk * 16u + 16u > end) {  // rows that do not count
         uint32_t keep[4];
 #pragma unroll
-        for (uint32_t j = 0; j < 4; ++j) keep[j] = blk * 16u + 4u * j + ln.c_ < T ? 0xFFFFu : 0u;
+        for (uint32_t j = 0; j < 4; ++j) keep[j] = blk * 16u + 4u * j + ln.c_ < end ? 0xFFFFu : 0u;
 #pragma unroll
         for (int pp = 0; pp < 8; ++pp) {
             t01[pp] &= keep[0] | (keep[1] << 16);
@@ -409,14 +410,14 @@ __device__ __forceinline__ void role_decode_rounds(const SharedSide &sd, uint32_
     };
 #pragma unroll
     for (int i = 0; i < 4; ++i) fetch(i, b0 + 4u * r + i);
+    const uint32_t end = b1 * 16u < T ? b1 * 16u : T;
     for (uint32_t rb = b0; rb < b1; rb += kRoleBlocks) {
-        // Blocks past the end are decoded like the others: the keys' scores are replaced, and the
-        // values, which the MFMAs take with weight zero, are numbers (zeros: all their tokens lie
-        // behind the document's, or run's, last).
+        // Blocks past the end are decoded like the others (from the last block's words): the keys'
+        // scores are replaced, and the values, which the MFMAs take with weight zero, are zeros.
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const uint32_t blk = rb + 4u * r + i;
-            role_decode<P, IS_K>(w[i], m[i], sd, blk, T, lds + set * kRoleSet + (2u * r + i / 2) * kRolePair, i & 1, ln);
+            role_decode<P, IS_K>(w[i], m[i], sd, blk, end, lds + set * kRoleSet + (2u * r + i / 2) * kRolePair, i & 1, ln);
             fetch(i, blk + kRoleBlocks);
         }
         lds_barrier();

@@ -783,3 +783,55 @@ def test_extreme_scores_and_values():
         check(out, lse, ref_out, ref_lse, spread, score_bound(cache, 0, T, qw, scale, H))
         assert abs(lse[0, 0] - np.log(T)) < 1e-5              # a zero query: uniform weights
     ctx.destroy()
+
+
+def attend_16_bit(kv, q, scale):
+    """One request over 16-bit documents kv (each binary32 [2][T][128], one KV head), queries q
+    [n_q][n_qh][128]: out and lse of the library (its workspace is of the size asked for, full of NaN), and
+    the cache and queries as BF16 words for the oracle."""
+    D, n_q, n_qh = 128, q.shape[0], q.shape[1]
+    srcs = [wl.f32_to_bf16_words(x[None, :, None]) for x in kv]
+    lens = [x.shape[1] for x in kv]
+    qw = wl.f32_to_bf16_words(q)
+    packs = [codec.quantize_pack_chunk(s, 16)[0] for s in srcs]
+    ctx = B.Context(1, 1, D, max(lens))
+    q_d = torch.from_numpy(qw.view(np.int16)).cuda()
+    out_d = torch.full((n_q, n_qh, D), float("nan"), dtype=torch.float32, device="cuda")
+    lse_d = torch.full((n_q, n_qh), float("nan"), dtype=torch.float32, device="cuda")
+    packs_d = [dev_u8(p) for p in packs]
+    call = [([(p, t, B.PREC_16, 0) for p, t in zip(packs_d, lens)], q_d, out_d, lse_d, n_q)]
+    nb = ctx.attend_workspace_bytes(call, n_qh)
+    ws = torch.full((max(nb, 16) // 4,), float("nan"), dtype=torch.float32, device="cuda")
+    ctx.attend_packed(call, 0, n_qh, scale, ws, nb)
+    torch.cuda.synchronize()
+    cache, _ = codec.load_chunks(packs, (1, 1, D), lens, [16] * len(lens), [128] * len(lens), list(range(len(lens))))
+    ctx.destroy()
+    return out_d.cpu().numpy(), lse_d.cpu().numpy(), cache, qw
+
+
+# query tokens of 4 heads on one KV head: one tile, two, three, six, sixteen and seventeen of 16 rows each,
+# i.e. both builds of the kernel of at most two tiles, the shared one with two and four waves, and the one with
+# eight scoring waves in one workgroup and in two
+TILES = [4, 8, 12, 24, 64, 65]
+
+
+@pytest.mark.parametrize("n_q", TILES)
+@pytest.mark.parametrize("lens", [[288], [144], [16], [33, 255]])
+def test_values_without_a_bound_stay_where_they_are(n_q, lens):
+    """An infinity among the values of a run's last block, which has no partner in its pair (runs of 9 and of 1
+    blocks; with [288] the run ends inside the document): it reaches its own dim of the result, with its
+    sign, and nothing else; the missing partner's weight of zero meets zeros."""
+    rng = np.random.default_rng(80)
+    kv = [rng.standard_normal((2, T, 128)).astype(np.float32) for T in lens]
+    at = 130 if lens[0] > 130 else 0                           # block 8, or block 0
+    kv[0][1, at, 5], kv[0][1, at, 6] = np.inf, -np.inf
+    if len(lens) > 1:
+        kv[1][1, 100, 5], kv[1][1, 100, 6] = np.inf, -np.inf   # block 6 of the second document: its run's tenth
+    q = 0.1 * rng.standard_normal((n_q, 4, 128)).astype(np.float32)
+    out, lse, cache, qw = attend_16_bit(kv, q, 0.088)
+    assert np.all(np.isposinf(out[..., 5])) and np.all(np.isneginf(out[..., 6]))
+    zeroed = np.where((cache & 0x7FFF) == 0x7F80, 0, cache).astype(np.uint16)
+    ref_out, ref_lse, spread = A.attend(zeroed, 0, sum(lens), qw, 0.088)
+    keep = np.r_[0:5, 7:128]
+    check(out[..., keep], lse, ref_out[..., keep], ref_lse, spread[..., keep],
+          score_bound(cache, 0, sum(lens), qw, 0.088, 1))
