@@ -530,8 +530,10 @@ __device__ __forceinline__ void shared_write_results(const K6Run &c, const Atten
 // How large the sum of a lane's eight weights of a pair and tile may get before the row's reference
 // maximum is brought up to date: no weight exceeds 2^kLazyMaxSlack.
 constexpr float kRoleMaxSum = 256.0f;
-// A reference that any score exceeds.  Finite: a masked score (-inf) minus it is still -inf.
-constexpr float kRoleNoRef = -1.0e30f;
+// The reference of a row that has none yet: the lowest number there is, which a row's first pair moves
+// (its weights overflow) unless its scores lie there themselves, and then their weights are right as they
+// are.  Finite: a masked score (-inf) minus it is still -inf.
+constexpr float kRoleNoRef = -__FLT_MAX__;
 constexpr int kRoleEarlyV = 6;  // V operands read before the softmax; the last two would not fit the registers
 
 // The weights of one tile and pair relative to the row's reference, and their sum in this lane.

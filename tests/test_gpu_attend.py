@@ -815,6 +815,72 @@ def attend_16_bit(kv, q, scale):
 TILES = [4, 8, 12, 24, 64, 65]
 
 
+@pytest.mark.parametrize("scale", [0.088, 3.0])
+@pytest.mark.parametrize("lens", [[70, 40, 90], [70, 40, 16, 130, 45, 33]])
+@pytest.mark.parametrize("n_q", TILES)
+def test_extreme_scores_and_values_in_every_attention_kernel(n_q, lens, scale):
+    """Query rows that are zero, tiny, huge and aligned with a key, several documents whose keys spread more
+    and more, with keys far out behind the blocks that set a row's first reference (in the same run and,
+    with the longer list, in another), ties, a dominant last valid token, values of both signs up to 1e30
+    and down to 1e-37."""
+    rng = np.random.default_rng(78)
+    kv = [rng.standard_normal((2, T, 128)).astype(np.float32) for T in lens]
+    for i, x in enumerate(kv):
+        x[0] *= np.float32(1.7) ** i
+    kv[0][0, 10] = kv[0][0, 11]                               # two identical keys
+    kv[1][0, 20] *= 30.0                                      # a key far out
+    kv[-1][0, -1] *= 50.0                                     # the last valid token dominates some rows
+    kv[0][1, 5], kv[0][1, 6] = 1e30, -1e30
+    kv[1][1, 3, :64] = 0.0
+    for x in kv:
+        x[1, :, 100:110] = 1e-37 * rng.standard_normal((x.shape[1], 10))
+    q = rng.standard_normal((n_q, 4, 128)).astype(np.float32)
+    q[0, 0] = 0.0
+    q[1, 1] *= 1e-20
+    q[2, 2] *= 40.0
+    q[3, 3] = kv[-1][0, -1] / 50.0
+    q[-1, 0] = -kv[1][0, 20] / 30.0                           # far below for the key far out
+    out, lse, cache, qw = attend_16_bit(kv, q, scale)
+    ref_out, ref_lse, spread = A.attend(cache, 0, sum(lens), qw, scale)
+    assert np.all(np.isfinite(out)) and np.all(np.isfinite(lse))
+    sabs = score_bound(cache, 0, sum(lens), qw, scale, 1)
+    check(out, lse, ref_out, ref_lse, spread, sabs)
+    assert abs(lse[0, 0] - np.log(sum(lens))) < 1e-5          # a zero query: uniform weights
+    tiny = np.s_[..., 100:110]                                # below the absolute part of check()'s bar
+    bar = (2.0 ** -8 + 2.0 ** -15 * (1.0 + sabs))[..., None] * spread[tiny]
+    # ... and of a sum of products below binary32's normal range: its own steps, one per block
+    assert np.all(np.abs(out[tiny].astype(np.float64) - ref_out[tiny]) <= bar + 64 * 2.0 ** -149)
+
+
+@pytest.mark.parametrize("n_q", TILES)
+def test_rows_whose_scores_all_lie_far_below_zero(n_q):
+    """Finite scores down to -2^122 (powers of two: exact in binary32, also times the scale) next to rows of
+    ordinary ones in the same tile: the largest still counts, whatever reference a row starts from."""
+    lens = [70, 40, 90]
+    rng = np.random.default_rng(79)
+    kv = [rng.standard_normal((2, T, 128)).astype(np.float32) for T in lens]
+    for x in kv:
+        x[0, :, 0] = -2.0 ** 60
+        x[0, 1::2, 0] = -2.0 ** 61                             # twice as far below: no weight
+    q = rng.standard_normal((n_q, 4, 128)).astype(np.float32)
+    q[:, :, 0] = 0.0
+    far = [2.0 ** 50, 2.0 ** 39, 2.0 ** 61]
+    for i, f in enumerate(far):
+        q[i % n_q, i] = 0.0
+        q[i % n_q, i, 0] = f
+    q[-1, :] = q[0, 0]                                         # a token all of whose rows are far below
+    is_far = q[:, :, 0] != 0
+    out, lse, cache, qw = attend_16_bit(kv, q, 0.088)
+    ref_out, ref_lse, spread = A.attend(cache, 0, sum(lens), qw, 0.088)
+    near = ~is_far
+    sabs = score_bound(cache, 0, sum(lens), qw, 0.088, 1)
+    check(out[near], lse[near], ref_out[near], ref_lse[near], spread[near], sabs[near])
+    # the far rows' scores are exact, so only the weights' rounding counts (all of them are equal); the
+    # log-sum-exp is that score times two constants in binary32
+    assert np.all(np.abs(out[is_far] - ref_out[is_far]) <= (2.0 ** -8 + 2.0 ** -15) * spread[is_far])
+    assert np.all(np.abs(lse[is_far] / ref_lse[is_far] - 1.0) <= 2.0 ** -21)
+
+
 @pytest.mark.parametrize("n_q", TILES)
 @pytest.mark.parametrize("lens", [[288], [144], [16], [33, 255]])
 def test_values_without_a_bound_stay_where_they_are(n_q, lens):
