@@ -110,9 +110,34 @@ uint32_t count_runs(const Plan &pl, const Doc *docs)
     return n;
 }
 
+// Steps of the longest of a request's runs of `len` blocks: a workgroup of the shared kernel takes
+// up to 1 << shift blocks at a time, all of one document.
+uint32_t longest_run_steps(const Plan &pl, const Doc *docs, uint32_t len, uint32_t shift)
+{
+    const uint32_t up = (1u << shift) - 1u;
+    uint32_t most = 0, steps = 0, left = len;
+    for (uint32_t i = 0; i < pl.n_docs; ++i) {
+        uint32_t nb = (docs[i].n_tokens + 15u) >> 4;
+        if (nb >= left) {  // a run ends in this document, the next ones lie inside it
+            steps += (left + up) >> shift;
+            if (steps > most) most = steps;
+            nb -= left;
+            if (nb >= len) {
+                nb %= len;
+                if ((len + up) >> shift > most) most = (len + up) >> shift;
+            }
+            steps = 0;
+            left = len;
+        }
+        steps += (nb + up) >> shift;
+        left -= nb;
+    }
+    return steps > most ? steps : most;
+}
+
 // Cuts every request into runs (plans[r].shared says by which kernel's rule) and lays the workspace
-// out.  Returns its size in binary32 words.
-uint64_t lay_out_runs(Plan *plans, uint32_t n_reqs, const Doc *docs, uint32_t H, uint32_t waves)
+// out.  Returns its size in binary32 words.  in_steps: see the cost of a run length.
+uint64_t lay_out_runs(Plan *plans, uint32_t n_reqs, const Doc *docs, uint32_t H, uint32_t waves, bool in_steps)
 {
     uint64_t total = 0;
     // A workgroup takes a run of its request's blocks and writes one record per query tile for
@@ -147,27 +172,58 @@ uint64_t lay_out_runs(Plan *plans, uint32_t n_reqs, const Doc *docs, uint32_t H,
     // four, 1.2 with two; a record costs the chip about 2 ns.  Without the last two terms three
     // requests of 96 to 201 query tokens took runs of 8 blocks, 0.9 GB of records: 460 us and
     // 210 us of merge per layer, against 220 and 9 with two runs per request.
+    // Blocks count in steps: a workgroup takes up to `waves` of them at a time, of one document, and the
+    // length's cost is that of the largest request's longest run.  Counted one by one, eight requests of
+    // four documents of 512 tokens took runs of 9 blocks instead of 8 at 12 query tokens (26.2 us per
+    // layer against 24.4), two of them in the paper's formats runs of 9 at 64 (28.4 against 26.0); counted
+    // in whole steps as if documents had no ends, 24 requests of four of 144 tokens took runs of 8
+    // instead of 9 at 16 (29.1 against 25.3).  (Not in_steps: one by one all the same, for a call whose
+    // records would otherwise not fit.)
     const uint64_t side_by_side = (uint64_t)kChipCUs * (8u / waves);  // two waves per SIMD: eight per CU
-    uint64_t most_blocks = 0;
+    const Plan *largest = nullptr;
     for (uint32_t r = 0; r < n_reqs; ++r)
-        if (plans[r].shared && plans[r].all_blocks > most_blocks) most_blocks = plans[r].all_blocks;
+        if (plans[r].shared && (!largest || plans[r].all_blocks > largest->all_blocks)) largest = &plans[r];
+    const uint64_t most_blocks = largest ? largest->all_blocks : 0;
+    const uint32_t shift = waves == 8u ? 3u : waves == 4u ? 2u : 1u;
+    const uint64_t all_steps = largest ? longest_run_steps(*largest, docs + largest->first_doc, ~0u, shift) : 0;
     const uint64_t recs_per_block = waves == 8u ? 280u : waves == 4u ? 450u : 600u;
-    uint64_t run_blocks = most_blocks, least = ~0ull;
+    uint64_t run_blocks = most_blocks, best = most_blocks, least = ~0ull, fewest = ~0ull;
     for (uint64_t n = 1; n <= most_blocks; ++n) {  // n runs for the largest request
         const uint64_t len = (most_blocks + n - 1u) / n;
         if (n > 1 && len < kAttendMinRunBlocks) break;
-        uint64_t wgs = 0, recs = 0;
+        uint64_t wgs = 0, recs = 0, my_wgs = 0, my_recs = 0;
+        const Plan *same = nullptr;  // requests of one size often follow one another
         for (uint32_t r = 0; r < n_reqs; ++r) {
             const Plan &pl = plans[r];
             if (!pl.shared) continue;
-            const uint64_t runs = (pl.all_blocks + len - 1u) / len;
-            wgs += runs * H * tile_groups(pl, waves);
-            if (runs > 1u) recs += runs * H * pl.n_mt;
+            if (!same || same->all_blocks != pl.all_blocks || same->n_mt != pl.n_mt) {
+                const uint64_t runs = (pl.all_blocks + len - 1u) / len;
+                my_wgs = runs * H * tile_groups(pl, waves);
+                my_recs = runs > 1u ? runs * H * pl.n_mt : 0u;
+                same = &pl;
+            }
+            wgs += my_wgs;
+            recs += my_recs;
         }
-        const uint64_t cost = (wgs + side_by_side - 1u) / side_by_side * (len + kAttendStartBlocks) + recs / recs_per_block;
-        if (cost < least) {
-            least = cost;
-            run_blocks = len;
+        const uint64_t rounds = (wgs + side_by_side - 1u) / side_by_side;
+        auto cost = [&](uint64_t blocks) { return rounds * (blocks + kAttendStartBlocks) + recs / recs_per_block; };
+        uint64_t c = cost(len);
+        if (in_steps) {
+            // The average of the runs (no run length's longest has fewer), which is close enough for runs of
+            // many documents; of a request of few the longest, if the average could do.
+            uint64_t steps = (len + waves - 1u) >> shift;
+            if (all_steps > steps * n) steps = (all_steps + n - 1u) / n;
+            c = cost(steps << shift);
+            if (c < least && largest->n_docs <= kAttendFewDocs)
+                c = cost((uint64_t)longest_run_steps(*largest, docs + largest->first_doc, (uint32_t)len, shift) << shift);
+        }
+        if (c < least) {
+            least = c;
+            best = len;
+        }
+        if (rounds * len < fewest) {  // more runs than here only for fewer rounds x blocks: it bounds the records
+            fewest = rounds * len;
+            run_blocks = best;
         }
         if (wgs >= 64u * side_by_side) break;  // finer than this gains nothing
     }
@@ -184,11 +240,11 @@ uint64_t lay_out_runs(Plan *plans, uint32_t n_reqs, const Doc *docs, uint32_t H,
 
 // Checks everything and lays the workspace out.  *floats = workspace size in binary32 words.
 // plans: n_reqs entries; docs, open_k, open_v: filled here, ENOSPC if one of them is too small
-// (never with lists as long as the call's chunk list).
+// (never with lists as long as the call's chunk list).  most_floats: what a workspace of fixed size holds.
 int plan_attend(ha_rag_ctx *c, const ha_rag_packed_chunk *chunks, const ha_rag_attend_request *reqs,
                 uint32_t n_reqs, uint32_t n_q_heads, Plan *plans, Fixed<Doc> *docs,
                 Fixed<uint32_t> open_k, Fixed<uint32_t> open_v, uint64_t *floats,
-                uint32_t *shared_waves, bool need_buffers)
+                uint32_t *shared_waves, bool need_buffers, uint64_t most_floats = ~0ull)
 {
     if (!c || !reqs || n_reqs == 0 || n_reqs > HA_RAG_MAX_ATTEND_REQUESTS) return HA_RAG_EINVAL;
     if (c->cfg.head_dim != kAttendHeadDim) return HA_RAG_EFORMAT;
@@ -270,25 +326,26 @@ int plan_attend(ha_rag_ctx *c, const ha_rag_packed_chunk *chunks, const ha_rag_a
     }
     const uint32_t waves = most_mt > 8u ? 8u : most_mt > 4u ? 4u : 2u;
     *shared_waves = waves;
-    uint64_t total = lay_out_runs(plans, n_reqs, docs->data, H, waves);
     // A call that needs the two-wave shared kernel anyway takes its requests of two query tiles there
     // as well: a block costs that kernel what it costs the other one (103 against 100 us per
     // call of 32 requests), and one launch fills the chip where two in a row do not (12 requests of
     // 6 to 16 query tokens: 48 against 63 us per layer).  Not if the partial results then took
     // more workspace.
-    if (most_mt && waves == 2u) {
+    auto lay_out = [&](bool in_steps) {
+        for (uint32_t r = 0; r < n_reqs; ++r) plans[r].shared = plans[r].n_mt > 2u;
+        const uint64_t apart = lay_out_runs(plans, n_reqs, docs->data, H, waves, in_steps);
+        if (!most_mt || waves != 2u) return apart;
         uint32_t moved = 0;
         for (uint32_t r = 0; r < n_reqs; ++r)
             if (plans[r].n_mt == 2u) plans[r].shared = moved = 1u;
-        if (moved) {
-            const uint64_t together = lay_out_runs(plans, n_reqs, docs->data, H, waves);
-            if (together <= total) total = together;
-            else {
-                for (uint32_t r = 0; r < n_reqs; ++r) plans[r].shared = plans[r].n_mt > 2u;
-                total = lay_out_runs(plans, n_reqs, docs->data, H, waves);
-            }
-        }
-    }
+        if (!moved) return apart;
+        const uint64_t together = lay_out_runs(plans, n_reqs, docs->data, H, waves, in_steps);
+        if (together <= apart) return together;
+        for (uint32_t r = 0; r < n_reqs; ++r) plans[r].shared = plans[r].n_mt > 2u;
+        return lay_out_runs(plans, n_reqs, docs->data, H, waves, in_steps);
+    };
+    uint64_t total = lay_out(true);
+    if (total > most_floats) total = lay_out(false);
     if (total * 4ull > (1ull << 40)) return HA_RAG_EINVAL;
     *floats = total;
     return HA_RAG_OK;
@@ -322,7 +379,8 @@ struct HeapPlanStore {
 };
 
 // checks, workspace layout and launches; the caller holds the context's lock.  *need (nullable)
-// receives the workspace bytes the lists ask for, also when the call then fails with ENOSPC.
+// receives the workspace bytes the lists ask for, also when the call then fails with ENOSPC; it is given
+// where the workspace's size is fixed and not the one asked for.
 int attend_locked(ha_rag_ctx *c, PlanStore ps, const ha_rag_packed_chunk *chunks,
                   const ha_rag_attend_request *reqs, uint32_t n_reqs, uint32_t layer,
                   uint32_t n_q_heads, float sm_scale, void *workspace, size_t workspace_bytes,
@@ -331,7 +389,7 @@ int attend_locked(ha_rag_ctx *c, PlanStore ps, const ha_rag_packed_chunk *chunks
     uint64_t floats = 0;
     uint32_t waves = 2;
     int rc = plan_attend(c, chunks, reqs, n_reqs, n_q_heads, ps.plans, &ps.docs, ps.open_k, ps.open_v,
-                         &floats, &waves, true);
+                         &floats, &waves, true, need ? workspace_bytes / 4u : ~0ull);
     if (rc) return rc;
     const Plan *plans = ps.plans;
     const Fixed<Doc> &docs = ps.docs;

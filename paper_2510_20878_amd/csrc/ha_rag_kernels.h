@@ -114,6 +114,7 @@ constexpr uint32_t kAttendMaxRunBlocks = 128;  // and a piece of one document is
 constexpr uint32_t kAttendTargetGroups = 2048; // pieces are halved while a launch has fewer workgroups
 // run lengths of the shared kernel: starting and ending one of its workgroups costs as much as this many blocks
 constexpr uint32_t kAttendStartBlocks = 8;
+constexpr uint32_t kAttendFewDocs = 32;       // and the longest run is looked for in a request of at most this many documents
 constexpr uint32_t kChipCUs = 256;            // compute units of the one GPU this library is built for
 constexpr uint32_t kAttendWaves = 2;          // waves of a workgroup; they interleave its blocks
 // Descriptors travel in the kernel argument buffer (36 KiB; launches with arguments of up to

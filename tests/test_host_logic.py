@@ -873,6 +873,47 @@ def test_attend_launch_descriptors_are_filled_and_checked_without_a_device():
     ctx.destroy()
 
 
+def test_attend_run_lengths_of_the_shared_kernel_count_whole_steps():
+    """A workgroup of the shared kernel takes 2, 4 or 8 blocks of one document at a time, and a run length
+    costs as many such steps as its longest run has: documents of 32 blocks are cut into runs of 8 (not of
+    9 or 11, which save records but no step), documents of 9 blocks not at all."""
+    ctx = B.Context(4, 8, 128, 2048, group_int8=128, group_int4=64, dry_run=True)
+    P = 0x7F0000001000
+    REC = (16 * 128 + 32) * 4
+    for n_reqs, n_docs, tokens, n_q, runs in [(8, 4, 512, 12, 16), (2, 4, 512, 64, 16), (8, 1, 512, 40, 4), (1, 8, 512, 64, 32),
+                                              (24, 4, 144, 16, 4), (2, 8, 304, 24, 17)]:
+        reqs = [([(P, tokens, B.PREC_INT4, 64, B.PART_KV)] * n_docs, P, P, None, n_q)] * n_reqs
+        tiles = (n_q * 4 + 15) // 16
+        assert ctx.attend_workspace_bytes(reqs, 32) == n_reqs * runs * 8 * tiles * REC, (n_reqs, n_docs, tokens, n_q)
+    # where those records do not fit the array of the entry point without a workspace, blocks are counted one by
+    # one: 24 runs of 11 blocks do (a call that was accepted before stays accepted)
+    reqs = [([(P, 512, B.PREC_INT4, 64, B.PART_KV)] * 8, P, P, None, 64)]
+    assert ctx.attend_workspace_bytes(reqs, 32) > B.ATTEND_STATIC_SCRATCH_BYTES
+    ctx.attend_packed_static(reqs, 0, 32, 0.1)
+    ctx.destroy()
+
+
+def test_attend_requests_of_two_tiles_move_only_where_the_workspace_does_not_grow():
+    """A call with requests of three or four query tiles takes those of two tiles to the same kernel, unless
+    the records of the two launches apart are fewer: then the call needs exactly what the two kinds of
+    requests need in calls of their own."""
+    P = 0x7F0000001000
+    ch = lambda t: (P, t, B.PREC_INT4, 64, B.PART_KV)
+    req = lambda lens, n_q: ([ch(t) for t in lens], P, P, None, n_q)
+    ctx = B.Context(1, 8, 128, 4096, group_int8=128, group_int4=64, dry_run=True)
+
+    def need(reqs):
+        n = ctx.attend_workspace_bytes(reqs, 32)
+        ctx.attend_packed(reqs, 0, 32, 0.1, P, n)
+        return n
+
+    assert need([req([144], 8)] + [req([512] * 3, 9)]) < need([req([144], 8)]) + need([req([512] * 3, 9)])
+    # four requests of one run each need no records; the one of two tiles would shorten their runs
+    for two, four in [([req([512], 8)], [req([144], 9)] * 4), ([req([2000] * 8, 8)] * 32, [req([2000] * 2, 16)])]:
+        assert need(two + four) == need(two) + need(four)
+    ctx.destroy()
+
+
 def test_attend_workspace_size_and_argument_checks():
     ctx = _attend_ctx()
     P = 0x7F0000001000
