@@ -409,27 +409,37 @@ __device__ __forceinline__ void role_decode_rounds(const SharedSide &sd, uint32_
     };
 #pragma unroll
     for (int i = 0; i < 4; ++i) fetch(i, b0 + 4u * r + i);
-    for (uint32_t rb = b0; rb < b1; rb += kRoleBlocks) {
-        // A block past the end is left out: the keys' scores are replaced whatever the buffer holds, and
-        // only if its partner exists the values, which the MFMAs then take with weight zero, have to be zeros.
-        // Its loads are issued all the same, see `fetch`.  Decoding absent blocks as well cost lists of short
-        // documents more than the eight-wave kernel took that decoded in turn: 30 documents of 16
-        // tokens in the paper's formats, 64 query tokens, 4 requests 46.1 us per layer (37.6 then, 32.9 now).
+    uint32_t rb = b0;
+    for (; rb + kRoleBlocks <= b1; rb += kRoleBlocks) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const uint32_t blk = rb + 4u * r + i;
-            uint8_t *pair = lds + set * kRoleSet + (2u * r + i / 2) * kRolePair;
-            if (blk < b1) role_decode<P, IS_K>(w[i], m[i], sd, blk, T, pair, i & 1, ln);
-            else if (!IS_K && (i & 1) && blk - 1u < b1) {
-#pragma unroll
-                for (int pp = 0; pp < 8; ++pp)
-                    *reinterpret_cast<u32x2 *>(pair + 2u * kRoleKeys + pp * 1024u + ln.lane * 16u + 8u) = u32x2{0u, 0u};
-            }
+            role_decode<P, IS_K>(w[i], m[i], sd, blk, T, lds + set * kRoleSet + (2u * r + i / 2) * kRolePair, i & 1, ln);
             fetch(i, blk + kRoleBlocks);
         }
         lds_barrier();
         set ^= 1u;
     }
+    if (rb >= b1) return;
+    // The document's (or run's) last round, if it is not a whole one.  A block that does not exist is left
+    // out: the keys' scores are replaced whatever the buffer holds, and only if its partner exists the
+    // values, which the MFMAs then take with weight zero, have to be zeros.  Decoding absent blocks as well cost
+    // lists of short documents more than the eight-wave kernel took that decoded in turn (30 documents of 16
+    // tokens in the paper's formats, 64 query tokens, 16 requests: 72.6 us per layer, 66.7 then, 49.8 now);
+    // leaving them out by a branch in the loop above cost whole rounds 1 %.
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const uint32_t blk = rb + 4u * r + i;
+        uint8_t *pair = lds + set * kRoleSet + (2u * r + i / 2) * kRolePair;
+        if (blk < b1) role_decode<P, IS_K>(w[i], m[i], sd, blk, T, pair, i & 1, ln);
+        else if (!IS_K && (i & 1) && blk - 1u < b1) {
+#pragma unroll
+            for (int pp = 0; pp < 8; ++pp)
+                *reinterpret_cast<u32x2 *>(pair + 2u * kRoleKeys + pp * 1024u + ln.lane * 16u + 8u) = u32x2{0u, 0u};
+        }
+    }
+    lds_barrier();
+    set ^= 1u;
 }
 
 template <bool IS_K>
