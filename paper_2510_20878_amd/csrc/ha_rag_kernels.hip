@@ -404,9 +404,42 @@ __device__ __forceinline__ void group_minmax(float &mn, float &mx)
     }
 }
 
-// Packed bytes are stored nontemporally (here and in the other packing kernels): nothing reads them
-// soon, and written through the caches they pushed out what was still to be read.  Ten 512-token chunks
-// of the 8B shape by class: int8 54 -> 48 us (6.3 TB/s), int4 75.9 -> 70.8 (6.0), 16-bit 43.2 -> 41.4 (6.5).
+// Stores of packed bytes: written through to memory (device scope) instead of left dirty in the L2s, which
+// then have no lines to write back while the next ones are packed.  What reads them next, the copy into the
+// pool or a load, still finds them in the last-level cache; nontemporal stores, which pack as fast, take
+// them past it.  512-token chunks of the 8B shape, sources that no cache holds, us with ordinary / nontemporal /
+// these stores:
+//              packing                      + copy into the pool    + load
+//   16-bit 2   44.3 / 42.3 / 41.5 (6.5 TB/s)  85 /  95 /  82           81 /  85 /  78
+//   int8 3     54.9 / 49.5 / 50.2 (6.1)       88 /  94 /  83           94 /  99 /  93
+//   int4 5     77.6 / 71.4 / 73.8 (5.8)      109 / 117 / 106          138 / 142 / 135
+//   E4M3 3     50.7 / 47.8 / 48.4 (6.2)       82 /  91 /  80           96 /  97 /  93
+// k2_pack_gse8 is the other way round (five chunks: 97 / 90 / 99, 163 / 161 / 174, 181 / 176 / 178) and stays
+// with nontemporal ones.
+// base: the same for the wave; off: the lane's, at most 2^31.
+__device__ __forceinline__ void st16_through(uint8_t *base, uint32_t off, u32x4 v)
+{
+    const uint64_t a = reinterpret_cast<uint64_t>(base);
+    const uint64_t u = (uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)(a >> 32)) << 32 |
+                       (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)a);
+    const __amdgpu_buffer_rsrc_t rsrc =
+        __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void *>(u), 0, 0x7FFFFFFF, 0x00027000);
+    __builtin_amdgcn_raw_buffer_store_b128(v, rsrc, (int)off, 0, 16);  // 16: the sc1 bit, device scope
+}
+
+// The four planes of a lane's block: elements e + 512 j .. + 7 of a tile of n_e, zeros behind its end.  The
+// loads are issued whatever n_e is (of the tile's first elements instead): with a branch around each the
+// compiler may wait for the first two before it issues the others (one int4 chunk 18.7 instead of 16.8 us).
+__device__ __forceinline__ void load_planes(const uint8_t *tile_in, uint32_t e, uint32_t n_e, u32x4 (&raw)[4])
+{
+#pragma unroll
+    for (uint32_t j = 0; j < 4; ++j)
+        raw[j] = ld16s<true>(tile_in + (uint64_t)(e + j * 512u < n_e ? e + j * 512u : 0u) * 2u);
+#pragma unroll
+    for (uint32_t j = 0; j < 4; ++j)
+        if (e + j * 512u >= n_e) raw[j] = u32x4{0, 0, 0, 0};
+}
+
 template <int BITS, int GSH>
 __global__ void __launch_bounds__(256) k2_quantize_pack(const K2Params p)
 {
@@ -422,14 +455,9 @@ __global__ void __launch_bounds__(256) k2_quantize_pack(const K2Params p)
     const uint32_t blk = (blockIdx.x - tile * wg_per_tile) * 4 + wave;
     if (tile >= p.n_tiles || blk >= nblk) return;  // the grid is as wide as the longest chunk
 
-    const uint8_t *in = src + (uint64_t)tile * n_e * 2u + (uint64_t)blk * 4096u + lane * 16u;
     const uint32_t e = blk * kBlockElems + lane * 8;
     u32x4 raw[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        raw[j] = u32x4{0, 0, 0, 0};
-        if (e + j * 512 < n_e) raw[j] = ld16s<true>(in + j * 1024);
-    }
+    load_planes(src + (uint64_t)tile * n_e * 2u, e, n_e, raw);
 
     constexpr uint32_t meta_blk = 8192u >> GSH;
     constexpr uint32_t pay_blk = 256u * BITS;
@@ -509,15 +537,14 @@ __global__ void __launch_bounds__(256) k2_quantize_pack(const K2Params p)
         }
     }
     if (BITS == 4) {
-        st16<true>(pay + (uint64_t)blk * pay_blk + lane * 16u,
-                    u32x4{code_lo[0], code_lo[1], code_lo[2], code_lo[3]});
+        st16_through(pay + (uint64_t)blk * pay_blk, lane * 16u, u32x4{code_lo[0], code_lo[1], code_lo[2], code_lo[3]});
     } else {
-        uint8_t *o = pay + (uint64_t)blk * pay_blk + lane * 16u;
-        st16<true>(o, u32x4{code_lo[0], code_hi[0], code_lo[1], code_hi[1]});
-        st16<true>(o + 1024, u32x4{code_lo[2], code_hi[2], code_lo[3], code_hi[3]});
+        uint8_t *o = pay + (uint64_t)blk * pay_blk;
+        st16_through(o, lane * 16u, u32x4{code_lo[0], code_hi[0], code_lo[1], code_hi[1]});
+        st16_through(o, lane * 16u + 1024u, u32x4{code_lo[2], code_hi[2], code_lo[3], code_hi[3]});
     }
     if ((lane & (lanes_per_group - 1)) == 0) {  // first lane of each group
-        st16<true>(meta + (uint64_t)blk * meta_blk + ((lane * 8u) >> GSH) * 16u, mrow);
+        st16_through(meta + (uint64_t)blk * meta_blk, ((lane * 8u) >> GSH) * 16u, mrow);
         if (saturated != nullptr && n_sat) atomicAdd(saturated, n_sat);
     }
 }
@@ -537,7 +564,7 @@ __global__ void __launch_bounds__(64) k2_pack16(const K2Params p)
     const uint32_t e = pl * 512u + threadIdx.x * 8u;
     u32x4 w = u32x4{0, 0, 0, 0};
     if (e < n_e) w = ld16s<true>(src + ((uint64_t)tile * n_e + e) * 2u);
-    st16<true>(dst + ((uint64_t)tile * planes_per_tile * 512u + e) * 2u, w);
+    st16_through(dst + ((uint64_t)tile * planes_per_tile + pl) * 1024u, threadIdx.x * 16u, w);
 }
 
 // FP8 tags: every element is rounded on its own (nearest, ties to even, by the hardware
@@ -555,14 +582,14 @@ __global__ void __launch_bounds__(256) k2_pack_fp8(const K2Params p)
     const uint32_t tile = blockIdx.x / wg_per_tile;
     const uint32_t blk = (blockIdx.x - tile * wg_per_tile) * 4 + wave;
     if (tile >= p.n_tiles || blk >= nblk) return;
-    const uint8_t *in = src + (uint64_t)tile * n_e * 2u + (uint64_t)blk * 4096u + lane * 16u;
     const uint32_t e = blk * kBlockElems + lane * 8;
+    u32x4 planes[4];
+    load_planes(src + (uint64_t)tile * n_e * 2u, e, n_e, planes);
     const float vmax = E5M2 ? 57344.0f : 448.0f;
     uint32_t code[4][2];
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-        u32x4 raw = u32x4{0, 0, 0, 0};
-        if (e + j * 512 < n_e) raw = ld16s<true>(in + j * 1024);
+        const u32x4 raw = planes[j];
 #pragma unroll
         for (int h = 0; h < 2; ++h) {  // four elements -> one dword of codes
             float x[4];
@@ -584,9 +611,9 @@ __global__ void __launch_bounds__(256) k2_pack_fp8(const K2Params p)
             code[j][h] = (uint32_t)w;
         }
     }
-    uint8_t *o = dst + (uint64_t)tile * nblk * 2048u + (uint64_t)blk * 2048u + lane * 16u;
-    st16<true>(o, u32x4{code[0][0], code[0][1], code[1][0], code[1][1]});
-    st16<true>(o + 1024, u32x4{code[2][0], code[2][1], code[3][0], code[3][1]});
+    uint8_t *o = dst + (uint64_t)tile * nblk * 2048u + (uint64_t)blk * 2048u;
+    st16_through(o, lane * 16u, u32x4{code[0][0], code[0][1], code[1][0], code[1][1]});
+    st16_through(o, lane * 16u + 1024u, u32x4{code[2][0], code[2][1], code[3][0], code[3][1]});
 }
 
 // GSE-8: one workgroup of up to 16 waves per tile (a tile is the unit that shares an exponent
@@ -667,8 +694,9 @@ __device__ __forceinline__ uint32_t pk_max_wave(uint32_t v)
 
 // Bound: memory once the encoding is 15 packed instructions per two values (it was 26: the index of
 // a zero field needs no masking, the signs of four codes are merged at once, and constants sit
-// in registers).  Seven ragged chunks of 2,351 tokens in all (462 MB read and written): 122 -> 99 us; with
-// loads and stores that bypass the caches, 86 us = 5.4 TB/s.  Eight or four waves per tile with more
+// in registers).  Seven ragged chunks of 2,351 tokens in all (462 MB read and written), the same ones again and
+// again: 122 -> 99 us; with loads and stores that bypass the caches, 86 us = 5.4 TB/s (five chunks of 512 tokens
+// that no cache holds: 105 us, 97 with the shorter encode, 90).  Eight or four waves per tile with more
 // blocks each measured the same.
 //
 // HELD: blocks of the tile that every wave keeps in registers between the two passes (the
