@@ -1,5 +1,6 @@
 // Host side of attention over packed chunks: argument checks, the workspace layout, and the
-// launches (one partial-attention launch per 416 documents, one merge launch per 64 requests).
+// launches (attention launches of up to 512 runs, as many as their descriptors fit, one merge launch per 64
+// requests).
 #include "ha_rag_internal.h"
 
 #include <cstdio>
@@ -42,7 +43,8 @@ struct Doc {
 struct Plan {               // one request
     uint32_t first_doc = 0, n_docs = 0;  // its documents that hold tokens
     uint32_t n_mt = 1;
-    uint32_t shared = 0;       // more than two query tiles: the kernel whose waves share each decoded block
+    uint32_t shared = 0;       // goes to the kernel whose waves share each decoded block: more than two query
+                               // tiles, or two in a call that needs that kernel's two-wave build anyway
     uint32_t run_blocks = 0;   // layout blocks per run (what one workgroup takes)
     uint64_t all_blocks = 0;   // layout blocks of all its documents
     uint32_t n_runs = 0;       // records per (KV head, tile)
@@ -57,8 +59,8 @@ uint32_t tile_groups(const Plan &pl, uint32_t waves)
 }
 
 // A run: the blocks one workgroup takes, a range of the request's blocks in list order.  For the
-// shared kernel it may start and end inside a document and span several; for the kernel of at
-// most two query tiles it is a piece of one document.
+// shared kernel it may start and end inside a document and span several; for k6_attend_partial
+// it is a piece of one document.
 struct Run {
     uint32_t doc, first_block;  // first document (index into the request's documents) and block in it
     uint32_t n_docs, end_block; // documents touched; end of the range in the last of them
@@ -170,8 +172,8 @@ uint64_t lay_out_runs(Plan *plans, uint32_t n_reqs, const Doc *docs, uint32_t H,
     // the one with the least of rounds x (blocks + start) + records is taken, in units of the time a
     // workgroup takes for a block with its neighbours: 0.57 us with eight scoring waves, 0.9 with
     // four, 1.2 with two; a record costs the chip about 2 ns.  Without the last two terms three
-    // requests of 96 to 201 query tokens took runs of 8 blocks, 0.9 GB of records: 460 us and
-    // 210 us of merge per layer, against 220 and 9 with two runs per request.
+    // requests of 96 to 201 query tokens took runs of 8 blocks, 0.9 GB of records: 647 us per layer, a
+    // third of it the merge, against 214 with two runs per request.
     // Blocks count in steps: a workgroup takes up to `waves` of them at a time, of one document, and the
     // length's cost is that of the largest request's longest run.  Counted one by one, eight requests of
     // four documents of 512 tokens took runs of 9 blocks instead of 8 at 12 query tokens (26.2 us per
@@ -179,7 +181,7 @@ uint64_t lay_out_runs(Plan *plans, uint32_t n_reqs, const Doc *docs, uint32_t H,
     // in whole steps as if documents had no ends, 24 requests of four of 144 tokens took runs of 8
     // instead of 9 at 16 (29.1 against 25.3).  (Not in_steps: one by one all the same, for a call whose
     // records would otherwise not fit.)
-    const uint64_t side_by_side = (uint64_t)kChipCUs * (8u / waves);  // two waves per SIMD: eight per CU
+    const uint64_t side_by_side = (uint64_t)kChipCUs * (8u / waves);  // two and four waves: two per SIMD; k6_attend_roles: one workgroup per CU, by its LDS
     const Plan *largest = nullptr;
     for (uint32_t r = 0; r < n_reqs; ++r)
         if (plans[r].shared && (!largest || plans[r].all_blocks > largest->all_blocks)) largest = &plans[r];
@@ -329,7 +331,7 @@ int plan_attend(ha_rag_ctx *c, const ha_rag_packed_chunk *chunks, const ha_rag_a
     // A call that needs the two-wave shared kernel anyway takes its requests of two query tiles there
     // as well: a block costs that kernel what it costs the other one (103 against 100 us per
     // call of 32 requests), and one launch fills the chip where two in a row do not (12 requests of
-    // 6 to 16 query tokens: 48 against 63 us per layer).  Not if the partial results then took
+    // 6 to 16 query tokens: 46 against 63 us per layer).  Not if the partial results then took
     // more workspace.
     auto lay_out = [&](bool in_steps) {
         for (uint32_t r = 0; r < n_reqs; ++r) plans[r].shared = plans[r].n_mt > 2u;
@@ -403,7 +405,7 @@ int attend_locked(ha_rag_ctx *c, PlanStore ps, const ha_rag_packed_chunk *chunks
     const uint32_t H = c->cfg.n_kv_heads;
     float *ws = static_cast<float *>(workspace);
 
-    // two launches in the making: requests of at most two query tiles, and the others
+    // two launches in the making: requests for k6_attend_partial, and those for the shared kernel
     K6Params kp{}, ks{};
     for (K6Params *q : {&kp, &ks}) {
         q->n_kv_heads = H;

@@ -144,8 +144,10 @@ constexpr float kLazyMaxLift = 8.0f;
 // weights that multiplied V, so that what rounding does to a weight does not also scale the result
 // (a row with one dominant key gets that key's value exactly); the log-sum-exp keeps the
 // unrounded sum.  One instruction per two weights.  Relative error of the output against 64 bits,
-// without and with it: one request at one query token 0.97e-3 and 0.20e-3 (ten documents of 512
-// tokens), 32 requests 1.4e-3 and 0.66e-3, 64 query tokens 1.3e-3 and 0.79e-3.
+// without and with it, over ten documents of 512 tokens (two 16-bit, three int8, five int4): one request at
+// one query token 0.62e-3 and 0.21e-3, 32 requests 1.1e-3 and 0.67e-3, at 64 query tokens 1.2e-3 and 0.80e-3.
+// It costs k6_attend_shared 1 to 2 % where the decode is long (32 requests over GSE-8, 24 query tokens: 164 ->
+// 166 us).
 __device__ __forceinline__ float add_weights(uint32_t pair, float sum)
 {
     const uint32_t ones = 0x3F803F80u;

@@ -1,6 +1,6 @@
-// gfx950 kernel for attention over packed chunks when a request has more query rows than one
+// gfx950 kernels for attention over packed chunks when a request has more query rows than one
 // wave can keep (more than two 16-row tiles: the question's prefill of Sec. 2.1, tens of query
-// tokens times the query heads of a KV head).
+// tokens times the query heads of a KV head), and for requests of two tiles next to such.
 //
 //  k6_attend_shared<W>   one workgroup of W waves (2 or 4) per (run of blocks across a request's
 //      documents in list order, KV head, group of 2 W query tiles).  Every wave owns two query
@@ -307,7 +307,7 @@ __device__ __forceinline__ void shared_rounds_any(uint32_t prec, const SharedSid
 }
 
 __device__ __forceinline__ SharedSide shared_side(const uint8_t *first, uint32_t prec, uint32_t gsh, uint32_t h,
-                                                  uint32_t nblk, bool wanted)
+                                                  uint32_t nblk)
 {
     SharedSide sd;
     const bool has_meta = prec == kInt4 || prec == kInt8;
@@ -318,7 +318,7 @@ __device__ __forceinline__ SharedSide shared_side(const uint8_t *first, uint32_t
     sd.tile = (gbytes)first + (uint64_t)h * ((uint64_t)nblk * (pay + sd.meta_blk) + (prec == kGSE8 ? 16u : 0u));
     sd.meta = sd.tile + (uint64_t)nblk * pay;
     sd.base = sd.top = 0;
-    if (wanted && prec == kGSE8) {  // the tile's exponent range follows its payload
+    if (prec == kGSE8) {  // the tile's exponent range follows its payload
         const uint32_t rg = *(const uint32_t __attribute__((address_space(1))) *)(sd.tile + (uint64_t)nblk * 2048u);
         sd.base = (int)(int8_t)(rg & 0xFFu);
         sd.top = (int)(int8_t)((rg >> 8) & 0xFFu) - 2;
@@ -743,11 +743,11 @@ __global__ void __launch_bounds__(64 * W, 2) k6_attend_shared(const K6Params p)
         if (b0 >= b1) continue;  // cannot happen with a checked launch
         if (is_k) {
             const uint32_t prec = dinfo & 0xFu;
-            const SharedSide sd = shared_side(dk, prec, (dinfo >> 4) & 0xFu, h, nblk, true);
+            const SharedSide sd = shared_side(dk, prec, (dinfo >> 4) & 0xFu, h, nblk);
             shared_rounds_any<true, W>(prec, sd, T, b0, b1, hdr.scale_log2, r, active, ln, lds, set, st);
         } else {
             const uint32_t prec = (dinfo >> 8) & 0xFu;
-            const SharedSide sd = shared_side(dv, prec, (dinfo >> 12) & 0xFu, h, nblk, true);
+            const SharedSide sd = shared_side(dv, prec, (dinfo >> 12) & 0xFu, h, nblk);
             shared_rounds_any<false, W>(prec, sd, T, b0, b1, hdr.scale_log2, r, active, ln, lds, set, st);
         }
     }
@@ -764,9 +764,9 @@ __global__ void __launch_bounds__(64 * W, 2) k6_attend_shared(const K6Params p)
 // whose registers hold no raw words, and a decoder that fills their gaps.
 //
 // Bound: the SIMDs' instruction slots and the clock.  32 requests x 5,120 tokens x 64 query tokens
-// x 32 heads (172 GFLOP a layer, one workgroup per CU, one run per request): 205-215 us with eight waves
-// that decoded and scored in turn, 180-187 now = 940 TFLOP/s, against 1,390 of a large matrix product on the
-// same card.  Of 383,000 clocks the matrix cores work 164,000 and vector instructions take about
+// x 32 heads (172 GFLOP a layer, one workgroup per CU, one run per request): 215-227 us with eight waves
+// that decoded and scored in turn, 187-192 on the same cards now = 907 TFLOP/s, against 1,390 of a large matrix
+// product.  Of 383,000 clocks the matrix cores work 164,000 and vector instructions take about
 // 160,000, which overlap with them only in part (two waves of 16 MFMAs and 64 fused multiply-adds
 // each take 355 ns where the MFMAs alone take 273); under this load the card runs at 2.07 GHz.  What gave how
 // much: the split into two kinds of waves 10 %; operands read ahead of what hides them 2 %; the maxima
@@ -827,7 +827,7 @@ __global__ void __launch_bounds__(64 * (kRoleScorers + kRoleDecoders), 3) k6_att
             const uint32_t b1 = d + 1u == run ? end_block : nblk;
             if (b0 >= b1) continue;  // cannot happen with a checked launch
             const uint32_t prec = info & 0xFu;
-            const SharedSide sd = shared_side(dp, prec, (info >> 4) & 0xFu, h, nblk, true);
+            const SharedSide sd = shared_side(dp, prec, (info >> 4) & 0xFu, h, nblk);
             if (is_k) role_decode_any<true>(prec, sd, T, b0, b1, r, ln, lds_bytes, set);
             else role_decode_any<false>(prec, sd, T, b0, b1, r, ln, lds_bytes, set);
         }

@@ -193,7 +193,7 @@ struct K7Params {
 // the run's blocks in turn.  check_only (here and below): every check, no launch -- what a
 // context without a device does with the descriptors it has filled.
 hipError_t launch_k6(K6Params &p, hipStream_t stream, bool check_only = false);
-// The same for requests with more than two query tiles: the `waves` (2, 4 or 8) scoring waves of a
+// The same for requests with two query tiles or more: the `waves` (2, 4 or 8) scoring waves of a
 // workgroup share every decoded block, each wave with two tiles of its own.
 hipError_t launch_k6_shared(K6Params &p, uint32_t waves, hipStream_t stream, bool check_only = false);
 // What both check of their arguments (max_mt: most query tiles of a run's request; narrow: no 16-bit side).

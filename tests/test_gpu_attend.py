@@ -4,8 +4,10 @@ bytes.
 
 Tolerance (derived from the kernel's arithmetic; K and V values are exact on both sides):
   * the softmax weights are rounded to BF16 (8 significant bits: relative 2^-8 each at worst)
-    before they multiply V while the normaliser keeps them in binary32: |out error| <=
-    2^-8 * spread, spread = sum_t softmax(s)[t] |V[t][d]| (the oracle returns it);
+    before they multiply V, and the normaliser of out is the binary32 sum of the rounded ones (that
+    of lse the sum of the unrounded): |out error| <= 2^-8 * sum_t softmax(s)[t] |V[t][d] - out[d]|.
+    That is at most twice 2^-8 * spread, spread = sum_t softmax(s)[t] |V[t][d]| (the oracle returns
+    it); the bar is 2^-8 * spread, what it was with a normaliser of unrounded weights;
   * scores are sums of 128 exact products accumulated in binary32: |s error| <= 2^-17 * sabs,
     sabs = sm_scale * sum_d |q[d] K[t][d]| (max over t); it shifts lse by as much and the
     weights by that relative amount.  The bar adds 2^-15 * (1 + sabs) (times spread for out),
@@ -199,7 +201,7 @@ def test_many_rows_kernel_with_runs_inside_long_documents(n_q, n_qh, H):
     """Few, long documents and many query rows: the call has few workgroups, so the runs are
     the shortest there are (8 blocks = 128 tokens) and most of them start and end inside a
     document; every run writes its own record for the tile-wise merge; 3, 10 and 9 query tiles
-    take workgroups of 2, 8 and 8 waves.  The second document's last block is ragged and the
+    take workgroups of two waves and, twice, of eight scoring ones.  The second document's last block is ragged and the
     last run of each request short."""
     reqs = [([2500, 700], [B.PREC_INT4, B.PREC_INT8], n_q), ([1333], [B.PREC_16], n_q)]
     run_case((1, H, 128), reqs, 0, n_qh, 0.07, 110 + n_q)
