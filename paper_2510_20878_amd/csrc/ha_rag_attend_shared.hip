@@ -765,7 +765,7 @@ __global__ void __launch_bounds__(64 * W, 2) k6_attend_shared(const K6Params p)
 //
 // Bound: the SIMDs' instruction slots and the clock.  32 requests x 5,120 tokens x 64 query tokens
 // x 32 heads (172 GFLOP a layer, one workgroup per CU, one run per request): 215-227 us with eight waves
-// that decoded and scored in turn, 187-192 on the same cards now = 907 TFLOP/s, against 1,390 of a large matrix
+// that decoded and scored in turn, 182-192 now = 907-944 TFLOP/s, against 1,390 of a large matrix
 // product.  Of 383,000 clocks the matrix cores work 164,000 and vector instructions take about
 // 160,000, which overlap with them only in part (two waves of 16 MFMAs and 64 fused multiply-adds
 // each take 355 ns where the MFMAs alone take 273); under this load the card runs at 2.07 GHz.  What gave how
