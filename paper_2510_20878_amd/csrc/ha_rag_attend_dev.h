@@ -64,7 +64,7 @@ __device__ __forceinline__ u32x4 pack_octet(const float (&f)[8])
 
 // the raw codes of one octet (x: int4; x, y: 8-bit formats; all four: 16-bit) -> 8 BF16
 template <uint32_t PREC>
-__device__ __forceinline__ u32x4 decode_octet(u32x4 raw, uint32_t meta, int base, int top)
+__device__ __forceinline__ u32x4 decode_octet(u32x4 raw, uint32_t meta, const Gse8Tab &tab)
 {
     if (PREC == kInt4 || PREC == kInt8) {
         float f[8];
@@ -74,14 +74,14 @@ __device__ __forceinline__ u32x4 decode_octet(u32x4 raw, uint32_t meta, int base
     }
     if (PREC == kE4M3) return decode_octet_fp8<false>(raw.x, raw.y);
     if (PREC == kE5M2) return decode_octet_fp8<true>(raw.x, raw.y);
-    if (PREC == kGSE8) return decode_octet_gse8(raw.x, raw.y, base, top);
+    if (PREC == kGSE8) return decode_octet_gse8(raw.x, raw.y, tab);
     return raw;
 }
 
 // Two octets of the same dims and two tokens a, b -> t[p] = {value p of a, value p of b}: the integer
-// formats are rounded straight into these pairs, the others are regrouped.
+// formats are rounded straight into these pairs, the others' words or codes are regrouped.
 template <uint32_t PREC>
-__device__ __forceinline__ void decode_octets_by_token(u32x4 ra, u32x4 rb, uint32_t ma, uint32_t mb, int base, int top,
+__device__ __forceinline__ void decode_octets_by_token(u32x4 ra, u32x4 rb, uint32_t ma, uint32_t mb, const Gse8Tab &tab,
                                                        uint32_t (&t)[8])
 {
     if (PREC == kInt4 || PREC == kInt8) {
@@ -95,12 +95,20 @@ __device__ __forceinline__ void decode_octets_by_token(u32x4 ra, u32x4 rb, uint3
         }
 #pragma unroll
         for (int p = 0; p < 8; ++p) t[p] = pack_bf16(a[p], b[p]);
-    } else {
-        const u32x4 a = decode_octet<PREC>(ra, ma, base, top), b = decode_octet<PREC>(rb, mb, base, top);
+    } else if (PREC == kP16) {
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            t[2 * q] = __builtin_amdgcn_perm(b[q], a[q], 0x05040100u);
-            t[2 * q + 1] = __builtin_amdgcn_perm(b[q], a[q], 0x07060302u);
+            t[2 * q] = __builtin_amdgcn_perm(rb[q], ra[q], 0x05040100u);
+            t[2 * q + 1] = __builtin_amdgcn_perm(rb[q], ra[q], 0x07060302u);
+        }
+    } else {  // the codes are regrouped: half as many bytes
+        const uint32_t a[2] = {ra.x, ra.y}, b[2] = {rb.x, rb.y};
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const u32x4 raw = {__builtin_amdgcn_perm(b[h], a[h], 0x05010400u), __builtin_amdgcn_perm(b[h], a[h], 0x07030602u), 0u, 0u};
+            const u32x4 v = decode_octet<PREC>(raw, 0u, tab);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) t[4 * h + q] = v[q];
         }
     }
 }
@@ -147,7 +155,7 @@ constexpr float kLazyMaxLift = 8.0f;
 // without and with it, over ten documents of 512 tokens (two 16-bit, three int8, five int4): one request at
 // one query token 0.62e-3 and 0.21e-3, 32 requests 1.1e-3 and 0.67e-3, at 64 query tokens 1.2e-3 and 0.80e-3.
 // It costs k6_attend_shared 1 to 2 % where the decode is long (32 requests over GSE-8, 24 query tokens: 164 ->
-// 166 us).
+// 166 us, with the decode as it was then).
 __device__ __forceinline__ float add_weights(uint32_t pair, float sum)
 {
     const uint32_t ones = 0x3F803F80u;

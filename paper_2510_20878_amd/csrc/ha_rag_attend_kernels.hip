@@ -66,17 +66,9 @@ __device__ __forceinline__ void attend_unit(const AttendHdr &p, const K6Run &c,
 
     const uint32_t b0 = c.first_block, b1 = c.end_block;  // the run: blocks of this one document
 
-    int kbase = 0, ktop = 0, vbase = 0, vtop = 0;
-    if (KP == kGSE8) {
-        const uint32_t kr = *(const uint32_t __attribute__((address_space(1))) *)(kt + (uint64_t)nblk * 2048u);
-        kbase = (int)(int8_t)(kr & 0xFFu);
-        ktop = (int)(int8_t)((kr >> 8) & 0xFFu) - 2;
-    }
-    if (VP == kGSE8) {
-        const uint32_t vr = *(const uint32_t __attribute__((address_space(1))) *)(vt + (uint64_t)nblk * 2048u);
-        vbase = (int)(int8_t)(vr & 0xFFu);
-        vtop = (int)(int8_t)((vr >> 8) & 0xFFu) - 2;
-    }
+    Gse8Tab ktab = {}, vtab = {};
+    if (KP == kGSE8) ktab = gse8_tab(*(const uint32_t __attribute__((address_space(1))) *)(kt + (uint64_t)nblk * 2048u));
+    if (VP == kGSE8) vtab = gse8_tab(*(const uint32_t __attribute__((address_space(1))) *)(vt + (uint64_t)nblk * 2048u));
 
     // Q as the B operand of S^T = K Q^T: lane (c_, n_) holds, for MFMA y, dims
     // 32 c_ + 8 y .. + 7 of query row n_ of the tile (zero rows beyond M)
@@ -157,7 +149,7 @@ __device__ __forceinline__ void attend_unit(const AttendHdr &p, const K6Run &c,
                 raw.x = t.x;
                 raw.y = t.y;
             }
-            ka[y] = __builtin_bit_cast(bf16x8, decode_octet<KP>(raw, cur.km, kbase, ktop));
+            ka[y] = __builtin_bit_cast(bf16x8, decode_octet<KP>(raw, cur.km, ktab));
         }
         wave_lds_sync();
 
@@ -204,22 +196,24 @@ __device__ __forceinline__ void attend_unit(const AttendHdr &p, const K6Run &c,
             pa[mt] = __builtin_bit_cast(s16x4, pk);
         }
 
-        // ---- V: decode the lane's four planes, regroup by position, O += P V
-        u32x4 vr[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-            vr[j] = decode_octet<VP>(plane_raw<VP>(cur.vw, j), cur.vm[j], vbase, vtop);
+        // ---- V: decode the lane's four planes, two tokens at a time: value pp of tokens c_ and 4 + c_ (t01), of
+        // 8 + c_ and 12 + c_ (t23); O += P V
+        uint32_t t01[8], t23[8];
+        decode_octets_by_token<VP>(plane_raw<VP>(cur.vw, 0), plane_raw<VP>(cur.vw, 1), cur.vm[0], cur.vm[1], vtab, t01);
+        decode_octets_by_token<VP>(plane_raw<VP>(cur.vw, 2), plane_raw<VP>(cur.vw, 3), cur.vm[2], cur.vm[3], vtab, t23);
         if (ragged) {  // rows past the chunk's end
+            uint32_t keep[4];
 #pragma unroll
-            for (int j = 0; j < 4; ++j)
-                if (b * 16u + 4u * j + c_ >= T) vr[j] = u32x4{0u, 0u, 0u, 0u};
+            for (uint32_t j = 0; j < 4; ++j) keep[j] = b * 16u + 4u * j + c_ < T ? 0xFFFFu : 0u;
+#pragma unroll
+            for (int pp = 0; pp < 8; ++pp) {
+                t01[pp] &= keep[0] | (keep[1] << 16);
+                t23[pp] &= keep[2] | (keep[3] << 16);
+            }
         }
 #pragma unroll
         for (int pp = 0; pp < 8; ++pp) {
-            const uint32_t sel = (pp & 1) ? 0x07060302u : 0x05040100u;
-            const u32x2 t = {__builtin_amdgcn_perm(vr[1][pp >> 1], vr[0][pp >> 1], sel),
-                             __builtin_amdgcn_perm(vr[3][pp >> 1], vr[2][pp >> 1], sel)};
-            const s16x4 vb = __builtin_bit_cast(s16x4, t);
+            const s16x4 vb = __builtin_bit_cast(s16x4, u32x2{t01[pp], t23[pp]});
 #pragma unroll
             for (int mt = 0; mt < MTW; ++mt)
                 O[mt][pp] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(pa[mt], vb, O[mt][pp], 0, 0, 0);

@@ -48,7 +48,7 @@ struct SharedState {  // a wave's two query tiles
 struct SharedSide {  // the keys or the values of one document's (layer, head) tile (uniform values)
     gbytes tile, meta;
     uint32_t meta_blk, gsh;
-    int base, top;
+    Gse8Tab tab;  // GSE-8
 };
 
 struct SharedLane {
@@ -228,7 +228,7 @@ __device__ __forceinline__ void shared_rounds(const SharedSide &sd, uint32_t T, 
             uint8_t *dst = pair + e * 4096u;
             u32x4 o[4];  // o[j] = token 4 j + c_, dims 8 n_ .. 8 n_ + 7 as BF16
 #pragma unroll
-            for (int j = 0; j < 4; ++j) o[j] = decode_octet<P>(plane_raw<P>(w[e], j), m[e][j], sd.base, sd.top);
+            for (int j = 0; j < 4; ++j) o[j] = decode_octet<P>(plane_raw<P>(w[e], j), m[e][j], sd.tab);
             if (IS_K) {
                 // token t = 4 j + c_, octet n_: slot (n_ ^ t) of row t
                 const uint32_t k_wr = fresh(ln.k_wr);
@@ -317,12 +317,9 @@ __device__ __forceinline__ SharedSide shared_side(const uint8_t *first, uint32_t
     // `first` points at the layer's tile of head 0; the heads' tile records follow one another
     sd.tile = (gbytes)first + (uint64_t)h * ((uint64_t)nblk * (pay + sd.meta_blk) + (prec == kGSE8 ? 16u : 0u));
     sd.meta = sd.tile + (uint64_t)nblk * pay;
-    sd.base = sd.top = 0;
-    if (prec == kGSE8) {  // the tile's exponent range follows its payload
-        const uint32_t rg = *(const uint32_t __attribute__((address_space(1))) *)(sd.tile + (uint64_t)nblk * 2048u);
-        sd.base = (int)(int8_t)(rg & 0xFFu);
-        sd.top = (int)(int8_t)((rg >> 8) & 0xFFu) - 2;
-    }
+    sd.tab = Gse8Tab{};
+    if (prec == kGSE8)  // the tile's exponent range follows its payload
+        sd.tab = gse8_tab(*(const uint32_t __attribute__((address_space(1))) *)(sd.tile + (uint64_t)nblk * 2048u));
     return sd;
 }
 
@@ -362,14 +359,14 @@ __device__ __forceinline__ void role_decode(const u32x4 *w, const u32x4 &m, cons
 #pragma unroll
         for (uint32_t j = 0; j < 4; ++j)
             *reinterpret_cast<u32x4 *>(dst + j * (4u * kRoleKeyRow)) =
-                decode_octet<P>(plane_raw<P>(w, j), m[j], sd.base, sd.top);
+                decode_octet<P>(plane_raw<P>(w, j), m[j], sd.tab);
         return;
     }
     // Operand pp of P V: value pp of the octet of each of the lane's four tokens; the pair's
     // second block fills the second half of the lane's 16 bytes.
     uint32_t t01[8], t23[8];  // value pp of tokens 4 * 0 + c_ and 4 * 1 + c_, of 4 * 2 + c_ and 4 * 3 + c_
-    decode_octets_by_token<P>(plane_raw<P>(w, 0), plane_raw<P>(w, 1), m[0], m[1], sd.base, sd.top, t01);
-    decode_octets_by_token<P>(plane_raw<P>(w, 2), plane_raw<P>(w, 3), m[2], m[3], sd.base, sd.top, t23);
+    decode_octets_by_token<P>(plane_raw<P>(w, 0), plane_raw<P>(w, 1), m[0], m[1], sd.tab, t01);
+    decode_octets_by_token<P>(plane_raw<P>(w, 2), plane_raw<P>(w, 3), m[2], m[3], sd.tab, t23);
     if (blk * 16u + 16u > T) {  // rows past the document's end
         uint32_t keep[4];
 #pragma unroll

@@ -195,20 +195,19 @@ __global__ void __launch_bounds__(1024) k1_gather_dequant_scatter(const K1Params
         const uint8_t *rec = c.src + (uint64_t)tile * ((uint64_t)nblk * 2048u + 16u);
         const uint8_t *b = rec + (uint64_t)blk * 2048u + lane_b;
         const uint32_t range = *reinterpret_cast<const uint32_t *>(rec + (uint64_t)nblk * 2048u);
-        const int base = (int)(int8_t)(range & 0xFFu);              // e_lo + 2 - 2
-        const int top = (int)(int8_t)((range >> 8) & 0xFFu) - 2;    // e_hi - 2
+        const Gse8Tab tab = gse8_tab(range);
         if (planes == 4) {
             const u32x4 w0 = ld16s<NT_LD>(b), w1 = ld16s<NT_LD>(b + 1024);
             locate();
-            put(0, decode_octet_gse8(w0.x, w0.y, base, top));
-            put(1, decode_octet_gse8(w0.z, w0.w, base, top));
-            put(2, decode_octet_gse8(w1.x, w1.y, base, top));
-            put(3, decode_octet_gse8(w1.z, w1.w, base, top));
+            put(0, decode_octet_gse8(w0.x, w0.y, tab));
+            put(1, decode_octet_gse8(w0.z, w0.w, tab));
+            put(2, decode_octet_gse8(w1.x, w1.y, tab));
+            put(3, decode_octet_gse8(w1.z, w1.w, tab));
         } else {
             const u32x4 w = ld16s<NT_LD>(b + (j0 >> 1) * 1024u);
             locate();
-            put(0, decode_octet_gse8(w.x, w.y, base, top));
-            put(1, decode_octet_gse8(w.z, w.w, base, top));
+            put(0, decode_octet_gse8(w.x, w.y, tab));
+            put(1, decode_octet_gse8(w.z, w.w, tab));
         }
     } else {
         const uint8_t *b = c.src + (uint64_t)tile * ((uint64_t)nblk * 4096u) +
@@ -956,13 +955,12 @@ __global__ void __launch_bounds__(256) k8_sq_error(const uint8_t *__restrict__ s
             const uint8_t *rec = packed + (uint64_t)tile * ((uint64_t)nblk * 2048u + 16u);
             const uint8_t *b = rec + (uint64_t)blk * 2048u + lane_b;
             const uint32_t range = *reinterpret_cast<const uint32_t *>(rec + (uint64_t)nblk * 2048u);
-            const int base = (int)(int8_t)(range & 0xFFu);
-            const int top = (int)(int8_t)((range >> 8) & 0xFFu) - 2;
+            const Gse8Tab tab = gse8_tab(range);
             const u32x4 w0 = ld16(b), w1 = ld16(b + 1024);
-            dec[0] = decode_octet_gse8(w0.x, w0.y, base, top);
-            dec[1] = decode_octet_gse8(w0.z, w0.w, base, top);
-            dec[2] = decode_octet_gse8(w1.x, w1.y, base, top);
-            dec[3] = decode_octet_gse8(w1.z, w1.w, base, top);
+            dec[0] = decode_octet_gse8(w0.x, w0.y, tab);
+            dec[1] = decode_octet_gse8(w0.z, w0.w, tab);
+            dec[2] = decode_octet_gse8(w1.x, w1.y, tab);
+            dec[3] = decode_octet_gse8(w1.z, w1.w, tab);
         } else {
             const uint8_t *b = packed + (uint64_t)tile * ((uint64_t)nblk * 4096u) + (uint64_t)blk * 4096u + lane_b;
 #pragma unroll

@@ -416,6 +416,28 @@ def test_gse8_tiles_whose_exponents_begin_at_the_bottom_of_the_format(lo_e):
     _gse_roundtrip(np.stack(tiles).reshape(2, 2, 2, 512, 128), 512)
 
 
+@pytest.mark.parametrize("e_lo, e_hi", [(0, 0), (-3, -2), (-5, -3), (2, 5), (-7, 10), (-20, 27), (-126, -126), (-126, -125),
+                                        (-125, -124), (-126, -79), (80, 127), (126, 127), (127, 127)])
+def test_gse8_decode_every_code(e_lo, e_hi):
+    """All 256 codes, also those the quantizer never writes (a zero field with an index, indices beyond the tile's last
+    exponent), for ranges that are not, partly and wholly clipped and those at both ends of the format."""
+    L, H, D, T = 1, 1, 128, 32                                           # 2 blocks per tile
+    packed = np.zeros(codec.chunk_bytes(L, H, D, T, 143), np.uint8)
+    rec = packed.size // 2
+    for tile in range(2):
+        for e in range(T * D):
+            packed[tile * rec + codec.octet_offset(e, 8) + e % 8] = (e * 7 + 37 * tile) % 256
+        packed[tile * rec + T * D:tile * rec + T * D + 2] = np.array([e_lo, e_hi], np.int8).view(np.uint8)
+    ref = np.zeros((L, 2, H, T, D), np.uint16)
+    codec.dequant_scatter_chunk(packed, (L, H, D), T, 143, 0, ref, 0)
+    ctx = B.Context(L, H, D, T)
+    out = torch.zeros((L, 2, H, T, D), dtype=torch.int16, device="cuda")
+    ctx.load_packed([(dev_u8(packed), T, B.PREC_GSE8, 0)], out, T)
+    torch.cuda.synchronize()
+    assert np.array_equal(host_u16(out), ref)
+    ctx.destroy()
+
+
 @pytest.mark.parametrize("shape", [(2, 2, 64, 128), (1, 2, 128, 100), (1, 1, 128, 1), (2, 1, 96, 40),
                                    (1, 2, 128, 272)])
 def test_gse8_shapes(shape):
