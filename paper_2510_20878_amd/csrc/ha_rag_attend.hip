@@ -4,6 +4,8 @@
 #include "ha_rag_internal.h"
 
 #include <cstdio>
+#include <memory>
+#include <type_traits>
 
 using namespace ha_rag_host;
 
@@ -17,7 +19,6 @@ struct Fixed {
     uint32_t cap = 0, n = 0;
     Fixed() = default;
     Fixed(T *d, uint32_t c) : data(d), cap(c) {}
-    explicit Fixed(std::vector<T> &v) : data(v.data()), cap((uint32_t)v.size()) {}
     bool push_back(const T &v)
     {
         if (n == cap) return false;
@@ -38,6 +39,7 @@ struct Doc {
                                                // values of a whole chunk; a layer is k_step records on
     uint32_t k_step = 0, v_step = 0;
     uint32_t n_tokens = 0, info = 0;
+    uint32_t n_blocks = 0;                     // layout blocks (16 tokens each)
 };
 
 struct Plan {               // one request
@@ -67,29 +69,27 @@ struct Run {
 };
 constexpr uint32_t kMaxRunDocs = 128;  // a run's documents are descriptors of one launch
 
+// How a document of a request that is not the shared kernel's is cut: equal pieces, none longer than
+// run_blocks.  Their length; *n = how many.
+uint32_t piece_blocks(const Plan &pl, const Doc &doc, uint32_t *n)
+{
+    const uint32_t nb = doc.n_blocks, parts = (nb + pl.run_blocks - 1u) / pl.run_blocks;
+    const uint32_t len = parts == 1u ? nb : (nb + parts - 1u) / parts;
+    *n = parts == 1u ? 1u : (nb + len - 1u) / len;
+    return len;
+}
+
 // The run that starts at block `blk` of document `doc` of the request (both moved to the next
-// run's start); false when the request has no block left.
+// run's start); false when the request has no block left.  For the shared kernel.
 bool next_run(const Plan &pl, const Doc *docs, uint32_t &doc, uint32_t &blk, Run *out)
 {
     if (doc >= pl.n_docs) return false;
     out->doc = doc;
     out->first_block = blk;
-    if (!pl.shared) {  // equal pieces of one document, none longer than run_blocks
-        const uint32_t nb = (docs[doc].n_tokens + 15u) / 16u;
-        const uint32_t n = (nb + pl.run_blocks - 1u) / pl.run_blocks, len = (nb + n - 1u) / n;
-        out->n_docs = 1;
-        out->end_block = nb - blk > len ? blk + len : nb;
-        blk = out->end_block;
-        if (blk == nb) {
-            ++doc;
-            blk = 0;
-        }
-        return true;
-    }
     out->n_docs = 0;
     uint32_t left = pl.run_blocks;
     for (;;) {
-        const uint32_t nb = (docs[doc].n_tokens + 15u) / 16u;
+        const uint32_t nb = docs[doc].n_blocks;
         ++out->n_docs;
         if (nb - blk > left) {  // the run ends inside this document
             blk += left;
@@ -107,6 +107,13 @@ bool next_run(const Plan &pl, const Doc *docs, uint32_t &doc, uint32_t &blk, Run
 uint32_t count_runs(const Plan &pl, const Doc *docs)
 {
     uint32_t doc = 0, blk = 0, n = 0;
+    if (!pl.shared) {
+        for (uint32_t i = 0; i < pl.n_docs; ++i) {
+            piece_blocks(pl, docs[i], &blk);
+            n += blk;
+        }
+        return n;
+    }
     Run r;
     while (next_run(pl, docs, doc, blk, &r)) ++n;
     return n;
@@ -119,7 +126,7 @@ uint32_t longest_run_steps(const Plan &pl, const Doc *docs, uint32_t len, uint32
     const uint32_t up = (1u << shift) - 1u;
     uint32_t most = 0, steps = 0, left = len;
     for (uint32_t i = 0; i < pl.n_docs; ++i) {
-        uint32_t nb = (docs[i].n_tokens + 15u) >> 4;
+        uint32_t nb = docs[i].n_blocks;
         if (nb >= left) {  // a run ends in this document, the next ones lie inside it
             steps += (left + up) >> shift;
             if (steps > most) most = steps;
@@ -147,24 +154,25 @@ uint64_t lay_out_runs(Plan *plans, uint32_t n_reqs, const Doc *docs, uint32_t H,
     // possible (every workgroup pays for fetching the queries and for writing a record), but
     // short enough that the launch fills the chip a few times over, since the hardware then
     // evens out what documents of different formats and lengths take.
-    auto groups_at = [&](uint32_t piece) {  // workgroups of the one/two-tile kernel with pieces this long
+    auto groups_at = [&](uint32_t shift) {  // workgroups of the one/two-tile kernel with pieces of 1 << shift blocks
         uint64_t groups = 0;
         for (uint32_t r = 0; r < n_reqs; ++r) {
             const Plan &pl = plans[r];
             if (pl.shared) continue;
             uint64_t runs = 0;
-            for (uint32_t i = 0; i < pl.n_docs; ++i)
-                runs += ((docs[pl.first_doc + i].n_tokens + 15u) / 16u + piece - 1u) / piece;
+            for (uint32_t i = 0; i < pl.n_docs; ++i) runs += (docs[pl.first_doc + i].n_blocks + (1u << shift) - 1u) >> shift;
             groups += runs * H * tile_groups(pl, waves);
         }
         return groups;
     };
-    uint32_t piece = kAttendMaxRunBlocks;
-    while (piece > kAttendMinRunBlocks && groups_at(piece) < kAttendTargetGroups) piece >>= 1;
+    static_assert(kAttendMaxRunBlocks == 128u, "a power of two");
+    uint32_t shift_p = 7;
+    while ((1u << shift_p) > kAttendMinRunBlocks && groups_at(shift_p) < kAttendTargetGroups) --shift_p;
     // A call of so few workgroups that even twice as many run side by side (four per CU) is
     // bound by how long one of them takes: halve once more (one request of 10 x 512 tokens:
     // 13.7 against 14.7 us; with two requests, 1,280 workgroups, it would cost 1.5 us).
-    if (piece == kAttendMinRunBlocks && groups_at(piece / 2u) <= 4ull * kChipCUs) piece /= 2u;
+    if ((1u << shift_p) == kAttendMinRunBlocks && groups_at(shift_p - 1u) <= 4ull * kChipCUs) --shift_p;
+    const uint32_t piece = 1u << shift_p;
     // The shared kernel: a run crosses document boundaries (equal runs finish together whatever
     // the documents' lengths).  Workgroups of one size finish in rounds of as many as the chip
     // holds side by side; every round pays for starting and ending a workgroup, and every record
@@ -189,24 +197,35 @@ uint64_t lay_out_runs(Plan *plans, uint32_t n_reqs, const Doc *docs, uint32_t H,
     const uint32_t shift = waves == 8u ? 3u : waves == 4u ? 2u : 1u;
     const uint64_t all_steps = largest ? longest_run_steps(*largest, docs + largest->first_doc, ~0u, shift) : 0;
     const uint64_t recs_per_block = waves == 8u ? 280u : waves == 4u ? 450u : 600u;
+    struct Size {  // requests of one size, in the order they come up first
+        uint64_t blocks;
+        uint32_t n_mt, count;
+    };
+    constexpr uint32_t kSizes = 32;
+    Size sizes[kSizes];
+    uint32_t n_sizes = 0, rest = 0;  // requests from `rest` on are looked at one by one
+    for (; rest < n_reqs; ++rest) {
+        const Plan &pl = plans[rest];
+        if (!pl.shared) continue;
+        uint32_t i = 0;
+        while (i < n_sizes && (sizes[i].blocks != pl.all_blocks || sizes[i].n_mt != pl.n_mt)) ++i;
+        if (i == kSizes) break;
+        if (i == n_sizes) sizes[n_sizes++] = Size{pl.all_blocks, pl.n_mt, 0u};
+        ++sizes[i].count;
+    }
     uint64_t run_blocks = most_blocks, best = most_blocks, least = ~0ull, fewest = ~0ull;
     for (uint64_t n = 1; n <= most_blocks; ++n) {  // n runs for the largest request
         const uint64_t len = (most_blocks + n - 1u) / n;
         if (n > 1 && len < kAttendMinRunBlocks) break;
-        uint64_t wgs = 0, recs = 0, my_wgs = 0, my_recs = 0;
-        const Plan *same = nullptr;  // requests of one size often follow one another
-        for (uint32_t r = 0; r < n_reqs; ++r) {
-            const Plan &pl = plans[r];
-            if (!pl.shared) continue;
-            if (!same || same->all_blocks != pl.all_blocks || same->n_mt != pl.n_mt) {
-                const uint64_t runs = (pl.all_blocks + len - 1u) / len;
-                my_wgs = runs * H * tile_groups(pl, waves);
-                my_recs = runs > 1u ? runs * H * pl.n_mt : 0u;
-                same = &pl;
-            }
-            wgs += my_wgs;
-            recs += my_recs;
-        }
+        uint64_t wgs = 0, recs = 0;
+        auto add = [&](uint64_t blocks, uint32_t n_mt, uint32_t count) {
+            const uint64_t runs = (blocks + len - 1u) / len * count;
+            wgs += runs * H * ((n_mt + 2u * waves - 1u) / (2u * waves));
+            if (blocks > len) recs += runs * H * n_mt;
+        };
+        for (uint32_t i = 0; i < n_sizes; ++i) add(sizes[i].blocks, sizes[i].n_mt, sizes[i].count);
+        for (uint32_t r = rest; r < n_reqs; ++r)
+            if (plans[r].shared) add(plans[r].all_blocks, plans[r].n_mt, 1u);
         const uint64_t rounds = (wgs + side_by_side - 1u) / side_by_side;
         auto cost = [&](uint64_t blocks) { return rounds * (blocks + kAttendStartBlocks) + recs / recs_per_block; };
         uint64_t c = cost(len);
@@ -250,7 +269,7 @@ int plan_attend(ha_rag_ctx *c, const ha_rag_packed_chunk *chunks, const ha_rag_a
 {
     if (!c || !reqs || n_reqs == 0 || n_reqs > HA_RAG_MAX_ATTEND_REQUESTS) return HA_RAG_EINVAL;
     if (c->cfg.head_dim != kAttendHeadDim) return HA_RAG_EFORMAT;
-    const uint32_t L = c->cfg.n_layers, H = c->cfg.n_kv_heads;
+    const uint32_t H = c->cfg.n_kv_heads;
     if (n_q_heads == 0 || n_q_heads % H || n_q_heads / H > 64) return HA_RAG_EINVAL;
     const uint32_t G = n_q_heads / H;
     uint64_t n_chunks = 0;
@@ -273,9 +292,9 @@ int plan_attend(ha_rag_ctx *c, const ha_rag_packed_chunk *chunks, const ha_rag_a
         size_t next_k = 0, next_v = 0;  // first entries of open_k / open_v not yet matched
         for (uint32_t i = 0; i < rq.n_chunks; ++i) {
             const ha_rag_packed_chunk &pc = chunks[n_chunks + i];
-            size_t bytes = 0;
-            int rc = chunk_bytes_impl(L, H, c->cfg.head_dim, pc.prec, pc.group, pc.n_tokens, nullptr,
-                                      nullptr, &bytes, pc.part);
+            size_t tile = 0;  // bytes of one tile record: what a keys-only chunk of one layer and head takes
+            int rc = chunk_bytes_impl(1, 1, c->cfg.head_dim, pc.prec, pc.group, pc.n_tokens, nullptr,
+                                      nullptr, &tile, pc.part == HA_RAG_PART_KV ? (uint32_t)HA_RAG_PART_K : pc.part);
             if (rc) return rc;
             if (pc.n_tokens == 0) continue;  // holds nothing, pairs with nothing
             if (need_buffers && (!pc.packed || ((uintptr_t)pc.packed & 15u))) return HA_RAG_EINVAL;
@@ -284,11 +303,12 @@ int plan_attend(ha_rag_ctx *c, const ha_rag_packed_chunk *chunks, const ha_rag_a
             if (pc.part == HA_RAG_PART_KV) {
                 Doc d;
                 d.k = d.v = ptr;
-                d.k_tile = d.v_tile = bytes / (2ull * L * H);
+                d.k_tile = d.v_tile = tile;
                 d.k_first = 0;
                 d.v_first = H;
                 d.k_step = d.v_step = 2u * H;
                 d.n_tokens = pc.n_tokens;
+                d.n_blocks = (pc.n_tokens + 15u) / 16u;
                 d.info = fmt | (fmt << 8);
                 if (!docs->push_back(d)) return HA_RAG_ENOSPC;
             } else {
@@ -305,10 +325,11 @@ int plan_attend(ha_rag_ctx *c, const ha_rag_packed_chunk *chunks, const ha_rag_a
                     di = (uint32_t)docs->size();
                     if (!docs->push_back(Doc()) || !mine.push_back(di)) return HA_RAG_ENOSPC;
                     (*docs)[di].n_tokens = pc.n_tokens;
+                    (*docs)[di].n_blocks = (pc.n_tokens + 15u) / 16u;
                 }
                 Doc &d = (*docs)[di];
                 (is_k ? d.k : d.v) = ptr;
-                (is_k ? d.k_tile : d.v_tile) = bytes / ((uint64_t)L * H);
+                (is_k ? d.k_tile : d.v_tile) = tile;
                 (is_k ? d.k_step : d.v_step) = H;
                 d.info |= is_k ? fmt : fmt << 8;
             }
@@ -324,7 +345,7 @@ int plan_attend(ha_rag_ctx *c, const ha_rag_packed_chunk *chunks, const ha_rag_a
         Plan &pl = plans[r];
         if (pl.shared && pl.n_mt > most_mt) most_mt = pl.n_mt;
         pl.all_blocks = 0;
-        for (uint32_t i = 0; i < pl.n_docs; ++i) pl.all_blocks += ((*docs)[pl.first_doc + i].n_tokens + 15u) / 16u;
+        for (uint32_t i = 0; i < pl.n_docs; ++i) pl.all_blocks += (*docs)[pl.first_doc + i].n_blocks;
     }
     const uint32_t waves = most_mt > 8u ? 8u : most_mt > 4u ? 4u : 2u;
     *shared_waves = waves;
@@ -362,22 +383,26 @@ struct PlanStore {
     Fixed<uint32_t> open_k, open_v;
 };
 
-struct HeapPlanStore {
-    std::vector<Plan> plans;
-    std::vector<Doc> docs;
-    std::vector<uint32_t> open_k, open_v;
+struct HeapPlanStore {  // one allocation, not cleared: the lists' entries are written when they are added
+    std::unique_ptr<char[]> mem;
+    PlanStore ps{};
     HeapPlanStore(const ha_rag_attend_request *reqs, uint32_t n_reqs)
     {
         uint64_t n = 0;
         if (reqs && n_reqs <= HA_RAG_MAX_ATTEND_REQUESTS)
             for (uint32_t r = 0; r < n_reqs; ++r) n += reqs[r].n_chunks;
         if (n > HA_RAG_MAX_REQUEST_CHUNKS) n = 0;  // the planning refuses the call anyway
-        plans.resize(n_reqs <= HA_RAG_MAX_ATTEND_REQUESTS ? n_reqs : 0);
-        docs.resize((size_t)n);
-        open_k.resize((size_t)n);
-        open_v.resize((size_t)n);
+        const size_t np = n_reqs <= HA_RAG_MAX_ATTEND_REQUESTS ? n_reqs : 0;
+        static_assert(std::is_trivially_copyable<Plan>::value && std::is_trivially_copyable<Doc>::value && alignof(Plan) == 8 && alignof(Doc) == 8, "");
+        mem.reset(new char[np * sizeof(Plan) + (size_t)n * (sizeof(Doc) + 2u * sizeof(uint32_t))]);
+        ps.plans = reinterpret_cast<Plan *>(mem.get());
+        Doc *docs = reinterpret_cast<Doc *>(ps.plans + np);
+        uint32_t *open = reinterpret_cast<uint32_t *>(docs + n);
+        ps.docs = Fixed<Doc>(docs, (uint32_t)n);
+        ps.open_k = Fixed<uint32_t>(open, (uint32_t)n);
+        ps.open_v = Fixed<uint32_t>(open + n, (uint32_t)n);
     }
-    PlanStore store() { return PlanStore{plans.data(), Fixed<Doc>(docs), Fixed<uint32_t>(open_k), Fixed<uint32_t>(open_v)}; }
+    PlanStore store() { return ps; }
 };
 
 // checks, workspace layout and launches; the caller holds the context's lock.  *need (nullable)
@@ -405,83 +430,120 @@ int attend_locked(ha_rag_ctx *c, PlanStore ps, const ha_rag_packed_chunk *chunks
     const uint32_t H = c->cfg.n_kv_heads;
     float *ws = static_cast<float *>(workspace);
 
-    // two launches in the making: requests for k6_attend_partial, and those for the shared kernel
-    K6Params kp{}, ks{};
-    for (K6Params *q : {&kp, &ks}) {
-        q->n_kv_heads = H;
-        q->n_q_heads = n_q_heads;
-        q->layer = layer;
-        q->scale_log2 = sm_scale * 1.44269504088896341f;
-    }
+    // The launch in the making (36 KiB, of which only what it uses is written): first the requests for
+    // k6_attend_partial, then those for the shared kernel.
+    K6Params kq;
+    kq.n_kv_heads = H;
+    kq.n_q_heads = n_q_heads;
+    kq.layer = layer;
+    kq.scale_log2 = sm_scale * 1.44269504088896341f;
     auto doc_k = [&](const Doc &doc) { return doc.k + (uint64_t)(doc.k_first + layer * doc.k_step) * doc.k_tile; };
     auto doc_v = [&](const Doc &doc) { return doc.v + (uint64_t)(doc.v_first + layer * doc.v_step) * doc.v_tile; };
-    // A launch lists its runs (one grid row each), then the runs' further documents run by run.
+    // ---- requests of at most two tiles: every run is a piece of one document
+    kq.n_runs = 0;
+    auto launch_pieces = [&]() {
+        kq.doc_first = kq.doc_end = K6Params::docs_behind(kq.n_runs);
+        const hipError_t e = launch_k6(kq, st, dry);
+        kq.n_runs = 0;
+        return e;
+    };
+    for (uint32_t r = 0; r < n_reqs; ++r) {
+        const Plan &pl = plans[r];
+        if (pl.shared) continue;
+        const ha_rag_attend_request &rq = reqs[r];
+        float *part = ws + pl.part_floats;
+        for (uint32_t i = 0; i < pl.n_docs; ++i) {
+            const Doc &doc = docs[pl.first_doc + i];
+            uint32_t n_pieces = 0;
+            const uint32_t len = piece_blocks(pl, doc, &n_pieces);
+            K6Run d;
+            d.k = doc_k(doc);
+            d.v = doc_v(doc);
+            d.q = static_cast<const uint16_t *>(rq.q);
+            d.n_tokens = doc.n_tokens;
+            d.info = doc.info;
+            d.n_q = rq.n_q;
+            d.final = 0;
+            d.n_docs = 1;
+            d.more = 0;
+            d.lse = nullptr;
+            for (uint32_t at = 0; at < doc.n_blocks; at += len) {
+                if (kq.n_runs == kAttendMaxRuns) HIPCHK(c, launch_pieces());
+                d.part = part;
+                d.first_block = at;
+                d.end_block = doc.n_blocks - at > len ? at + len : doc.n_blocks;
+                kq.run[kq.n_runs++] = d;
+                part += (uint64_t)H * pl.n_mt * kAttendRecFloats;
+            }
+        }
+    }
+    if (kq.n_runs) HIPCHK(c, launch_pieces());
+
+    // ---- the others: a launch lists its runs (one grid row each), then the runs' further documents run by run.
     // A run never straddles two launches: first count the runs that fit, then fill.
     struct RunPos {
         uint32_t r, doc, blk, run_no;  // request, start of the next run in it, number of that run
     };
-    for (uint32_t sh = 0; sh < 2u; ++sh) {  // the kernel of at most two tiles, then the shared one
-        K6Params &kq = sh ? ks : kp;
-        auto settle = [&](RunPos &p) {  // moves p to the next run there is; false at the end
-            while (p.r < n_reqs && (plans[p.r].shared != sh || p.doc >= plans[p.r].n_docs)) {
-                ++p.r;
-                p.doc = p.blk = p.run_no = 0;
-            }
-            return p.r < n_reqs;
-        };
-        auto take = [&](RunPos &p, Run *run) {  // the run at p; p moves behind it
-            const Plan &pl = plans[p.r];
-            next_run(pl, docs.data + pl.first_doc, p.doc, p.blk, run);
-            ++p.run_no;
-        };
-        RunPos at = {0, 0, 0, 0};
-        while (settle(at)) {
-            uint32_t n_runs = 0, n_more = 0;
-            for (RunPos p = at; settle(p);) {
-                Run run;
-                take(p, &run);
-                if ((uint64_t)(K6Params::docs_behind(n_runs + 1u) + n_more + run.n_docs - 1u) > kAttendMaxDocs) break;
-                ++n_runs;
-                n_more += run.n_docs - 1u;
-            }
-            kq.n_runs = n_runs;
-            kq.doc_first = K6Params::docs_behind(n_runs);
-            uint32_t later = kq.doc_first;  // where the next run's further documents go
-            for (uint32_t k = 0; k < n_runs; ++k) {
-                settle(at);
-                const Plan &pl = plans[at.r];
-                const ha_rag_attend_request &rq = reqs[at.r];
-                const uint32_t run_no = at.run_no;
-                Run run;
-                take(at, &run);
-                const Doc &first = docs[pl.first_doc + run.doc];
-                K6Run &d = kq.run[k];
-                d.k = doc_k(first);
-                d.v = doc_v(first);
-                d.q = static_cast<const uint16_t *>(rq.q);
-                d.part = pl.final ? rq.out : ws + pl.part_floats + (uint64_t)run_no * H * pl.n_mt * kAttendRecFloats;
-                d.final = pl.final;
-                d.lse = pl.final ? rq.lse : nullptr;
-                d.n_tokens = first.n_tokens;
-                d.info = first.info;
-                d.n_q = rq.n_q;
-                d.n_docs = run.n_docs;
-                d.more = later;
-                d.first_block = run.first_block;
-                d.end_block = run.end_block;
-                for (uint32_t i = 1; i < run.n_docs; ++i) {
-                    const Doc &doc = docs[pl.first_doc + run.doc + i];
-                    kq.doc[later++] = K6Doc{doc_k(doc), doc_v(doc), doc.n_tokens, doc.info};
-                }
-            }
-            kq.doc_end = later;
-            HIPCHK(c, sh ? launch_k6_shared(kq, waves, st, dry) : launch_k6(kq, st, dry));
+    auto settle = [&](RunPos &p) {  // moves p to the next run there is; false at the end
+        while (p.r < n_reqs && (!plans[p.r].shared || p.doc >= plans[p.r].n_docs)) {
+            ++p.r;
+            p.doc = p.blk = p.run_no = 0;
         }
+        return p.r < n_reqs;
+    };
+    auto take = [&](RunPos &p, Run *run) {  // the run at p; p moves behind it
+        const Plan &pl = plans[p.r];
+        next_run(pl, docs.data + pl.first_doc, p.doc, p.blk, run);
+        ++p.run_no;
+    };
+    RunPos at = {0, 0, 0, 0};
+    while (settle(at)) {
+        uint32_t n_runs = 0, n_more = 0;
+        for (RunPos p = at; settle(p);) {
+            Run run;
+            take(p, &run);
+            if ((uint64_t)(K6Params::docs_behind(n_runs + 1u) + n_more + run.n_docs - 1u) > kAttendMaxDocs) break;
+            ++n_runs;
+            n_more += run.n_docs - 1u;
+        }
+        kq.n_runs = n_runs;
+        kq.doc_first = K6Params::docs_behind(n_runs);
+        uint32_t later = kq.doc_first;  // where the next run's further documents go
+        for (uint32_t k = 0; k < n_runs; ++k) {
+            settle(at);
+            const Plan &pl = plans[at.r];
+            const ha_rag_attend_request &rq = reqs[at.r];
+            const uint32_t run_no = at.run_no;
+            Run run;
+            take(at, &run);
+            const Doc &first = docs[pl.first_doc + run.doc];
+            K6Run &d = kq.run[k];
+            d.k = doc_k(first);
+            d.v = doc_v(first);
+            d.q = static_cast<const uint16_t *>(rq.q);
+            d.part = pl.final ? rq.out : ws + pl.part_floats + (uint64_t)run_no * H * pl.n_mt * kAttendRecFloats;
+            d.final = pl.final;
+            d.lse = pl.final ? rq.lse : nullptr;
+            d.n_tokens = first.n_tokens;
+            d.info = first.info;
+            d.n_q = rq.n_q;
+            d.n_docs = run.n_docs;
+            d.more = later;
+            d.first_block = run.first_block;
+            d.end_block = run.end_block;
+            for (uint32_t i = 1; i < run.n_docs; ++i) {
+                const Doc &doc = docs[pl.first_doc + run.doc + i];
+                kq.doc[later++] = K6Doc{doc_k(doc), doc_v(doc), doc.n_tokens, doc.info};
+            }
+        }
+        kq.doc_end = later;
+        HIPCHK(c, launch_k6_shared(kq, waves, st, dry));
     }
 
-    K7Params mp{};
+    K7Params mp;
     mp.n_kv_heads = H;
     mp.n_q_heads = n_q_heads;
+    mp.n_reqs = mp.pad = 0;
     for (uint32_t r = 0; r < n_reqs; ++r) {
         if (plans[r].final) continue;  // written by the run's own workgroups
         K7Req &d = mp.r[mp.n_reqs++];

@@ -234,4 +234,13 @@ __device__ __forceinline__ float sum_over_lane_groups(float x)
     return __builtin_bit_cast(float, t0) + __builtin_bit_cast(float, t1);
 }
 
+// Launches a kernel of one argument from where the argument lies.  (The launch syntax passes it by value
+// first: another copy of up to 36 KiB.)
+template <class P>
+inline hipError_t launch_args(void (*kernel)(const P), dim3 grid, dim3 block, uint32_t lds_bytes, hipStream_t stream, P &p)
+{
+    void *args[] = {&p};
+    return hipLaunchKernel(reinterpret_cast<const void *>(kernel), grid, block, args, lds_bytes, stream);
+}
+
 }  // namespace ha_rag

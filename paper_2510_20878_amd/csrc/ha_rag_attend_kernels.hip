@@ -412,7 +412,9 @@ hipError_t check_k6_args(const K6Params &p, uint32_t *max_mt, bool *narrow)
     uint32_t next = p.doc_first;  // the runs' further documents lie in the runs' order, without gaps
     for (uint32_t i = 0; i < p.n_runs; ++i) {
         const K6Run &c = p.run[i];
-        if (!doc_ok(c.k, c.v, c.n_tokens, c.info) || c.n_docs == 0 || !c.q || !c.part || c.n_q == 0 ||
+        const K6Run *const last = i ? &p.run[i - 1u] : nullptr;
+        const bool same = last && last->k == c.k && last->v == c.v && last->n_tokens == c.n_tokens && last->info == c.info;
+        if ((!same && !doc_ok(c.k, c.v, c.n_tokens, c.info)) || c.n_docs == 0 || !c.q || !c.part || c.n_q == 0 ||
             ((uintptr_t)c.q & 15u) || ((uintptr_t)c.part & 15u) || (uint64_t)c.n_q * G > 0xFFFFFFull ||
             c.final > 1u || (!c.final && c.lse) || ((uintptr_t)c.lse & 3u))
             return hipErrorInvalidValue;
@@ -446,10 +448,9 @@ hipError_t launch_k6(K6Params &p, hipStream_t stream, bool check_only)
     if (width > 0x7FFFFFFFull) return hipErrorInvalidValue;
     if (check_only) return hipSuccess;
     dim3 grid((uint32_t)width, p.n_runs), block(64 * kAttendWaves);
-    if (p.mtw == 2) hipLaunchKernelGGL((k6_attend_partial<2, false>), grid, block, 0, stream, p);
-    else if (narrow) hipLaunchKernelGGL((k6_attend_partial<1, true>), grid, block, 0, stream, p);
-    else hipLaunchKernelGGL((k6_attend_partial<1, false>), grid, block, 0, stream, p);
-    return hipGetLastError();
+    if (p.mtw == 2) return launch_args(k6_attend_partial<2, false>, grid, block, 0, stream, p);
+    if (narrow) return launch_args(k6_attend_partial<1, true>, grid, block, 0, stream, p);
+    return launch_args(k6_attend_partial<1, false>, grid, block, 0, stream, p);
 }
 
 // ---------------------------------------------------------------------------
@@ -461,8 +462,8 @@ hipError_t launch_k6(K6Params &p, hipStream_t stream, bool check_only)
 constexpr uint32_t kMergeGroups = 32;  // at most: 1024 threads
 
 // MAXG: groups the build has LDS and an unrolled end for; U: records a group has under way at a time.
-template <uint32_t MAXG, uint32_t U>
-__global__ void __launch_bounds__(32 * MAXG) k7_attend_merge(const K7Params p)
+template <uint32_t MAXG, uint32_t U, class P>
+__global__ void __launch_bounds__(32 * MAXG) k7_attend_merge(const P p)
 {
     __shared__ __attribute__((aligned(16))) float s_acc[MAXG][128];
     __shared__ float s_m[MAXG], s_l[MAXG];
@@ -558,8 +559,8 @@ __global__ void __launch_bounds__(32 * MAXG) k7_attend_merge(const K7Params p)
 // hundreds of rows needs hundreds of workgroups instead of one for each of its rows.
 // Bound: the records' bytes in a batch (44 MB in 10.3 us), the latency of the rounds of loads in a
 // small launch (a group has four records under way at a time), where four groups share them.
-template <uint32_t NG>
-__global__ void __launch_bounds__(256 * NG) k7_attend_merge_tiles(const K7Params p)
+template <uint32_t NG, class P>
+__global__ void __launch_bounds__(256 * NG) k7_attend_merge_tiles(const P p)
 {
     typedef const float __attribute__((address_space(1))) *gfloats;
     typedef const f32x4 __attribute__((address_space(1))) *gquads;
@@ -665,6 +666,15 @@ __global__ void __launch_bounds__(256 * NG) k7_attend_merge_tiles(const K7Params
         r.lse[orow] = l_sum > 0.0f ? (m_max + __builtin_log2f(l_sum)) * 0.69314718055994531f : neg_inf();
 }
 
+template <class P>
+static hipError_t launch_merge(P &p, bool many, uint32_t groups, dim3 grid, dim3 block, hipStream_t stream)
+{
+    if (many && groups <= 16u) return launch_args(k7_attend_merge<16, 8, P>, grid, block, 0, stream, p);
+    if (many) return launch_args(k7_attend_merge<kMergeGroups, 8, P>, grid, block, 0, stream, p);
+    if (groups <= 8u) return launch_args(k7_attend_merge<8, 4, P>, grid, block, 0, stream, p);
+    return launch_args(k7_attend_merge<16, 4, P>, grid, block, 0, stream, p);
+}
+
 hipError_t launch_k7(K7Params &p, hipStream_t stream, bool check_only)
 {
     if (p.n_reqs == 0) return hipSuccess;
@@ -687,15 +697,23 @@ hipError_t launch_k7(K7Params &p, hipStream_t stream, bool check_only)
     }
     if (width > 0x7FFFFFFFull) return hipErrorInvalidValue;
     if (check_only) return hipSuccess;
+    const bool few = p.n_reqs <= kFewMergeReqs;
+    K7ParamsFew pf;
+    if (few) {
+        pf.n_kv_heads = p.n_kv_heads;
+        pf.n_q_heads = p.n_q_heads;
+        pf.n_reqs = p.n_reqs;
+        pf.pad = 0;
+        for (uint32_t i = 0; i < p.n_reqs; ++i) pf.r[i] = p.r[i];
+    }
     if (max_mt > 2u) {  // the requests of the shared kernel: merge tile by tile
         // Four groups where one would need more than four rounds of loads, in a launch small enough
         // for that to show.  Large workgroups start more slowly: 5 records a tile in 256 workgroups
         // took 2 us more with four groups, 1,936 workgroups (most without a tile) 0.7 us.
         const dim3 grid((uint32_t)tile_width, p.n_reqs);
         if (max_units <= 16u || tile_width * p.n_reqs > 2u * kChipCUs)
-            hipLaunchKernelGGL(k7_attend_merge_tiles<1>, grid, dim3(256), 0, stream, p);
-        else hipLaunchKernelGGL(k7_attend_merge_tiles<4>, grid, dim3(1024), 0, stream, p);
-        return hipGetLastError();
+            return few ? launch_args(k7_attend_merge_tiles<1, K7ParamsFew>, grid, dim3(256), 0, stream, pf) : launch_args(k7_attend_merge_tiles<1, K7Params>, grid, dim3(256), 0, stream, p);
+        return few ? launch_args(k7_attend_merge_tiles<4, K7ParamsFew>, grid, dim3(1024), 0, stream, pf) : launch_args(k7_attend_merge_tiles<4, K7Params>, grid, dim3(1024), 0, stream, p);
     }
     // Bound: the launch, one round of loads and the end that brings the groups together, which grows
     // with the groups.  Up to 32 records one group per two of them (a group has four under way); more
@@ -707,11 +725,8 @@ hipError_t launch_k7(K7Params &p, hipStream_t stream, bool check_only)
     uint32_t groups = want < 4u ? 4u : want > kMergeGroups ? kMergeGroups : (uint32_t)want;
     groups = (groups + 1u) & ~1u;
     const dim3 grid((uint32_t)width, p.n_reqs), block(32 * groups);
-    if (many && groups <= 16u) hipLaunchKernelGGL((k7_attend_merge<16, 8>), grid, block, 0, stream, p);
-    else if (many) hipLaunchKernelGGL((k7_attend_merge<kMergeGroups, 8>), grid, block, 0, stream, p);
-    else if (groups <= 8u) hipLaunchKernelGGL((k7_attend_merge<8, 4>), grid, block, 0, stream, p);
-    else hipLaunchKernelGGL((k7_attend_merge<16, 4>), grid, block, 0, stream, p);
-    return hipGetLastError();
+    if (few) return launch_merge(pf, many, groups, grid, block, stream);
+    return launch_merge(p, many, groups, grid, block, stream);
 }
 
 }  // namespace ha_rag

@@ -893,14 +893,11 @@ hipError_t launch_k6_shared(K6Params &p, uint32_t waves, hipStream_t stream, boo
     if (check_only) return hipSuccess;
     dim3 grid((uint32_t)width, p.n_runs);
     const uint32_t lds_bytes = 2u * waves * kSharedBlockLds;
-    if (waves == 2u) hipLaunchKernelGGL((k6_attend_shared<2>), grid, dim3(128), lds_bytes, stream, p);
-    else if (waves == 4u) hipLaunchKernelGGL((k6_attend_shared<4>), grid, dim3(256), lds_bytes, stream, p);
-    else {
-        e = prepare_k6_shared();  // done at ha_rag_create; a no-op from then on
-        if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(k6_attend_roles, grid, dim3(64 * (kRoleScorers + kRoleDecoders)), 2u * kRoleSet, stream, p);
-    }
-    return hipGetLastError();
+    if (waves == 2u) return launch_args(k6_attend_shared<2>, grid, dim3(128), lds_bytes, stream, p);
+    if (waves == 4u) return launch_args(k6_attend_shared<4>, grid, dim3(256), lds_bytes, stream, p);
+    e = prepare_k6_shared();  // done at ha_rag_create; a no-op from then on
+    if (e != hipSuccess) return e;
+    return launch_args(k6_attend_roles, grid, dim3(64 * (kRoleScorers + kRoleDecoders)), 2u * kRoleSet, stream, p);
 }
 
 }  // namespace ha_rag
