@@ -46,19 +46,14 @@ struct Plan {               // one request
     uint32_t first_doc = 0, n_docs = 0;  // its documents that hold tokens
     uint32_t n_mt = 1;
     uint32_t shared = 0;       // goes to the kernel whose waves share each decoded block: more than two query
-                               // tiles, or two in a call that needs that kernel's two-wave build anyway
+                               // tiles, or two in a call whose largest request has three to eight
     uint32_t run_blocks = 0;   // layout blocks per run (what one workgroup takes)
     uint64_t all_blocks = 0;   // layout blocks of all its documents
+    uint64_t wide_blocks = 0;  // those of documents with a 16-bit side
     uint32_t n_runs = 0;       // records per (KV head, tile)
     uint32_t final = 0;        // one run of the shared kernel is all there is: it writes the output itself
     uint64_t part_floats = 0;  // offset of its records in the workspace
 };
-
-// workgroups per (run, KV head) of a request
-uint32_t tile_groups(const Plan &pl, uint32_t waves)
-{
-    return pl.shared ? (pl.n_mt + 2u * waves - 1u) / (2u * waves) : (pl.n_mt + 1u) / 2u;
-}
 
 // A run: the blocks one workgroup takes, a range of the request's blocks in list order.  For the
 // shared kernel it may start and end inside a document and span several; for k6_attend_partial
@@ -144,59 +139,47 @@ uint32_t longest_run_steps(const Plan &pl, const Doc *docs, uint32_t len, uint32
     return steps > most ? steps : most;
 }
 
-// Cuts every request into runs (plans[r].shared says by which kernel's rule) and lays the workspace
-// out.  Returns its size in binary32 words.  in_steps: see the cost of a run length.
-uint64_t lay_out_runs(Plan *plans, uint32_t n_reqs, const Doc *docs, uint32_t H, uint32_t waves, bool in_steps)
+// What a call costs the shared kernel in each of its forms, in ns: `waves` = 2 (k6_attend_shared), 4 or 8
+// (k6_attend_roles<4>, <8>).  Workgroups of one size finish in rounds of as many as the chip holds side by side; a round
+// costs what starting and ending a workgroup does, its steps (a workgroup takes up to `blocks` of them at a time, all of
+// one document), and for k6_attend_roles, alone on its compute unit, a trip to memory at the start of every document;
+// steps get slower the more workgroups share a compute unit, or the memory and the power there is.  A run that is longer
+// than the average one costs a third of the difference: its neighbours are done by then.  Every record is 8 KiB that is
+// written, flushed at the kernel's end and read by another launch.  Fitted to 1,700 timings of 142 calls of 1 to 32
+// requests of 7 to 1,024 blocks at 3 to 402 query tokens, whose runs and forms were set by hand: what it chooses is on
+// average 0.5 % slower than the fastest of those, 9 % at worst; of short calls it is within 14 % of the time, of those
+// that run into the power limit it is too low by a third.
+struct Form {
+    uint32_t waves, shift, side_by_side;   // 1 << shift blocks a step
+    uint32_t call, round, doc;             // ns: once; a round; a document
+    uint32_t step[4];                      // ns: a step with up to a quarter, a half, three quarters and all places taken
+    uint32_t wide;                         // added to a step times the share of blocks with a 16-bit side
+    uint32_t lean;                         // 1 / lean of what the longest run has more steps than the average one counts
+    uint32_t merge, rec_num, rec_den;      // ns: a merge at all; rec_num / rec_den a record
+    bool bounded;                          // no more runs than the fewest rounds x blocks take
+};
+constexpr Form kForms[3] = {
+    {2u, 1u, 4u * kChipCUs, 2000u, 5600u, 0u, {1330u, 2115u, 2120u, 2300u}, 460u, 3u, 3740u, 19u, 10u, false},
+    {4u, 3u, kChipCUs, 5000u, 2900u, 600u, {2000u, 2160u, 2410u, 2770u}, 210u, 3u, 3740u, 19u, 10u, false},
+    {8u, 3u, kChipCUs, 2500u, 6100u, 0u, {3050u, 3230u, 3540u, 3960u}, 210u, 3u, 3740u, 19u, 10u, false},
+};
+// The rule that a call's workspace is sized by (steps, rounds and records in units of a block's time; forms of 2, 4
+// and 8 waves that all score), which stays what it was: the runs are chosen among those whose records fit.  By step, and
+// by block where that does not fit the array of the entry point without a workspace.
+constexpr Form kLimitForms[2][3] = {
+    {{2u, 1u, 4u * kChipCUs, 0u, 8u, 0u, {2u, 2u, 2u, 2u}, 0u, 1u, 0u, 1u, 600u, true},
+     {4u, 2u, 2u * kChipCUs, 0u, 8u, 0u, {4u, 4u, 4u, 4u}, 0u, 1u, 0u, 1u, 450u, true},
+     {8u, 3u, kChipCUs, 0u, 8u, 0u, {8u, 8u, 8u, 8u}, 0u, 1u, 0u, 1u, 280u, true}},
+    {{2u, 0u, 4u * kChipCUs, 0u, 8u, 0u, {1u, 1u, 1u, 1u}, 0u, 1u, 0u, 1u, 600u, true},
+     {4u, 0u, 2u * kChipCUs, 0u, 8u, 0u, {1u, 1u, 1u, 1u}, 0u, 1u, 0u, 1u, 450u, true},
+     {8u, 0u, kChipCUs, 0u, 8u, 0u, {1u, 1u, 1u, 1u}, 0u, 1u, 0u, 1u, 280u, true}},
+};
+
+// The run length of the shared kernel that costs least, of those whose records take no more than most_floats
+// words (one run a request takes none); or only what run length `only` costs (0: any).  A run crosses document
+// boundaries (equal runs finish together whatever the documents' lengths).
+uint64_t best_run(const Form &f, const Plan *plans, uint32_t n_reqs, const Doc *docs, uint32_t H, uint64_t most_floats, uint64_t only, uint64_t *ns)
 {
-    uint64_t total = 0;
-    // A workgroup takes a run of its request's blocks and writes one record per query tile for
-    // it.  Requests of at most two query tiles: a run is a piece of one document, as long as
-    // possible (every workgroup pays for fetching the queries and for writing a record), but
-    // short enough that the launch fills the chip a few times over, since the hardware then
-    // evens out what documents of different formats and lengths take.
-    auto groups_at = [&](uint32_t shift) {  // workgroups of the one/two-tile kernel with pieces of 1 << shift blocks
-        uint64_t groups = 0;
-        for (uint32_t r = 0; r < n_reqs; ++r) {
-            const Plan &pl = plans[r];
-            if (pl.shared) continue;
-            uint64_t runs = 0;
-            for (uint32_t i = 0; i < pl.n_docs; ++i) runs += (docs[pl.first_doc + i].n_blocks + (1u << shift) - 1u) >> shift;
-            groups += runs * H * tile_groups(pl, waves);
-        }
-        return groups;
-    };
-    static_assert(kAttendMaxRunBlocks == 128u, "a power of two");
-    uint32_t shift_p = 7;
-    while ((1u << shift_p) > kAttendMinRunBlocks && groups_at(shift_p) < kAttendTargetGroups) --shift_p;
-    // A call of so few workgroups that even twice as many run side by side (four per CU) is
-    // bound by how long one of them takes: halve once more (one request of 10 x 512 tokens:
-    // 13.7 against 14.7 us; with two requests, 1,280 workgroups, it would cost 1.5 us).
-    if ((1u << shift_p) == kAttendMinRunBlocks && groups_at(shift_p - 1u) <= 4ull * kChipCUs) --shift_p;
-    const uint32_t piece = 1u << shift_p;
-    // The shared kernel: a run crosses document boundaries (equal runs finish together whatever
-    // the documents' lengths).  Workgroups of one size finish in rounds of as many as the chip
-    // holds side by side; every round pays for starting and ending a workgroup, and every record
-    // is written and read again, 16 KiB in all.  Of the run lengths (at least kAttendMinRunBlocks)
-    // the one with the least of rounds x (blocks + start) + records is taken, in units of the time a
-    // workgroup takes for a block with its neighbours: 0.57 us with eight scoring waves, 0.9 with
-    // four, 1.2 with two; a record costs the chip about 2 ns.  Without the last two terms three
-    // requests of 96 to 201 query tokens took runs of 8 blocks, 0.9 GB of records: 647 us per layer, a
-    // third of it the merge, against 214 with two runs per request.
-    // Blocks count in steps: a workgroup takes up to `waves` of them at a time, of one document, and the
-    // length's cost is that of the largest request's longest run.  Counted one by one, eight requests of
-    // four documents of 512 tokens took runs of 9 blocks instead of 8 at 12 query tokens (26.2 us per
-    // layer against 24.4), two of them in the paper's formats runs of 9 at 64 (28.4 against 26.0); counted
-    // in whole steps as if documents had no ends, 24 requests of four of 144 tokens took runs of 8
-    // instead of 9 at 16 (29.1 against 25.3).  (Not in_steps: one by one all the same, for a call whose
-    // records would otherwise not fit.)
-    const uint64_t side_by_side = (uint64_t)kChipCUs * (8u / waves);  // two and four waves: two per SIMD; k6_attend_roles: one workgroup per CU, by its LDS
-    const Plan *largest = nullptr;
-    for (uint32_t r = 0; r < n_reqs; ++r)
-        if (plans[r].shared && (!largest || plans[r].all_blocks > largest->all_blocks)) largest = &plans[r];
-    const uint64_t most_blocks = largest ? largest->all_blocks : 0;
-    const uint32_t shift = waves == 8u ? 3u : waves == 4u ? 2u : 1u;
-    const uint64_t all_steps = largest ? longest_run_steps(*largest, docs + largest->first_doc, ~0u, shift) : 0;
-    const uint64_t recs_per_block = waves == 8u ? 280u : waves == 4u ? 450u : 600u;
     struct Size {  // requests of one size, in the order they come up first
         uint64_t blocks;
         uint32_t n_mt, count;
@@ -213,50 +196,150 @@ uint64_t lay_out_runs(Plan *plans, uint32_t n_reqs, const Doc *docs, uint32_t H,
         if (i == n_sizes) sizes[n_sizes++] = Size{pl.all_blocks, pl.n_mt, 0u};
         ++sizes[i].count;
     }
-    uint64_t run_blocks = most_blocks, best = most_blocks, least = ~0ull, fewest = ~0ull;
-    for (uint64_t n = 1; n <= most_blocks; ++n) {  // n runs for the largest request
+    const Plan *largest = nullptr;
+    uint64_t all = 0, wide = 0;
+    for (uint32_t r = 0; r < n_reqs; ++r) {
+        if (!plans[r].shared) continue;
+        if (!largest || plans[r].all_blocks > largest->all_blocks) largest = &plans[r];
+        all += plans[r].all_blocks;
+        wide += plans[r].wide_blocks;
+    }
+    *ns = 0;
+    if (!largest || !largest->all_blocks) return 1;
+    const uint64_t most_blocks = largest->all_blocks;
+    const uint64_t all_steps = longest_run_steps(*largest, docs + largest->first_doc, ~0u, f.shift);
+    const uint64_t wide_ns = f.wide * wide / all;
+    uint64_t best = most_blocks, least = ~0ull, bounded = most_blocks, fewest = ~0ull;
+    for (uint64_t n = only ? (most_blocks + only - 1u) / only : 1u; n <= most_blocks; ++n) {  // n runs for the largest request
         const uint64_t len = (most_blocks + n - 1u) / n;
         if (n > 1 && len < kAttendMinRunBlocks) break;
         uint64_t wgs = 0, recs = 0;
         auto add = [&](uint64_t blocks, uint32_t n_mt, uint32_t count) {
             const uint64_t runs = (blocks + len - 1u) / len * count;
-            wgs += runs * H * ((n_mt + 2u * waves - 1u) / (2u * waves));
+            wgs += runs * H * ((n_mt + 2u * f.waves - 1u) / (2u * f.waves));
             if (blocks > len) recs += runs * H * n_mt;
         };
         for (uint32_t i = 0; i < n_sizes; ++i) add(sizes[i].blocks, sizes[i].n_mt, sizes[i].count);
         for (uint32_t r = rest; r < n_reqs; ++r)
             if (plans[r].shared) add(plans[r].all_blocks, plans[r].n_mt, 1u);
-        const uint64_t rounds = (wgs + side_by_side - 1u) / side_by_side;
-        auto cost = [&](uint64_t blocks) { return rounds * (blocks + kAttendStartBlocks) + recs / recs_per_block; };
-        uint64_t c = cost(len);
-        if (in_steps) {
-            // The average of the runs (no run length's longest has fewer), which is close enough for runs of
-            // many documents; of a request of few the longest, if the average could do.
-            uint64_t steps = (len + waves - 1u) >> shift;
-            if (all_steps > steps * n) steps = (all_steps + n - 1u) / n;
-            c = cost(steps << shift);
-            if (c < least && largest->n_docs <= kAttendFewDocs)
-                c = cost((uint64_t)longest_run_steps(*largest, docs + largest->first_doc, (uint32_t)len, shift) << shift);
+        if (n > 1 && recs * kAttendRecFloats > most_floats) break;
+        const uint64_t rounds = (wgs + f.side_by_side - 1u) / f.side_by_side;
+        const uint64_t taken = wgs < f.side_by_side ? wgs : f.side_by_side;  // places
+        const uint64_t quarter = f.side_by_side / 4u, q = taken <= quarter ? 0u : (taken - 1u) / quarter - 1u;
+        uint64_t step = f.step[q] + wide_ns;  // between two of the four
+        if (taken > quarter) step += (f.step[q + 1u] - f.step[q]) * (taken - (q + 1u) * quarter) / quarter;
+        const uint64_t in_docs = (largest->n_docs * len + most_blocks - 1u) / most_blocks * f.doc;
+        // The average of the runs (no run length's longest has fewer), which is close enough for runs of
+        // many documents; of a request of few the longest too, if the average could do.
+        uint64_t steps = (len + (1u << f.shift) - 1u) >> f.shift;
+        if (all_steps > steps * n) steps = (all_steps + n - 1u) / n;
+        uint64_t c = f.call + rounds * (f.round + steps * step + in_docs) + (recs ? f.merge + recs * f.rec_num / f.rec_den : 0u);
+        if (c < least && largest->n_docs <= kAttendFewDocs) {
+            const uint32_t longest = longest_run_steps(*largest, docs + largest->first_doc, (uint32_t)len, f.shift);
+            if (longest > steps) c += rounds * ((longest - steps) * step / f.lean);
         }
         if (c < least) {
             least = c;
             best = len;
         }
-        if (rounds * len < fewest) {  // more runs than here only for fewer rounds x blocks: it bounds the records
+        if (rounds * len < fewest) {
             fewest = rounds * len;
-            run_blocks = best;
+            bounded = best;
         }
-        if (wgs >= 64u * side_by_side) break;  // finer than this gains nothing
+        if (only || wgs >= 64u * f.side_by_side) break;  // finer than this gains nothing
     }
+    *ns = least;
+    return f.bounded ? bounded : best;
+}
+
+// Cuts the requests of one kernel (the shared one or the other) into runs and lays their part of the workspace out,
+// from word `total` on.  Returns where it ends.
+uint64_t cut(Plan *plans, uint32_t n_reqs, const Doc *docs, uint32_t H, bool shared, uint64_t run_blocks, uint64_t total)
+{
     for (uint32_t r = 0; r < n_reqs; ++r) {
         Plan &pl = plans[r];
-        pl.run_blocks = !pl.shared ? piece : run_blocks > 0xFFFFFFFFull ? 0xFFFFFFFFu : (uint32_t)(run_blocks ? run_blocks : 1u);
+        if ((pl.shared != 0u) != shared) continue;
+        pl.run_blocks = run_blocks > 0xFFFFFFFFull ? 0xFFFFFFFFu : (uint32_t)(run_blocks ? run_blocks : 1u);
         pl.n_runs = count_runs(pl, docs + pl.first_doc);
-        pl.final = pl.shared && pl.n_runs == 1u;  // no record, no merge
+        pl.final = shared && pl.n_runs == 1u;  // no record, no merge
         pl.part_floats = total;
         if (!pl.final) total += (uint64_t)pl.n_runs * H * pl.n_mt * kAttendRecFloats;
     }
     return total;
+}
+
+// Requests of at most two query tiles: a run is a piece of one document, as long as
+// possible (every workgroup pays for fetching the queries and for writing a record), but
+// short enough that the launch fills the chip a few times over, since the hardware then
+// evens out what documents of different formats and lengths take.
+uint32_t piece_length(const Plan *plans, uint32_t n_reqs, const Doc *docs, uint32_t H)
+{
+    auto groups_at = [&](uint32_t shift) {  // workgroups with pieces of 1 << shift blocks
+        uint64_t groups = 0;
+        for (uint32_t r = 0; r < n_reqs; ++r) {
+            const Plan &pl = plans[r];
+            if (pl.shared) continue;
+            uint64_t runs = 0;
+            for (uint32_t i = 0; i < pl.n_docs; ++i) runs += (docs[pl.first_doc + i].n_blocks + (1u << shift) - 1u) >> shift;
+            groups += runs * H * ((pl.n_mt + 1u) / 2u);
+        }
+        return groups;
+    };
+    static_assert(kAttendMaxRunBlocks == 128u, "a power of two");
+    uint32_t shift = 7;
+    while ((1u << shift) > kAttendMinRunBlocks && groups_at(shift) < kAttendTargetGroups) --shift;
+    // A call of so few workgroups that even twice as many run side by side (four per CU) is
+    // bound by how long one of them takes: halve once more (one request of 10 x 512 tokens:
+    // 13.7 against 14.7 us; with two requests, 1,280 workgroups, it would cost 1.5 us).
+    if ((1u << shift) == kAttendMinRunBlocks && groups_at(shift - 1u) <= 4ull * kChipCUs) --shift;
+    return 1u << shift;
+}
+
+// Cuts every request into runs and lays the workspace out; plans[r].shared says by which kernel's rule.  Returns its
+// size in binary32 words.  *waves: the form of the shared kernel, chosen here among those
+// whose workgroups are not mostly empty for the call's largest request (most_mt query tiles).
+uint64_t lay_out_runs(Plan *plans, uint32_t n_reqs, const Doc *docs, uint32_t H, uint32_t most_mt, uint32_t by_block, uint64_t most_floats, uint32_t *waves)
+{
+    const uint64_t pieces = cut(plans, n_reqs, docs, H, false, piece_length(plans, n_reqs, docs, H), 0);
+    const uint64_t room = most_floats > pieces ? most_floats - pieces : 0u;
+    // The shared kernel: four scorers (up to 8 tiles a workgroup) for every call; eight where a request has more
+    // tiles, which then decodes every block once less; and k6_attend_shared, whose four workgroups on a compute unit all
+    // decode and score in turn, for requests of up to four tiles, where half of four scorers would have none.  Measured, us
+    // a layer, k6_attend_shared / four scorers / eight: 12 query tokens, 8 requests x 4 x 512 tokens 23.9 / 23.0, 32 x 10 x
+    // 512 109 / 136, 12 ragged requests in the paper's formats 42 / 53; 64 query tokens, 2 x 4 x 512 - / 23.1 / 26.5, 16 x
+    // 4 x 512 - / 72.9 / 60.7, 32 x 10 x 512 - / 288 / 205.
+    // Four scorers are as exact in long runs as in short ones (role_add_round) and take the length that costs least; the
+    // others keep the runs that the workspace is sized for: longer ones cost them up to 1.8 times the error.
+    uint64_t run_blocks = 1, least = ~0ull;
+    for (const Form &f : kForms) {
+        if (f.waves == 2u ? most_mt > 4u : f.waves == 8u && most_mt <= 8u) continue;
+        uint64_t ns = 0, len = 0;
+        if (f.waves != 4u) len = best_run(kLimitForms[by_block][f.waves == 8u ? 2 : 0], plans, n_reqs, docs, H, room, 0, &ns);
+        len = best_run(f, plans, n_reqs, docs, H, room, len, &ns);
+        if (f.waves == 4u) ns += ns / 32u;  // on an even estimate the form that was there before
+        if (ns < least) {
+            least = ns;
+            run_blocks = len;
+            *waves = f.waves;
+        }
+    }
+    return cut(plans, n_reqs, docs, H, true, run_blocks, pieces);
+}
+
+// Words of the workspace by the rule of kLimitForms, two-tile requests with the shared kernel's (a call of requests of at
+// most four) or not, whichever takes less.
+uint64_t limit_floats(Plan *plans, uint32_t n_reqs, const Doc *docs, uint32_t H, uint32_t most_mt, uint32_t by_block)
+{
+    const Form &f = kLimitForms[by_block][most_mt > 8u ? 2 : most_mt > 4u ? 1 : 0];
+    uint64_t least = ~0ull;
+    for (uint32_t with : {0u, 1u}) {
+        if (with && (!most_mt || most_mt > 4u)) break;
+        for (uint32_t r = 0; r < n_reqs; ++r) plans[r].shared = plans[r].n_mt > 2u || (with && plans[r].n_mt == 2u);
+        uint64_t ns = 0, total = cut(plans, n_reqs, docs, H, false, piece_length(plans, n_reqs, docs, H), 0);
+        total = cut(plans, n_reqs, docs, H, true, best_run(f, plans, n_reqs, docs, H, ~0ull, 0, &ns), total);
+        if (total < least) least = total;
+    }
+    return least;
 }
 
 // Checks everything and lays the workspace out.  *floats = workspace size in binary32 words.
@@ -338,37 +421,39 @@ int plan_attend(ha_rag_ctx *c, const ha_rag_packed_chunk *chunks, const ha_rag_a
         pl.n_docs = (uint32_t)docs->size() - pl.first_doc;
         n_chunks += rq.n_chunks;
     }
-    // The shared kernel runs with as many waves (two tiles each) as the call's largest request
-    // has use for: 2 or 4, or the eight scoring waves of k6_attend_roles.
-    uint32_t most_mt = 0;
+    uint32_t most_mt = 0;  // of the requests with more than two tiles
     for (uint32_t r = 0; r < n_reqs; ++r) {
         Plan &pl = plans[r];
         if (pl.shared && pl.n_mt > most_mt) most_mt = pl.n_mt;
-        pl.all_blocks = 0;
-        for (uint32_t i = 0; i < pl.n_docs; ++i) pl.all_blocks += (*docs)[pl.first_doc + i].n_blocks;
+        pl.all_blocks = pl.wide_blocks = 0;
+        for (uint32_t i = 0; i < pl.n_docs; ++i) {
+            const Doc &doc = (*docs)[pl.first_doc + i];
+            pl.all_blocks += doc.n_blocks;
+            if ((doc.info & 0xFu) == HA_RAG_PREC_16 || ((doc.info >> 8) & 0xFu) == HA_RAG_PREC_16) pl.wide_blocks += doc.n_blocks;
+        }
     }
-    const uint32_t waves = most_mt > 8u ? 8u : most_mt > 4u ? 4u : 2u;
-    *shared_waves = waves;
-    // A call that needs the two-wave shared kernel anyway takes its requests of two query tiles there
-    // as well: a block costs that kernel what it costs the other one (103 against 100 us per
-    // call of 32 requests), and one launch fills the chip where two in a row do not (12 requests of
-    // 6 to 16 query tokens: 46 against 63 us per layer).  Not if the partial results then took
-    // more workspace.
-    auto lay_out = [&](bool in_steps) {
-        for (uint32_t r = 0; r < n_reqs; ++r) plans[r].shared = plans[r].n_mt > 2u;
-        const uint64_t apart = lay_out_runs(plans, n_reqs, docs->data, H, waves, in_steps);
-        if (!most_mt || waves != 2u) return apart;
+    // A call whose largest request has three to eight tiles takes its requests of two tiles to the shared kernel
+    // as well: a block costs that kernel what it costs the other one (103 against 100 us per call of 32
+    // requests), and one launch fills the chip where two in a row do not (12 requests of 6 to 16 query tokens: 46
+    // against 63 us per layer).  Not if the partial results of the other kernel then took more workspace than there is.
+    *shared_waves = 2;
+    uint64_t total;
+    if (!most_mt) {
+        total = cut(plans, n_reqs, docs->data, H, false, piece_length(plans, n_reqs, docs->data, H), 0);
+    } else {
+        uint32_t by_block = 0;
+        total = limit_floats(plans, n_reqs, docs->data, H, most_mt, by_block);
+        if (total > most_floats) total = limit_floats(plans, n_reqs, docs->data, H, most_mt, by_block = 1u);
         uint32_t moved = 0;
-        for (uint32_t r = 0; r < n_reqs; ++r)
-            if (plans[r].n_mt == 2u) plans[r].shared = moved = 1u;
-        if (!moved) return apart;
-        const uint64_t together = lay_out_runs(plans, n_reqs, docs->data, H, waves, in_steps);
-        if (together <= apart) return together;
-        for (uint32_t r = 0; r < n_reqs; ++r) plans[r].shared = plans[r].n_mt > 2u;
-        return lay_out_runs(plans, n_reqs, docs->data, H, waves, in_steps);
-    };
-    uint64_t total = lay_out(true);
-    if (total > most_floats) total = lay_out(false);
+        for (uint32_t r = 0; r < n_reqs; ++r) {
+            plans[r].shared = plans[r].n_mt > 2u;
+            if (most_mt <= 8u && plans[r].n_mt == 2u) plans[r].shared = moved = 1u;
+        }
+        if (lay_out_runs(plans, n_reqs, docs->data, H, most_mt, by_block, total, shared_waves) > total && moved) {
+            for (uint32_t r = 0; r < n_reqs; ++r) plans[r].shared = plans[r].n_mt > 2u;
+            lay_out_runs(plans, n_reqs, docs->data, H, most_mt, by_block, total, shared_waves);
+        }
+    }
     if (total * 4ull > (1ull << 40)) return HA_RAG_EINVAL;
     *floats = total;
     return HA_RAG_OK;

@@ -2,20 +2,22 @@
 // wave can keep (more than two 16-row tiles: the question's prefill of Sec. 2.1, tens of query
 // tokens times the query heads of a KV head), and for requests of two tiles next to such.
 //
-//  k6_attend_shared<W>   one workgroup of W waves (2 or 4) per (run of blocks across a request's
-//      documents in list order, KV head, group of 2 W query tiles).  Every wave owns two query
+//  k6_attend_shared   one workgroup of two waves per (run of blocks across a request's
+//      documents in list order, KV head, group of four query tiles).  Every wave owns two query
 //      tiles for the whole run: their queries, reference maxima, sums and output rows stay in its
-//      registers.  The layout blocks are taken W at a time: half the waves decode the keys and
-//      half the values of the round, two blocks each, to BF16 (the values a load would write)
-//      and leave them in LDS in the form the MFMAs take their operands in; after one barrier
-//      every wave scores all W blocks against its own tiles, two blocks (a pair) at a time.  A
-//      block is therefore fetched and decoded once per 32 W query rows.  The rounds alternate
+//      registers.  The layout blocks are taken two at a time: one wave decodes the keys and
+//      one the values of the round to BF16 (the values a load would write)
+//      and leaves them in LDS in the form the MFMAs take their operands in; after one barrier
+//      both waves score the blocks (a pair) against their own tiles.  A
+//      block is therefore fetched and decoded once per 64 query rows.  The rounds alternate
 //      between two sets of LDS buffers, so one barrier per round is enough: a wave that writes
 //      round r + 1 has passed barrier r, which every wave reaches only after it has read all of
 //      round r - 1.
-//  k6_attend_roles       the same for requests of more than eight tiles, with waves of two kinds:
-//      eight that score (two tiles each, so 256 query rows) and four that decode the next round
-//      meanwhile.  Described at the kernel.
+//  k6_attend_roles    the same with waves of two kinds: four or eight that score (two tiles each, so 128
+//      or 256 query rows) and four that decode the next round of eight blocks meanwhile.  Described at
+//      the kernel.
+// Which of them a call takes, and in runs of what length, follows from what each is expected to cost (kForms in
+// ha_rag_attend.hip).
 //
 // Block geometry as for k6_attend_partial: lane (c = lane / 16, n = lane % 16) of the wave that
 // reads a block holds, in plane j, token 4 j + c, dims 8 n .. 8 n + 7.
@@ -335,7 +337,7 @@ __device__ __forceinline__ void lds_barrier()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
-constexpr uint32_t kRoleScorers = 8, kRoleDecoders = 4;  // waves of a workgroup
+constexpr uint32_t kRoleDecoders = 4;                      // waves of a workgroup besides the scoring ones
 constexpr uint32_t kRoleBlocks = 8;                       // layout blocks per round
 // LDS of a pair of blocks: the keys of each block as 16 rows of 256 bytes, 16 bytes apart so that
 // the lanes of a column reach different banks with constant offsets (an exclusive-or of row and
@@ -564,6 +566,41 @@ __device__ __forceinline__ float role_weights(const f32x4 &s0, const f32x4 &s1, 
     return ((pr[0] + pr[1]) + (pr[2] + pr[3])) + ((pr[4] + pr[5]) + (pr[6] + pr[7]));
 }
 
+// What the rounds before this one came to, for a scorer with registers to spare (S = 4).  A round's rows are scaled by
+// what rounding did to that round's weights (their sum before over their sum after) when they are added here, so that a
+// long run is about as exact as runs of one round each, whose records the merge adds up the same way.  Error against 64 bits
+// of 8 requests x 4 x 512 tokens at 12 query tokens: runs of 8 blocks 0.44e-3, of 32 with one factor a run 0.76e-3, with one a
+// round 0.48e-3.  Over the 28 of 70 calls (1 to 32 requests, 3 to 402 query tokens) that S = 4 took over, 0.94 times the error
+// they had, 0.55 to 1.12.
+struct RoleTotal {
+    f32x4 O[2][8];
+    float l_run[2];
+};
+
+// Adds a round to the total; the next one's first products overwrite st.O.  The factors come first, while the round's
+// last MFMAs run.  (Sums below the smallest normal number have no reciprocal; their rows' factor is 1.)
+__device__ __forceinline__ void role_add_round(const RoleLane &ln, SharedState &st, RoleTotal &tot)
+{
+    const uint32_t c_ = fresh(ln.lane) >> 4;
+    float f[2][4];  // of output rows 4 c_ + jj
+#pragma unroll
+    for (int mt = 0; mt < 2; ++mt) {
+        const float l = sum_over_lane_groups(st.l_run[mt]), r = sum_over_lane_groups(st.r_run[mt]);
+        const float fit = r >= __FLT_MIN__ * 4.0f ? l * __builtin_amdgcn_rcpf(r) : 1.0f;
+#pragma unroll
+        for (int jj = 0; jj < 4; ++jj) f[mt][jj] = __shfl(fit, (int)(4u * c_ + jj));
+        tot.l_run[mt] += st.l_run[mt];
+        st.l_run[mt] = st.r_run[mt] = 0.0f;
+    }
+    mfma_result_wait();
+#pragma unroll
+    for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+        for (int pp = 0; pp < 8; ++pp)
+#pragma unroll
+            for (int jj = 0; jj < 4; ++jj) tot.O[mt][pp][jj] = __builtin_fmaf(st.O[mt][pp][jj], f[mt][jj], tot.O[mt][pp][jj]);
+}
+
 // A round of a scorer: its two tiles against `nb` blocks, two (a pair) at a time.  The LDS reads are
 // issued ahead of what hides them: the keys of a pair's first block before the P V MFMAs of the
 // pair before, those of the second before the first's MFMAs, the values before the softmax.
@@ -571,8 +608,9 @@ __device__ __forceinline__ float role_weights(const f32x4 &s0, const f32x4 &s1, 
 // is, and only if their sum says that one of them may be too large (or there is no reference yet)
 // the row maxima are taken, what is accumulated is rescaled and the weights are formed again.
 // That saves the maxima of every pair, a fifth of the softmax's instructions.
+template <bool TOTAL>
 __device__ __forceinline__ void role_score_round(const uint8_t *base, uint32_t rb, uint32_t nb, uint32_t end,
-                                                 float scale_log2, const RoleLane &ln, SharedState &st)
+                                                 float scale_log2, const RoleLane &ln, SharedState &st, RoleTotal &tot)
 {
     u32x4 ka0[4], ka1[4];
     const uint8_t *key = base + ln.key;
@@ -632,13 +670,17 @@ __device__ __forceinline__ void role_score_round(const uint8_t *base, uint32_t r
                 const float alpha = __builtin_amdgcn_exp2f(st.m_run[mt] - m_new);  // 0 where there was no reference, 1 if nothing moved
                 st.l_run[mt] *= alpha;
                 st.r_run[mt] *= alpha;
+                if (TOTAL) tot.l_run[mt] *= alpha;
                 st.m_run[mt] = m_new;
                 const uint32_t c_ = fresh(ln.lane) >> 4;
 #pragma unroll
                 for (int jj = 0; jj < 4; ++jj) {
                     const float ar = __shfl(alpha, (int)(4u * c_ + jj));  // factor of output row 4 c_ + jj
 #pragma unroll
-                    for (int pp = 0; pp < 8; ++pp) st.O[mt][pp][jj] *= ar;
+                    for (int pp = 0; pp < 8; ++pp) {
+                        st.O[mt][pp][jj] *= ar;
+                        if (TOTAL) tot.O[mt][pp][jj] *= ar;
+                    }
                 }
                 sum[mt] = role_weights(S[0][mt], S[1][mt], scale_log2, m_new, P8[mt]);
             }
@@ -656,23 +698,37 @@ __device__ __forceinline__ void role_score_round(const uint8_t *base, uint32_t r
 #pragma unroll
         for (uint32_t y = 0; y < 4; ++y) ka0[y] = *reinterpret_cast<const u32x4 *>(key + 16u * y);
         __builtin_amdgcn_sched_barrier(0);
+        if (TOTAL && pr == 0u) {
 #pragma unroll
-        for (int pp = 0; pp < 8; ++pp) {
-            const bf16x8 v = __builtin_bit_cast(bf16x8, vq[pp]);
+            for (int pp = 0; pp < 8; ++pp) {
+                const bf16x8 v = __builtin_bit_cast(bf16x8, vq[pp]);
 #pragma unroll
-            for (int mt = 0; mt < 2; ++mt)
-                st.O[mt][pp] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(P8[mt], v, st.O[mt][pp], 0, 0, 0);
+                for (int mt = 0; mt < 2; ++mt)
+                    st.O[mt][pp] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(P8[mt], v, f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+            }
+        } else {
+#pragma unroll
+            for (int pp = 0; pp < 8; ++pp) {
+                const bf16x8 v = __builtin_bit_cast(bf16x8, vq[pp]);
+#pragma unroll
+                for (int mt = 0; mt < 2; ++mt)
+                    st.O[mt][pp] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(P8[mt], v, st.O[mt][pp], 0, 0, 0);
+            }
         }
     }
+    if (TOTAL) role_add_round(ln, st, tot);
 }
 
 }  // namespace
 
-// W = 2 or 4 waves, half of them decoding keys and half values; two waves per SIMD keep 256 registers
+// Two waves, one decoding keys and one values; two waves per SIMD keep 256 registers
 // each (two tiles of output, their queries, the raw words of two blocks).
-template <int W>
-__global__ void __launch_bounds__(64 * W, 2) k6_attend_shared(const K6Params p)
+// Bound: instructions.  Of 4,080 clocks a round (16 query tokens, 32 requests x 5,120 tokens) a wave decodes 1,290 and scores
+// 1,970, waits 210 for its loads and 320 at the barrier; another wave on its SIMD does the same.  (16-bit documents: 2,480 of
+// 6,300 wait for loads.)
+__global__ void __launch_bounds__(128, 2) k6_attend_shared(const K6Params p)
 {
+    constexpr int W = 2;
     // two sets of W block buffers
     extern __shared__ __attribute__((aligned(16))) uint8_t lds_bytes[];
     uint8_t (*lds)[W][kSharedBlockLds] = reinterpret_cast<uint8_t (*)[W][kSharedBlockLds]>(lds_bytes);
@@ -755,12 +811,19 @@ __global__ void __launch_bounds__(64 * W, 2) k6_attend_shared(const K6Params p)
     shared_write_results(c, hdr, h, tile0, M, ln.c_, ln.n_, st);
 }
 
-// Eight waves score, two query tiles each (up to 256 query rows a workgroup), four decode: two the
+// S = 4 or 8 waves score, two query tiles each (up to 128 or 256 query rows a workgroup), four decode: two the
 // keys and two the values of a round of eight blocks, for the round after the one that is being
-// scored.  One barrier per round, for LDS only.  Three waves per SIMD (168 registers): two scorers,
-// whose registers hold no raw words, and a decoder that fills their gaps.
+// scored.  One barrier per round, for LDS only.  With S = 8 three waves per SIMD (168 registers): two scorers,
+// whose registers hold no raw words, and a decoder that fills their gaps.  With S = 4 one scorer and one decoder per
+// SIMD: a round takes 2.2 us instead of 3.1 to 4.3, so that a call with compute units to spare, or with no more than
+// eight tiles a request, is done sooner.  Without the rounds' factors (role_add_round, a tenth of the time) a scorer takes
+// 3,600 clocks a round and a decoder 3,800 to 4,000; eight decoders, loads two rounds ahead and 32x32x16 MFMAs over two
+// pairs at a time all measured the same or worse.
+// S = 4 against what took these calls before, us a layer: one request of 8 x 512 tokens, 64 query tokens (S = 8): 25.8 -> 22.0;
+// two of 4 x 512: 25.5 -> 21.7; one of 8 x 1,024, 16 query tokens (k6_attend_shared): 26.3 -> 21.2; 32 requests x 5,120 tokens,
+// 32 query tokens (four waves that decoded and scored in turn): 143 -> 140.
 //
-// Bound: the SIMDs' instruction slots and the clock.  32 requests x 5,120 tokens x 64 query tokens
+// S = 8 is bound by the SIMDs' instruction slots and the clock.  32 requests x 5,120 tokens x 64 query tokens
 // x 32 heads (172 GFLOP a layer, one workgroup per CU, one run per request): 215-227 us with eight waves
 // that decoded and scored in turn, 182-192 now = 907-944 TFLOP/s, against 1,390 of a large matrix
 // product.  Of 383,000 clocks the matrix cores work 164,000 and vector instructions take about
@@ -769,8 +832,10 @@ __global__ void __launch_bounds__(64 * W, 2) k6_attend_shared(const K6Params p)
 // much: the split into two kinds of waves 10 %; operands read ahead of what hides them 2 %; the maxima
 // after the fact, keys without address arithmetic, codes without conversions and values rounded
 // straight into operands 4 %; the reference lifted above the maximum 3 %; loads issued in the order they are
-// decoded in (before, the compiler waited for all of them at the top of the loop) 2 %.
-__global__ void __launch_bounds__(64 * (kRoleScorers + kRoleDecoders), 3) k6_attend_roles(const K6Params p)
+// decoded in (before, the compiler waited for all of them at the top of the loop) 2 %.  It runs at the card's power limit:
+// scoring with 32x32x16 MFMAs took 6 % fewer clocks at a clock 5 % lower, 186.5 -> 189.5 us.
+template <int S>
+__global__ void __launch_bounds__(64 * (S + kRoleDecoders), (S + kRoleDecoders) / 4) k6_attend_roles(const K6Params p)
 {
     extern __shared__ __attribute__((aligned(16))) uint8_t lds_bytes[];
     K6Run c = p.run[blockIdx.y];
@@ -793,7 +858,7 @@ __global__ void __launch_bounds__(64 * (kRoleScorers + kRoleDecoders), 3) k6_att
     pin(end_block);
     const uint32_t H = hdr.n_kv_heads, G = hdr.n_q_heads / H, M = c.n_q * G;
     const uint32_t n_mt = (M + 15u) >> 4;
-    const uint32_t n_mtg = (n_mt + 2u * kRoleScorers - 1u) / (2u * kRoleScorers);
+    const uint32_t n_mtg = (n_mt + 2u * (uint32_t)S - 1u) / (2u * (uint32_t)S);
     const uint32_t u = blockIdx.x;
     if (u >= H * n_mtg) return;  // the grid is as wide as the widest run
     const uint32_t mtg = u % n_mtg, h = u / n_mtg;
@@ -805,9 +870,9 @@ __global__ void __launch_bounds__(64 * (kRoleScorers + kRoleDecoders), 3) k6_att
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     uint32_t set = 0;
 
-    if (wave >= kRoleScorers) {
+    if (wave >= (uint32_t)S) {
         ln.key = ln.c_ * kRoleKeyRow + ln.n_ * 16u;
-        const uint32_t dec = wave - kRoleScorers;
+        const uint32_t dec = wave - (uint32_t)S;
         const bool is_k = dec < kRoleDecoders / 2u;
         const uint32_t r = dec & 1u;
         for (uint32_t d = 0; d < run; ++d) {
@@ -831,7 +896,7 @@ __global__ void __launch_bounds__(64 * (kRoleScorers + kRoleDecoders), 3) k6_att
         return;
     }
 
-    const uint32_t tile0 = (mtg * kRoleScorers + wave) * 2u;  // this wave's tiles: tile0, tile0 + 1
+    const uint32_t tile0 = (mtg * (uint32_t)S + wave) * 2u;  // this wave's tiles: tile0, tile0 + 1
     const bool active = tile0 < n_mt;
     // the token of MFMA row n_ is 4 (n_ % 4) + n_ / 4, so that score register jj of lane group c_
     // belongs to token 4 jj + c_, the token whose values the lane group's plane jj holds
@@ -839,6 +904,7 @@ __global__ void __launch_bounds__(64 * (kRoleScorers + kRoleDecoders), 3) k6_att
     SharedState st;
     shared_load_queries(c, hdr, h, tile0, M, ln.lane >> 4, ln.lane & 15u, st);
     st.m_run[0] = st.m_run[1] = kRoleNoRef;
+    RoleTotal tot = {};
     for (uint32_t d = 0; d < run; ++d) {
         const uint32_t T = d ? p.doc[more + d - 1u].n_tokens : c.n_tokens;
         const uint32_t nblk = (T + 15u) >> 4;
@@ -850,13 +916,21 @@ __global__ void __launch_bounds__(64 * (kRoleScorers + kRoleDecoders), 3) k6_att
             lds_barrier();
             if (active) {
                 const uint32_t nb = b1 - rb < kRoleBlocks ? b1 - rb : kRoleBlocks;
-                role_score_round(lds_bytes + set * kRoleSet, rb, nb, end, hdr.scale_log2, ln, st);
+                role_score_round<S == 4>(lds_bytes + set * kRoleSet, rb, nb, end, hdr.scale_log2, ln, st, tot);
             }
             set ^= 1u;
         }
         mfma_result_wait();
     }
     if (!active) return;
+    if (S == 4) {
+#pragma unroll
+        for (int mt = 0; mt < 2; ++mt) {
+            st.l_run[mt] = st.r_run[mt] = tot.l_run[mt];  // rounding is accounted for
+#pragma unroll
+            for (int pp = 0; pp < 8; ++pp) st.O[mt][pp] = tot.O[mt][pp];
+        }
+    }
     const uint32_t lane_ = fresh(ln.lane);
     shared_write_results(c, hdr, h, tile0, M, lane_ >> 4, lane_ & 15u, st);
 }
@@ -872,9 +946,10 @@ hipError_t prepare_k6_shared()
     if (e != hipSuccess) return e;
     if (dev < 0 || dev >= 64) return hipErrorInvalidDevice;
     if (asked.load(std::memory_order_acquire) >> dev & 1u) return hipSuccess;
-    e = hipFuncSetAttribute(reinterpret_cast<const void *>(k6_attend_roles),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)(2u * kRoleSet));
-    if (e != hipSuccess) return e;
+    for (const void *k : {reinterpret_cast<const void *>(k6_attend_roles<4>), reinterpret_cast<const void *>(k6_attend_roles<8>)}) {
+        e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)(2u * kRoleSet));
+        if (e != hipSuccess) return e;
+    }
     asked.fetch_or(1ull << dev, std::memory_order_release);
     return hipSuccess;
 }
@@ -892,12 +967,12 @@ hipError_t launch_k6_shared(K6Params &p, uint32_t waves, hipStream_t stream, boo
     p.mtw = 2;
     if (check_only) return hipSuccess;
     dim3 grid((uint32_t)width, p.n_runs);
-    const uint32_t lds_bytes = 2u * waves * kSharedBlockLds;
-    if (waves == 2u) return launch_args(k6_attend_shared<2>, grid, dim3(128), lds_bytes, stream, p);
-    if (waves == 4u) return launch_args(k6_attend_shared<4>, grid, dim3(256), lds_bytes, stream, p);
+    if (waves == 2u) return launch_args(k6_attend_shared, grid, dim3(128), 2u * 2u * kSharedBlockLds, stream, p);
     e = prepare_k6_shared();  // done at ha_rag_create; a no-op from then on
     if (e != hipSuccess) return e;
-    return launch_args(k6_attend_roles, grid, dim3(64 * (kRoleScorers + kRoleDecoders)), 2u * kRoleSet, stream, p);
+    const dim3 block(64u * (waves + kRoleDecoders));
+    if (waves == 4u) return launch_args(k6_attend_roles<4>, grid, block, 2u * kRoleSet, stream, p);
+    return launch_args(k6_attend_roles<8>, grid, block, 2u * kRoleSet, stream, p);
 }
 
 }  // namespace ha_rag

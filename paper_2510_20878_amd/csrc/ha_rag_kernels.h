@@ -112,9 +112,7 @@ constexpr uint32_t kAttendMinRunBlocks = 8;    // a workgroup takes at least thi
                                                // half as many in a call of very few workgroups),
 constexpr uint32_t kAttendMaxRunBlocks = 128;  // and a piece of one document is at most this long (a power of two)
 constexpr uint32_t kAttendTargetGroups = 2048; // pieces are halved while a launch has fewer workgroups
-// run lengths of the shared kernel: starting and ending one of its workgroups costs as much as this many blocks
-constexpr uint32_t kAttendStartBlocks = 8;
-constexpr uint32_t kAttendFewDocs = 32;       // and the longest run is looked for in a request of at most this many documents
+constexpr uint32_t kAttendFewDocs = 32;       // run lengths of the shared kernel: the longest run is looked for in a request of at most this many documents
 constexpr uint32_t kChipCUs = 256;            // compute units of the one GPU this library is built for
 constexpr uint32_t kAttendWaves = 2;          // waves of a workgroup; they interleave its blocks
 // Descriptors travel in the kernel argument buffer (36 KiB; launches with arguments of up to
@@ -198,12 +196,12 @@ typedef K7ParamsOf<kFewMergeReqs> K7ParamsFew;
 // the run's blocks in turn.  check_only (here and below): every check, no launch -- what a
 // context without a device does with the descriptors it has filled.
 hipError_t launch_k6(K6Params &p, hipStream_t stream, bool check_only = false);
-// The same for requests with two query tiles or more: the `waves` (2, 4 or 8) scoring waves of a
-// workgroup share every decoded block, each wave with two tiles of its own.
+// The same for requests with two query tiles or more: the `waves` scoring waves of a workgroup share every
+// decoded block, each wave with two tiles of its own (2: k6_attend_shared, 4 or 8: k6_attend_roles).
 hipError_t launch_k6_shared(K6Params &p, uint32_t waves, hipStream_t stream, bool check_only = false);
 // What both check of their arguments (max_mt: most query tiles of a run's request; narrow: no 16-bit side).
 hipError_t check_k6_args(const K6Params &p, uint32_t *max_mt, bool *narrow);
-// Once per device, before the first launch with eight scoring waves (its LDS allowance).
+// Once per device, before the first launch of k6_attend_roles (its LDS allowance).
 hipError_t prepare_k6_shared();
 // Merges the partial results of each request into out and lse.
 hipError_t launch_k7(K7Params &p, hipStream_t stream, bool check_only = false);

@@ -1070,3 +1070,22 @@ def test_place_chunks_is_algorithm_2_without_the_decode():
     rc = B.lib().ha_rag_place_chunks(ctx._h, None, None, 0, 4, None, None, None)
     assert rc == B.EINVAL
     ctx.destroy()
+
+
+@pytest.mark.parametrize("H,G,n_reqs,n_docs,tokens,n_q,fits", [
+    (8, 4, 1, 10, 512, 64, True), (8, 4, 2, 10, 512, 64, False), (8, 4, 3, 10, 512, 64, True), (8, 4, 8, 4, 512, 64, False),
+    (8, 4, 2, 4, 512, 64, True), (8, 4, 16, 4, 512, 16, False), (8, 4, 32, 10, 512, 16, False), (8, 4, 24, 4, 144, 16, True),
+    (8, 4, 40, 10, 512, 12, True), (8, 4, 16, 8, 304, 32, False), (8, 8, 1, 16, 1024, 100, True), (2, 8, 1, 4, 2048, 256, False),
+    (8, 4, 32, 10, 512, 1, True), (8, 4, 48, 8, 512, 8, False)])
+def test_static_attention_entry_takes_the_same_calls_whatever_the_runs_are(H, G, n_reqs, n_docs, tokens, n_q, fits):
+    """Which calls the scratch array holds is fixed by a rule of its own, not by the run lengths of the day."""
+    ctx = B.Context(2, H, 128, 4096, group_int8=128, group_int4=128, dry_run=True)
+    P = 0x7F0000001000
+    reqs = [([(P, tokens, B.PREC_INT4, 128, 0)] * n_docs, P, P, None, n_q) for _ in range(n_reqs)]
+    if fits:
+        ctx.attend_packed_static(reqs, 0, H * G, 0.1)
+    else:
+        with pytest.raises(B.HaRagError) as e:
+            ctx.attend_packed_static(reqs, 0, H * G, 0.1)
+        assert e.value.code == B.ENOSPC
+    ctx.destroy()
