@@ -326,18 +326,36 @@ uint64_t lay_out_runs(Plan *plans, uint32_t n_reqs, const Doc *docs, uint32_t H,
     return cut(plans, n_reqs, docs, H, true, run_blocks, pieces);
 }
 
-// Words of the workspace by the rule of kLimitForms, two-tile requests with the shared kernel's (a call of requests of at
-// most four) or not, whichever takes less.
-uint64_t limit_floats(Plan *plans, uint32_t n_reqs, const Doc *docs, uint32_t H, uint32_t most_mt, uint32_t by_block)
+// The layout that a call's workspace is sized by (kLimitForms): two-tile requests with the shared kernel's (a call of
+// requests of at most four) or not, whichever takes less.
+struct Limit {
+    uint64_t floats, run_blocks;  // words; runs of the shared kernel
+    bool two_tiles;               // it takes the requests of two tiles as well
+};
+
+void set_shared(Plan *plans, uint32_t n_reqs, bool two_tiles)
+{
+    for (uint32_t r = 0; r < n_reqs; ++r) plans[r].shared = plans[r].n_mt > 2u || (two_tiles && plans[r].n_mt == 2u);
+}
+
+uint64_t lay_out_limit(Plan *plans, uint32_t n_reqs, const Doc *docs, uint32_t H, const Limit &l)
+{
+    set_shared(plans, n_reqs, l.two_tiles);
+    const uint64_t pieces = cut(plans, n_reqs, docs, H, false, piece_length(plans, n_reqs, docs, H), 0);
+    return cut(plans, n_reqs, docs, H, true, l.run_blocks, pieces);
+}
+
+Limit workspace_limit(Plan *plans, uint32_t n_reqs, const Doc *docs, uint32_t H, uint32_t most_mt, uint32_t by_block)
 {
     const Form &f = kLimitForms[by_block][most_mt > 8u ? 2 : most_mt > 4u ? 1 : 0];
-    uint64_t least = ~0ull;
-    for (uint32_t with : {0u, 1u}) {
-        if (with && (!most_mt || most_mt > 4u)) break;
-        for (uint32_t r = 0; r < n_reqs; ++r) plans[r].shared = plans[r].n_mt > 2u || (with && plans[r].n_mt == 2u);
-        uint64_t ns = 0, total = cut(plans, n_reqs, docs, H, false, piece_length(plans, n_reqs, docs, H), 0);
-        total = cut(plans, n_reqs, docs, H, true, best_run(f, plans, n_reqs, docs, H, ~0ull, 0, &ns), total);
-        if (total < least) least = total;
+    Limit least = {~0ull, 1, false};
+    for (bool with : {false, true}) {
+        if (with && most_mt > 4u) break;
+        set_shared(plans, n_reqs, with);
+        uint64_t ns = 0;
+        Limit l = {0, best_run(f, plans, n_reqs, docs, H, ~0ull, 0, &ns), with};
+        l.floats = lay_out_limit(plans, n_reqs, docs, H, l);
+        if (l.floats < least.floats) least = l;
     }
     return least;
 }
@@ -442,17 +460,24 @@ int plan_attend(ha_rag_ctx *c, const ha_rag_packed_chunk *chunks, const ha_rag_a
         total = cut(plans, n_reqs, docs->data, H, false, piece_length(plans, n_reqs, docs->data, H), 0);
     } else {
         uint32_t by_block = 0;
-        total = limit_floats(plans, n_reqs, docs->data, H, most_mt, by_block);
-        if (total > most_floats) total = limit_floats(plans, n_reqs, docs->data, H, most_mt, by_block = 1u);
-        uint32_t moved = 0;
-        for (uint32_t r = 0; r < n_reqs; ++r) {
-            plans[r].shared = plans[r].n_mt > 2u;
-            if (most_mt <= 8u && plans[r].n_mt == 2u) plans[r].shared = moved = 1u;
+        Limit limit = workspace_limit(plans, n_reqs, docs->data, H, most_mt, by_block);
+        if (limit.floats > most_floats) limit = workspace_limit(plans, n_reqs, docs->data, H, most_mt, by_block = 1u);
+        total = limit.floats;
+        const bool joins = most_mt <= 8u;
+        set_shared(plans, n_reqs, joins);
+        uint64_t used = lay_out_runs(plans, n_reqs, docs->data, H, most_mt, by_block, total, shared_waves);
+        if (used > total && joins) {
+            set_shared(plans, n_reqs, false);
+            used = lay_out_runs(plans, n_reqs, docs->data, H, most_mt, by_block, total, shared_waves);
         }
-        if (lay_out_runs(plans, n_reqs, docs->data, H, most_mt, by_block, total, shared_waves) > total && moved) {
-            for (uint32_t r = 0; r < n_reqs; ++r) plans[r].shared = plans[r].n_mt > 2u;
-            lay_out_runs(plans, n_reqs, docs->data, H, most_mt, by_block, total, shared_waves);
+        // The run lengths were chosen by the quotient of blocks and length, but a run also ends after kMaxRunDocs
+        // documents, so that a request of more than that may have more runs.  Any form takes runs of any length:
+        // where they do not fit, those that the workspace is sized by.
+        if (used > total) {
+            used = lay_out_limit(plans, n_reqs, docs->data, H, limit);
+            *shared_waves = most_mt > 8u ? 8u : most_mt > 4u ? 4u : 2u;
         }
+        if (used > total) return HA_RAG_EINVAL;  // never: the same layout as above
     }
     if (total * 4ull > (1ull << 40)) return HA_RAG_EINVAL;
     *floats = total;
@@ -524,6 +549,11 @@ int attend_locked(ha_rag_ctx *c, PlanStore ps, const ha_rag_packed_chunk *chunks
     kq.scale_log2 = sm_scale * 1.44269504088896341f;
     auto doc_k = [&](const Doc &doc) { return doc.k + (uint64_t)(doc.k_first + layer * doc.k_step) * doc.k_tile; };
     auto doc_v = [&](const Doc &doc) { return doc.v + (uint64_t)(doc.v_first + layer * doc.v_step) * doc.v_tile; };
+    // Every run's records lie in the workspace (the planning sees to it; nothing is launched that would not).
+    auto record_fits = [&](const float *part, const Plan &pl) {
+        const uint64_t at = (uint64_t)((uintptr_t)part - (uintptr_t)ws) / 4u;
+        return at + (uint64_t)H * pl.n_mt * kAttendRecFloats <= floats;
+    };
     // ---- requests of at most two tiles: every run is a piece of one document
     kq.n_runs = 0;
     auto launch_pieces = [&]() {
@@ -554,6 +584,7 @@ int attend_locked(ha_rag_ctx *c, PlanStore ps, const ha_rag_packed_chunk *chunks
             d.lse = nullptr;
             for (uint32_t at = 0; at < doc.n_blocks; at += len) {
                 if (kq.n_runs == kAttendMaxRuns) HIPCHK(c, launch_pieces());
+                if (!record_fits(part, pl)) return HA_RAG_EINVAL;
                 d.part = part;
                 d.first_block = at;
                 d.end_block = doc.n_blocks - at > len ? at + len : doc.n_blocks;
@@ -607,6 +638,7 @@ int attend_locked(ha_rag_ctx *c, PlanStore ps, const ha_rag_packed_chunk *chunks
             d.v = doc_v(first);
             d.q = static_cast<const uint16_t *>(rq.q);
             d.part = pl.final ? rq.out : ws + pl.part_floats + (uint64_t)run_no * H * pl.n_mt * kAttendRecFloats;
+            if (!pl.final && !record_fits(d.part, pl)) return HA_RAG_EINVAL;
             d.final = pl.final;
             d.lse = pl.final ? rq.lse : nullptr;
             d.n_tokens = first.n_tokens;
