@@ -50,6 +50,7 @@ struct Plan {               // one request
     uint32_t run_blocks = 0;   // layout blocks per run (what one workgroup takes)
     uint64_t all_blocks = 0;   // layout blocks of all its documents
     uint64_t wide_blocks = 0;  // those of documents with a 16-bit side
+    uint32_t least_blocks = 0; // of its shortest document
     uint32_t n_runs = 0;       // records per (KV head, tile)
     uint32_t final = 0;        // one run of the shared kernel is all there is: it writes the output itself
     uint64_t part_floats = 0;  // offset of its records in the workspace
@@ -109,6 +110,9 @@ uint32_t count_runs(const Plan &pl, const Doc *docs)
         }
         return n;
     }
+    // No run ends for its documents: 127 whole ones and a block of another are as long as a run.
+    if (pl.n_docs <= kMaxRunDocs || (uint64_t)(kMaxRunDocs - 1u) * pl.least_blocks + 1u >= pl.run_blocks)
+        return (uint32_t)((pl.all_blocks + pl.run_blocks - 1u) / pl.run_blocks);
     Run r;
     while (next_run(pl, docs, doc, blk, &r)) ++n;
     return n;
@@ -139,118 +143,273 @@ uint32_t longest_run_steps(const Plan &pl, const Doc *docs, uint32_t len, uint32
     return steps > most ? steps : most;
 }
 
-// What a call costs the shared kernel in each of its forms, in ns: `waves` = 2 (k6_attend_shared), 4 or 8
+// The requests of a call that go to the shared kernel, those of one size together.
+struct SharedCall {
+    struct Size {
+        uint64_t blocks;
+        uint32_t n_mt, count;
+    };
+    static constexpr uint32_t kSizes = 32;
+    const Plan *plans = nullptr;
+    const Doc *docs = nullptr;
+    uint32_t n_reqs = 0, H = 0;
+    Size sizes[kSizes];             // in the order they come up first
+    uint32_t n_sizes = 0, rest = 0; // requests from `rest` on are looked at one by one
+    const Plan *largest = nullptr;
+    uint64_t all = 0, wide = 0;     // blocks; those of documents with a 16-bit side
+
+    SharedCall() = default;
+    SharedCall(const Plan *plans_, uint32_t n_reqs_, const Doc *docs_, uint32_t H_) : plans(plans_), docs(docs_), n_reqs(n_reqs_), H(H_)
+    {
+        for (; rest < n_reqs; ++rest) {
+            const Plan &pl = plans[rest];
+            if (!pl.shared) continue;
+            uint32_t i = 0;
+            while (i < n_sizes && (sizes[i].blocks != pl.all_blocks || sizes[i].n_mt != pl.n_mt)) ++i;
+            if (i == kSizes) break;
+            if (i == n_sizes) sizes[n_sizes++] = Size{pl.all_blocks, pl.n_mt, 0u};
+            ++sizes[i].count;
+        }
+        for (uint32_t r = 0; r < n_reqs; ++r) {
+            if (!plans[r].shared) continue;
+            if (!largest || plans[r].all_blocks > largest->all_blocks) largest = &plans[r];
+            all += plans[r].all_blocks;
+            wide += plans[r].wide_blocks;
+        }
+    }
+    template <class F>
+    void each(F f) const
+    {
+        for (uint32_t i = 0; i < n_sizes; ++i) f(sizes[i].blocks, sizes[i].n_mt, sizes[i].count);
+        for (uint32_t r = rest; r < n_reqs; ++r)
+            if (plans[r].shared) f(plans[r].all_blocks, plans[r].n_mt, 1u);
+    }
+    // Workgroups and records with runs of len blocks, two tiles for each of 1 << wshift waves.
+    uint64_t wgs = 0, recs = 0;
+    void count(uint64_t len, uint32_t wshift)
+    {
+        if (len == counted_len && wshift == counted_wshift) return;
+        counted_len = len;
+        counted_wshift = wshift;
+        wgs = recs = 0;
+        each([&](uint64_t blocks, uint32_t n_mt, uint32_t times) {
+            const uint64_t up = blocks + len - 1u, runs = (up >> 32 ? up / len : (uint32_t)up / (uint32_t)len) * times * H;
+            wgs += runs * ((n_mt + (2u << wshift) - 1u) >> (wshift + 1u));
+            if (blocks > len) recs += runs * n_mt;
+        });
+    }
+    uint64_t counted_len = 0;
+    uint32_t counted_wshift = 0;
+    // Blocks that all workgroups take together: their number times their length is no less.
+    uint64_t work(uint32_t wshift) const
+    {
+        uint64_t w = 0;
+        each([&](uint64_t blocks, uint32_t n_mt, uint32_t times) { w += blocks * times * H * ((n_mt + (2u << wshift) - 1u) >> (wshift + 1u)); });
+        return w;
+    }
+};
+
+// The run lengths there are, by how many runs n the largest request gets: n = 1 .. last(), of ceil(blocks / n) blocks
+// each, at least kAttendMinRunBlocks unless there is one.
+struct RunLengths {
+    uint64_t blocks;  // of the largest request, not 0
+    uint64_t last() const { return blocks > kAttendMinRunBlocks ? (blocks - 1u) / (kAttendMinRunBlocks - 1u) : 1u; }
+    uint64_t of(uint64_t n) const { return (blocks + n - 1u) / n; }
+    uint64_t first_n(uint64_t len) const { return of(len); }                                          // the fewest runs of this length
+    uint64_t last_n(uint64_t len) const { return len > 1u ? (blocks - 1u) / (len - 1u) : blocks; }  // the most
+    // the largest n up to last() for whose length ok() holds, if it holds for 1 and ends to hold once; else 1
+    template <class F>
+    uint64_t last_where(F ok) const
+    {
+        uint64_t lo = 1, hi = last();
+        if (hi == 1u || ok(of(hi))) return hi;
+        --hi;
+        while (2u * lo <= hi && ok(of(2u * lo))) lo *= 2u;  // often few: many requests fill the chip
+        if (2u * lo <= hi) hi = 2u * lo - 1u;
+        while (lo < hi) {
+            const uint64_t mid = hi - (hi - lo) / 2u;
+            if (ok(of(mid))) lo = mid;
+            else hi = mid - 1u;
+        }
+        return lo;
+    }
+};
+
+// What the cost of a run length counts as a workgroup's steps: those of the average run of the largest request (no run
+// length's longest has fewer), and of a request of few documents those of its longest run too.
+struct Steps {
+    const SharedCall &call;
+    uint32_t shift;    // a step takes up to 1 << shift blocks of one document
+    uint64_t of_all;   // steps of all blocks in one run
+    Steps(const SharedCall &c, uint32_t shift_)
+        : call(c), shift(shift_), of_all(longest_run_steps(*c.largest, c.docs + c.largest->first_doc, ~0u, shift_)) {}
+    uint64_t average(uint64_t n, uint64_t len) const
+    {
+        const uint64_t steps = (len + (1u << shift) - 1u) >> shift, mean = (of_all + n - 1u) / n;
+        return steps > mean ? steps : mean;
+    }
+    bool few_docs() const { return call.largest->n_docs <= kAttendFewDocs; }
+    uint64_t longest(uint64_t len) const { return longest_run_steps(*call.largest, call.docs + call.largest->first_doc, (uint32_t)len, shift); }
+};
+
+// The rule that a call's workspace is sized by.  It is older than the kernels' forms and stays what it was, since callers
+// keep workspaces: for requests of up to 4, up to 8 and more tiles as if 2, 4 and 8 waves took as many blocks a
+// step (in turn), which costs rounds x (blocks + 8) and a block's time for every so many records.  Of the lengths up to the
+// one that takes the fewest rounds x blocks, that bounds the records.
+struct Limit {
+    uint32_t wshift;         // 1 << wshift waves
+    uint32_t side_by_side;   // workgroups on the chip
+    uint32_t recs_per_block;
+};
+constexpr Limit kLimits[3] = {{1u, 4u * kChipCUs, 600u}, {2u, 2u * kChipCUs, 450u}, {3u, kChipCUs, 280u}};
+
+// in_steps: blocks count by step, not one by one (which is for a call that otherwise does not fit the array of the
+// entry point without a workspace).
+uint64_t limit_run(const Limit &f, SharedCall &call, bool in_steps)
+{
+    if (!call.largest || !call.largest->all_blocks) return 1;
+    const RunLengths lengths = {call.largest->all_blocks};
+    const uint64_t last = lengths.last(), side = f.side_by_side;
+    auto rounds = [&](uint64_t len) {
+        call.count(len, f.wshift);
+        return (call.wgs + side - 1u) / side;
+    };
+    // The fewest rounds x blocks.  Up to the last length of one round that is the shortest; from there on until no
+    // later one can take fewer (more rounds of at least 8 blocks, or all workgroups' blocks in full rounds).
+    const uint64_t full = (call.work(f.wshift) + side - 1u) / side;
+    uint64_t n = lengths.last_where([&](uint64_t len) { return rounds(len) <= 1u; });
+    uint64_t bound = n, fewest = ~0ull;
+    while (n <= last) {
+        const uint64_t len = lengths.of(n), k = rounds(len);
+        if (k * len < fewest) {
+            fewest = k * len;
+            bound = n;
+        }
+        if (fewest <= full || k * kAttendMinRunBlocks >= fewest || call.wgs >= 64u * side) break;
+        n = lengths.last_n(len) + 1u;
+    }
+    // The least cost of n = 1 .. bound, the smaller n of equals.  Of the n of one length the largest costs least.
+    const Steps steps(call, in_steps ? f.wshift : 0u);
+    constexpr uint64_t kStart = 8;
+    uint64_t best = lengths.of(bound), least = ~0ull;
+    for (n = lengths.first_n(best); n; n = lengths.first_n(lengths.of(n)) - 1u) {
+        const uint64_t len = lengths.of(n);
+        if (len + kStart > least) break;  // and so for all longer ones
+        const uint64_t k = rounds(len), mean = steps.average(n, len);
+        auto cost = [&](uint64_t s) { return k * ((s << steps.shift) + kStart) + call.recs / f.recs_per_block; };
+        uint64_t c = cost(mean);
+        if (c <= least && steps.few_docs()) {
+            const uint64_t longest = steps.longest(len);
+            if (longest > mean) c = cost(longest);
+        }
+        if (c <= least) {
+            least = c;
+            best = len;
+        }
+    }
+    return best;
+}
+
+// What a call costs the shared kernel in each of its forms, in ns: 2 scoring waves (k6_attend_shared), 4 or 8
 // (k6_attend_roles<4>, <8>).  Workgroups of one size finish in rounds of as many as the chip holds side by side; a round
-// costs what starting and ending a workgroup does, its steps (a workgroup takes up to `blocks` of them at a time, all of
+// costs what starting and ending a workgroup does, its steps (a workgroup takes a few blocks at a time, all of
 // one document), and for k6_attend_roles, alone on its compute unit, a trip to memory at the start of every document;
 // steps get slower the more workgroups share a compute unit, or the memory and the power there is.  A run that is longer
 // than the average one costs a third of the difference: its neighbours are done by then.  Every record is 8 KiB that is
 // written, flushed at the kernel's end and read by another launch.  Fitted to 1,700 timings of 142 calls of 1 to 32
-// requests of 7 to 1,024 blocks at 3 to 402 query tokens, whose runs and forms were set by hand: what it chooses is on
-// average 0.5 % slower than the fastest of those, 9 % at worst; of short calls it is within 14 % of the time, of those
-// that run into the power limit it is too low by a third.
+// requests of 7 to 1,024 blocks at 3 to 402 query tokens, whose runs and forms were set by hand: for these same calls, what
+// it chooses is on average 0.5 % slower than the fastest, 9 % at worst; of short calls it is within 14 % of the time, of
+// those that run into the power limit it is too low by a third.  The time to choose is not part of it: 0.5 to 5 us a call.
 struct Form {
-    uint32_t waves, shift, side_by_side;   // 1 << shift blocks a step
+    uint32_t wshift, shift, side_by_side;  // 1 << wshift waves; 1 << shift blocks a step
     uint32_t call, round, doc;             // ns: once; a round; a document
     uint32_t step[4];                      // ns: a step with up to a quarter, a half, three quarters and all places taken
     uint32_t wide;                         // added to a step times the share of blocks with a 16-bit side
-    uint32_t lean;                         // 1 / lean of what the longest run has more steps than the average one counts
-    uint32_t merge, rec_num, rec_den;      // ns: a merge at all; rec_num / rec_den a record
-    bool bounded;                          // no more runs than the fewest rounds x blocks take
 };
 constexpr Form kForms[3] = {
-    {2u, 1u, 4u * kChipCUs, 2000u, 5600u, 0u, {1330u, 2115u, 2120u, 2300u}, 460u, 3u, 3740u, 19u, 10u, false},
-    {4u, 3u, kChipCUs, 5000u, 2900u, 600u, {2000u, 2160u, 2410u, 2770u}, 210u, 3u, 3740u, 19u, 10u, false},
-    {8u, 3u, kChipCUs, 2500u, 6100u, 0u, {3050u, 3230u, 3540u, 3960u}, 210u, 3u, 3740u, 19u, 10u, false},
+    {1u, 1u, 4u * kChipCUs, 2000u, 5600u, 0u, {1330u, 2115u, 2120u, 2300u}, 460u},
+    {2u, 3u, kChipCUs, 5000u, 2900u, 600u, {2000u, 2160u, 2410u, 2770u}, 210u},
+    {3u, 3u, kChipCUs, 2500u, 6100u, 0u, {3050u, 3230u, 3540u, 3960u}, 210u},
 };
-// The rule that a call's workspace is sized by (steps, rounds and records in units of a block's time; forms of 2, 4
-// and 8 waves that all score), which stays what it was: the runs are chosen among those whose records fit.  By step, and
-// by block where that does not fit the array of the entry point without a workspace.
-constexpr Form kLimitForms[2][3] = {
-    {{2u, 1u, 4u * kChipCUs, 0u, 8u, 0u, {2u, 2u, 2u, 2u}, 0u, 1u, 0u, 1u, 600u, true},
-     {4u, 2u, 2u * kChipCUs, 0u, 8u, 0u, {4u, 4u, 4u, 4u}, 0u, 1u, 0u, 1u, 450u, true},
-     {8u, 3u, kChipCUs, 0u, 8u, 0u, {8u, 8u, 8u, 8u}, 0u, 1u, 0u, 1u, 280u, true}},
-    {{2u, 0u, 4u * kChipCUs, 0u, 8u, 0u, {1u, 1u, 1u, 1u}, 0u, 1u, 0u, 1u, 600u, true},
-     {4u, 0u, 2u * kChipCUs, 0u, 8u, 0u, {1u, 1u, 1u, 1u}, 0u, 1u, 0u, 1u, 450u, true},
-     {8u, 0u, kChipCUs, 0u, 8u, 0u, {1u, 1u, 1u, 1u}, 0u, 1u, 0u, 1u, 280u, true}},
-};
+constexpr uint64_t kMergeNs = 3740, kRecNsNum = 19, kRecNsDen = 10;  // a merge at all; a record
 
-// The run length of the shared kernel that costs least, of those whose records take no more than most_floats
-// words (one run a request takes none); or only what run length `only` costs (0: any).  A run crosses document
-// boundaries (equal runs finish together whatever the documents' lengths).
-uint64_t best_run(const Form &f, const Plan *plans, uint32_t n_reqs, const Doc *docs, uint32_t H, uint64_t most_floats, uint64_t only, uint64_t *ns)
-{
-    struct Size {  // requests of one size, in the order they come up first
-        uint64_t blocks;
-        uint32_t n_mt, count;
-    };
-    constexpr uint32_t kSizes = 32;
-    Size sizes[kSizes];
-    uint32_t n_sizes = 0, rest = 0;  // requests from `rest` on are looked at one by one
-    for (; rest < n_reqs; ++rest) {
-        const Plan &pl = plans[rest];
-        if (!pl.shared) continue;
-        uint32_t i = 0;
-        while (i < n_sizes && (sizes[i].blocks != pl.all_blocks || sizes[i].n_mt != pl.n_mt)) ++i;
-        if (i == kSizes) break;
-        if (i == n_sizes) sizes[n_sizes++] = Size{pl.all_blocks, pl.n_mt, 0u};
-        ++sizes[i].count;
+struct FormCost {
+    const Form &f;
+    SharedCall &call;
+    const RunLengths lengths;
+    const Steps steps;
+    const uint64_t wide_ns;
+
+    FormCost(const Form &f_, SharedCall &c)
+        : f(f_), call(c), lengths{c.largest->all_blocks}, steps(c, f_.shift), wide_ns(f_.wide * c.wide / c.all) {}
+    uint64_t rounds(uint64_t len)
+    {
+        call.count(len, f.wshift);
+        return (call.wgs + f.side_by_side - 1u) / f.side_by_side;
     }
-    const Plan *largest = nullptr;
-    uint64_t all = 0, wide = 0;
-    for (uint32_t r = 0; r < n_reqs; ++r) {
-        if (!plans[r].shared) continue;
-        if (!largest || plans[r].all_blocks > largest->all_blocks) largest = &plans[r];
-        all += plans[r].all_blocks;
-        wide += plans[r].wide_blocks;
-    }
-    *ns = 0;
-    if (!largest || !largest->all_blocks) return 1;
-    const uint64_t most_blocks = largest->all_blocks;
-    const uint64_t all_steps = longest_run_steps(*largest, docs + largest->first_doc, ~0u, f.shift);
-    const uint64_t wide_ns = f.wide * wide / all;
-    uint64_t best = most_blocks, least = ~0ull, bounded = most_blocks, fewest = ~0ull;
-    for (uint64_t n = only ? (most_blocks + only - 1u) / only : 1u; n <= most_blocks; ++n) {  // n runs for the largest request
-        const uint64_t len = (most_blocks + n - 1u) / n;
-        if (n > 1 && len < kAttendMinRunBlocks) break;
-        uint64_t wgs = 0, recs = 0;
-        auto add = [&](uint64_t blocks, uint32_t n_mt, uint32_t count) {
-            const uint64_t runs = (blocks + len - 1u) / len * count;
-            wgs += runs * H * ((n_mt + 2u * f.waves - 1u) / (2u * f.waves));
-            if (blocks > len) recs += runs * H * n_mt;
-        };
-        for (uint32_t i = 0; i < n_sizes; ++i) add(sizes[i].blocks, sizes[i].n_mt, sizes[i].count);
-        for (uint32_t r = rest; r < n_reqs; ++r)
-            if (plans[r].shared) add(plans[r].all_blocks, plans[r].n_mt, 1u);
-        if (n > 1 && recs * kAttendRecFloats > most_floats) break;
-        const uint64_t rounds = (wgs + f.side_by_side - 1u) / f.side_by_side;
-        const uint64_t taken = wgs < f.side_by_side ? wgs : f.side_by_side;  // places
+    uint64_t step_ns() const  // with as many workgroups as counted last, between two of the four
+    {
+        const uint64_t taken = call.wgs < f.side_by_side ? call.wgs : f.side_by_side;  // places
         const uint64_t quarter = f.side_by_side / 4u, q = taken <= quarter ? 0u : (taken - 1u) / quarter - 1u;
-        uint64_t step = f.step[q] + wide_ns;  // between two of the four
+        uint64_t step = f.step[q] + wide_ns;
         if (taken > quarter) step += (f.step[q + 1u] - f.step[q]) * (taken - (q + 1u) * quarter) / quarter;
-        const uint64_t in_docs = (largest->n_docs * len + most_blocks - 1u) / most_blocks * f.doc;
-        // The average of the runs (no run length's longest has fewer), which is close enough for runs of
-        // many documents; of a request of few the longest too, if the average could do.
-        uint64_t steps = (len + (1u << f.shift) - 1u) >> f.shift;
-        if (all_steps > steps * n) steps = (all_steps + n - 1u) / n;
-        uint64_t c = f.call + rounds * (f.round + steps * step + in_docs) + (recs ? f.merge + recs * f.rec_num / f.rec_den : 0u);
-        if (c < least && largest->n_docs <= kAttendFewDocs) {
-            const uint32_t longest = longest_run_steps(*largest, docs + largest->first_doc, (uint32_t)len, f.shift);
-            if (longest > steps) c += rounds * ((longest - steps) * step / f.lean);
-        }
-        if (c < least) {
-            least = c;
-            best = len;
-        }
-        if (rounds * len < fewest) {
-            fewest = rounds * len;
-            bounded = best;
-        }
-        if (only || wgs >= 64u * f.side_by_side) break;  // finer than this gains nothing
+        return step;
     }
-    *ns = least;
-    return f.bounded ? bounded : best;
-}
+    uint64_t merge_ns() const { return call.recs ? kMergeNs + call.recs * kRecNsNum / kRecNsDen : 0u; }
+    // of n runs, len = lengths.of(n), if that is no more than `most`; else at least not less than it costs on average
+    uint64_t of(uint64_t n, uint64_t len, uint64_t most)
+    {
+        const uint64_t k = rounds(len), step = step_ns(), mean = steps.average(n, len);
+        const uint64_t in_docs = (call.largest->n_docs * len + lengths.blocks - 1u) / lengths.blocks * f.doc;
+        uint64_t c = f.call + k * (f.round + mean * step + in_docs) + merge_ns();
+        if (c <= most && steps.few_docs()) {
+            const uint64_t longest = steps.longest(len);
+            if (longest > mean) c += k * ((longest - mean) * step / 3u);
+        }
+        return c;
+    }
+    // The length that costs least of those whose records take no more than most_floats words (one run a request takes
+    // none), the smaller n of equals; of the n of one length the largest costs least.  *ns: what it costs, or as it was if
+    // that is no more.
+    uint64_t best(uint64_t most_floats, uint64_t *ns)
+    {
+        const uint64_t last = lengths.last(), side = f.side_by_side;
+        auto fits = [&]() { return call.recs * kAttendRecFloats <= most_floats; };
+        const uint64_t start = lengths.last_where([&](uint64_t len) { return rounds(len) <= 1u && fits(); });
+        uint64_t least = *ns, best_len = lengths.of(start);
+        auto most_n = [&](uint64_t len) {
+            const uint64_t n = lengths.last_n(len);
+            return n < last ? n : last;
+        };
+        for (uint64_t n = most_n(best_len); n; n = lengths.first_n(lengths.of(n)) - 1u) {  // longer and longer ones
+            const uint64_t len = lengths.of(n);
+            if (f.call + f.round + ((len + (1u << f.shift) - 1u) >> f.shift) * (f.step[0] + wide_ns) > least) break;
+            const uint64_t c = of(n, len, least);
+            if (c <= least) {
+                least = c;
+                best_len = len;
+            }
+        }
+        // shorter and shorter ones, until rounds, records and all workgroups' blocks in full rounds cost as much
+        const uint64_t full = call.work(f.wshift), full_steps = (full + (side << f.shift) - 1u) / (side << f.shift);
+        uint64_t len = lengths.of(start);
+        rounds(len);
+        while (call.wgs < 64u * side && lengths.last_n(len) < last) {  // finer than this gains nothing
+            uint64_t n = lengths.last_n(len) + 1u;
+            len = lengths.of(n);
+            const uint64_t k = rounds(len);
+            if (!fits() || f.call + k * f.round + full_steps * step_ns() + merge_ns() >= least) break;
+            if (call.wgs < 64u * side) n = most_n(len);
+            const uint64_t c = of(n, len, least);
+            if (c < least) {
+                least = c;
+                best_len = len;
+            }
+        }
+        *ns = least;
+        return best_len;
+    }
+};
 
 // Cuts the requests of one kernel (the shared one or the other) into runs and lays their part of the workspace out,
 // from word `total` on.  Returns where it ends.
@@ -295,14 +454,63 @@ uint32_t piece_length(const Plan *plans, uint32_t n_reqs, const Doc *docs, uint3
     return 1u << shift;
 }
 
-// Cuts every request into runs and lays the workspace out; plans[r].shared says by which kernel's rule.  Returns its
-// size in binary32 words.  *waves: the form of the shared kernel, chosen here among those
-// whose workgroups are not mostly empty for the call's largest request (most_mt query tiles).
-uint64_t lay_out_runs(Plan *plans, uint32_t n_reqs, const Doc *docs, uint32_t H, uint32_t most_mt, uint32_t by_block, uint64_t most_floats, uint32_t *waves)
+void set_shared(Plan *plans, uint32_t n_reqs, bool two_tiles)  // two_tiles: requests of two tiles as well
 {
-    const uint64_t pieces = cut(plans, n_reqs, docs, H, false, piece_length(plans, n_reqs, docs, H), 0);
-    const uint64_t room = most_floats > pieces ? most_floats - pieces : 0u;
-    // The shared kernel: four scorers (up to 8 tiles a workgroup) for every call; eight where a request has more
+    for (uint32_t r = 0; r < n_reqs; ++r) plans[r].shared = plans[r].n_mt > 2u || (two_tiles && plans[r].n_mt == 2u);
+}
+
+// Lays out the requests that are not the shared kernel's; words.
+uint64_t lay_out_pieces(Plan *plans, uint32_t n_reqs, const Doc *docs, uint32_t H)
+{
+    for (uint32_t r = 0; r < n_reqs; ++r)
+        if (!plans[r].shared) return cut(plans, n_reqs, docs, H, false, piece_length(plans, n_reqs, docs, H), 0);
+    return 0;
+}
+
+// Lays out a call whose largest request has most_mt > 2 tiles.  Returns the words of the workspace it asks for (see
+// Limit), which the layout stays within; *waves: the form of the shared kernel.
+uint64_t lay_out_shared(Plan *plans, uint32_t n_reqs, const Doc *docs, uint32_t H, uint32_t most_mt, uint64_t most_floats, uint32_t *waves)
+{
+    SharedCall call;
+    uint64_t pieces = 0;
+    auto set = [&](bool two_tiles) {  // the shared kernel's requests, those of two tiles among them or not; lays out the others
+        for (uint32_t r = 0; r < n_reqs; ++r) plans[r].shared = plans[r].n_mt > 2u || (two_tiles && plans[r].n_mt == 2u);
+        call = SharedCall(plans, n_reqs, docs, H);
+        pieces = lay_out_pieces(plans, n_reqs, docs, H);
+    };
+    auto lay_out = [&](uint64_t run_blocks) { return cut(plans, n_reqs, docs, H, true, run_blocks, pieces); };
+    bool twos = false;
+    for (uint32_t r = 0; r < n_reqs; ++r) twos |= plans[r].n_mt == 2u;
+
+    // The layout that the workspace is sized by.  A call whose largest request has three or four tiles takes its requests of
+    // two to the shared kernel as well, unless that needs more workspace: a block costs that kernel what it costs the
+    // other one (103 against 100 us per call of 32 requests), and one launch fills the chip where two in a row
+    // do not (12 requests of 6 to 16 query tokens: 46 against 63 us per layer).
+    const Limit &limit = kLimits[most_mt > 8u ? 2 : most_mt > 4u ? 1 : 0];
+    const uint32_t limit_waves = most_mt > 8u ? 8u : most_mt > 4u ? 4u : 2u;
+    bool limit_twos = false;
+    uint64_t limit_len = 1, total = 0;
+    for (bool in_steps : {true, false}) {
+        set(limit_twos = false);
+        limit_len = limit_run(limit, call, in_steps);
+        total = lay_out(limit_len);
+        if (twos && most_mt <= 4u) {
+            set(limit_twos = true);
+            const uint64_t len = limit_run(limit, call, in_steps), together = lay_out(len);
+            if (together <= total) {
+                total = together;
+                limit_len = len;
+            } else {
+                set(limit_twos = false);
+                lay_out(limit_len);
+            }
+        }
+        if (total <= most_floats) break;
+    }
+    *waves = limit_waves;
+    if (!call.all) return total;
+
+    // The forms: four scorers (up to 8 tiles a workgroup) for every call; eight where a request has more
     // tiles, which then decodes every block once less; and k6_attend_shared, whose four workgroups on a compute unit all
     // decode and score in turn, for requests of up to four tiles, where half of four scorers would have none.  Measured, us
     // a layer, k6_attend_shared / four scorers / eight: 12 query tokens, 8 requests x 4 x 512 tokens 23.9 / 23.0, 32 x 10 x
@@ -310,54 +518,36 @@ uint64_t lay_out_runs(Plan *plans, uint32_t n_reqs, const Doc *docs, uint32_t H,
     // 4 x 512 - / 72.9 / 60.7, 32 x 10 x 512 - / 288 / 205.
     // Four scorers are as exact in long runs as in short ones (role_add_round) and take the length that costs least; the
     // others keep the runs that the workspace is sized for: longer ones cost them up to 1.8 times the error.
-    uint64_t run_blocks = 1, least = ~0ull;
-    for (const Form &f : kForms) {
-        if (f.waves == 2u ? most_mt > 4u : f.waves == 8u && most_mt <= 8u) continue;
-        uint64_t ns = 0, len = 0;
-        if (f.waves != 4u) len = best_run(kLimitForms[by_block][f.waves == 8u ? 2 : 0], plans, n_reqs, docs, H, room, 0, &ns);
-        len = best_run(f, plans, n_reqs, docs, H, room, len, &ns);
-        if (f.waves == 4u) ns += ns / 32u;  // on an even estimate the form that was there before
-        if (ns < least) {
-            least = ns;
-            run_blocks = len;
-            *waves = f.waves;
+    auto choose = [&]() {  // lays out what is set in the form that costs least; words
+        uint64_t other_ns = ~0ull;
+        if (limit_waves != 4u) {
+            FormCost other(kForms[limit_waves == 8u ? 2 : 0], call);
+            other_ns = other.of(other.lengths.first_n(limit_len), limit_len, ~0ull);
         }
+        uint64_t ns = other_ns;
+        const uint64_t len = FormCost(kForms[1], call).best(total > pieces ? total - pieces : 0u, &ns);
+        if (other_ns != ~0ull && other_ns <= ns + ns / 32u) {  // also on an even estimate
+            *waves = limit_waves;
+            return total;  // laid out already
+        }
+        *waves = 4u;
+        return lay_out(len);
+    };
+    uint64_t used = ~0ull;
+    if (twos && limit_waves == 4u) {  // those of two tiles go there too if the workspace holds that
+        set(true);
+        used = choose();
+        if (used > total) set(false);
     }
-    return cut(plans, n_reqs, docs, H, true, run_blocks, pieces);
-}
-
-// The layout that a call's workspace is sized by (kLimitForms): two-tile requests with the shared kernel's (a call of
-// requests of at most four) or not, whichever takes less.
-struct Limit {
-    uint64_t floats, run_blocks;  // words; runs of the shared kernel
-    bool two_tiles;               // it takes the requests of two tiles as well
-};
-
-void set_shared(Plan *plans, uint32_t n_reqs, bool two_tiles)
-{
-    for (uint32_t r = 0; r < n_reqs; ++r) plans[r].shared = plans[r].n_mt > 2u || (two_tiles && plans[r].n_mt == 2u);
-}
-
-uint64_t lay_out_limit(Plan *plans, uint32_t n_reqs, const Doc *docs, uint32_t H, const Limit &l)
-{
-    set_shared(plans, n_reqs, l.two_tiles);
-    const uint64_t pieces = cut(plans, n_reqs, docs, H, false, piece_length(plans, n_reqs, docs, H), 0);
-    return cut(plans, n_reqs, docs, H, true, l.run_blocks, pieces);
-}
-
-Limit workspace_limit(Plan *plans, uint32_t n_reqs, const Doc *docs, uint32_t H, uint32_t most_mt, uint32_t by_block)
-{
-    const Form &f = kLimitForms[by_block][most_mt > 8u ? 2 : most_mt > 4u ? 1 : 0];
-    Limit least = {~0ull, 1, false};
-    for (bool with : {false, true}) {
-        if (with && most_mt > 4u) break;
-        set_shared(plans, n_reqs, with);
-        uint64_t ns = 0;
-        Limit l = {0, best_run(f, plans, n_reqs, docs, H, ~0ull, 0, &ns), with};
-        l.floats = lay_out_limit(plans, n_reqs, docs, H, l);
-        if (l.floats < least.floats) least = l;
+    if (used > total) used = choose();
+    // The run length was chosen by the quotient of blocks and length, but a run also ends after kMaxRunDocs
+    // documents, so that a request of more than that may have more runs.  Any form takes runs of any length:
+    // where they do not fit, those that the workspace is sized by.
+    if (used > total) {
+        lay_out(limit_len);
+        *waves = limit_waves;
     }
-    return least;
+    return total;
 }
 
 // Checks everything and lays the workspace out.  *floats = workspace size in binary32 words.
@@ -448,37 +638,12 @@ int plan_attend(ha_rag_ctx *c, const ha_rag_packed_chunk *chunks, const ha_rag_a
             const Doc &doc = (*docs)[pl.first_doc + i];
             pl.all_blocks += doc.n_blocks;
             if ((doc.info & 0xFu) == HA_RAG_PREC_16 || ((doc.info >> 8) & 0xFu) == HA_RAG_PREC_16) pl.wide_blocks += doc.n_blocks;
+            if (i == 0 || doc.n_blocks < pl.least_blocks) pl.least_blocks = doc.n_blocks;
         }
     }
-    // A call whose largest request has three to eight tiles takes its requests of two tiles to the shared kernel
-    // as well: a block costs that kernel what it costs the other one (103 against 100 us per call of 32
-    // requests), and one launch fills the chip where two in a row do not (12 requests of 6 to 16 query tokens: 46
-    // against 63 us per layer).  Not if the partial results of the other kernel then took more workspace than there is.
     *shared_waves = 2;
-    uint64_t total;
-    if (!most_mt) {
-        total = cut(plans, n_reqs, docs->data, H, false, piece_length(plans, n_reqs, docs->data, H), 0);
-    } else {
-        uint32_t by_block = 0;
-        Limit limit = workspace_limit(plans, n_reqs, docs->data, H, most_mt, by_block);
-        if (limit.floats > most_floats) limit = workspace_limit(plans, n_reqs, docs->data, H, most_mt, by_block = 1u);
-        total = limit.floats;
-        const bool joins = most_mt <= 8u;
-        set_shared(plans, n_reqs, joins);
-        uint64_t used = lay_out_runs(plans, n_reqs, docs->data, H, most_mt, by_block, total, shared_waves);
-        if (used > total && joins) {
-            set_shared(plans, n_reqs, false);
-            used = lay_out_runs(plans, n_reqs, docs->data, H, most_mt, by_block, total, shared_waves);
-        }
-        // The run lengths were chosen by the quotient of blocks and length, but a run also ends after kMaxRunDocs
-        // documents, so that a request of more than that may have more runs.  Any form takes runs of any length:
-        // where they do not fit, those that the workspace is sized by.
-        if (used > total) {
-            used = lay_out_limit(plans, n_reqs, docs->data, H, limit);
-            *shared_waves = most_mt > 8u ? 8u : most_mt > 4u ? 4u : 2u;
-        }
-        if (used > total) return HA_RAG_EINVAL;  // never: the same layout as above
-    }
+    const uint64_t total = most_mt ? lay_out_shared(plans, n_reqs, docs->data, H, most_mt, most_floats, shared_waves)
+                                   : lay_out_pieces(plans, n_reqs, docs->data, H);
     if (total * 4ull > (1ull << 40)) return HA_RAG_EINVAL;
     *floats = total;
     return HA_RAG_OK;

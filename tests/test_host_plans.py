@@ -60,3 +60,106 @@ def test_records_lie_in_the_workspace_when_runs_end_at_the_most_documents(plans_
 
 def test_random_calls_lay_every_record_out_once_and_inside(plans_host):
     assert "plans_host ok" in run(plans_host, ["random", "7", "2500"])
+
+
+def test_planning_takes_less_than_the_descriptors_of_a_batch(plans_host):
+    """Run lengths and forms are found without trying every length: long documents cost no more to plan than 320 short
+    ones cost to list.  (Trying every one three or four times took 2.4, 11 and 49 times as long.)"""
+    batch = "time 200 8 32" + " / 1 512*10" * 32
+    rows = ["time 200 8 32 / 16 1024*16", "time 200 8 32 / 16 4096*32", "time 100 8 32 / 16 65536*32"]
+    out = [l.split() for l in run(plans_host, ["calls"], "\n".join([batch] + rows) + "\n").splitlines()]
+    assert all(rc == "0" for rc, _ in out)
+    for _, us in out[1:]:
+        assert float(us) < float(out[0][1]), out
+
+
+# ---- the rule that workspaces are sized by, every run length tried -----------------------------------------
+
+
+def longest_steps(lens, run, per_step):
+    most, steps, left = 0, 0, run
+    for n in lens:
+        while n:
+            take = min(n, left)
+            steps += -(-take // per_step)
+            n, left = n - take, left - take
+            if not left:
+                most, steps, left = max(most, steps), 0, run
+    return max(most, steps)
+
+
+def limit_words(H, reqs, tiles_waves, in_steps):
+    """reqs: (tiles, blocks of each document).  Words with runs as long as costs least, each length tried."""
+    if not reqs:
+        return 0
+    _, waves, side, per_block = tiles_waves
+    largest = max((lens for _, lens in reqs), key=sum)
+    per_step = waves if in_steps else 1
+    blocks = sum(largest)
+    all_steps = sum(-(-n // per_step) for n in largest)
+    least = fewest = None
+    best = chosen = blocks
+    for n in range(1, blocks + 1):
+        run = -(-blocks // n)
+        if n > 1 and run < 8:
+            break
+        runs = [-(-sum(lens) // run) for _, lens in reqs]
+        wgs = sum(k * H * -(-mt // (2 * waves)) for k, (mt, _) in zip(runs, reqs))
+        recs = sum(k * H * mt for k, (mt, _) in zip(runs, reqs) if k > 1)
+        rounds = -(-wgs // side)
+        steps = max(-(-run // per_step), -(-all_steps // n))
+        if len(largest) <= 32:
+            steps = max(steps, longest_steps(largest, run, per_step))
+        cost = rounds * (steps * per_step + 8) + recs // per_block
+        if least is None or cost < least:
+            least, best = cost, run
+        if fewest is None or rounds * run < fewest:
+            fewest, chosen = rounds * run, best
+        if wgs >= 64 * side:
+            break
+    return sum(k * H * mt for k, mt in ((-(-sum(lens) // chosen), mt) for mt, lens in reqs) if k > 1) * 2080
+
+
+def piece_words(H, reqs):
+    def groups(piece):
+        return sum(-(-n // piece) * H * -(-mt // 2) for mt, lens in reqs for n in lens)
+    piece = 128
+    while piece > 8 and groups(piece) < 2048:
+        piece //= 2
+    if piece == 8 and groups(4) <= 1024:
+        piece = 4
+    total = 0
+    for mt, lens in reqs:
+        for n in lens:
+            parts = -(-n // piece)
+            total += -(-n // -(-n // parts)) * H * mt
+    return total * 2080
+
+
+def test_workspace_sizes_are_those_of_the_rule(plans_host):
+    import random
+    rnd = random.Random(11)
+    lines, expect = [], []
+    for _ in range(300):
+        H, G = rnd.choice([1, 2, 8, 16]), rnd.choice([1, 4, 8])
+        most_q = rnd.choice([8, 16, 40, 200])
+        same = rnd.random() < 0.3
+        first = [max(1, int(2 ** rnd.uniform(0, 11))) for _ in range(rnd.randint(1, 12))]
+        reqs, text = [], ""
+        for _ in range(max(1, int(2 ** rnd.uniform(0, 5.3)))):
+            lens = first if same else [max(1, int(2 ** rnd.uniform(0, 11))) for _ in range(rnd.randint(0, 12 if rnd.random() < 0.9 else 40))]
+            n_q = rnd.randint(1, most_q)
+            reqs.append((-(-n_q * G // 16), [-(-t // 16) for t in lens]))
+            text += " / %d %s" % (n_q, " ".join(map(str, lens)))
+        most = max(mt for mt, _ in reqs)
+        rule = (4, 2, 1024, 600) if most <= 4 else (8, 4, 512, 450) if most <= 8 else (0, 8, 256, 280)
+        some = [(mt, lens) for mt, lens in reqs if lens]
+
+        def words(split):
+            return piece_words(H, [r for r in some if r[0] <= split]) + limit_words(H, [r for r in some if r[0] > split], rule, True)
+        total = words(2)
+        if 2 < most <= 4:
+            total = min(total, words(1))
+        lines.append("workspace %d %d%s" % (H, H * G, text))
+        expect.append(4 * total)
+    assert [c[1] for c in calls(plans_host, lines)] == expect
