@@ -235,12 +235,14 @@ __device__ __forceinline__ float sum_over_lane_groups(float x)
 }
 
 // Launches a kernel of one argument from where the argument lies.  (The launch syntax passes it by value
-// first: another copy of up to 36 KiB.)
+// first: another copy of up to 36 KiB.)  What it reports is the thread's last error, fetched, as the other launchers
+// do: left there, it would be taken for the next call's.
 template <class P>
 inline hipError_t launch_args(void (*kernel)(const P), dim3 grid, dim3 block, uint32_t lds_bytes, hipStream_t stream, P &p)
 {
     void *args[] = {&p};
-    return hipLaunchKernel(reinterpret_cast<const void *>(kernel), grid, block, args, lds_bytes, stream);
+    (void)hipLaunchKernel(reinterpret_cast<const void *>(kernel), grid, block, args, lds_bytes, stream);
+    return hipGetLastError();
 }
 
 }  // namespace ha_rag

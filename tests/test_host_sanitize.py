@@ -83,3 +83,17 @@ def test_pageable_and_file_tiers_with_real_files_under_asan_ubsan(tmp_path):
     r = subprocess.run([exe, str(pools)], capture_output=True, text=True, env=env, timeout=300)
     assert r.returncode == 0, (r.stdout + r.stderr)[-4000:]
     assert "tiers_host ok" in r.stdout
+
+
+@pytest.mark.skipif(shutil.which("hipcc") is None and not os.path.exists("/opt/rocm/bin/hipcc"),
+                    reason="needs hipcc")
+def test_a_refused_launch_leaves_no_error_behind(tmp_path):
+    hipcc = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
+    exe = str(tmp_path / "launch_host")
+    r = subprocess.run([hipcc, "--offload-arch=gfx950", "-O1", "-std=c++17", "-Xclang", "-target-feature", "-Xclang",
+                        "-packed-fp32-ops", "-Wno-unused-command-line-argument", "-x", "hip",
+                        os.path.join(ROOT, "tests", "host_sanitize", "launch_host.cpp"), "-o", exe],
+                       capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-3000:]
+    r = subprocess.run([exe], capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0 and "launch_host ok" in r.stdout, r.stdout + r.stderr
