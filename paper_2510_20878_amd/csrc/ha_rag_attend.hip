@@ -46,7 +46,7 @@ struct Plan {               // one request
     uint32_t first_doc = 0, n_docs = 0;  // its documents that hold tokens
     uint32_t n_mt = 1;
     uint32_t shared = 0;       // goes to the kernel whose waves share each decoded block: more than two query
-                               // tiles, or two in a call whose largest request has three to eight
+                               // tiles, or two in some calls whose largest request has three to eight
     uint32_t run_blocks = 0;   // layout blocks per run (what one workgroup takes)
     uint64_t all_blocks = 0;   // layout blocks of all its documents
     uint64_t wide_blocks = 0;  // those of documents with a 16-bit side
@@ -467,6 +467,24 @@ uint64_t lay_out_pieces(Plan *plans, uint32_t n_reqs, const Doc *docs, uint32_t 
     return 0;
 }
 
+// What k6_attend_partial costs a call whose largest request has five to eight tiles, in ns: a launch, and per block and KV
+// head 1.25 ns up to 28,000 of them, 0.82 from there on, when pieces are long and all places taken.  Two-tile requests in a
+// launch of their own or with the others in k6_attend_roles<4>, where each keeps one of four scorers busy; us a layer, 10 x
+// 512 tokens: one request of 32 query tokens and 31 of 8: 110.6 / 127.0 (paper's formats 117.4 / 124.2), 8 of 20 and 24 of 5:
+// 117.5 / 126.1 (123.5 / 123.9), 16 of 32 and 16 of 8: 140.2 / 130.1 (145.6 / 127.3), one of 32 and 15 of 8: 76.5 / 70.6, one
+// and seven: 59.3 / 41.0, one and one: 38.7 / 23.9; 16 of 700 and 333 tokens at 20, 6, 1 and 8, where there is a launch for the
+// one-tile requests anyway: 42.0 / 44.4.  Fitted to these and 35 calls like them, where it chooses the faster way each time; of 34 others drawn
+// at random it was off the faster one by 5 to 6 % in three, by up to 2 % in two, and the other way would have cost up to 71 %.
+uint64_t pieces_ns(const Plan *plans, uint32_t n_reqs, uint32_t H)
+{
+    uint64_t blocks = 0;
+    for (uint32_t r = 0; r < n_reqs; ++r)
+        if (!plans[r].shared) blocks += plans[r].all_blocks * H;
+    if (!blocks) return 0;
+    constexpr uint64_t kFew = 28000;
+    return 14000u + (blocks < kFew ? blocks * 5u / 4u : kFew * 5u / 4u + (blocks - kFew) * 41u / 50u);
+}
+
 // Lays out a call whose largest request has most_mt > 2 tiles.  Returns the words of the workspace it asks for (see
 // Limit), which the layout stays within; *waves: the form of the shared kernel.
 uint64_t lay_out_shared(Plan *plans, uint32_t n_reqs, const Doc *docs, uint32_t H, uint32_t most_mt, uint64_t most_floats, uint32_t *waves)
@@ -534,9 +552,14 @@ uint64_t lay_out_shared(Plan *plans, uint32_t n_reqs, const Doc *docs, uint32_t 
         return lay_out(len);
     };
     uint64_t used = ~0ull;
-    if (twos && limit_waves == 4u) {  // those of two tiles go there too if the workspace holds that
+    if (twos && limit_waves == 4u) {  // those of two tiles go there too if that costs less and the workspace holds it
+        uint64_t apart_ns = ~0ull, ns = ~0ull;
+        FormCost(kForms[1], call).best(total > pieces ? total - pieces : 0u, &apart_ns);
+        apart_ns += pieces_ns(plans, n_reqs, H);
         set(true);
-        used = choose();
+        const uint64_t len = FormCost(kForms[1], call).best(total > pieces ? total - pieces : 0u, &ns);
+        if (ns + pieces_ns(plans, n_reqs, H) <= apart_ns) used = lay_out(len);
+        *waves = 4u;
         if (used > total) set(false);
     }
     if (used > total) used = choose();

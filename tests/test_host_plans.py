@@ -163,3 +163,13 @@ def test_workspace_sizes_are_those_of_the_rule(plans_host):
         lines.append("workspace %d %d%s" % (H, H * G, text))
         expect.append(4 * total)
     assert [c[1] for c in calls(plans_host, lines)] == expect
+
+
+@pytest.mark.parametrize("many,few,alone", [(31, 1, True), (28, 4, True), (16, 16, False), (15, 1, False), (7, 1, False), (1, 1, False)])
+def test_two_tile_requests_join_ones_of_eight_tiles_where_one_launch_costs_less(plans_host, many, few, alone):
+    """10 x 512 tokens, `few` requests of 32 query tokens (8 tiles) and `many` of 8 (2 tiles): most of a batch alone, a few
+    with the others."""
+    text = " / 32 512*10" * few + " / 8 512*10" * many
+    (rc, need, end, waves, pieces, runs, _), = calls(plans_host, ["workspace 8 32" + text])
+    assert rc == OK and end <= need and waves == 4
+    assert (pieces > 0) == alone
