@@ -173,3 +173,27 @@ def test_two_tile_requests_join_ones_of_eight_tiles_where_one_launch_costs_less(
     (rc, need, end, waves, pieces, runs, _), = calls(plans_host, ["workspace 8 32" + text])
     assert rc == OK and end <= need and waves == 4
     assert (pieces > 0) == alone
+
+
+def call_line(n_reqs, n_docs, tokens, n_q, G, tag=2):
+    """One call over 8 KV heads; document lengths and query tokens taken in turn."""
+    text = "workspace 8 %d" % (8 * G)
+    for r in range(n_reqs):
+        text += " / %d" % n_q[r % len(n_q)]
+        text += "".join(" %d*1*%d" % (tokens[(r * n_docs + i) % len(tokens)], tag) for i in range(n_docs))
+    return text
+
+
+def form(exe, *shape):
+    """Scoring waves of the form a call takes and its longest run."""
+    (rc, need, end, waves, _, _, longest), = calls(exe, [call_line(*shape)])
+    assert rc == OK and end <= need
+    return waves, longest
+
+
+@pytest.mark.parametrize("shape,waves", [
+    ((10, 4, [256], [31], 8), 8),          # 16 tiles: 32.8 us in two runs of eight scorers, 35.6 in one of four
+    ((24, 2, [700, 333], [8, 7, 4], 8), 2),  # up to four tiles: 30.2 us in k6_attend_shared, 33.8
+    ((20, 1, [256], [5, 7, 7], 8), 4)])    # 15.1 us, 18.8 in k6_attend_shared
+def test_a_run_that_writes_the_output_itself_pays_for_its_end(plans_host, shape, waves):
+    assert form(plans_host, *shape)[0] == waves
