@@ -156,7 +156,9 @@ struct SharedCall {
     Size sizes[kSizes];             // in the order they come up first
     uint32_t n_sizes = 0, rest = 0; // requests from `rest` on are looked at one by one
     const Plan *largest = nullptr;
+    uint32_t least_mt = ~0u, most_mt = 0;  // query tiles
     uint64_t all = 0, wide = 0;     // blocks; those of documents with a 16-bit side
+    uint64_t fewest = ~0ull;        // blocks of the shortest request that has any
 
     SharedCall() = default;
     SharedCall(const Plan *plans_, uint32_t n_reqs_, const Doc *docs_, uint32_t H_) : plans(plans_), docs(docs_), n_reqs(n_reqs_), H(H_)
@@ -173,6 +175,9 @@ struct SharedCall {
         for (uint32_t r = 0; r < n_reqs; ++r) {
             if (!plans[r].shared) continue;
             if (!largest || plans[r].all_blocks > largest->all_blocks) largest = &plans[r];
+            if (plans[r].all_blocks && plans[r].all_blocks < fewest) fewest = plans[r].all_blocks;
+            if (plans[r].n_mt > most_mt) most_mt = plans[r].n_mt;
+            if (plans[r].n_mt < least_mt) least_mt = plans[r].n_mt;
             all += plans[r].all_blocks;
             wide += plans[r].wide_blocks;
         }
@@ -184,7 +189,14 @@ struct SharedCall {
         for (uint32_t r = rest; r < n_reqs; ++r)
             if (plans[r].shared) f(plans[r].all_blocks, plans[r].n_mt, 1u);
     }
-    // Workgroups and records with runs of len blocks, two tiles for each of 1 << wshift waves.
+    // Workgroups of a run when 1 << wshift waves take two tiles each.
+    uint32_t groups(uint32_t n_mt, uint32_t wshift) const { return H * ((n_mt + (2u << wshift) - 1u) >> (wshift + 1u)); }
+    static uint64_t runs_of(uint64_t blocks, uint64_t len)
+    {
+        const uint64_t up = blocks + len - 1u;
+        return up >> 32 ? up / len : (uint32_t)up / (uint32_t)len;
+    }
+    // Workgroups and records with runs of len blocks.
     uint64_t wgs = 0, recs = 0;
     void count(uint64_t len, uint32_t wshift)
     {
@@ -193,9 +205,9 @@ struct SharedCall {
         counted_wshift = wshift;
         wgs = recs = 0;
         each([&](uint64_t blocks, uint32_t n_mt, uint32_t times) {
-            const uint64_t up = blocks + len - 1u, runs = (up >> 32 ? up / len : (uint32_t)up / (uint32_t)len) * times * H;
-            wgs += runs * ((n_mt + (2u << wshift) - 1u) >> (wshift + 1u));
-            if (blocks > len) recs += runs * n_mt;
+            const uint64_t runs = runs_of(blocks, len) * times;
+            wgs += runs * groups(n_mt, wshift);
+            if (blocks > len) recs += runs * H * n_mt;
         });
     }
     uint64_t counted_len = 0;
@@ -204,8 +216,34 @@ struct SharedCall {
     uint64_t work(uint32_t wshift) const
     {
         uint64_t w = 0;
-        each([&](uint64_t blocks, uint32_t n_mt, uint32_t times) { w += blocks * times * H * ((n_mt + (2u << wshift) - 1u) >> (wshift + 1u)); });
+        each([&](uint64_t blocks, uint32_t n_mt, uint32_t times) { w += blocks * times * groups(n_mt, wshift); });
         return w;
+    }
+    // Rounds that wgs workgroups (those counted last) take, `side` of them at a time.  A launch is as wide as its widest run and
+    // workgroups beyond a narrower one's exit at once.  The hardware deals the launch's workgroups, those too, to the
+    // chip's 32 shader engines in turn, so that an engine may get one more than it has places for while others have
+    // none: 6 requests of 4, 4 and 2 groups in 9 runs, 240 workgroups of one head's width 4, took 32.6 us where one round
+    // takes 17; 5 requests of 5 to 7 groups 146.9 instead of 86.6.
+    uint64_t rounds(uint64_t side) const
+    {
+        const uint64_t even = (wgs + side - 1u) / side;
+        const uint32_t width = groups(most_mt, counted_wshift);
+        if (groups(least_mt, counted_wshift) == width || even > 4u) return even;  // (then they even out)
+        constexpr uint32_t kEngines = 32;
+        uint32_t got[kEngines] = {};
+        uint32_t most = 0, whole = 0, at = 0;
+        for (uint32_t r = 0; r < n_reqs; ++r) {
+            if (!plans[r].shared) continue;
+            const uint32_t mine = groups(plans[r].n_mt, counted_wshift);
+            for (uint64_t k = runs_of(plans[r].all_blocks, counted_len); k; --k, at += width) {
+                whole += mine / kEngines;
+                for (uint32_t i = 0; i < mine % kEngines; ++i) ++got[(at + i) % kEngines];
+            }
+        }
+        for (uint32_t n : got)
+            if (n > most) most = n;
+        const uint64_t places = side / kEngines;
+        return (whole + most + places - 1u) / places;
     }
 };
 
@@ -346,7 +384,7 @@ struct FormCost {
 
     FormCost(const Form &f_, SharedCall &c)
         : f(f_), call(c), lengths{c.largest->all_blocks}, steps(c, f_.shift), wide_ns(f_.wide * c.wide / c.all) {}
-    uint64_t rounds(uint64_t len)
+    uint64_t full_rounds(uint64_t len)  // no more than it takes
     {
         call.count(len, f.wshift);
         return (call.wgs + f.side_by_side - 1u) / f.side_by_side;
@@ -363,12 +401,16 @@ struct FormCost {
     // of n runs, len = lengths.of(n), if that is no more than `most`; else at least not less than it costs on average
     uint64_t of(uint64_t n, uint64_t len, uint64_t most)
     {
-        const uint64_t k = rounds(len), step = step_ns(), mean = steps.average(n, len);
+        const uint64_t full = full_rounds(len), more = call.rounds(f.side_by_side) - full, step = step_ns(), mean = steps.average(n, len);
         const uint64_t in_docs = (call.largest->n_docs * len + lengths.blocks - 1u) / lengths.blocks * f.doc;
-        uint64_t c = f.call + k * (f.round + mean * step + in_docs) + end_ns();
+        uint64_t c = f.call + full * (f.round + mean * step + in_docs) + end_ns();
+        if (more) {  // what an engine has no place for starts when its first workgroups end
+            const uint64_t blocks = call.fewest < len ? call.fewest : len;
+            c += more * (f.round + ((blocks + (1u << f.shift) - 1u) >> f.shift) * step);
+        }
         if (c <= most && steps.few_docs()) {
             const uint64_t longest = steps.longest(len);
-            if (longest > mean) c += k * ((longest - mean) * step / 3u);
+            if (longest > mean) c += full * ((longest - mean) * step / 3u);
         }
         return c;
     }
@@ -379,7 +421,7 @@ struct FormCost {
     {
         const uint64_t last = lengths.last(), side = f.side_by_side;
         auto fits = [&]() { return call.recs * kAttendRecFloats <= most_floats; };
-        const uint64_t start = lengths.last_where([&](uint64_t len) { return rounds(len) <= 1u && fits(); });
+        const uint64_t start = lengths.last_where([&](uint64_t len) { return full_rounds(len) <= 1u && fits(); });
         uint64_t least = *ns, best_len = lengths.of(start);
         auto most_n = [&](uint64_t len) {
             const uint64_t n = lengths.last_n(len);
@@ -397,11 +439,11 @@ struct FormCost {
         // shorter and shorter ones, until rounds, records and all workgroups' blocks in full rounds cost as much
         const uint64_t full = call.work(f.wshift), full_steps = (full + (side << f.shift) - 1u) / (side << f.shift);
         uint64_t len = lengths.of(start);
-        rounds(len);
+        full_rounds(len);
         while (call.wgs < 64u * side && lengths.last_n(len) < last) {  // finer than this gains nothing
             uint64_t n = lengths.last_n(len) + 1u;
             len = lengths.of(n);
-            const uint64_t k = rounds(len);
+            const uint64_t k = full_rounds(len);
             if (!fits() || f.call + k * f.round + full_steps * step_ns() + end_ns() >= least) break;
             if (call.wgs < 64u * side) n = most_n(len);
             const uint64_t c = of(n, len, least);

@@ -197,3 +197,15 @@ def form(exe, *shape):
     ((20, 1, [256], [5, 7, 7], 8), 4)])    # 15.1 us, 18.8 in k6_attend_shared
 def test_a_run_that_writes_the_output_itself_pays_for_its_end(plans_host, shape, waves):
     assert form(plans_host, *shape)[0] == waves
+
+
+@pytest.mark.parametrize("shape,taken", [
+    # 5 to 7 workgroups a head in 5 runs: 31 for the 32 places of an XCD, but 9 for the 8 of one engine
+    ((5, 13, [100, 300], [163, 209, 142], 4), (8, 59)),   # 85.9 us, 146.8 with four scorers in one run
+    # 2 to 4 workgroups a head in 9 runs: 30 for 32 places, 9 for 8
+    ((6, 1, [700, 333], [47, 114, 105], 4), (8, 15)),     # 28.4 us, 37.0 with four scorers in runs of 22 blocks
+    # as uneven, but every engine has a place for each
+    ((7, 2, [700, 333], [40, 23, 106, 33], 8), (4, 65)),  # 36.3 us, 53.6 with eight scorers
+    ((3, 4, [256], [179, 76, 69], 4), (8, 16))])          # 25.0 us, 33.3 with four scorers
+def test_requests_of_different_widths_are_counted_by_engine(plans_host, shape, taken):
+    assert form(plans_host, *shape) == taken
