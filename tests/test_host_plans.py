@@ -209,3 +209,10 @@ def test_a_run_that_writes_the_output_itself_pays_for_its_end(plans_host, shape,
     ((3, 4, [256], [179, 76, 69], 4), (8, 16))])          # 25.0 us, 33.3 with four scorers
 def test_requests_of_different_widths_are_counted_by_engine(plans_host, shape, taken):
     assert form(plans_host, *shape) == taken
+
+
+@pytest.mark.parametrize("shape,waves", [
+    ((29, 2, [700, 333], [123, 160, 72], 4, 0), 8),   # 113.9 us in three rounds, 140.8 in four of four scorers
+    ((26, 3, [256], [20, 38, 21], 8), 4)])            # 57.4 us, 64.6 in two rounds of eight
+def test_later_rounds_of_eight_scorers_count_less(plans_host, shape, waves):
+    assert form(plans_host, *shape)[0] == waves
