@@ -348,24 +348,26 @@ uint64_t limit_run(const Limit &f, SharedCall &call, bool in_steps)
     return best;
 }
 
-// What a call costs the shared kernel in each of its forms, in ns: 2 scoring waves (k6_attend_shared), 4 or 8
-// (k6_attend_roles<4>, <8>).  Workgroups of one size finish in rounds of as many as the chip holds side by side; a round
-// costs what starting and ending a workgroup does, its steps (a workgroup takes a few blocks at a time, all of
-// one document), and for k6_attend_roles, alone on its compute unit, a trip to memory at the start of every document;
-// steps get slower the more workgroups share a compute unit, or the memory and the power there is.  A run that is longer
+// What a call costs the shared kernel in each of its forms, in ns.  Workgroups of one size finish in rounds of as many as
+// the chip holds side by side; a round costs what starting and ending a workgroup does, its steps (a workgroup takes a few
+// blocks at a time, all of one document), and for k6_attend_roles<4>, alone on its compute unit, a trip to memory at the start
+// of every document; steps get slower the more workgroups share a compute unit, or the memory and the power there is, and
+// for k6_attend_roles<4> they are quicker with few blocks in them (documents of 60 tokens: half).  A run that is longer
 // than the average one costs a third of the difference: its neighbours are done by then.  Every record is 8 KiB that is
-// written, flushed at the kernel's end and read by another launch.  Fitted to 1,700 timings of 142 calls of 1 to 32
-// requests of 7 to 1,024 blocks at 3 to 402 query tokens, whose runs and forms were set by hand: for these same calls, what
-// it chooses is on average 0.5 % slower than the fastest, 9 % at worst; of short calls it is within 14 % of the time, of
-// those that run into the power limit it is too low by a third.  The time to choose is not part of it: 0.5 to 5 us a call.
+// written, flushed at the kernel's end and read by another launch.  k6_attend_shared<2> and k6_attend_roles<8> were fitted to
+// timings of 142 calls whose runs and forms were set by hand, <4> of both to 79 and 492 timings of random calls, of which they
+// are off by 8 and 6 %.  180 random calls that were no part of it, of 1 to 32 requests, 1 to 16 documents and 3 and more
+// tiles, take 0.92 of the time on average that they took when forms went by tiles alone, 1.11 at worst, 0.69 at best.  The
+// time to choose is not part of it: 1 to 5 us of host time a call.
 struct Form {
     uint32_t wshift, shift, side_by_side;  // 1 << wshift waves; 1 << shift blocks a step
     uint32_t call, round, doc;             // ns: once; a round; a document
     uint32_t step[4];                      // ns: a step with up to a quarter, a half, three quarters and all places taken
     uint32_t wide;                         // added to a step times the share of blocks with a 16-bit side
 };
-constexpr Form kForms[3] = {
+constexpr Form kForms[4] = {  // by SharedForm
     {1u, 1u, 4u * kChipCUs, 2000u, 5600u, 0u, {1330u, 2115u, 2120u, 2300u}, 460u},
+    {2u, 2u, 2u * kChipCUs, 7800u, 0u, 0u, {1220u, 2530u, 2710u, 2710u}, 0u},
     {2u, 3u, kChipCUs, 5000u, 2900u, 600u, {2000u, 2160u, 2410u, 2770u}, 210u},
     {3u, 3u, kChipCUs, 2500u, 6100u, 0u, {3050u, 3230u, 3540u, 3960u}, 210u},
 };
@@ -382,6 +384,7 @@ struct FormCost {
     const Steps steps;
     const uint64_t wide_ns;
 
+
     FormCost(const Form &f_, SharedCall &c)
         : f(f_), call(c), lengths{c.largest->all_blocks}, steps(c, f_.shift), wide_ns(f_.wide * c.wide / c.all) {}
     uint64_t full_rounds(uint64_t len)  // no more than it takes
@@ -393,9 +396,9 @@ struct FormCost {
     {
         const uint64_t taken = call.wgs < f.side_by_side ? call.wgs : f.side_by_side;  // places
         const uint64_t quarter = f.side_by_side / 4u, q = taken <= quarter ? 0u : (taken - 1u) / quarter - 1u;
-        uint64_t step = f.step[q] + wide_ns;
+        uint64_t step = f.step[q];
         if (taken > quarter) step += (f.step[q + 1u] - f.step[q]) * (taken - (q + 1u) * quarter) / quarter;
-        return step;
+        return step + wide_ns;
     }
     uint64_t end_ns() const { return call.recs ? kMergeNs + call.recs * kRecNsNum / kRecNsDen : kFinalNs; }
     // of n runs, len = lengths.of(n), if that is no more than `most`; else at least not less than it costs on average
@@ -535,8 +538,8 @@ uint64_t pieces_ns(const Plan *plans, uint32_t n_reqs, uint32_t H)
 }
 
 // Lays out a call whose largest request has most_mt > 2 tiles.  Returns the words of the workspace it asks for (see
-// Limit), which the layout stays within; *waves: the form of the shared kernel.
-uint64_t lay_out_shared(Plan *plans, uint32_t n_reqs, const Doc *docs, uint32_t H, uint32_t most_mt, uint64_t most_floats, uint32_t *waves)
+// Limit), which the layout stays within; *form: the shared kernel's.
+uint64_t lay_out_shared(Plan *plans, uint32_t n_reqs, const Doc *docs, uint32_t H, uint32_t most_mt, uint64_t most_floats, SharedForm *form)
 {
     SharedCall call;
     uint64_t pieces = 0;
@@ -554,7 +557,7 @@ uint64_t lay_out_shared(Plan *plans, uint32_t n_reqs, const Doc *docs, uint32_t 
     // other one (103 against 100 us per call of 32 requests), and one launch fills the chip where two in a row
     // do not (12 requests of 6 to 16 query tokens: 46 against 63 us per layer).
     const Limit &limit = kLimits[most_mt > 8u ? 2 : most_mt > 4u ? 1 : 0];
-    const uint32_t limit_waves = most_mt > 8u ? 8u : most_mt > 4u ? 4u : 2u;
+    const SharedForm limit_form = most_mt > 8u ? SharedForm::kRoles8 : most_mt > 4u ? SharedForm::kShared4 : SharedForm::kShared2;
     bool limit_twos = false;
     uint64_t limit_len = 1, total = 0;
     for (bool in_steps : {true, false}) {
@@ -574,7 +577,7 @@ uint64_t lay_out_shared(Plan *plans, uint32_t n_reqs, const Doc *docs, uint32_t 
         }
         if (total <= most_floats) break;
     }
-    *waves = limit_waves;
+    *form = limit_form;
     if (!call.all) return total;
 
     // The forms: four scorers (up to 8 tiles a workgroup) for every call; eight where a request has more
@@ -585,39 +588,41 @@ uint64_t lay_out_shared(Plan *plans, uint32_t n_reqs, const Doc *docs, uint32_t 
     // 4 x 512 - / 72.9 / 60.7, 32 x 10 x 512 - / 288 / 205.
     // Four scorers are as exact in long runs as in short ones (role_add_round) and take the length that costs least; the
     // others keep the runs that the workspace is sized for: longer ones cost them up to 1.8 times the error.
-    auto choose = [&]() {  // lays out what is set in the form that costs least; words
-        uint64_t other_ns = ~0ull;
-        if (limit_waves != 4u) {
-            FormCost other(kForms[limit_waves == 8u ? 2 : 0], call);
-            other_ns = other.of(other.lengths.first_n(limit_len), limit_len, ~0ull);
-        }
-        uint64_t ns = other_ns;
-        const uint64_t len = FormCost(kForms[1], call).best(total > pieces ? total - pieces : 0u, &ns);
-        if (other_ns != ~0ull && other_ns <= ns + ns / 32u) {  // also on an even estimate
-            *waves = limit_waves;
-            return total;  // laid out already
-        }
-        *waves = 4u;
-        return lay_out(len);
-    };
+    const bool middle = limit_form == SharedForm::kShared4;
+    const Form &four = kForms[(uint32_t)SharedForm::kRoles4];
     uint64_t used = ~0ull;
-    if (twos && limit_waves == 4u) {  // those of two tiles go there too if that costs less and the workspace holds it
+    if (twos && middle) {  // those of two tiles go there too if that costs less and the workspace holds it
         uint64_t apart_ns = ~0ull, ns = ~0ull;
-        FormCost(kForms[1], call).best(total > pieces ? total - pieces : 0u, &apart_ns);
+        FormCost(four, call).best(total > pieces ? total - pieces : 0u, &apart_ns);
         apart_ns += pieces_ns(plans, n_reqs, H);
         set(true);
-        const uint64_t len = FormCost(kForms[1], call).best(total > pieces ? total - pieces : 0u, &ns);
+        const uint64_t len = FormCost(four, call).best(total > pieces ? total - pieces : 0u, &ns);
         if (ns + pieces_ns(plans, n_reqs, H) <= apart_ns) used = lay_out(len);
-        *waves = 4u;
-        if (used > total) set(false);
+        *form = SharedForm::kRoles4;
+        if (used > total) {
+            set(false);
+            lay_out(limit_len);
+        }
     }
-    if (used > total) used = choose();
+    if (used > total) {
+        FormCost other(kForms[(uint32_t)limit_form], call);
+        const uint64_t other_ns = other.of(other.lengths.first_n(limit_len), limit_len, ~0ull);
+        uint64_t ns = middle ? ~0ull : other_ns;
+        const uint64_t len = FormCost(four, call).best(total > pieces ? total - pieces : 0u, &ns);
+        // The form that the workspace is sized by also on an even estimate; k6_attend_shared<4>, whose costs are the least
+        // certain, where it is expected to take a twelfth less: of 180 random calls 33, 0.83 to 1.10 times what four scorers
+        // take, 0.96 on average.
+        *form = limit_form;
+        if (other_ns <= (middle ? ns - ns / 12u : ns + ns / 32u)) return total;  // laid out already
+        *form = SharedForm::kRoles4;
+        used = lay_out(len);
+    }
     // The run length was chosen by the quotient of blocks and length, but a run also ends after kMaxRunDocs
     // documents, so that a request of more than that may have more runs.  Any form takes runs of any length:
     // where they do not fit, those that the workspace is sized by.
     if (used > total) {
         lay_out(limit_len);
-        *waves = limit_waves;
+        *form = limit_form;
     }
     return total;
 }
@@ -628,7 +633,7 @@ uint64_t lay_out_shared(Plan *plans, uint32_t n_reqs, const Doc *docs, uint32_t 
 int plan_attend(ha_rag_ctx *c, const ha_rag_packed_chunk *chunks, const ha_rag_attend_request *reqs,
                 uint32_t n_reqs, uint32_t n_q_heads, Plan *plans, Fixed<Doc> *docs,
                 Fixed<uint32_t> open_k, Fixed<uint32_t> open_v, uint64_t *floats,
-                uint32_t *shared_waves, bool need_buffers, uint64_t most_floats = ~0ull)
+                SharedForm *form, bool need_buffers, uint64_t most_floats = ~0ull)
 {
     if (!c || !reqs || n_reqs == 0 || n_reqs > HA_RAG_MAX_ATTEND_REQUESTS) return HA_RAG_EINVAL;
     if (c->cfg.head_dim != kAttendHeadDim) return HA_RAG_EFORMAT;
@@ -713,8 +718,8 @@ int plan_attend(ha_rag_ctx *c, const ha_rag_packed_chunk *chunks, const ha_rag_a
             if (i == 0 || doc.n_blocks < pl.least_blocks) pl.least_blocks = doc.n_blocks;
         }
     }
-    *shared_waves = 2;
-    const uint64_t total = most_mt ? lay_out_shared(plans, n_reqs, docs->data, H, most_mt, most_floats, shared_waves)
+    *form = SharedForm::kShared2;
+    const uint64_t total = most_mt ? lay_out_shared(plans, n_reqs, docs->data, H, most_mt, most_floats, form)
                                    : lay_out_pieces(plans, n_reqs, docs->data, H);
     if (total * 4ull > (1ull << 40)) return HA_RAG_EINVAL;
     *floats = total;
@@ -761,9 +766,9 @@ int attend_locked(ha_rag_ctx *c, PlanStore ps, const ha_rag_packed_chunk *chunks
                   void *stream, uint64_t *need = nullptr)
 {
     uint64_t floats = 0;
-    uint32_t waves = 2;
+    SharedForm form = SharedForm::kShared2;
     int rc = plan_attend(c, chunks, reqs, n_reqs, n_q_heads, ps.plans, &ps.docs, ps.open_k, ps.open_v,
-                         &floats, &waves, true, need ? workspace_bytes / 4u : ~0ull);
+                         &floats, &form, true, need ? workspace_bytes / 4u : ~0ull);
     if (rc) return rc;
     const Plan *plans = ps.plans;
     const Fixed<Doc> &docs = ps.docs;
@@ -891,7 +896,7 @@ int attend_locked(ha_rag_ctx *c, PlanStore ps, const ha_rag_packed_chunk *chunks
             }
         }
         kq.doc_end = later;
-        HIPCHK(c, launch_k6_shared(kq, waves, st, dry));
+        HIPCHK(c, launch_k6_shared(kq, form, st, dry));
     }
 
     K7Params mp;
@@ -996,9 +1001,9 @@ int ha_rag_attend_workspace_bytes(ha_rag_ctx *c, const ha_rag_packed_chunk *chun
     HeapPlanStore hs(reqs, n_reqs);
     PlanStore ps = hs.store();
     uint64_t floats = 0;
-    uint32_t waves = 0;
+    SharedForm form;
     int rc = plan_attend(c, chunks, reqs, n_reqs, n_q_heads, ps.plans, &ps.docs, ps.open_k, ps.open_v,
-                         &floats, &waves, false);
+                         &floats, &form, false);
     if (rc) return rc;
     *bytes = (size_t)(floats * 4ull);
     return HA_RAG_OK;
@@ -1072,9 +1077,9 @@ int ha_rag_attend_chunks_workspace_bytes(ha_rag_ctx *c, const uint64_t *ids,
     HeapPlanStore hs(reqs, n_reqs);
     PlanStore ps = hs.store();
     uint64_t floats = 0;
-    uint32_t waves = 0;
+    SharedForm form;
     rc = plan_attend(c, chunks.data(), reqs, n_reqs, n_q_heads, ps.plans, &ps.docs, ps.open_k, ps.open_v,
-                     &floats, &waves, false);
+                     &floats, &form, false);
     if (rc) return rc;
     *bytes = (size_t)(floats * 4ull);
     return HA_RAG_OK;

@@ -2,14 +2,14 @@
 // wave can keep (more than two 16-row tiles: the question's prefill of Sec. 2.1, tens of query
 // tokens times the query heads of a KV head), and for requests of two tiles next to such.
 //
-//  k6_attend_shared   one workgroup of two waves per (run of blocks across a request's
-//      documents in list order, KV head, group of four query tiles).  Every wave owns two query
+//  k6_attend_shared<W>   one workgroup of W waves (2 or 4) per (run of blocks across a request's
+//      documents in list order, KV head, group of 2 W query tiles).  Every wave owns two query
 //      tiles for the whole run: their queries, reference maxima, sums and output rows stay in its
-//      registers.  The layout blocks are taken two at a time: one wave decodes the keys and
-//      one the values of the round to BF16 (the values a load would write)
-//      and leaves them in LDS in the form the MFMAs take their operands in; after one barrier
-//      both waves score the blocks (a pair) against their own tiles.  A
-//      block is therefore fetched and decoded once per 64 query rows.  The rounds alternate
+//      registers.  The layout blocks are taken W at a time: half the waves decode the keys and
+//      half the values of the round, two blocks each (W = 2: one wave each), to BF16 (the values a load would write)
+//      and leave them in LDS in the form the MFMAs take their operands in; after one barrier
+//      every wave scores all W blocks against its own tiles, two blocks (a pair) at a time.  A
+//      block is therefore fetched and decoded once per 32 W query rows.  The rounds alternate
 //      between two sets of LDS buffers, so one barrier per round is enough: a wave that writes
 //      round r + 1 has passed barrier r, which every wave reaches only after it has read all of
 //      round r - 1.
@@ -721,14 +721,17 @@ __device__ __forceinline__ void role_score_round(const uint8_t *base, uint32_t r
 
 }  // namespace
 
-// Two waves, one decoding keys and one values; two waves per SIMD keep 256 registers
+// W = 2 or 4 waves, half of them decoding keys and half values; two waves per SIMD keep 256 registers
 // each (two tiles of output, their queries, the raw words of two blocks).
-// Bound: instructions.  Of 4,080 clocks a round (16 query tokens, 32 requests x 5,120 tokens) a wave decodes 1,290 and scores
-// 1,970, waits 210 for its loads and 320 at the barrier; another wave on its SIMD does the same.  (16-bit documents: 2,480 of
-// 6,300 wait for loads.)
-__global__ void __launch_bounds__(128, 2) k6_attend_shared(const K6Params p)
+// Bound: instructions.  Of 4,080 clocks a round (W = 2, 16 query tokens, 32 requests x 5,120 tokens) a wave decodes 1,290 and
+// scores 1,970, waits 210 for its loads and 320 at the barrier; another wave on its SIMD does the same.  (16-bit documents:
+// 2,480 of 6,300 wait for loads.)
+// W = 4 is for calls of five to eight tiles whose requests leave k6_attend_roles<4> with a third of its compute units idle or
+// a round nearly empty; two of its workgroups share a compute unit.  us a layer, k6_attend_roles<4> / this: 25 requests of 11 x
+// 1,024 tokens at 21 query tokens 254 / 213, 12 of 11 x 129 at 13 38.7 / 33.1; 27 of 2 x 256 at 18 23.0 / 26.1.
+template <int W>
+__global__ void __launch_bounds__(64 * W, 2) k6_attend_shared(const K6Params p)
 {
-    constexpr int W = 2;
     // two sets of W block buffers
     extern __shared__ __attribute__((aligned(16))) uint8_t lds_bytes[];
     uint8_t (*lds)[W][kSharedBlockLds] = reinterpret_cast<uint8_t (*)[W][kSharedBlockLds]>(lds_bytes);
@@ -954,10 +957,11 @@ hipError_t prepare_k6_shared()
     return hipSuccess;
 }
 
-hipError_t launch_k6_shared(K6Params &p, uint32_t waves, hipStream_t stream, bool check_only)
+hipError_t launch_k6_shared(K6Params &p, SharedForm form, hipStream_t stream, bool check_only)
 {
     if (p.n_runs == 0) return hipSuccess;
-    if (waves != 2u && waves != 4u && waves != 8u) return hipErrorInvalidValue;
+    if (form > SharedForm::kRoles8) return hipErrorInvalidValue;
+    const uint32_t waves = scoring_waves(form);
     uint32_t max_mt = 1;
     bool narrow = true;
     hipError_t e = check_k6_args(p, &max_mt, &narrow);
@@ -967,11 +971,12 @@ hipError_t launch_k6_shared(K6Params &p, uint32_t waves, hipStream_t stream, boo
     p.mtw = 2;
     if (check_only) return hipSuccess;
     dim3 grid((uint32_t)width, p.n_runs);
-    if (waves == 2u) return launch_args(k6_attend_shared, grid, dim3(128), 2u * 2u * kSharedBlockLds, stream, p);
+    if (form == SharedForm::kShared2) return launch_args(k6_attend_shared<2>, grid, dim3(128), 2u * 2u * kSharedBlockLds, stream, p);
+    if (form == SharedForm::kShared4) return launch_args(k6_attend_shared<4>, grid, dim3(256), 2u * 4u * kSharedBlockLds, stream, p);
     e = prepare_k6_shared();  // done at ha_rag_create; a no-op from then on
     if (e != hipSuccess) return e;
     const dim3 block(64u * (waves + kRoleDecoders));
-    if (waves == 4u) return launch_args(k6_attend_roles<4>, grid, block, 2u * kRoleSet, stream, p);
+    if (form == SharedForm::kRoles4) return launch_args(k6_attend_roles<4>, grid, block, 2u * kRoleSet, stream, p);
     return launch_args(k6_attend_roles<8>, grid, block, 2u * kRoleSet, stream, p);
 }
 

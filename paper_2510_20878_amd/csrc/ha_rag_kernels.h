@@ -196,9 +196,11 @@ typedef K7ParamsOf<kFewMergeReqs> K7ParamsFew;
 // the run's blocks in turn.  check_only (here and below): every check, no launch -- what a
 // context without a device does with the descriptors it has filled.
 hipError_t launch_k6(K6Params &p, hipStream_t stream, bool check_only = false);
-// The same for requests with two query tiles or more: the `waves` scoring waves of a workgroup share every
-// decoded block, each wave with two tiles of its own (2: k6_attend_shared, 4 or 8: k6_attend_roles).
-hipError_t launch_k6_shared(K6Params &p, uint32_t waves, hipStream_t stream, bool check_only = false);
+// The same for requests with two query tiles or more: the scoring waves of a workgroup share every
+// decoded block, each wave with two tiles of its own.
+enum class SharedForm : uint32_t { kShared2, kShared4, kRoles4, kRoles8 };  // k6_attend_shared<W>, k6_attend_roles<S>
+constexpr uint32_t scoring_waves(SharedForm f) { return f == SharedForm::kShared2 ? 2u : f == SharedForm::kRoles8 ? 8u : 4u; }
+hipError_t launch_k6_shared(K6Params &p, SharedForm form, hipStream_t stream, bool check_only = false);
 // What both check of their arguments (max_mt: most query tiles of a run's request; narrow: no 16-bit side).
 hipError_t check_k6_args(const K6Params &p, uint32_t *max_mt, bool *narrow);
 // Once per device, before the first launch of k6_attend_roles (its LDS allowance).

@@ -37,7 +37,7 @@ struct Seen {
     std::vector<Range> records;
     std::vector<Range> merged;
     std::vector<uint64_t> blocks;        // by request, told from the queries' address
-    uint32_t waves = 0, pieces = 0, runs = 0, longest = 0;
+    uint32_t form = 0, pieces = 0, runs = 0, longest = 0;
     uint64_t end = 0;                    // of the last record
     bool quiet = false;                  // only timed
 } seen;
@@ -80,11 +80,12 @@ hipError_t launch_k6(K6Params &p, hipStream_t, bool)
     return hipSuccess;
 }
 
-hipError_t launch_k6_shared(K6Params &p, uint32_t waves, hipStream_t, bool)
+hipError_t launch_k6_shared(K6Params &p, SharedForm form, hipStream_t, bool)
 {
     if (seen.quiet) return hipSuccess;
-    if (seen.waves && seen.waves != waves) fail("two forms of the shared kernel in one call");
-    seen.waves = waves;
+    const uint32_t id = 10u * scoring_waves(form) + (form >= SharedForm::kRoles4);  // 20, 40: k6_attend_shared; 41, 81: k6_attend_roles
+    if (seen.form && seen.form != id) fail("two forms of the shared kernel in one call");
+    seen.form = id;
     seen.runs += p.n_runs;
     for (uint32_t i = 0; i < p.n_runs; ++i) take_run(p, i, true);
     return hipSuccess;
@@ -237,8 +238,8 @@ void random_call(Call &c)
 }
 
 // One call: "static|workspace|time N HEADS QUERY_HEADS" then per request "/ n_q tokens*count ...".  Prints the return
-// code, the workspace asked for, the end of the last record, the scoring waves (0: no request of more than two tiles),
-// pieces and runs launched and the blocks of the longest, or the us of a call.
+// code, the workspace asked for, the end of the last record, the shared kernel's form (0: not
+// launched), pieces and runs launched and the blocks of the longest, or the us of a call.
 void run_line(char *line)
 {
     Call c = Call();
@@ -282,7 +283,7 @@ void run_line(char *line)
         return;
     }
     if (rc == HA_RAG_OK) rc = attend(c, how == "static", how == "static" ? HA_RAG_ATTEND_STATIC_SCRATCH_BYTES : need);
-    std::printf("%d %zu %llu %u %u %u %u\n", rc, need, (unsigned long long)(rc ? 0 : seen.end), rc ? 0 : seen.waves, rc ? 0 : seen.pieces, rc ? 0 : seen.runs, rc ? 0 : seen.longest);
+    std::printf("%d %zu %llu %u %u %u %u\n", rc, need, (unsigned long long)(rc ? 0 : seen.end), rc ? 0 : seen.form, rc ? 0 : seen.pieces, rc ? 0 : seen.runs, rc ? 0 : seen.longest);
 }
 
 }  // namespace

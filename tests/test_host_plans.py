@@ -14,6 +14,7 @@ HIPCC = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
 pytestmark = pytest.mark.skipif(not os.path.exists(HIPCC), reason="needs hipcc")
 
 OK, ENOSPC = 0, -3
+SHARED2, SHARED4, ROLES4, ROLES8 = 20, 40, 41, 81  # forms of the shared kernel
 
 
 @pytest.fixture(scope="module")
@@ -37,7 +38,7 @@ def run(exe, args, text=None):
 
 
 def calls(exe, lines):
-    """Per line: return code, workspace bytes, end of the last record, scoring waves, pieces, runs, longest run."""
+    """Per line: return code, workspace bytes, end of the last record, form, pieces, runs, longest run."""
     return [[int(x) for x in l.split()] for l in run(exe, ["calls"], "\n".join(lines) + "\n").splitlines()]
 
 
@@ -170,8 +171,8 @@ def test_two_tile_requests_join_ones_of_eight_tiles_where_one_launch_costs_less(
     """10 x 512 tokens, `few` requests of 32 query tokens (8 tiles) and `many` of 8 (2 tiles): most of a batch alone, a few
     with the others."""
     text = " / 32 512*10" * few + " / 8 512*10" * many
-    (rc, need, end, waves, pieces, runs, _), = calls(plans_host, ["workspace 8 32" + text])
-    assert rc == OK and end <= need and waves == 4
+    (rc, need, end, taken, pieces, runs, _), = calls(plans_host, ["workspace 8 32" + text])
+    assert rc == OK and end <= need and taken == ROLES4
     assert (pieces > 0) == alone
 
 
@@ -185,34 +186,43 @@ def call_line(n_reqs, n_docs, tokens, n_q, G, tag=2):
 
 
 def form(exe, *shape):
-    """Scoring waves of the form a call takes and its longest run."""
-    (rc, need, end, waves, _, _, longest), = calls(exe, [call_line(*shape)])
+    """The form a call takes and its longest run."""
+    (rc, need, end, taken, _, _, longest), = calls(exe, [call_line(*shape)])
     assert rc == OK and end <= need
-    return waves, longest
+    return taken, longest
 
 
-@pytest.mark.parametrize("shape,waves", [
-    ((10, 4, [256], [31], 8), 8),          # 16 tiles: 32.8 us in two runs of eight scorers, 35.6 in one of four
-    ((24, 2, [700, 333], [8, 7, 4], 8), 2),  # up to four tiles: 30.2 us in k6_attend_shared, 33.8
-    ((20, 1, [256], [5, 7, 7], 8), 4)])    # 15.1 us, 18.8 in k6_attend_shared
-def test_a_run_that_writes_the_output_itself_pays_for_its_end(plans_host, shape, waves):
-    assert form(plans_host, *shape)[0] == waves
+@pytest.mark.parametrize("shape,taken", [
+    ((10, 4, [256], [31], 8), ROLES8),     # 16 tiles: 32.8 us in two runs of eight scorers, 35.6 in one of four
+    ((24, 2, [700, 333], [8, 7, 4], 8), SHARED2),  # up to four tiles: 30.2 us in k6_attend_shared, 33.8
+    ((20, 1, [256], [5, 7, 7], 8), ROLES4)])    # 15.1 us, 18.8 in k6_attend_shared
+def test_a_run_that_writes_the_output_itself_pays_for_its_end(plans_host, shape, taken):
+    assert form(plans_host, *shape)[0] == taken
 
 
 @pytest.mark.parametrize("shape,taken", [
     # 5 to 7 workgroups a head in 5 runs: 31 for the 32 places of an XCD, but 9 for the 8 of one engine
-    ((5, 13, [100, 300], [163, 209, 142], 4), (8, 59)),   # 85.9 us, 146.8 with four scorers in one run
+    ((5, 13, [100, 300], [163, 209, 142], 4), (ROLES8, 59)),   # 85.9 us, 146.8 with four scorers in one run
     # 2 to 4 workgroups a head in 9 runs: 30 for 32 places, 9 for 8
-    ((6, 1, [700, 333], [47, 114, 105], 4), (8, 15)),     # 28.4 us, 37.0 with four scorers in runs of 22 blocks
+    ((6, 1, [700, 333], [47, 114, 105], 4), (ROLES8, 15)),     # 28.4 us, 37.0 with four scorers in runs of 22 blocks
     # as uneven, but every engine has a place for each
-    ((7, 2, [700, 333], [40, 23, 106, 33], 8), (4, 65)),  # 36.3 us, 53.6 with eight scorers
-    ((3, 4, [256], [179, 76, 69], 4), (8, 16))])          # 25.0 us, 33.3 with four scorers
+    ((7, 2, [700, 333], [40, 23, 106, 33], 8), (ROLES4, 65)),  # 36.3 us, 53.6 with eight scorers
+    ((3, 4, [256], [179, 76, 69], 4), (ROLES8, 16))])          # 25.0 us, 33.3 with four scorers
 def test_requests_of_different_widths_are_counted_by_engine(plans_host, shape, taken):
     assert form(plans_host, *shape) == taken
 
 
-@pytest.mark.parametrize("shape,waves", [
-    ((29, 2, [700, 333], [123, 160, 72], 4, 0), 8),   # 113.9 us in three rounds, 140.8 in four of four scorers
-    ((26, 3, [256], [20, 38, 21], 8), 4)])            # 57.4 us, 64.6 in two rounds of eight
-def test_later_rounds_of_eight_scorers_count_less(plans_host, shape, waves):
-    assert form(plans_host, *shape)[0] == waves
+@pytest.mark.parametrize("shape,taken", [
+    ((29, 2, [700, 333], [123, 160, 72], 4, 0), ROLES8),   # 113.9 us in three rounds, 140.8 in four of four scorers
+    ((26, 3, [256], [20, 38, 21], 8), ROLES4)])            # 57.4 us, 64.6 in two rounds of eight
+def test_later_rounds_of_eight_scorers_count_less(plans_host, shape, taken):
+    assert form(plans_host, *shape)[0] == taken
+
+
+@pytest.mark.parametrize("shape,taken", [
+    ((12, 11, [129], [8, 13, 14], 8, 3), SHARED4),  # 33.1 us, 38.7 with four scorers
+    ((18, 11, [1024], [10], 8, 3), SHARED4),        # 150 us, 177
+    ((27, 2, [256], [18], 4, 1), ROLES4),           # 23.0 us, 26.1 in k6_attend_shared
+    ((4, 12, [700, 333], [28], 4, 5), ROLES4)])  # 37.0 us, 40.1
+def test_four_scorers_or_four_waves_that_do_both(plans_host, shape, taken):
+    assert form(plans_host, *shape)[0] == taken
