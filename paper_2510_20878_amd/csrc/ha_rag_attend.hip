@@ -364,12 +364,13 @@ struct Form {
     uint32_t call, round, doc;             // ns: once; a round; a document
     uint32_t step[4];                      // ns: a step with up to a quarter, a half, three quarters and all places taken
     uint32_t wide;                         // added to a step times the share of blocks with a 16-bit side
+    uint32_t idle;                         // percent: what a step without any block would take less than a full one
 };
 constexpr Form kForms[4] = {  // by SharedForm
-    {1u, 1u, 4u * kChipCUs, 2000u, 5600u, 0u, {1330u, 2115u, 2120u, 2300u}, 460u},
-    {2u, 2u, 2u * kChipCUs, 7800u, 0u, 0u, {1220u, 2530u, 2710u, 2710u}, 0u},
-    {2u, 3u, kChipCUs, 5000u, 2900u, 600u, {2000u, 2160u, 2410u, 2770u}, 210u},
-    {3u, 3u, kChipCUs, 2500u, 6100u, 0u, {3050u, 3230u, 3540u, 3960u}, 210u},
+    {1u, 1u, 4u * kChipCUs, 2000u, 5600u, 0u, {1330u, 2115u, 2120u, 2300u}, 460u, 0u},
+    {2u, 2u, 2u * kChipCUs, 7800u, 0u, 0u, {1220u, 2530u, 2710u, 2710u}, 0u, 0u},
+    {2u, 3u, kChipCUs, 4700u, 2500u, 300u, {1700u, 2780u, 2780u, 2940u}, 180u, 50u},
+    {3u, 3u, kChipCUs, 2500u, 6100u, 0u, {3050u, 3230u, 3540u, 3960u}, 210u, 0u},
 };
 constexpr uint64_t kMergeNs = 3740, kRecNsNum = 19, kRecNsDen = 10;  // a merge at all; a record
 // Without a merge: the runs' own end, which divides the rows and finds their place in the output.  1.6 to 3.5 us were missing
@@ -382,11 +383,13 @@ struct FormCost {
     SharedCall &call;
     const RunLengths lengths;
     const Steps steps;
-    const uint64_t wide_ns;
+    const uint64_t wide_ns, fill;  // fill: of 1024, blocks in the steps of the largest request
 
 
     FormCost(const Form &f_, SharedCall &c)
-        : f(f_), call(c), lengths{c.largest->all_blocks}, steps(c, f_.shift), wide_ns(f_.wide * c.wide / c.all) {}
+        : f(f_), call(c), lengths{c.largest->all_blocks}, steps(c, f_.shift), wide_ns(f_.wide * c.wide / c.all),
+          fill(1024u * lengths.blocks / (steps.of_all << f_.shift)) {}
+    uint64_t filled(uint64_t ns) const { return ns + wide_ns - (ns + wide_ns) * (1024u - fill) * f.idle / (1024u * 100u); }
     uint64_t full_rounds(uint64_t len)  // no more than it takes
     {
         call.count(len, f.wshift);
@@ -398,7 +401,7 @@ struct FormCost {
         const uint64_t quarter = f.side_by_side / 4u, q = taken <= quarter ? 0u : (taken - 1u) / quarter - 1u;
         uint64_t step = f.step[q];
         if (taken > quarter) step += (f.step[q + 1u] - f.step[q]) * (taken - (q + 1u) * quarter) / quarter;
-        return step + wide_ns;
+        return filled(step);
     }
     uint64_t end_ns() const { return call.recs ? kMergeNs + call.recs * kRecNsNum / kRecNsDen : kFinalNs; }
     // of n runs, len = lengths.of(n), if that is no more than `most`; else at least not less than it costs on average
@@ -435,7 +438,7 @@ struct FormCost {
         };
         for (uint64_t n = most_n(best_len); n; n = lengths.first_n(lengths.of(n)) - 1u) {  // longer and longer ones
             const uint64_t len = lengths.of(n);
-            if (f.call + f.round + ((len + (1u << f.shift) - 1u) >> f.shift) * (f.step[0] + wide_ns) > least) break;
+            if (f.call + f.round + ((len + (1u << f.shift) - 1u) >> f.shift) * filled(f.step[0]) > least) break;
             const uint64_t c = of(n, len, least);
             if (c <= least) {
                 least = c;
@@ -610,10 +613,9 @@ uint64_t lay_out_shared(Plan *plans, uint32_t n_reqs, const Doc *docs, uint32_t 
         uint64_t ns = middle ? ~0ull : other_ns;
         const uint64_t len = FormCost(four, call).best(total > pieces ? total - pieces : 0u, &ns);
         // The form that the workspace is sized by also on an even estimate; k6_attend_shared<4>, whose costs are the least
-        // certain, where it is expected to take a twelfth less: of 180 random calls 33, 0.83 to 1.10 times what four scorers
-        // take, 0.96 on average.
+        // certain, where it is expected to take a sixteenth less: 43 of 213 calls, 0.73 to 1.08 times what four scorers take.
         *form = limit_form;
-        if (other_ns <= (middle ? ns - ns / 12u : ns + ns / 32u)) return total;  // laid out already
+        if (other_ns <= (middle ? ns - ns / 16u : ns + ns / 32u)) return total;  // laid out already
         *form = SharedForm::kRoles4;
         used = lay_out(len);
     }

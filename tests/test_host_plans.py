@@ -226,3 +226,17 @@ def test_later_rounds_of_eight_scorers_count_less(plans_host, shape, taken):
     ((4, 12, [700, 333], [28], 4, 5), ROLES4)])  # 37.0 us, 40.1
 def test_four_scorers_or_four_waves_that_do_both(plans_host, shape, taken):
     assert form(plans_host, *shape)[0] == taken
+
+
+def requests_line(H, G, reqs):
+    """reqs as tests/test_gpu_attend.py lists them."""
+    return "workspace %d %d" % (H, H * G) + "".join(
+        " / %d" % n_q + "".join(" %d*1*%d" % tp for tp in zip(tokens, precs)) for tokens, precs, n_q in reqs)
+
+
+def test_gpu_tests_of_the_forms_take_the_forms_that_they_name(plans_host):
+    import test_gpu_attend as gpu
+    lines = [requests_line(1, 4, gpu.form_call(n_q, *call)) for call in gpu.FORM_CALLS for n_q in gpu.FORM_QUERIES]
+    lines += [requests_line(1, 4, gpu.batch_call(n_q)) for n_q in gpu.FORM_QUERIES]
+    assert [c[3] for c in calls(plans_host, lines)] == \
+        [ROLES4] * 21 + [SHARED2, SHARED2, SHARED4, SHARED4, ROLES8, ROLES8, ROLES8]
