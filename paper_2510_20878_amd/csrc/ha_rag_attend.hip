@@ -352,7 +352,7 @@ uint64_t limit_run(const Limit &f, SharedCall &call, bool in_steps)
 // the chip holds side by side; a round costs what starting and ending a workgroup does, its steps (a workgroup takes a few
 // blocks at a time, all of one document), and for k6_attend_roles<4>, alone on its compute unit, a trip to memory at the start
 // of every document; steps get slower the more workgroups share a compute unit, or the memory and the power there is, and
-// for k6_attend_roles<4> they are quicker with few blocks in them (documents of 60 tokens: half).  A run that is longer
+// for k6_attend_roles they are quicker with few blocks in them (documents of 60 tokens: half).  A run that is longer
 // than the average one costs a third of the difference: its neighbours are done by then.  Every record is 8 KiB that is
 // written, flushed at the kernel's end and read by another launch.  k6_attend_shared<2> and k6_attend_roles<8> were fitted to
 // timings of 142 calls whose runs and forms were set by hand, <4> of both to 79 and 492 timings of random calls, of which they
@@ -370,7 +370,7 @@ constexpr Form kForms[4] = {  // by SharedForm
     {1u, 1u, 4u * kChipCUs, 2000u, 5600u, 0u, {1330u, 2115u, 2120u, 2300u}, 460u, 0u},
     {2u, 2u, 2u * kChipCUs, 7800u, 0u, 0u, {1220u, 2530u, 2710u, 2710u}, 0u, 0u},
     {2u, 3u, kChipCUs, 4700u, 2500u, 300u, {1700u, 2780u, 2780u, 2940u}, 180u, 50u},
-    {3u, 3u, kChipCUs, 2500u, 6100u, 0u, {3050u, 3230u, 3540u, 3960u}, 210u, 0u},
+    {3u, 3u, kChipCUs, 2500u, 6100u, 0u, {3050u, 3230u, 3540u, 3960u}, 210u, 50u},
 };
 constexpr uint64_t kMergeNs = 3740, kRecNsNum = 19, kRecNsDen = 10;  // a merge at all; a record
 // Without a merge: the runs' own end, which divides the rows and finds their place in the output.  1.6 to 3.5 us were missing

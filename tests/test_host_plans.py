@@ -228,6 +228,11 @@ def test_four_scorers_or_four_waves_that_do_both(plans_host, shape, taken):
     assert form(plans_host, *shape)[0] == taken
 
 
+def test_steps_of_few_blocks_count_less_for_eight_scorers_too(plans_host):
+    assert form(plans_host, 5, 7, [304, 144, 600], [96], 4)[0] == ROLES8     # 45.3 us, 49.7 with four scorers
+    assert form(plans_host, 19, 1, [100, 300], [55, 246, 148], 4, 0)[0] == ROLES8  # 46.7 us, 56.9
+
+
 def requests_line(H, G, reqs):
     """reqs as tests/test_gpu_attend.py lists them."""
     return "workspace %d %d" % (H, H * G) + "".join(
