@@ -653,7 +653,8 @@ def run_attend(args, B, wl, torch):
     call_flops = 4.0 * rows * D * H * sum(sum(c[1] for c in rc) for rc in set_chunks[0])
     t_hbm, t_mfma = step_bytes / L / (HBM_PEAK_GBPS * 1e9), call_flops / (MFMA_BF16_PEAK_TFLOPS * 1e12)
     tiles = (n_q * G + 15) // 16
-    kname = "k6_attend_partial" if tiles <= 2 else "k6_attend_shared" if tiles <= 8 else "k6_attend_roles"
+    # which of the two takes 3 to 8 tiles follows from what the library expects each to cost
+    kname = "k6_attend_partial" if tiles <= 2 else "k6_attend_shared or k6_attend_roles" if tiles <= 8 else "k6_attend_roles"
     stored = (R, n_q, T) == (32, 1, 512) and not args.mix
     if t_mfma > t_hbm:
         tf = call_flops / (call_ms * 1e-3) / 1e12

@@ -56,9 +56,8 @@ struct Plan {               // one request
     uint64_t part_floats = 0;  // offset of its records in the workspace
 };
 
-// A run: the blocks one workgroup takes, a range of the request's blocks in list order.  For the
-// shared kernel it may start and end inside a document and span several; for k6_attend_partial
-// it is a piece of one document.
+// A run of the shared kernel: the blocks one workgroup takes, a range of the request's blocks in list order.  It may
+// start and end inside a document and span several.
 struct Run {
     uint32_t doc, first_block;  // first document (index into the request's documents) and block in it
     uint32_t n_docs, end_block; // documents touched; end of the range in the last of them
@@ -76,7 +75,7 @@ uint32_t piece_blocks(const Plan &pl, const Doc &doc, uint32_t *n)
 }
 
 // The run that starts at block `blk` of document `doc` of the request (both moved to the next
-// run's start); false when the request has no block left.  For the shared kernel.
+// run's start); false when the request has no block left.
 bool next_run(const Plan &pl, const Doc *docs, uint32_t &doc, uint32_t &blk, Run *out)
 {
     if (doc >= pl.n_docs) return false;
@@ -584,8 +583,9 @@ uint64_t lay_out_shared(Plan *plans, uint32_t n_reqs, const Doc *docs, uint32_t 
     if (!call.all) return total;
 
     // The forms: four scorers (up to 8 tiles a workgroup) for every call; eight where a request has more
-    // tiles, which then decodes every block once less; and k6_attend_shared, whose four workgroups on a compute unit all
-    // decode and score in turn, for requests of up to four tiles, where half of four scorers would have none.  Measured, us
+    // tiles, which then decodes every block once less; and k6_attend_shared, whose workgroups on a compute unit (four of two
+    // waves, two of four) all decode and score in turn, for requests of up to four tiles, where half of four scorers would have
+    // none, and of five to eight (see there).  Measured, us
     // a layer, k6_attend_shared / four scorers / eight: 12 query tokens, 8 requests x 4 x 512 tokens 23.9 / 23.0, 32 x 10 x
     // 512 109 / 136, 12 ragged requests in the paper's formats 42 / 53; 64 query tokens, 2 x 4 x 512 - / 23.1 / 26.5, 16 x
     // 4 x 512 - / 72.9 / 60.7, 32 x 10 x 512 - / 288 / 205.

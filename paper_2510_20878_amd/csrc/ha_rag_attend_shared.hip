@@ -824,7 +824,7 @@ __global__ void __launch_bounds__(64 * W, 2) k6_attend_shared(const K6Params p)
 // pairs at a time all measured the same or worse.
 // S = 4 against what took these calls before, us a layer: one request of 8 x 512 tokens, 64 query tokens (S = 8): 25.8 -> 22.0;
 // two of 4 x 512: 25.5 -> 21.7; one of 8 x 1,024, 16 query tokens (k6_attend_shared): 26.3 -> 21.2; 32 requests x 5,120 tokens,
-// 32 query tokens (four waves that decoded and scored in turn): 143 -> 140.
+// 32 query tokens (k6_attend_shared<4>): 146 -> 142.
 //
 // S = 8 is bound by the SIMDs' instruction slots and the clock.  32 requests x 5,120 tokens x 64 query tokens
 // x 32 heads (172 GFLOP a layer, one workgroup per CU, one run per request): 215-227 us with eight waves
@@ -835,8 +835,8 @@ __global__ void __launch_bounds__(64 * W, 2) k6_attend_shared(const K6Params p)
 // much: the split into two kinds of waves 10 %; operands read ahead of what hides them 2 %; the maxima
 // after the fact, keys without address arithmetic, codes without conversions and values rounded
 // straight into operands 4 %; the reference lifted above the maximum 3 %; loads issued in the order they are
-// decoded in (before, the compiler waited for all of them at the top of the loop) 2 %.  It runs at the card's power limit:
-// scoring with 32x32x16 MFMAs took 6 % fewer clocks at a clock 5 % lower, 186.5 -> 189.5 us.
+// decoded in (before, the compiler waited for all of them at the top of the loop) 2 %.  Scoring with 32x32x16
+// MFMAs took 6 % fewer clocks at a clock 5 % lower, 186.5 -> 189.5 us, as at a power limit.
 template <int S>
 __global__ void __launch_bounds__(64 * (S + kRoleDecoders), (S + kRoleDecoders) / 4) k6_attend_roles(const K6Params p)
 {
