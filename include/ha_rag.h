@@ -37,8 +37,9 @@
  *    (Sec. 2.2.2, Fig. 7): value = +-field * 2^(G_k - 2), G_k = min(e_lo + 2 + 3k,
  *    e_hi), field = floor(|x| * 2^(2 - G_k)) for the smallest G_k >= exponent(x)
  *    (truncating, as the paper's shift does); e_lo / e_hi are the smallest /
- *    largest exponent of the tile's nonzero values (e_lo raised to e_hi - 47 if
- *    the tile spans more than 48 binades).  Payload like INT8, and each tile
+ *    largest exponent of the tile's nonzero values (BF16 subnormals count as -126,
+ *    the least e_lo there is; e_lo raised to e_hi - 47 if the tile spans more than
+ *    48 binades).  Payload like INT8, and each tile
  *    record ends with 16 bytes {int8 e_lo, int8 e_hi, 14 zero bytes}.
  *  - Packed byte layout of a chunk: tile records (l*2+kv)*H+h back to back; a tile
  *    is cut into blocks of 2048 elements (last one zero padded); payload blocks

@@ -117,8 +117,8 @@ __device__ __forceinline__ Gse8Tab gse8_tab(uint32_t range)
 {
     const int base = (int)(int8_t)(range & 0xFFu), top = (int)(int8_t)((range >> 8) & 0xFFu) - 2;
     const int least = base < top ? base : top;
-    // three significant bits: the upper halves of the binary32 numbers are the BF16 values.  (Subnormal ones can only
-    // be there where least = top: nothing is added to their exponents.)
+    // three significant bits: the upper halves of the binary32 numbers are the BF16 values.  (The format's
+    // e_lo is at least -126, so subnormal ones can only be there where least = top: nothing is added to their exponents.)
     uint32_t w[8];
 #pragma unroll
     for (int f = 0; f < 8; ++f) w[f] = __builtin_bit_cast(uint32_t, __builtin_ldexpf((float)f, least));
