@@ -245,6 +245,16 @@ def test_kernels_of_a_full_chip_at_the_edges_of_rounds_and_tiles(n_q):
     run_case((1, 1, 128), batch_call(n_q), 0, 4, 0.1, 8150 + n_q, spreads=2.0)
 
 
+def long_lists_call(n_q):
+    return [([1] * 150, [ALL[(r + i) % 6] for i in range(150)], n_q) for r in range(4)]
+
+
+@pytest.mark.parametrize("n_q,H", [(9, 256), (33, 64)])
+def test_runs_that_end_at_the_most_documents(n_q, H):
+    """As many heads as make one run a request the shortest call; it ends for its 128 documents, and the requests have two."""
+    run_case((1, H, 128), long_lists_call(n_q), 0, 4 * H, 0.1, 9150 + n_q)
+
+
 FORM_QUERIES = [9, 16, 17, 32, 33, 64, 65]
 FORM_CALLS = [(1, [300, 47, 16, 129]), (48, [40, 16]), (3, [1024])]
 

@@ -245,3 +245,6 @@ def test_gpu_tests_of_the_forms_take_the_forms_that_they_name(plans_host):
     lines += [requests_line(1, 4, gpu.batch_call(n_q)) for n_q in gpu.FORM_QUERIES]
     assert [c[3] for c in calls(plans_host, lines)] == \
         [ROLES4] * 21 + [SHARED2, SHARED2, SHARED4, SHARED4, ROLES8, ROLES8, ROLES8]
+    for n_q, H in ((9, 256), (33, 64)):
+        (rc, need, end, _, _, runs, longest), = calls(plans_host, [requests_line(H, 4, gpu.long_lists_call(n_q))])
+        assert rc == OK and end == need and (runs, longest) == (8, 128)
