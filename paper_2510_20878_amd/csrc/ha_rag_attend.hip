@@ -729,6 +729,39 @@ int plan_attend(ha_rag_ctx *c, const ha_rag_packed_chunk *chunks, const ha_rag_a
 }
 
 
+// Whether k6_attend_partial reads its documents past the last-level cache (what it gives and costs is measured there).  A
+// layer's bytes are asked for again by the next query token, after those of all other layers: beyond the cache's size they
+// are gone by then.  us a pass with ordinary and nontemporal loads, by the bytes of all layers, 10 x 512 tokens a request in 20 /
+// 30 / 50 % of 16, 8 and 4 bits: 122 MB (24 requests, one layer) 53.7 / 64.2, 163 (8, four) 110 / 120, 204 (20, two) 107 / 109, 245 (24, two)
+// 124 / 125, 286 (28, two) 135.5 / 129.7, 326 (32, two) 158.5 / 150.5; 326 (2, 32 layers) 500 / 445.
+// Documents that several requests of the call list come out of the cache for the second of them: with more than a
+// quarter such, of the first kLooked, the loads stay as they are.
+bool read_past_cache(const ha_rag_ctx *c, const Plan *plans, uint32_t n_reqs, const Doc *docs)
+{
+    uint64_t bytes = 0;  // of one layer and head
+    for (uint32_t r = 0; r < n_reqs; ++r) {
+        if (plans[r].shared) continue;
+        const Doc *d = docs + plans[r].first_doc;
+        for (uint32_t i = 0; i < plans[r].n_docs; ++i) bytes += d[i].k_tile + d[i].v_tile;
+    }
+    if (bytes * c->cfg.n_kv_heads <= kLastLevelBytes / c->cfg.n_layers) return false;
+    constexpr uint32_t kLooked = 1024, kBits = 8 * kLooked;
+    uint64_t seen[kBits / 64] = {};  // documents by a hash of where their keys lie
+    uint32_t n = 0, repeated = 0;
+    for (uint32_t r = 0; r < n_reqs && n < kLooked; ++r) {
+        if (plans[r].shared) continue;
+        const Doc *d = docs + plans[r].first_doc;
+        for (uint32_t i = 0; i < plans[r].n_docs && n < kLooked; ++i, ++n) {
+            const uint32_t bit = (uint32_t)(((uint64_t)(uintptr_t)d[i].k >> 4) * 0x9E3779B97F4A7C15ull >> 51);
+            static_assert(kBits == 1u << 13, "what the shift leaves");
+            uint64_t &word = seen[bit >> 6];
+            repeated += (uint32_t)(word >> (bit & 63u) & 1u);
+            word |= 1ull << (bit & 63u);
+        }
+    }
+    return repeated * 4u <= n;
+}
+
 // Storage of one call's plan.  The ordinary entry points size it for the call on the heap; the
 // entry point that allocates nothing keeps a small one on the stack.
 struct PlanStore {
@@ -800,6 +833,8 @@ int attend_locked(ha_rag_ctx *c, PlanStore ps, const ha_rag_packed_chunk *chunks
     };
     // ---- requests of at most two tiles: every run is a piece of one document
     kq.n_runs = 0;
+    kq.past = read_past_cache(c, plans, n_reqs, docs.data);
+    kq.pad = 0;
     auto launch_pieces = [&]() {
         kq.doc_first = kq.doc_end = K6Params::docs_behind(kq.n_runs);
         const hipError_t e = launch_k6(kq, st, dry);

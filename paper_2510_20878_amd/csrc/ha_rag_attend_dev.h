@@ -204,6 +204,14 @@ __device__ __forceinline__ u32x4 ldg16(gbytes p)
     return *(const u32x4 __attribute__((address_space(1))) *)p;
 }
 
+// the same, past the last-level cache if ONCE
+template <bool ONCE>
+__device__ __forceinline__ u32x4 ldg16_of(gbytes p)
+{
+    if (ONCE) return __builtin_nontemporal_load((const u32x4 __attribute__((address_space(1))) *)p);
+    return ldg16(p);
+}
+
 // max of a value over the four lanes l, l ^ 16, l ^ 32, l ^ 48 (one per lane group), in every
 // lane.  The row swaps exchange registers between lane rows without a trip through LDS: after
 // swapping the odd rows of one copy with the even rows of another, the two copies hold the

@@ -40,7 +40,8 @@ struct AttendLds {
 
 // KP, VP: the formats of the chunk's keys and of its values (the same for a chunk stored whole).
 // NARROW: the instance belongs to the kernel that runs three waves per SIMD (168 registers).
-template <uint32_t KP, uint32_t VP, int MTW, bool NARROW>
+// PAST: the packed bytes are read past the last-level cache (see k6_attend_partial).
+template <uint32_t KP, uint32_t VP, int MTW, bool NARROW, bool PAST>
 __device__ __forceinline__ void attend_unit(const AttendHdr &p, const K6Run &c,
                                             uint32_t h, uint32_t mtg, uint8_t *lds_all,
                                             float (*sm)[MTW * 16], float (*sl)[2][MTW * 16],
@@ -112,15 +113,15 @@ __device__ __forceinline__ void attend_unit(const AttendHdr &p, const K6Run &c,
     auto load_block = [&](uint32_t b, BlockRegs<KP, VP> &r) {
 #pragma unroll
         for (uint32_t a = 0; a < FK::kWords; ++a)
-            r.kw[a] = ldg16(kt + ((uint64_t)b * FK::kPayload + a * 1024u + lane * 16u));
+            r.kw[a] = ldg16_of<PAST>(kt + ((uint64_t)b * FK::kPayload + a * 1024u + lane * 16u));
 #pragma unroll
         for (uint32_t a = 0; a < FV::kWords; ++a)
-            r.vw[a] = ldg16(vt + ((uint64_t)b * FV::kPayload + a * 1024u + lane * 16u));
+            r.vw[a] = ldg16_of<PAST>(vt + ((uint64_t)b * FV::kPayload + a * 1024u + lane * 16u));
         r.km = 0;
         r.vm = u32x4{0u, 0u, 0u, 0u};
         if (FK::kMeta)
             r.km = *(const uint32_t __attribute__((address_space(1))) *)(kmeta + ((uint64_t)b * kmeta_blk + 4u * k_entry));
-        if (FV::kMeta) r.vm = ldg16(vmeta + ((uint64_t)b * vmeta_blk + ((lane * 8u) >> vgsh) * 16u));
+        if (FV::kMeta) r.vm = ldg16_of<PAST>(vmeta + ((uint64_t)b * vmeta_blk + ((lane * 8u) >> vgsh) * 16u));
         // Blocks are requested in the order they are worked on, before the loop as in it: the compiler
         // turned the first ones round, and then waited at the top of the loop for all of them.
         __builtin_amdgcn_sched_barrier(0);
@@ -317,27 +318,27 @@ blocks_done:
 // One instance per pair of formats (whole chunks use the six on the diagonal).  The kernel for
 // narrow formats leaves out every pair with a 16-bit side: those need more registers than three
 // waves per SIMD leave.
-template <uint32_t KP, uint32_t VP, int MTW, bool NARROW>
+template <uint32_t KP, uint32_t VP, int MTW, bool NARROW, bool PAST>
 __device__ __forceinline__ void attend_pair(const AttendHdr &hdr, const K6Run &c, uint32_t h,
                                             uint32_t mtg, uint8_t *lds, float (*sm)[MTW * 16],
                                             float (*sl)[2][MTW * 16], float (*sf)[MTW * 16])
 {
     if constexpr (!(NARROW && (KP == kP16 || VP == kP16)))
-        attend_unit<KP, VP, MTW, NARROW>(hdr, c, h, mtg, lds, sm, sl, sf);
+        attend_unit<KP, VP, MTW, NARROW, PAST>(hdr, c, h, mtg, lds, sm, sl, sf);
 }
 
-template <uint32_t KP, int MTW, bool NARROW>
+template <uint32_t KP, int MTW, bool NARROW, bool PAST>
 __device__ __forceinline__ void attend_values(const AttendHdr &hdr, const K6Run &c, uint32_t h,
                                               uint32_t mtg, uint8_t *lds, float (*sm)[MTW * 16],
                                               float (*sl)[2][MTW * 16], float (*sf)[MTW * 16])
 {
     switch ((c.info >> 8) & 0xFu) {
-    case kP16: attend_pair<KP, kP16, MTW, NARROW>(hdr, c, h, mtg, lds, sm, sl, sf); break;
-    case kInt8: attend_pair<KP, kInt8, MTW, NARROW>(hdr, c, h, mtg, lds, sm, sl, sf); break;
-    case kInt4: attend_pair<KP, kInt4, MTW, NARROW>(hdr, c, h, mtg, lds, sm, sl, sf); break;
-    case kE4M3: attend_pair<KP, kE4M3, MTW, NARROW>(hdr, c, h, mtg, lds, sm, sl, sf); break;
-    case kE5M2: attend_pair<KP, kE5M2, MTW, NARROW>(hdr, c, h, mtg, lds, sm, sl, sf); break;
-    default: attend_pair<KP, kGSE8, MTW, NARROW>(hdr, c, h, mtg, lds, sm, sl, sf); break;
+    case kP16: attend_pair<KP, kP16, MTW, NARROW, PAST>(hdr, c, h, mtg, lds, sm, sl, sf); break;
+    case kInt8: attend_pair<KP, kInt8, MTW, NARROW, PAST>(hdr, c, h, mtg, lds, sm, sl, sf); break;
+    case kInt4: attend_pair<KP, kInt4, MTW, NARROW, PAST>(hdr, c, h, mtg, lds, sm, sl, sf); break;
+    case kE4M3: attend_pair<KP, kE4M3, MTW, NARROW, PAST>(hdr, c, h, mtg, lds, sm, sl, sf); break;
+    case kE5M2: attend_pair<KP, kE5M2, MTW, NARROW, PAST>(hdr, c, h, mtg, lds, sm, sl, sf); break;
+    default: attend_pair<KP, kGSE8, MTW, NARROW, PAST>(hdr, c, h, mtg, lds, sm, sl, sf); break;
     }
 }
 
@@ -346,7 +347,13 @@ __device__ __forceinline__ void attend_values(const AttendHdr &hdr, const K6Run 
 // rescale branch, and every pair of formats fits.  Without a 16-bit side one query tile fits
 // in the 168 registers of three waves per SIMD, which measured 10 % faster (the kernel is bound
 // by instruction issue); 16-bit pairs spill there and lose a quarter.
-template <int MTW, bool NARROW>
+//
+// PAST: nontemporal loads of the packed bytes, for calls whose documents the 256 MB last-level cache cannot hold
+// until the next query token asks for them (kLastLevelBytes says when).  What is read is then not put there either, which
+// costs the memory time: 32 requests x 5,120 tokens at one query token, us a layer: 20 / 30 / 50 % of 16, 8 and 4 bits
+// 78.5 -> 74.7, FP8 74.5 -> 65.5, 4 bits unchanged.  A call that it does hold loses by them: 24 requests of that mix, one
+// layer, 54 -> 64; 8 requests, four layers, 27.5 -> 30.  At two query tiles neither way matters.
+template <int MTW, bool NARROW, bool PAST>
 __global__ void __launch_bounds__(64 * kAttendWaves, NARROW ? 3 : 2) k6_attend_partial(const K6Params p)
 {
     __shared__ __attribute__((aligned(16))) uint8_t lds[AttendLds<MTW>::kBytes];
@@ -376,12 +383,12 @@ __global__ void __launch_bounds__(64 * kAttendWaves, NARROW ? 3 : 2) k6_attend_p
     const uint32_t mtg = u % n_mtg;
     const uint32_t h = u / n_mtg;
     switch (c.info & 0xFu) {
-    case kP16: attend_values<kP16, MTW, NARROW>(hdr, c, h, mtg, lds, sm, sl, sf); break;
-    case kInt8: attend_values<kInt8, MTW, NARROW>(hdr, c, h, mtg, lds, sm, sl, sf); break;
-    case kInt4: attend_values<kInt4, MTW, NARROW>(hdr, c, h, mtg, lds, sm, sl, sf); break;
-    case kE4M3: attend_values<kE4M3, MTW, NARROW>(hdr, c, h, mtg, lds, sm, sl, sf); break;
-    case kE5M2: attend_values<kE5M2, MTW, NARROW>(hdr, c, h, mtg, lds, sm, sl, sf); break;
-    default: attend_values<kGSE8, MTW, NARROW>(hdr, c, h, mtg, lds, sm, sl, sf); break;
+    case kP16: attend_values<kP16, MTW, NARROW, PAST>(hdr, c, h, mtg, lds, sm, sl, sf); break;
+    case kInt8: attend_values<kInt8, MTW, NARROW, PAST>(hdr, c, h, mtg, lds, sm, sl, sf); break;
+    case kInt4: attend_values<kInt4, MTW, NARROW, PAST>(hdr, c, h, mtg, lds, sm, sl, sf); break;
+    case kE4M3: attend_values<kE4M3, MTW, NARROW, PAST>(hdr, c, h, mtg, lds, sm, sl, sf); break;
+    case kE5M2: attend_values<kE5M2, MTW, NARROW, PAST>(hdr, c, h, mtg, lds, sm, sl, sf); break;
+    default: attend_values<kGSE8, MTW, NARROW, PAST>(hdr, c, h, mtg, lds, sm, sl, sf); break;
     }
 }
 
@@ -448,9 +455,11 @@ hipError_t launch_k6(K6Params &p, hipStream_t stream, bool check_only)
     if (width > 0x7FFFFFFFull) return hipErrorInvalidValue;
     if (check_only) return hipSuccess;
     dim3 grid((uint32_t)width, p.n_runs), block(64 * kAttendWaves);
-    if (p.mtw == 2) return launch_args(k6_attend_partial<2, false>, grid, block, 0, stream, p);
-    if (narrow) return launch_args(k6_attend_partial<1, true>, grid, block, 0, stream, p);
-    return launch_args(k6_attend_partial<1, false>, grid, block, 0, stream, p);
+    if (p.mtw == 2) return launch_args(k6_attend_partial<2, false, false>, grid, block, 0, stream, p);
+    if (p.past && narrow) return launch_args(k6_attend_partial<1, true, true>, grid, block, 0, stream, p);
+    if (p.past) return launch_args(k6_attend_partial<1, false, true>, grid, block, 0, stream, p);
+    if (narrow) return launch_args(k6_attend_partial<1, true, false>, grid, block, 0, stream, p);
+    return launch_args(k6_attend_partial<1, false, false>, grid, block, 0, stream, p);
 }
 
 // ---------------------------------------------------------------------------

@@ -114,6 +114,7 @@ constexpr uint32_t kAttendMaxRunBlocks = 128;  // and a piece of one document is
 constexpr uint32_t kAttendTargetGroups = 2048; // pieces are halved while a launch has fewer workgroups
 constexpr uint32_t kAttendFewDocs = 32;       // run lengths of the shared kernel: the longest run is looked for in a request of at most this many documents
 constexpr uint32_t kChipCUs = 256;            // compute units of the one GPU this library is built for
+constexpr uint64_t kLastLevelBytes = 256ull << 20;  // its last-level cache
 constexpr uint32_t kAttendWaves = 2;          // waves of a workgroup; they interleave its blocks
 // Descriptors travel in the kernel argument buffer (36 KiB; launches with arguments of up to
 // 62.5 KiB were checked to work on this runtime).  A workgroup fetches its run's descriptor in one go
@@ -162,6 +163,7 @@ struct K6Params {
     float scale_log2;      // sm_scale * log2(e)
     uint32_t doc_first;    // the runs' further documents: doc[doc_first .. doc_end), behind the runs
     uint32_t doc_end;
+    uint32_t past, pad;    // launch_k6: the packed bytes are read past the last-level cache
     union {                // two views of the same bytes
         K6Run run[kAttendMaxRuns];
         K6Doc doc[kAttendMaxDocs];

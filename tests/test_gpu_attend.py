@@ -656,6 +656,43 @@ def test_every_pair_of_formats_as_documents_of_one_request(with_16_bit):
     ctx.destroy()
 
 
+@pytest.mark.parametrize("with_16_bit", [True, False])
+def test_documents_that_the_last_level_cache_does_not_hold(with_16_bit):
+    """A call whose documents take more than 256 MiB over all layers reads them with other loads
+    (read_past_cache): the same bytes, so the same results, to the bit, as through a context of one layer."""
+    L, H, D, g, n_qh, scale = 1500, 1, 128, 64, 4, 0.1
+    ORC = [16, 8, 4, 43, 52, 143]
+    precs = range(6) if with_16_bit else range(1, 6)
+    many = B.Context(L, H, D, 64, group_int8=g, group_int4=g)
+    one = B.Context(1, H, D, 64, group_int8=g, group_int4=g)
+    grp = lambda p: g if p in (B.PREC_INT8, B.PREC_INT4) else 0
+    units, total = [], 0
+    for i, (kp, vp) in enumerate((a, b) for a in precs for b in precs):
+        T = 9 + (7 * i) % 40                                     # ragged, one to three blocks
+        src = wl.kv_chunk(1, H, D, T, 940 + i)
+        for part, prec in ((B.PART_K, kp), (B.PART_V, vp)):
+            pk = codec.quantize_pack_half(np.ascontiguousarray(src[:, part - 1]), ORC[prec], g)[0]
+            buf = torch.zeros(many.chunk_bytes(prec, T, part=part), dtype=torch.uint8, device="cuda")
+            buf[:len(pk)] = dev_u8(pk)                           # layer 0
+            total += buf.numel()
+            units.append((buf, T, prec, grp(prec), part))
+    assert total > 256 << 20
+    q_d = torch.from_numpy(q_words(1, n_qh, D, 991).view(np.int16)).cuda()
+    results = []
+    for ctx in (one, many):
+        out_d = torch.full((1, n_qh, D), float("nan"), dtype=torch.float32, device="cuda")
+        lse_d = torch.full((1, n_qh), float("nan"), dtype=torch.float32, device="cuda")
+        call = [(units, q_d, out_d, lse_d, 1)]
+        nb = ctx.attend_workspace_bytes(call, n_qh)
+        ws = torch.full((nb // 4,), float("nan"), dtype=torch.float32, device="cuda")
+        ctx.attend_packed(call, 0, n_qh, scale, ws, nb)
+        torch.cuda.synchronize()
+        results.append((out_d.cpu(), lse_d.cpu()))
+        ctx.destroy()
+    assert torch.isfinite(results[0][0]).all() and torch.isfinite(results[0][1]).all()
+    assert torch.equal(results[0][0], results[1][0]) and torch.equal(results[0][1], results[1][1])
+
+
 def test_the_most_query_tokens_and_the_widest_head_group_one_call_takes():
     # 4096 query tokens of one head group member (4096 query rows = 256 tiles over one chunk)
     run_case((1, 1, 128), [([48], [B.PREC_INT4], 4096)], 0, 1, 0.1, 810)
