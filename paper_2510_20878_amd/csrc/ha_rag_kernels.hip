@@ -622,6 +622,7 @@ __global__ void __launch_bounds__(256) k2_pack_fp8(const K2Params p)
 // and all arithmetic is 16-bit integer work on both BF16 words of a dword at once (packed
 // 16-bit instructions): about half the instructions of an element-by-element version.
 typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
 __device__ __forceinline__ u16x2 splat16(uint32_t v)
 {
@@ -633,40 +634,51 @@ __device__ __forceinline__ u16x2 splat16(uint32_t v)
 // in vector registers so that masking and setting a bit is one instruction.
 struct Gse8Enc {
     u16x2 lo, lo7, hi5;
+    u16x2 lo43;  // -43 lo
+    u16x2 eight;
     uint32_t low7, lead;
 };
 
+// How a tile's values are encoded (uniform).  kPlain: every value is a normal number within the tile's
+// 16 shared exponents, none is zero.  kFewLow: no exponent the tile shares lies near the bottom of the format
+// (biased e_lo >= 4), so zeros and subnormals, whose leading one is not there, are shifted out whether or not it is set.
+enum Gse8Mode { kPlain, kFewLow, kGeneral };
+
 // Index and field (no sign) of the two BF16 words of a dword, one code per 16-bit half.
-// FEW_LOW: no exponent the tile shares lies near the bottom of the format (biased e_lo >= 4), so
-// zeros and subnormals, whose leading one is not there, are shifted out whether or not it is set.
-template <bool FEW_LOW>
+template <Gse8Mode MODE>
 __device__ __forceinline__ u16x2 gse8_encode_pair(uint32_t r, const Gse8Enc &c)
 {
     const uint32_t magw = r & 0x7FFF7FFFu;
     const u16x2 mag = __builtin_bit_cast(u16x2, magw);
     u16x2 eb = mag >> splat16(7);
-    if (!FEW_LOW) eb = __builtin_elementwise_max(eb, splat16(1));               // subnormal: 1
-    const u16x2 rel = __builtin_elementwise_sub_sat(eb, c.lo);                  // exponent above e_lo, at most 47
-    const u16x2 k = (rel * splat16(43)) >> splat16(7);                          // rel / 3
+    u16x2 k;  // rel / 3, rel the exponent above e_lo, at most 47
+    if (MODE == kPlain) {
+        k = (u16x2)(eb * splat16(43) + c.lo43) >> splat16(7);
+    } else {
+        if (MODE == kGeneral) eb = __builtin_elementwise_max(eb, splat16(1));  // subnormal: 1
+        const u16x2 rel = __builtin_elementwise_sub_sat(eb, c.lo);
+        k = (rel * splat16(43)) >> splat16(7);
+    }
     // G + 5, G the k-th shared exponent min(e_lo + 2 + 3k, e_hi)
     const u16x2 g5 = __builtin_elementwise_min(k * splat16(3) + c.lo7, c.hi5);
     // significand with its leading one (none for subnormals) as an 8-bit integer: |x| =
     // sig / 128 * 2^(eb - 127), so floor(|x| * 2^(2 - G)) = sig >> (G - eb + 5); G >= eb always.
-    u16x2 sig = __builtin_bit_cast(u16x2, (magw & c.low7) | c.lead);
+    u16x2 sig = __builtin_bit_cast(u16x2, (r & c.low7) | c.lead);
     // min(mag, that) is that integer also without a leading one: a normal value is at least 0x80
-    if (!FEW_LOW) sig = __builtin_elementwise_min(mag, sig);
-    const u16x2 sh = __builtin_elementwise_min(g5 - eb, splat16(15));
+    if (MODE == kGeneral) sig = __builtin_elementwise_min(mag, __builtin_bit_cast(u16x2, (magw & c.low7) | c.lead));
+    u16x2 sh = g5 - eb;  // 5, 6 or 7 for a value that is not below e_lo
+    if (MODE != kPlain) sh = __builtin_elementwise_min(sh, splat16(15));
     // A zero field is stored with index 0, and has it: in an unclipped group the shift is 5, 6 or 7,
     // which leaves a field of at least 1, so a zero field means an exponent at or below e_lo.
-    return k * splat16(8) + (sig >> sh);
+    return k * c.eight + (sig >> sh);
 }
 
 // the four codes of two dwords, signs included (bit 7 of each from bit 15 of its word)
-template <bool FEW_LOW>
+template <Gse8Mode MODE>
 __device__ __forceinline__ uint32_t gse8_encode_quad(uint32_t r0, uint32_t r1, const Gse8Enc &c)
 {
-    const uint32_t c01 = __builtin_bit_cast(uint32_t, gse8_encode_pair<FEW_LOW>(r0, c));
-    const uint32_t c23 = __builtin_bit_cast(uint32_t, gse8_encode_pair<FEW_LOW>(r1, c));
+    const uint32_t c01 = __builtin_bit_cast(uint32_t, gse8_encode_pair<MODE>(r0, c));
+    const uint32_t c23 = __builtin_bit_cast(uint32_t, gse8_encode_pair<MODE>(r1, c));
     return (__builtin_amdgcn_perm(r1, r0, 0x07050301u) & 0x80808080u) | __builtin_amdgcn_perm(c23, c01, 0x06040200u);
 }
 
@@ -691,12 +703,109 @@ __device__ __forceinline__ uint32_t pk_max_wave(uint32_t v)
     return v;
 }
 
-// Bound: memory once the encoding is 15 packed instructions per two values (it was 26: the index of
-// a zero field needs no masking, the signs of four codes are merged at once, and constants sit
-// in registers).  Seven ragged chunks of 2,351 tokens in all (462 MB read and written), the same ones again and
-// again: 122 -> 99 us; with loads and stores that bypass the caches, 86 us = 5.4 TB/s (five chunks of 512 tokens
-// that no cache holds: 105 us, 97 with the shorter encode, 90).  Eight or four waves per tile with more
-// blocks each measured the same.
+// The range follows from the largest magnitude and the smallest nonzero one (the exponent
+// is monotonic in the magnitude word).  ZEROS: mag - 1 wraps a zero to 0xFFFF, so zeros drop out of
+// the minimum of mag - 1; without, the minimum is that of mag, one instruction in four less, and says
+// whether there are any.
+template <bool ZEROS>
+__device__ __forceinline__ void gse8_extremes(const u32x4 (&planes)[4], u16x2 &lo2, u16x2 &hi2)
+{
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const u32x4 raw = planes[j];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const uint32_t r = raw[k];  // a copy: bit_cast of the vector element itself reads element 0
+            const u16x2 mag = __builtin_bit_cast(u16x2, r & 0x7FFF7FFFu);
+            lo2 = __builtin_elementwise_min(lo2, ZEROS ? (u16x2)(mag - splat16(1)) : mag);
+            hi2 = __builtin_elementwise_max(hi2, mag);
+        }
+        __builtin_amdgcn_sched_barrier(0);  // registers: one plane after the other
+    }
+}
+
+// Both extremes of a wave as maxima, one in each half: the complement of the smallest magnitude
+// (gse8_extremes<false>) or of the smallest nonzero one - 1 (<true>), and the largest magnitude.
+__device__ __forceinline__ uint32_t gse8_wave_range(u16x2 lo2, u16x2 hi2)
+{
+    const uint32_t lo_pair = __builtin_bit_cast(uint32_t, lo2), hi_pair = __builtin_bit_cast(uint32_t, hi2);
+    const uint32_t min_own = (lo_pair & 0xFFFFu) < (lo_pair >> 16) ? (lo_pair & 0xFFFFu) : (lo_pair >> 16);
+    const uint32_t max_own = (hi_pair & 0xFFFFu) > (hi_pair >> 16) ? (hi_pair & 0xFFFFu) : (hi_pair >> 16);
+    return pk_max_wave((min_own ^ 0xFFFFu) | (max_own << 16));
+}
+
+struct Gse8Range {
+    uint32_t lo, hi;  // biased exponents
+    Gse8Mode mode;
+};
+
+// What the waves of a tile left, over all of them: .x as gse8_wave_range gives it after gse8_extremes<true>, .y whether
+// there are zeros.
+__device__ __forceinline__ Gse8Range gse8_tile_range(const u32x2 *waves, uint32_t n_waves)
+{
+    uint32_t range = waves[0].x, zeros = waves[0].y;
+    for (uint32_t w = 1; w < n_waves; ++w) {
+        const u32x2 v = waves[w];
+        const uint32_t vx = v.x;
+        range = __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(u16x2, range), __builtin_bit_cast(u16x2, vx)));
+        zeros |= v.y;
+    }
+    const uint32_t min_m1 = __builtin_amdgcn_readfirstlane((range & 0xFFFFu) ^ 0xFFFFu);
+    const uint32_t max_m = __builtin_amdgcn_readfirstlane(range >> 16);
+    zeros = __builtin_amdgcn_readfirstlane(zeros);
+    // magnitudes -> biased exponents (a subnormal counts as 1; no nonzero value: 0xFFFF)
+    Gse8Range r;
+    r.lo = min_m1 == 0xFFFFu ? 0xFFFFu : ((min_m1 + 1u) >> 7 ? (min_m1 + 1u) >> 7 : 1u);
+    r.hi = max_m >> 7 ? max_m >> 7 : 1u;
+    const bool clipped = r.lo + 47u < r.hi;  // 16 shared exponents, 3 apart, reach 48 binades
+    if (r.lo > r.hi) r.lo = r.hi = 127;      // all zero: range (e_lo, e_hi) = (0, 0)
+    if (clipped) r.lo = r.hi - 47;
+    r.mode = !zeros && !clipped && min_m1 + 1u >= 0x80u ? kPlain : r.lo >= 4u ? kFewLow : kGeneral;
+    return r;
+}
+
+__device__ __forceinline__ Gse8Enc gse8_enc(const Gse8Range &r)
+{
+    Gse8Enc enc = {splat16(r.lo), splat16(r.lo + 7u), splat16(r.hi + 5u), splat16(0u - 43u * r.lo), splat16(8u), 0x007F007Fu, 0x00800080u};
+    uint32_t eight = 0x00080008u;  // unknown to the compiler, which would make a shift and an addition of the multiply-add
+    asm("" : "+v"(enc.low7), "+v"(enc.lead), "+s"(eight));
+    enc.eight = __builtin_bit_cast(u16x2, eight);
+    return enc;
+}
+
+// Lanes past the tile's end hold zeros, whose codes are zero bytes, as the padding is.
+template <Gse8Mode MODE>
+__device__ __forceinline__ void gse8_encode_block(const u32x4 (&planes)[4], uint8_t *out, uint32_t lane, const Gse8Enc &enc)
+{
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        uint32_t code[2][2];
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const u32x4 raw = planes[2 * h + j];
+#pragma unroll
+            for (int d = 0; d < 2; ++d)  // four elements -> one dword of codes
+                code[j][d] = gse8_encode_quad<MODE>(raw[2 * d], raw[2 * d + 1], enc);
+        }
+        st16<true>(out + (1024u * h + lane * 16u), u32x4{code[0][0], code[0][1], code[1][0], code[1][1]});
+        __builtin_amdgcn_sched_barrier(0);  // registers: one half after the other
+    }
+}
+
+// the block behind a tile's payload
+__device__ __forceinline__ void gse8_store_range(uint8_t *dst, const Gse8Range &r)
+{
+    const uint32_t e_lo = (r.lo - 127u) & 0xFFu, e_hi = (r.hi - 127u) & 0xFFu;
+    st16<true>(dst, u32x4{e_lo | (e_hi << 8), 0, 0, 0});
+}
+
+// Bound: memory and its latency (two workgroups of 16 waves a compute unit load, reduce and encode a tile each, in
+// phases): 5.8 TB/s over chunks of one length.  Seven ragged chunks of 2,351 tokens in all (462 MB read and written),
+// the same ones again and again: 122 -> 99 us with 15 instead of 26 packed instructions per two values; with loads and
+// stores that bypass the caches, 86 us = 5.4 TB/s.  Tiles of normal numbers, kPlain, take 12 (and 3 instead of 4 for the
+// range): four chunks of 1,024 tokens 161.1 -> 156.8, of 600 and 540 97.3 -> 93.4, one of 512 18.2 -> 17.7.  Eight or four waves per tile
+// with more blocks each measured the same; a workgroup that loads its next tile while it encodes one (16 waves a compute
+// unit then) 87.9 against 86.4 us for five chunks of 512 tokens, 83 against 74 for ten of 250 and 201.
 //
 // HELD: blocks of the tile that every wave keeps in registers between the two passes (the
 // tile is then read once); 0: the tile is longer than 16 waves can hold and pass 2 reads it
@@ -704,13 +813,13 @@ __device__ __forceinline__ uint32_t pk_max_wave(uint32_t v)
 template <int HELD>
 __global__ void __launch_bounds__(1024) k2_pack_gse8(const K2Params p)
 {
-    __shared__ uint32_t s_range[16];
+    __shared__ u32x2 s_range[16];
     const K2Chunk c = p.c[blockIdx.y];
     const uint8_t *__restrict__ src = c.src;
     uint8_t *__restrict__ dst = c.dst;
     const uint32_t n_e = c.n_tokens * p.head_dim;
     const uint32_t nblk = (n_e + kBlockElems - 1) / kBlockElems;
-    const uint32_t wave = threadIdx.x >> 6, lane = threadIdx.x & 63u;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63u;
     const uint32_t n_waves = blockDim.x >> 6;
     const uint32_t tile = blockIdx.x;
     const uint8_t *in = src + (uint64_t)tile * n_e * 2u;
@@ -720,7 +829,7 @@ __global__ void __launch_bounds__(1024) k2_pack_gse8(const K2Params p)
 
     // all four loads of a block are issued before the first use: a lane past the tile's end
     // re-reads the tile's first words, which changes neither extreme of the range
-    auto load_block = [&](uint32_t blk, u32x4 *planes) {
+    auto load_block = [&](uint32_t blk, u32x4 (&planes)[4]) {
         const uint32_t e = blk * kBlockElems + lane * 8;
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
@@ -728,93 +837,65 @@ __global__ void __launch_bounds__(1024) k2_pack_gse8(const K2Params p)
             planes[j] = ld16s<(HELD > 0)>(in + (uint64_t)(ej < n_e ? ej : 0u) * 2u);  // read once, unless the tile is read twice
         }
     };
-    // The range follows from the largest magnitude and the smallest nonzero one (the exponent
-    // is monotonic in the magnitude word).  mag - 1 wraps a zero to 0xFFFF, so zeros drop out of
-    // the minimum; a tile without nonzero values ends with lo > hi.
     u16x2 lo2 = splat16(0xFFFFu), hi2 = splat16(0);
-    auto range_block = [&](const u32x4 *planes) {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const u32x4 raw = planes[j];
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const uint32_t r = raw[k];  // a copy: bit_cast of the vector element itself reads element 0
-                const u16x2 mag = __builtin_bit_cast(u16x2, r & 0x7FFF7FFFu);
-                lo2 = __builtin_elementwise_min(lo2, (u16x2)(mag - splat16(1)));
-                hi2 = __builtin_elementwise_max(hi2, mag);
-            }
-        }
-    };
+    u32x2 own = {0u, 0u};
     if (HELD > 0) {
 #pragma unroll
         for (int i = 0; i < kHold; ++i)  // every wave's loads are all in flight together
             if (wave + i * n_waves < nblk) load_block(wave + i * n_waves, held[i]);
 #pragma unroll
         for (int i = 0; i < kHold; ++i)
-            if (wave + i * n_waves < nblk) range_block(held[i]);
+            if (wave + i * n_waves < nblk) gse8_extremes<false>(held[i], lo2, hi2);
+        own.x = gse8_wave_range(lo2, hi2);
+        if ((own.x & 0xFFFFu) == 0xFFFFu) {  // the wave holds zeros: again without them
+            lo2 = splat16(0xFFFFu);
+#pragma unroll
+            for (int i = 0; i < kHold; ++i)
+                if (wave + i * n_waves < nblk) gse8_extremes<true>(held[i], lo2, hi2);
+            own.x = gse8_wave_range(lo2, hi2);
+            own.y = 1u;
+        } else if (wave < nblk) {
+            own.x += 1u;  // the complement of the smallest magnitude - 1
+        }
     } else {
         for (uint32_t blk = wave; blk < nblk; blk += n_waves) {
             load_block(blk, held[0]);
-            range_block(held[0]);
+            gse8_extremes<true>(held[0], lo2, hi2);
         }
+        own = u32x2{gse8_wave_range(lo2, hi2), 1u};
     }
-    // both extremes as maxima, one in each half: the complement of the smallest nonzero magnitude - 1,
-    // and the largest magnitude
-    const uint32_t lo_pair = __builtin_bit_cast(uint32_t, lo2), hi_pair = __builtin_bit_cast(uint32_t, hi2);
-    const uint32_t min_own = (lo_pair & 0xFFFFu) < (lo_pair >> 16) ? (lo_pair & 0xFFFFu) : (lo_pair >> 16);
-    const uint32_t max_own = (hi_pair & 0xFFFFu) > (hi_pair >> 16) ? (hi_pair & 0xFFFFu) : (hi_pair >> 16);
-    uint32_t range = pk_max_wave((min_own ^ 0xFFFFu) | (max_own << 16));
-    if (lane == 0) s_range[wave] = range;
+    if (lane == 0) s_range[wave] = own;
     __syncthreads();
-    range = s_range[0];
-    for (uint32_t w = 1; w < n_waves; ++w)
-        range = __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(u16x2, range), __builtin_bit_cast(u16x2, s_range[w])));
-    const uint32_t min_m1 = __builtin_amdgcn_readfirstlane((range & 0xFFFFu) ^ 0xFFFFu);
-    const uint32_t max_m = __builtin_amdgcn_readfirstlane(range >> 16);
-    // magnitudes -> biased exponents (a subnormal counts as 1; no nonzero value: 0xFFFF)
-    uint32_t lo = min_m1 == 0xFFFFu ? 0xFFFFu : ((min_m1 + 1u) >> 7 ? (min_m1 + 1u) >> 7 : 1u);
-    uint32_t hi = max_m >> 7 ? max_m >> 7 : 1u;
-    if (lo > hi) lo = hi = 127;          // all zero: range (e_lo, e_hi) = (0, 0)
-    if (lo + 47 < hi) lo = hi - 47;      // 16 shared exponents, 3 apart, reach 48 binades
-
-    Gse8Enc enc = {splat16(lo), splat16(lo + 7u), splat16(hi + 5u), 0x007F007Fu, 0x00800080u};
-    asm("" : "+v"(enc.low7), "+v"(enc.lead));
-    auto encode_block = [&](auto few_low, uint32_t blk, const u32x4 *planes) {
-        constexpr bool kFewLow = decltype(few_low)::value;
-        const uint32_t e = blk * kBlockElems + lane * 8;
-        uint32_t code[4][2];
+    const Gse8Range r = gse8_tile_range(s_range, n_waves);
+    const Gse8Enc enc = gse8_enc(r);
+    auto encode = [&](auto mode, uint32_t blk, u32x4 (&planes)[4]) {
+        constexpr Gse8Mode kMode = decltype(mode)::value;
+        uint8_t *out = rec + (uint64_t)blk * 2048u;
+        const bool ragged = blk * kBlockElems + kBlockElems > n_e;
+        if (ragged) {  // the padding behind the tile's end is zero bytes: the codes of zeros
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const u32x4 raw = planes[j];
-            const bool live = e + j * 512 < n_e;  // the padding behind the tile's end is zero bytes
-#pragma unroll
-            for (int d = 0; d < 2; ++d) {  // four elements -> one dword of codes
-                const uint32_t quad = gse8_encode_quad<kFewLow>(raw[2 * d], raw[2 * d + 1], enc);
-                code[j][d] = live ? quad : 0u;
-            }
+            for (int j = 0; j < 4; ++j)
+                if (blk * kBlockElems + lane * 8 + j * 512 >= n_e) planes[j] = u32x4{0u, 0u, 0u, 0u};
         }
-        uint8_t *o = rec + (uint64_t)blk * 2048u + lane * 16u;
-        st16<true>(o, u32x4{code[0][0], code[0][1], code[1][0], code[1][1]});
-        st16<true>(o + 1024, u32x4{code[2][0], code[2][1], code[3][0], code[3][1]});
+        if (kMode == kPlain && ragged) gse8_encode_block<kGeneral>(planes, out, lane, enc);
+        else gse8_encode_block<kMode>(planes, out, lane, enc);
     };
-    auto encode_all = [&](auto few_low) {
+    auto encode_all = [&](auto mode) {
         if (HELD > 0) {
 #pragma unroll
             for (int i = 0; i < kHold; ++i)
-                if (wave + i * n_waves < nblk) encode_block(few_low, wave + i * n_waves, held[i]);
+                if (wave + i * n_waves < nblk) encode(mode, wave + i * n_waves, held[i]);
         } else {
             for (uint32_t blk = wave; blk < nblk; blk += n_waves) {
                 load_block(blk, held[0]);
-                encode_block(few_low, blk, held[0]);
+                encode(mode, blk, held[0]);
             }
         }
     };
-    if (lo >= 4u) encode_all(std::true_type{});
-    else encode_all(std::false_type{});
-    if (threadIdx.x == 0) {
-        const uint32_t e_lo = (lo - 127u) & 0xFFu, e_hi = (hi - 127u) & 0xFFu;
-        st16<true>(rec + (uint64_t)nblk * 2048u, u32x4{e_lo | (e_hi << 8), 0, 0, 0});
-    }
+    if (HELD > 0 && r.mode == kPlain) encode_all(std::integral_constant<Gse8Mode, kPlain>{});
+    else if (r.lo >= 4u) encode_all(std::integral_constant<Gse8Mode, kFewLow>{});
+    else encode_all(std::integral_constant<Gse8Mode, kGeneral>{});
+    if (threadIdx.x == 0) gse8_store_range(rec + (uint64_t)nblk * 2048u, r);
 }
 
 template <int BITS>

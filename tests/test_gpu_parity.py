@@ -438,6 +438,24 @@ def test_gse8_decode_every_code(e_lo, e_hi):
     ctx.destroy()
 
 
+@pytest.mark.parametrize("T", [33, 256, 300, 700, 1030])
+def test_gse8_tiles_of_normal_numbers_and_one_value_that_is_none(T):
+    """The encoder's shortest form takes tiles whose values are all normal and within 48 binades; one zero, one
+    subnormal or one value far below the others, in the tile's first, a middle or its last word, takes the tile out of it.
+    T: one to four blocks a wave and the form that reads a tile twice, each with a ragged last block or without."""
+    rng = np.random.Generator(np.random.PCG64(T))
+    n, odd = T * 128, [None, 0x0000, 0x8000, 0x0001, 0x807F, 0x1000, 0x2F80, 0x2800]
+    tiles = []
+    for i, word in enumerate(odd):
+        e = rng.integers(87 if i % 2 else 120, 135, n)             # biased exponents: 48 binades or few
+        w = (rng.integers(0, 2, n) << 15 | e << 7 | rng.integers(0, 128, n)).astype(np.uint16)
+        w[n // 3] = 134 << 7                                       # the top one is there
+        if word is not None:
+            w[(0, n // 2, n - 1)[i % 3]] = word
+        tiles.append(w)
+    _gse_roundtrip(np.stack(tiles).reshape(2, 2, 2, T, 128), T)
+
+
 @pytest.mark.parametrize("shape", [(2, 2, 64, 128), (1, 2, 128, 100), (1, 1, 128, 1), (2, 1, 96, 40),
                                    (1, 2, 128, 272)])
 def test_gse8_shapes(shape):
