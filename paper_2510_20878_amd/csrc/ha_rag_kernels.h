@@ -86,7 +86,8 @@ hipError_t launch_k1(K1Params &p, const K1Launch &cfg, hipStream_t stream);
 struct K2Chunk {
     const uint8_t *src;
     uint8_t *dst;
-    uint32_t n_tokens, pad;
+    uint32_t n_tokens;
+    uint32_t share;          // GSE-8: how its tiles share workgroups (share_gse8_tiles)
 };
 constexpr uint32_t kMaxK2Chunks = 128;
 struct K2Params {
@@ -95,6 +96,13 @@ struct K2Params {
     K2Chunk c[kMaxK2Chunks];
 };
 hipError_t launch_k2(const K2Params &p, uint32_t prec, uint32_t group, hipStream_t stream);
+
+// A launch of k2_pack_gse8 whose longest tile has max_blk blocks: waves of a workgroup, and the blocks a wave holds in
+// registers between the two passes (tiles of up to 1,024 tokens x 128 dims; longer ones, 0, are read twice).
+inline uint32_t gse8_wg_waves(uint32_t max_blk) { return max_blk < 16u ? max_blk : 16u; }
+inline uint32_t gse8_held(uint32_t max_blk) { return max_blk <= 16u ? 1u : max_blk <= 32u ? 2u : max_blk <= 64u ? 4u : 0u; }
+// Fills K2Chunk::share for such a launch; before launch_k2.
+void share_gse8_tiles(K2Params &p);
 
 // Adds to *sum_sq (device, binary64) the squared error between src (BF16 [n_tiles][n_tokens][D])
 // and what `packed` decodes to.

@@ -818,10 +818,16 @@ __global__ void __launch_bounds__(1024) k2_pack_gse8(const K2Params p)
     const uint8_t *__restrict__ src = c.src;
     uint8_t *__restrict__ dst = c.dst;
     const uint32_t n_e = c.n_tokens * p.head_dim;
-    const uint32_t nblk = (n_e + kBlockElems - 1) / kBlockElems;
-    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63u;
-    const uint32_t n_waves = blockDim.x >> 6;
-    const uint32_t tile = blockIdx.x;
+    const uint32_t blocks = (n_e + kBlockElems - 1) / kBlockElems;
+    const uint32_t lane = threadIdx.x & 63u;
+    const uint32_t wg_wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    // n_waves to a tile, this one is number `wave` of its tile's (K2Chunk::share)
+    const uint32_t per_wg = c.share & 0xFFu, n_waves = (c.share >> 8) & 0xFFu;
+    const uint32_t sub = (wg_wave * (c.share >> 16)) >> 8, wave = wg_wave - sub * n_waves;
+    const uint32_t tile = blockIdx.x * per_wg + sub;
+    if (blockIdx.x * per_wg >= p.n_tiles) return;  // the grid is as wide as the chunk of the longest tiles needs
+    const bool alive = sub < per_wg && tile < p.n_tiles;  // the others only reach the barrier
+    const uint32_t nblk = alive ? blocks : 0u;
     const uint8_t *in = src + (uint64_t)tile * n_e * 2u;
     uint8_t *rec = dst + (uint64_t)tile * ((uint64_t)nblk * 2048u + 16u);
     constexpr int kHold = HELD > 0 ? HELD : 1;
@@ -864,9 +870,10 @@ __global__ void __launch_bounds__(1024) k2_pack_gse8(const K2Params p)
         }
         own = u32x2{gse8_wave_range(lo2, hi2), 1u};
     }
-    if (lane == 0) s_range[wave] = own;
+    if (lane == 0) s_range[wg_wave] = own;
     __syncthreads();
-    const Gse8Range r = gse8_tile_range(s_range, n_waves);
+    if (!alive) return;
+    const Gse8Range r = gse8_tile_range(s_range + (wg_wave - wave), n_waves);
     const Gse8Enc enc = gse8_enc(r);
     auto encode = [&](auto mode, uint32_t blk, u32x4 (&planes)[4]) {
         constexpr Gse8Mode kMode = decltype(mode)::value;
@@ -895,7 +902,7 @@ __global__ void __launch_bounds__(1024) k2_pack_gse8(const K2Params p)
     if (HELD > 0 && r.mode == kPlain) encode_all(std::integral_constant<Gse8Mode, kPlain>{});
     else if (r.lo >= 4u) encode_all(std::integral_constant<Gse8Mode, kFewLow>{});
     else encode_all(std::integral_constant<Gse8Mode, kGeneral>{});
-    if (threadIdx.x == 0) gse8_store_range(rec + (uint64_t)nblk * 2048u, r);
+    if (wave == 0 && lane == 0) gse8_store_range(rec + (uint64_t)nblk * 2048u, r);
 }
 
 template <int BITS>
@@ -930,14 +937,15 @@ hipError_t launch_k2(const K2Params &p, uint32_t prec, uint32_t group, hipStream
     while ((1u << gsh) < group) ++gsh;
     dim3 grid((uint32_t)gx, p.n_chunks);
     if (prec == kGSE8) {
-        const uint32_t waves = max_blk < 16u ? max_blk : 16u;
-        const dim3 g2(p.n_tiles, p.n_chunks), b2(waves * 64u);
-        // up to four blocks per wave stay in registers between the passes (tiles of up to 1024
-        // tokens x 128 dims); longer tiles are read twice
-        if (max_blk <= 16u) hipLaunchKernelGGL(k2_pack_gse8<1>, g2, b2, 0, stream, p);
-        else if (max_blk <= 32u) hipLaunchKernelGGL(k2_pack_gse8<2>, g2, b2, 0, stream, p);
-        else if (max_blk <= 64u) hipLaunchKernelGGL(k2_pack_gse8<4>, g2, b2, 0, stream, p);
-        else hipLaunchKernelGGL(k2_pack_gse8<0>, g2, b2, 0, stream, p);
+        for (uint32_t i = 0; i < p.n_chunks; ++i)
+            if (!p.c[i].share) return hipErrorInvalidValue;
+        const dim3 g2(p.n_tiles, p.n_chunks), b2(gse8_wg_waves(max_blk) * 64u);
+        switch (gse8_held(max_blk)) {
+        case 1: hipLaunchKernelGGL(k2_pack_gse8<1>, g2, b2, 0, stream, p); break;
+        case 2: hipLaunchKernelGGL(k2_pack_gse8<2>, g2, b2, 0, stream, p); break;
+        case 4: hipLaunchKernelGGL(k2_pack_gse8<4>, g2, b2, 0, stream, p); break;
+        default: hipLaunchKernelGGL(k2_pack_gse8<0>, g2, b2, 0, stream, p); break;
+        }
     } else if (prec == kE4M3 || prec == kE5M2) {
         if (prec == kE5M2) hipLaunchKernelGGL(k2_pack_fp8<true>, grid, dim3(256), 0, stream, p);
         else hipLaunchKernelGGL(k2_pack_fp8<false>, grid, dim3(256), 0, stream, p);

@@ -456,6 +456,24 @@ def test_gse8_tiles_of_normal_numbers_and_one_value_that_is_none(T):
     _gse_roundtrip(np.stack(tiles).reshape(2, 2, 2, T, 128), T)
 
 
+@pytest.mark.parametrize("tokens", [[16, 9, 100, 256, 33], [512, 1, 129, 250, 16, 300], [700, 20, 1024, 333, 70], [1040, 16, 200]])
+def test_gse8_tiles_of_short_chunks_share_workgroups(tokens):
+    """Launches of more tiles than the chip holds workgroups: tiles of 1, 2, 3, .. waves next to those of 16, a number
+    of tiles that they do not divide (share_gse8_tiles), for 1, 2 and 4 blocks a wave and tiles that are read twice."""
+    L, H, D = 33, 4, 128
+    ctx = B.Context(L, H, D, max(tokens))
+    srcs = [wl.kv_chunk(L, H, D, t, 300 + i) for i, t in enumerate(tokens)]
+    dsrc = [torch.from_numpy(s.view(np.int16)).cuda() for s in srcs]
+    ddst = [torch.full((ctx.chunk_bytes(B.PREC_GSE8, t) + 64,), 0xA5, dtype=torch.uint8, device="cuda") for t in tokens]
+    ctx.quantize_chunks(dsrc, tokens, B.PREC_GSE8, 0, ddst)
+    torch.cuda.synchronize()
+    for s, d in zip(srcs, ddst):
+        ref, _ = codec.quantize_pack_chunk(s, 143)
+        got = d.cpu().numpy()
+        assert np.array_equal(got[:len(ref)], ref) and np.all(got[len(ref):] == 0xA5)
+    ctx.destroy()
+
+
 @pytest.mark.parametrize("shape", [(2, 2, 64, 128), (1, 2, 128, 100), (1, 1, 128, 1), (2, 1, 96, 40),
                                    (1, 2, 128, 272)])
 def test_gse8_shapes(shape):
