@@ -5,6 +5,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include <type_traits>
 
 namespace ha_rag {
 
@@ -67,34 +68,24 @@ __device__ __forceinline__ u32x4 dequant_octet8(uint32_t c0, uint32_t c1, uint32
     return r;
 }
 
-// 8 FP8 codes (two dwords) of one plane -> 8 BF16.  The hardware conversion to fp32 is
-// exact and every FP8 value is a BF16 value, so no rounding conversion is needed.
+// 8 FP8 codes (two dwords) of one plane -> 8 BF16: one conversion per two codes.  Every FP8 value is a BF16 value, so
+// with scale 1 nothing is rounded.  (By way of binary32 and a byte permute of the upper halves, two instructions: 16 requests x
+// 5,120 tokens, two layers, 12 query tokens 105.7 -> 103.0 us, 30 (512- and 300-token documents) 135.2 -> 132.2, one query token
+// of 32 requests 128.5 -> 127.2.)
 template <bool E5M2>
 __device__ __forceinline__ u32x4 decode_octet_fp8(uint32_t c0, uint32_t c1)
 {
-    f32x2 a, b, c, d;
-    if (E5M2) {
-        a = __builtin_amdgcn_cvt_pk_f32_bf8(c0, false);
-        b = __builtin_amdgcn_cvt_pk_f32_bf8(c0, true);
-        c = __builtin_amdgcn_cvt_pk_f32_bf8(c1, false);
-        d = __builtin_amdgcn_cvt_pk_f32_bf8(c1, true);
-    } else {
-        a = __builtin_amdgcn_cvt_pk_f32_fp8(c0, false);
-        b = __builtin_amdgcn_cvt_pk_f32_fp8(c0, true);
-        c = __builtin_amdgcn_cvt_pk_f32_fp8(c1, false);
-        d = __builtin_amdgcn_cvt_pk_f32_fp8(c1, true);
-    }
-    // the upper halves of the binary32 results are the BF16 values: a byte permute per pair
-    // (the elements are copied to scalars first: a bit cast of a vector element reads element 0)
-    auto upper = [](f32x2 v) {
-        const float lo = v.x, hi = v.y;
-        return __builtin_amdgcn_perm(__builtin_bit_cast(uint32_t, hi), __builtin_bit_cast(uint32_t, lo), 0x07060302u);
+    auto two = [](uint32_t c, auto high) -> uint32_t {
+        bf16x2 v;
+        if (E5M2) v = __builtin_amdgcn_cvt_scalef32_pk_bf16_bf8(c, 1.0f, decltype(high)::value);
+        else v = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(c, 1.0f, decltype(high)::value);
+        return __builtin_bit_cast(uint32_t, v);
     };
     u32x4 r;
-    r.x = upper(a);
-    r.y = upper(b);
-    r.z = upper(c);
-    r.w = upper(d);
+    r.x = two(c0, std::false_type{});
+    r.y = two(c0, std::true_type{});
+    r.z = two(c1, std::false_type{});
+    r.w = two(c1, std::true_type{});
     return r;
 }
 
