@@ -834,7 +834,9 @@ int attend_locked(ha_rag_ctx *c, PlanStore ps, const ha_rag_packed_chunk *chunks
     // ---- requests of at most two tiles: every run is a piece of one document
     kq.n_runs = 0;
     kq.past = read_past_cache(c, plans, n_reqs, docs.data);
-    kq.pad = 0;
+    kq.heads_first = 0;
+    for (uint32_t r = 0; r < n_reqs; ++r)  // the call's longest run
+        kq.heads_first |= plans[r].shared && std::min<uint64_t>(plans[r].run_blocks, plans[r].all_blocks) >= kHeadsFirstBlocks;
     auto launch_pieces = [&]() {
         kq.doc_first = kq.doc_end = K6Params::docs_behind(kq.n_runs);
         const hipError_t e = launch_k6(kq, st, dry);

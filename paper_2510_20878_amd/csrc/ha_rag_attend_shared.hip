@@ -835,7 +835,13 @@ __global__ void __launch_bounds__(64 * W, 2) k6_attend_shared(const K6Params p)
 // much: the split into two kinds of waves 10 %; operands read ahead of what hides them 2 %; the maxima
 // after the fact, keys without address arithmetic, codes without conversions and values rounded
 // straight into operands 4 %; the reference lifted above the maximum 3 %; loads issued in the order they are
-// decoded in (before, the compiler waited for all of them at the top of the loop) 2 %.  Scoring with 32x32x16
+// decoded in (before, the compiler waited for all of them at the top of the loop) 2 %.
+// The tile groups of a head read the same blocks.  Numbered one after the other they are dealt to the eight XCDs, each
+// of which fetches the blocks into an L2 of its own; with the heads first (heads_first; 8 KV heads) they meet in one L2.  us for
+// two layers, without / with: two requests of 16 x 1,024 tokens in 16 bits, 256 query tokens, 64 query heads 550 / 516; eight of
+// 10 x 512 and 200 at 90 to 256 486 / 454; three of 16 documents of up to 1,024 at 96 to 201 418 / 404; eight of 4 x 512 at 100
+// 147 / 142.  Short runs lose by it, whose groups all wait for the same lines at their start: one of 10 x 512 at 200 (80 blocks
+// a run) 103.6 / 107.9, two of 4 x 512 at 100 (32 blocks) 66.5 / 72.3; 114 blocks a run 128.5 / 122.8.  Hence kHeadsFirstBlocks.  Scoring with 32x32x16
 // MFMAs took 6 % fewer clocks at a clock 5 % lower, 186.5 -> 189.5 us, as at a power limit.
 template <int S>
 __global__ void __launch_bounds__(64 * (S + kRoleDecoders), (S + kRoleDecoders) / 4) k6_attend_roles(const K6Params p)
@@ -864,7 +870,8 @@ __global__ void __launch_bounds__(64 * (S + kRoleDecoders), (S + kRoleDecoders) 
     const uint32_t n_mtg = (n_mt + 2u * (uint32_t)S - 1u) / (2u * (uint32_t)S);
     const uint32_t u = blockIdx.x;
     if (u >= H * n_mtg) return;  // the grid is as wide as the widest run
-    const uint32_t mtg = u % n_mtg, h = u / n_mtg;
+    const bool heads_first = S == 8 && p.heads_first;
+    const uint32_t h = heads_first ? u % H : u / n_mtg, mtg = heads_first ? u / H : u % n_mtg;
 
     RoleLane ln;
     ln.lane = threadIdx.x & 63u;

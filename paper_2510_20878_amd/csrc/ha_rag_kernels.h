@@ -120,6 +120,7 @@ constexpr uint32_t kAttendMinRunBlocks = 8;    // a workgroup takes at least thi
                                                // half as many in a call of very few workgroups),
 constexpr uint32_t kAttendMaxRunBlocks = 128;  // and a piece of one document is at most this long (a power of two)
 constexpr uint32_t kAttendTargetGroups = 2048; // pieces are halved while a launch has fewer workgroups
+constexpr uint32_t kHeadsFirstBlocks = 96;    // runs from this length on have their workgroups ordered by heads (k6_attend_roles)
 constexpr uint32_t kAttendFewDocs = 32;       // run lengths of the shared kernel: the longest run is looked for in a request of at most this many documents
 constexpr uint32_t kChipCUs = 256;            // compute units of the one GPU this library is built for
 constexpr uint64_t kLastLevelBytes = 256ull << 20;  // its last-level cache
@@ -171,7 +172,8 @@ struct K6Params {
     float scale_log2;      // sm_scale * log2(e)
     uint32_t doc_first;    // the runs' further documents: doc[doc_first .. doc_end), behind the runs
     uint32_t doc_end;
-    uint32_t past, pad;    // launch_k6: the packed bytes are read past the last-level cache
+    uint32_t past;         // launch_k6: the packed bytes are read past the last-level cache
+    uint32_t heads_first;  // k6_attend_roles<8>: workgroups number the heads of a tile group first, not a head's tile groups
     union {                // two views of the same bytes
         K6Run run[kAttendMaxRuns];
         K6Doc doc[kAttendMaxDocs];

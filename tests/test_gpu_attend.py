@@ -274,6 +274,47 @@ def test_forms_of_the_many_rows_kernel_at_the_edges_of_their_tiles(n_q, n_reqs, 
     run_case((1, 1, 128), form_call(n_q, n_reqs, docs), 0, 4, 0.0883, 4100 + n_q, spreads=2.0)
 
 
+@pytest.mark.parametrize("H,n_reqs,n_q", [(8, 8, 70), (3, 24, 67), (8, 16, 33)])
+def test_tile_groups_of_long_runs_ordered_by_heads(H, n_reqs, n_q):
+    """Requests of more query tiles than one workgroup takes, in runs of 96 blocks and more: workgroups then number the
+    heads first (heads_first).  Against binary64 attention over the cache that a load writes, bars as in check()."""
+    D, G, T, scale = 128, 8, [1600, 90], 0.09
+    ctx = B.Context(1, H, D, max(T), group_int8=128, group_int4=128)
+    call, refs = [], []
+    for r in range(n_reqs):
+        precs = [(B.PREC_16, B.PREC_INT4, B.PREC_GSE8, B.PREC_FP8_E4M3)[(r + i) % 4] for i in range(2)]
+        docs = []
+        for i, (t, p) in enumerate(zip(T, precs)):
+            src = torch.from_numpy(wl.kv_chunk(1, H, D, t, 2000 + 2 * r + i).view(np.int16)).cuda()
+            buf = torch.empty(ctx.chunk_bytes(p, t), dtype=torch.uint8, device="cuda")
+            ctx.quantize_chunk(src, t, p, ctx.group_of(p), buf)
+            torch.cuda.synchronize()
+            docs.append((buf, t, p, ctx.group_of(p)))
+        cache = torch.zeros((1, 2, H, sum(T), D), dtype=torch.bfloat16, device="cuda")
+        ctx.load_packed(docs, cache, sum(T))
+        n = n_q + r % 3
+        q = torch.from_numpy(q_words(n, H * G, D, 2100 + r).view(np.int16)).cuda()
+        out = torch.full((n, H * G, D), float("nan"), dtype=torch.float32, device="cuda")
+        lse = torch.full((n, H * G), float("nan"), dtype=torch.float32, device="cuda")
+        call.append((docs, q, out, lse, n))
+        refs.append(cache)
+    assert ctx.attend_workspace_bytes(call, H * G) == 0              # one run a request: all of its 106 blocks
+    ws = torch.empty(4, dtype=torch.float32, device="cuda")
+    ctx.attend_packed(call, 0, H * G, scale, ws, 0)
+    torch.cuda.synchronize()
+    for (docs, q, out, lse, n), cache in zip(call, refs):
+        k, v = cache[0, 0].double(), cache[0, 1].double()              # [H][T][D]
+        qd = q.view(torch.bfloat16).double().reshape(n, H, G, D).permute(1, 0, 2, 3).reshape(H, n * G, D)
+        sc = torch.matmul(qd, k.transpose(1, 2).contiguous()) * scale
+        z = torch.logsumexp(sc, -1)
+        w = torch.exp(sc - z[..., None])
+        back = lambda x: x.reshape(H, n, G, -1).permute(1, 0, 2, 3).reshape(n, H * G, -1).cpu().numpy()
+        sabs = scale * torch.matmul(qd.abs(), k.abs().transpose(1, 2).contiguous()).amax(-1)
+        check(out.cpu().numpy(), lse.cpu().numpy(), back(torch.matmul(w, v)), back(z)[..., 0], back(torch.matmul(w, v.abs())),
+              back(sabs)[..., 0])
+    ctx.destroy()
+
+
 def test_requests_of_two_tiles_go_with_those_of_three_and_four():
     """A call with requests of three or four query tiles takes its requests of two tiles to the same
     kernel (runs across documents), those of one tile stay with the other."""
