@@ -3,6 +3,7 @@
 #pragma once
 #include "ha_rag_kernels.h"
 #include "ha_rag_decode.h"
+#include <cstring>
 
 namespace ha_rag {
 
@@ -251,6 +252,26 @@ inline hipError_t launch_args(void (*kernel)(const P), dim3 grid, dim3 block, ui
     void *args[] = {&p};
     (void)hipLaunchKernel(reinterpret_cast<const void *>(kernel), grid, block, args, lds_bytes, stream);
     return hipGetLastError();
+}
+
+// launch(p), or launch of a copy of p in the structure of few where that holds what p does (see K6ParamsOf).
+template <class F>
+inline hipError_t launch_few_or_all(K6Params &p, F launch)
+{
+    if (p.doc_end > K6ParamsFew::kMaxDocs) return launch(p);  // doc_end lies behind the runs (check_k6_args)
+    K6ParamsFew f;
+    f.n_kv_heads = p.n_kv_heads;
+    f.n_q_heads = p.n_q_heads;
+    f.layer = p.layer;
+    f.n_runs = p.n_runs;
+    f.mtw = p.mtw;
+    f.scale_log2 = p.scale_log2;
+    f.doc_first = p.doc_first;
+    f.doc_end = p.doc_end;
+    f.past = p.past;
+    f.heads_first = p.heads_first;
+    std::memcpy(f.doc, p.doc, p.doc_end * sizeof(K6Doc));
+    return launch(f);
 }
 
 }  // namespace ha_rag

@@ -353,8 +353,8 @@ __device__ __forceinline__ void attend_values(const AttendHdr &hdr, const K6Run 
 // costs the memory time: 32 requests x 5,120 tokens at one query token, us a layer: 20 / 30 / 50 % of 16, 8 and 4 bits
 // 78.5 -> 74.7, FP8 74.5 -> 65.5, 4 bits unchanged.  A call that it does hold loses by them: 24 requests of that mix, one
 // layer, 54 -> 64; 8 requests, four layers, 27.5 -> 30.  At two query tiles neither way matters.
-template <int MTW, bool NARROW, bool PAST>
-__global__ void __launch_bounds__(64 * kAttendWaves, NARROW ? 3 : 2) k6_attend_partial(const K6Params p)
+template <int MTW, bool NARROW, bool PAST, class P>
+__global__ void __launch_bounds__(64 * kAttendWaves, NARROW ? 3 : 2) k6_attend_partial(const P p)
 {
     __shared__ __attribute__((aligned(16))) uint8_t lds[AttendLds<MTW>::kBytes];
     __shared__ float sm[kAttendWaves][MTW * 16], sl[kAttendWaves][2][MTW * 16];  // reference; sums of the weights (unrounded, rounded)
@@ -439,6 +439,16 @@ hipError_t check_k6_args(const K6Params &p, uint32_t *max_mt, bool *narrow)
     return next == p.doc_end ? hipSuccess : hipErrorInvalidValue;
 }
 
+template <class P>
+static hipError_t launch_partial(P &p, bool narrow, dim3 grid, dim3 block, hipStream_t stream)
+{
+    if (p.mtw == 2) return launch_args(k6_attend_partial<2, false, false, P>, grid, block, 0, stream, p);
+    if (p.past && narrow) return launch_args(k6_attend_partial<1, true, true, P>, grid, block, 0, stream, p);
+    if (p.past) return launch_args(k6_attend_partial<1, false, true, P>, grid, block, 0, stream, p);
+    if (narrow) return launch_args(k6_attend_partial<1, true, false, P>, grid, block, 0, stream, p);
+    return launch_args(k6_attend_partial<1, false, false, P>, grid, block, 0, stream, p);
+}
+
 hipError_t launch_k6(K6Params &p, hipStream_t stream, bool check_only)
 {
     if (p.n_runs == 0) return hipSuccess;
@@ -455,11 +465,7 @@ hipError_t launch_k6(K6Params &p, hipStream_t stream, bool check_only)
     if (width > 0x7FFFFFFFull) return hipErrorInvalidValue;
     if (check_only) return hipSuccess;
     dim3 grid((uint32_t)width, p.n_runs), block(64 * kAttendWaves);
-    if (p.mtw == 2) return launch_args(k6_attend_partial<2, false, false>, grid, block, 0, stream, p);
-    if (p.past && narrow) return launch_args(k6_attend_partial<1, true, true>, grid, block, 0, stream, p);
-    if (p.past) return launch_args(k6_attend_partial<1, false, true>, grid, block, 0, stream, p);
-    if (narrow) return launch_args(k6_attend_partial<1, true, false>, grid, block, 0, stream, p);
-    return launch_args(k6_attend_partial<1, false, false>, grid, block, 0, stream, p);
+    return launch_few_or_all(p, [&](auto &q) { return launch_partial(q, narrow, grid, block, stream); });
 }
 
 // ---------------------------------------------------------------------------

@@ -32,6 +32,7 @@
 // k6_attend_roles differs in the rows of K: kRoleKeyRow).
 #include "ha_rag_attend_dev.h"
 #include <atomic>
+#include <type_traits>
 
 namespace ha_rag {
 
@@ -729,8 +730,8 @@ __device__ __forceinline__ void role_score_round(const uint8_t *base, uint32_t r
 // W = 4 is for calls of five to eight tiles whose requests leave k6_attend_roles<4> with a third of its compute units idle or
 // a round nearly empty; two of its workgroups share a compute unit.  us a layer, k6_attend_roles<4> / this: 25 requests of 11 x
 // 1,024 tokens at 21 query tokens 254 / 213, 12 of 11 x 129 at 13 38.7 / 33.1; 27 of 2 x 256 at 18 23.0 / 26.1.
-template <int W>
-__global__ void __launch_bounds__(64 * W, 2) k6_attend_shared(const K6Params p)
+template <int W, class P>
+__global__ void __launch_bounds__(64 * W, 2) k6_attend_shared(const P p)
 {
     // two sets of W block buffers
     extern __shared__ __attribute__((aligned(16))) uint8_t lds_bytes[];
@@ -843,8 +844,8 @@ __global__ void __launch_bounds__(64 * W, 2) k6_attend_shared(const K6Params p)
 // 147 / 142.  Short runs lose by it, whose groups all wait for the same lines at their start: one of 10 x 512 at 200 (80 blocks
 // a run) 103.6 / 107.9, two of 4 x 512 at 100 (32 blocks) 66.5 / 72.3; 114 blocks a run 128.5 / 122.8.  Hence kHeadsFirstBlocks.  Scoring with 32x32x16
 // MFMAs took 6 % fewer clocks at a clock 5 % lower, 186.5 -> 189.5 us, as at a power limit.
-template <int S>
-__global__ void __launch_bounds__(64 * (S + kRoleDecoders), (S + kRoleDecoders) / 4) k6_attend_roles(const K6Params p)
+template <int S, class P>
+__global__ void __launch_bounds__(64 * (S + kRoleDecoders), (S + kRoleDecoders) / 4) k6_attend_roles(const P p)
 {
     extern __shared__ __attribute__((aligned(16))) uint8_t lds_bytes[];
     K6Run c = p.run[blockIdx.y];
@@ -956,7 +957,8 @@ hipError_t prepare_k6_shared()
     if (e != hipSuccess) return e;
     if (dev < 0 || dev >= 64) return hipErrorInvalidDevice;
     if (asked.load(std::memory_order_acquire) >> dev & 1u) return hipSuccess;
-    for (const void *k : {reinterpret_cast<const void *>(k6_attend_roles<4>), reinterpret_cast<const void *>(k6_attend_roles<8>)}) {
+    for (const void *k : {reinterpret_cast<const void *>(k6_attend_roles<4, K6Params>), reinterpret_cast<const void *>(k6_attend_roles<8, K6Params>),
+                          reinterpret_cast<const void *>(k6_attend_roles<4, K6ParamsFew>), reinterpret_cast<const void *>(k6_attend_roles<8, K6ParamsFew>)}) {
         e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)(2u * kRoleSet));
         if (e != hipSuccess) return e;
     }
@@ -978,13 +980,20 @@ hipError_t launch_k6_shared(K6Params &p, SharedForm form, hipStream_t stream, bo
     p.mtw = 2;
     if (check_only) return hipSuccess;
     dim3 grid((uint32_t)width, p.n_runs);
-    if (form == SharedForm::kShared2) return launch_args(k6_attend_shared<2>, grid, dim3(128), 2u * 2u * kSharedBlockLds, stream, p);
-    if (form == SharedForm::kShared4) return launch_args(k6_attend_shared<4>, grid, dim3(256), 2u * 4u * kSharedBlockLds, stream, p);
-    e = prepare_k6_shared();  // done at ha_rag_create; a no-op from then on
-    if (e != hipSuccess) return e;
-    const dim3 block(64u * (waves + kRoleDecoders));
-    if (form == SharedForm::kRoles4) return launch_args(k6_attend_roles<4>, grid, block, 2u * kRoleSet, stream, p);
-    return launch_args(k6_attend_roles<8>, grid, block, 2u * kRoleSet, stream, p);
+    if (form == SharedForm::kRoles4 || form == SharedForm::kRoles8) {
+        e = prepare_k6_shared();  // done at ha_rag_create; a no-op from then on
+        if (e != hipSuccess) return e;
+    }
+    return launch_few_or_all(p, [&](auto &q) {
+        typedef std::remove_reference_t<decltype(q)> P;
+        const dim3 roles(64u * (waves + kRoleDecoders));
+        switch (form) {
+        case SharedForm::kShared2: return launch_args(k6_attend_shared<2, P>, grid, dim3(128), 2u * 2u * kSharedBlockLds, stream, q);
+        case SharedForm::kShared4: return launch_args(k6_attend_shared<4, P>, grid, dim3(256), 2u * 4u * kSharedBlockLds, stream, q);
+        case SharedForm::kRoles4: return launch_args(k6_attend_roles<4, P>, grid, roles, 2u * kRoleSet, stream, q);
+        default: return launch_args(k6_attend_roles<8, P>, grid, roles, 2u * kRoleSet, stream, q);
+        }
+    });
 }
 
 }  // namespace ha_rag

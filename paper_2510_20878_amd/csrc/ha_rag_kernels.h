@@ -130,6 +130,7 @@ constexpr uint32_t kAttendWaves = 2;          // waves of a workgroup; they inte
 // and one short descriptor per further document: the argument buffer may live in host memory,
 // where every dependent read costs a trip over the link.
 constexpr uint32_t kAttendArgBytes = 36864;
+constexpr uint32_t kAttendFewArgBytes = 8192;  // those of a launch of few
 
 // One document: its keys and its values, which may come from one whole chunk or from a
 // keys-only and a values-only chunk of different formats.
@@ -162,10 +163,12 @@ struct K6Run {
     float *lse;           // final runs: binary32 [n_q][n_q_heads] or null
 };
 
-constexpr uint32_t kAttendMaxRuns = kAttendArgBytes / sizeof(K6Run);
-constexpr uint32_t kAttendMaxDocs = kAttendArgBytes / sizeof(K6Doc);
-
-struct K6Params {
+// BYTES: room for descriptors.  A launch of few has a structure of few, since writing the arguments is part of what a
+// launch costs the host, and calls of few documents are bound by that: with 8 instead of 36 KiB at one query token, us a pass, one
+// request of 10 x 512 tokens, 32 layers 392 -> 369, two of them 458 -> 425; one of two of 128, four layers 42.6 -> 39.6.
+template <uint32_t BYTES>
+struct K6ParamsOf {
+    static constexpr uint32_t kMaxRuns = BYTES / sizeof(K6Run), kMaxDocs = BYTES / sizeof(K6Doc);
     uint32_t n_kv_heads, n_q_heads, layer;
     uint32_t n_runs;       // run[0 .. n_runs)
     uint32_t mtw;          // 16-row query tiles per workgroup: 1 or 2 (set by launch_k6)
@@ -175,12 +178,16 @@ struct K6Params {
     uint32_t past;         // launch_k6: the packed bytes are read past the last-level cache
     uint32_t heads_first;  // k6_attend_roles<8>: workgroups number the heads of a tile group first, not a head's tile groups
     union {                // two views of the same bytes
-        K6Run run[kAttendMaxRuns];
-        K6Doc doc[kAttendMaxDocs];
+        K6Run run[kMaxRuns];
+        K6Doc doc[kMaxDocs];
     };
     // index in doc of the first short descriptor behind n runs
     static constexpr uint32_t docs_behind(uint32_t n) { return (n * (uint32_t)sizeof(K6Run) + (uint32_t)sizeof(K6Doc) - 1u) / (uint32_t)sizeof(K6Doc); }
 };
+typedef K6ParamsOf<kAttendArgBytes> K6Params;
+typedef K6ParamsOf<kAttendFewArgBytes> K6ParamsFew;
+constexpr uint32_t kAttendMaxRuns = K6Params::kMaxRuns;
+constexpr uint32_t kAttendMaxDocs = K6Params::kMaxDocs;
 
 struct K7Req {
     const float *part;    // records [n_runs][n_kv_heads][n_mtiles]

@@ -315,6 +315,14 @@ def test_tile_groups_of_long_runs_ordered_by_heads(H, n_reqs, n_q):
     ctx.destroy()
 
 
+@pytest.mark.parametrize("n_docs", [113, 114, 341, 342])
+@pytest.mark.parametrize("n_q", [1, 12, 80])
+def test_launches_at_the_edge_of_few_descriptors(n_docs, n_q):
+    """A launch whose descriptors (72 bytes a run, 24 a further document) take up to 8 KiB has a structure of its own."""
+    tags = [B.PREC_INT4, B.PREC_16, B.PREC_GSE8]
+    run_case((1, 1, 128), [([16] * n_docs, [tags[i % 3] for i in range(n_docs)], n_q)], 0, 8, 0.09, 5000 + n_docs)
+
+
 def test_requests_of_two_tiles_go_with_those_of_three_and_four():
     """A call with requests of three or four query tiles takes its requests of two tiles to the same
     kernel (runs across documents), those of one tile stay with the other."""
