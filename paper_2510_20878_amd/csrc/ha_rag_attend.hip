@@ -730,10 +730,12 @@ int plan_attend(ha_rag_ctx *c, const ha_rag_packed_chunk *chunks, const ha_rag_a
 
 
 // Whether k6_attend_partial reads its documents past the last-level cache (what it gives and costs is measured there).  A
-// layer's bytes are asked for again by the next query token, after those of all other layers: beyond the cache's size they
-// are gone by then.  us a pass with ordinary and nontemporal loads, by the bytes of all layers, 10 x 512 tokens a request in 20 /
-// 30 / 50 % of 16, 8 and 4 bits: 122 MB (24 requests, one layer) 53.7 / 64.2, 163 (8, four) 110 / 120, 204 (20, two) 107 / 109, 245 (24, two)
-// 124 / 125, 286 (28, two) 135.5 / 129.7, 326 (32, two) 158.5 / 150.5; 326 (2, 32 layers) 500 / 445.
+// layer's bytes are asked for again by the next query token, after those of all other layers: well beyond the cache's size
+// they are gone by then.  Not far beyond it part of them is still there, and more of it where a call is small next to the cache.
+// Ordinary loads / nontemporal ones, us a pass, by the MB of all layers (of one): 122 (122) 53.7 / 64.2, 163 (41) 110 / 120,
+// 245 (122) 124 / 125, 270 (90) 100 / 118, 315 (105) 125 / 135, 358 (90) 120 / 135, 436 (109) 141 / 148; 286 (143) 135.5 / 129.7,
+// 326 (163) 156.2 / 147.0, 400 (133) 250 / 239, 421 (105) 125 / 116, 483 (161) 268 / 252, 512 (256) 146 / 132, 699 (350) 186 / 178,
+// 1,125 (375) 253 / 242.  So: from 400 MB on, and beyond the cache's size where one layer is half of it.
 // Documents that several requests of the call list come out of the cache for the second of them: with more than a
 // quarter such, of the first kLooked, the loads stay as they are.
 bool read_past_cache(const ha_rag_ctx *c, const Plan *plans, uint32_t n_reqs, const Doc *docs)
@@ -744,7 +746,8 @@ bool read_past_cache(const ha_rag_ctx *c, const Plan *plans, uint32_t n_reqs, co
         const Doc *d = docs + plans[r].first_doc;
         for (uint32_t i = 0; i < plans[r].n_docs; ++i) bytes += d[i].k_tile + d[i].v_tile;
     }
-    if (bytes * c->cfg.n_kv_heads <= kLastLevelBytes / c->cfg.n_layers) return false;
+    const uint64_t layer = bytes * c->cfg.n_kv_heads, most = layer > kLastLevelBytes / 2u ? kLastLevelBytes : kLastLevelBytes * 25u / 16u;
+    if (layer <= most / c->cfg.n_layers) return false;
     constexpr uint32_t kLooked = 1024, kBits = 8 * kLooked;
     uint64_t seen[kBits / 64] = {};  // documents by a hash of where their keys lie
     uint32_t n = 0, repeated = 0;

@@ -349,7 +349,7 @@ __device__ __forceinline__ void attend_values(const AttendHdr &hdr, const K6Run 
 // by instruction issue); 16-bit pairs spill there and lose a quarter.
 //
 // PAST: nontemporal loads of the packed bytes, for calls whose documents the 256 MB last-level cache cannot hold
-// until the next query token asks for them (kLastLevelBytes says when).  What is read is then not put there either, which
+// until the next query token asks for them (read_past_cache says when).  What is read is then not put there either, which
 // costs the memory time: 32 requests x 5,120 tokens at one query token, us a layer: 20 / 30 / 50 % of 16, 8 and 4 bits
 // 78.5 -> 74.7, FP8 74.5 -> 65.5, 4 bits unchanged.  A call that it does hold loses by them: 24 requests of that mix, one
 // layer, 54 -> 64; 8 requests, four layers, 27.5 -> 30.  At two query tiles neither way matters.
