@@ -729,25 +729,40 @@ int plan_attend(ha_rag_ctx *c, const ha_rag_packed_chunk *chunks, const ha_rag_a
 }
 
 
-// Whether k6_attend_partial reads its documents past the last-level cache (what it gives and costs is measured there).  A
-// layer's bytes are asked for again by the next query token, after those of all other layers: well beyond the cache's size
-// they are gone by then.  Not far beyond it part of them is still there, and more of it where a call is small next to the cache.
-// Ordinary loads / nontemporal ones, us a pass, by the MB of all layers (of one): 122 (122) 53.7 / 64.2, 163 (41) 110 / 120,
-// 245 (122) 124 / 125, 270 (90) 100 / 118, 315 (105) 125 / 135, 358 (90) 120 / 135, 436 (109) 141 / 148; 286 (143) 135.5 / 129.7,
-// 326 (163) 156.2 / 147.0, 400 (133) 250 / 239, 421 (105) 125 / 116, 483 (161) 268 / 252, 512 (256) 146 / 132, 699 (350) 186 / 178,
-// 1,125 (375) 253 / 242.  So: from 400 MB on, and beyond the cache's size where one layer is half of it.
+// Whether k6_attend_partial reads its documents past the last-level cache, with nontemporal loads.  A layer's bytes are asked
+// for again by the next query token, after those of all other layers, so what counts is their sum over the layers: up to the
+// cache's size they come out of it, from a quarter more on they do not.  Beyond that it is the work that decides: short
+// runs wait for their first loads, which take longer this way, and 16-bit blocks, four times the bytes of 4-bit ones, still find
+// some of them in the cache.  Nontemporal loads / ordinary ones, means of the ratio of a pass at one query token, 4,400 random
+// calls of 1 to 32 layers (up to 1,000 MB, 2 to 16 KV heads, 128 to 2,000 tokens a document), by the MB of all layers:
+//                                            200-256  256-290  290-320  320-360  360-420  420-537  537-700  from 700
+//   no 16-bit side, runs of 4 to 8 blocks       1.05     1.02     0.99     0.98     0.98     0.98     0.97     0.97
+//   no 16-bit side, 13 blocks and more          1.08     1.05     1.00     0.95     0.94     0.95     0.94     0.94
+//   a fifth to a half in 16 bits, 7 to 9        1.14     1.09     1.04     1.04     1.02     1.03     1.02     1.02
+//   a fifth to a half in 16 bits, 18 to 125     1.07     1.07     1.06     0.97     0.95     0.95     0.94     0.95
+//   all in 16 bits, 7 to 9                      1.28     1.24     1.18     1.17     1.15     1.12     1.07     1.10
+//   all in 16 bits, 18 to 40                       -        -        -        -     0.97        -     0.97     0.98
+// (13 to 18 blocks, partly or all in 16 bits: 0.98 to 1.05.)  With the cache full of other data, as behind the
+// weights of a layer, the same: 0.99, 0.95, 1.03, 0.96, 1.11 and 0.98.  us a pass, ordinary / nontemporal, 10 x 512 tokens
+// a request: 32 requests in 20 / 30 / 50 % of 16, 8 and 4 bits, two layers (655 MB) 151 / 141; 12 of them, four layers (507 MB) 153 /
+// 166; FP8, 20 requests, two layers (419 MB) 98 / 93; 16 bits, 10 requests, two layers (419 MB) 101 / 118.  By this rule 1.4 % of
+// the calls take more than 2 % longer than with ordinary loads: 4-bit ones of eight layers, up to 7 %.
 // Documents that several requests of the call list come out of the cache for the second of them: with more than a
 // quarter such, of the first kLooked, the loads stay as they are.
 bool read_past_cache(const ha_rag_ctx *c, const Plan *plans, uint32_t n_reqs, const Doc *docs)
 {
-    uint64_t bytes = 0;  // of one layer and head
+    uint64_t bytes = 0, blocks = 0, wide = 0, n_runs = 0;  // bytes: of one layer and head
     for (uint32_t r = 0; r < n_reqs; ++r) {
-        if (plans[r].shared) continue;
-        const Doc *d = docs + plans[r].first_doc;
-        for (uint32_t i = 0; i < plans[r].n_docs; ++i) bytes += d[i].k_tile + d[i].v_tile;
+        const Plan &pl = plans[r];
+        if (pl.shared) continue;
+        const Doc *d = docs + pl.first_doc;
+        for (uint32_t i = 0; i < pl.n_docs; ++i) bytes += d[i].k_tile + d[i].v_tile;
+        blocks += pl.all_blocks;
+        wide += pl.wide_blocks;
+        n_runs += pl.n_runs;
     }
-    const uint64_t layer = bytes * c->cfg.n_kv_heads, most = layer > kLastLevelBytes / 2u ? kLastLevelBytes : kLastLevelBytes * 25u / 16u;
-    if (layer <= most / c->cfg.n_layers) return false;
+    if (bytes * c->cfg.n_kv_heads <= kLastLevelBytes / 4u * 5u / c->cfg.n_layers) return false;
+    if (wide && blocks < n_runs * kPastWideRunBlocks) return false;
     constexpr uint32_t kLooked = 1024, kBits = 8 * kLooked;
     uint64_t seen[kBits / 64] = {};  // documents by a hash of where their keys lie
     uint32_t n = 0, repeated = 0;

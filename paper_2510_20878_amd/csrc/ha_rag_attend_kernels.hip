@@ -348,11 +348,11 @@ __device__ __forceinline__ void attend_values(const AttendHdr &hdr, const K6Run 
 // in the 168 registers of three waves per SIMD, which measured 10 % faster (the kernel is bound
 // by instruction issue); 16-bit pairs spill there and lose a quarter.
 //
-// PAST: nontemporal loads of the packed bytes, for calls whose documents the 256 MB last-level cache cannot hold
-// until the next query token asks for them (read_past_cache says when).  What is read is then not put there either, which
-// costs the memory time: 32 requests x 5,120 tokens at one query token, us a layer: 20 / 30 / 50 % of 16, 8 and 4 bits
-// 78.5 -> 74.7, FP8 74.5 -> 65.5, 4 bits unchanged.  A call that it does hold loses by them: 24 requests of that mix, one
-// layer, 54 -> 64; 8 requests, four layers, 27.5 -> 30.  At two query tiles neither way matters.
+// PAST: nontemporal loads of the packed bytes, for calls whose documents the 256 MiB last-level cache cannot hold
+// until the next query token asks for them.  What is read is then not put there either, which costs the memory time: 32
+// requests x 5,120 tokens at one query token, us a layer: 20 / 30 / 50 % of 16, 8 and 4 bits 76 -> 71, FP8 70 -> 62, 4 bits
+// unchanged.  Calls that it does hold lose by them: 23 requests of that mix, one layer (232 MB), 46 -> 57.  read_past_cache says
+// when, with what was measured between.  At two query tiles neither way matters.
 template <int MTW, bool NARROW, bool PAST, class P>
 __global__ void __launch_bounds__(64 * kAttendWaves, NARROW ? 3 : 2) k6_attend_partial(const P p)
 {

@@ -40,6 +40,7 @@ struct Seen {
     uint32_t form = 0, pieces = 0, runs = 0, longest = 0;
     uint64_t end = 0;                    // of the last record
     bool quiet = false;                  // only timed
+    bool past = false;                   // k6_attend_partial reads past the last-level cache
 } seen;
 
 uint32_t request_of(const void *p) { return (uint32_t)(((uintptr_t)p - kOut) / kOutStep); }
@@ -76,6 +77,7 @@ hipError_t launch_k6(K6Params &p, hipStream_t, bool)
 {
     if (seen.quiet) return hipSuccess;
     seen.pieces += p.n_runs;
+    seen.past = p.past;
     for (uint32_t i = 0; i < p.n_runs; ++i) take_run(p, i, false);
     return hipSuccess;
 }
@@ -114,7 +116,8 @@ hipError_t prepare_k6_shared() { return hipSuccess; }
 namespace {
 
 struct Call {
-    uint32_t H, n_q_heads;
+    uint32_t H, n_q_heads, layers = 2;
+    uint64_t apart = 0;  // bytes between chunks
     std::vector<ha_rag_attend_request> reqs;
     std::vector<ha_rag_packed_chunk> chunks;
     void request(uint32_t n_q)
@@ -127,28 +130,34 @@ struct Call {
         rq.n_q = n_q;
         reqs.push_back(rq);
     }
-    void documents(uint32_t n_tokens, uint32_t count, uint32_t prec = HA_RAG_PREC_INT4)
+    // back: each is the chunk listed so many before it
+    void documents(uint32_t n_tokens, uint32_t count, uint32_t prec = HA_RAG_PREC_INT4, uint32_t back = 0, uint32_t part = HA_RAG_PART_KV)
     {
         ha_rag_packed_chunk pc;
         std::memset(&pc, 0, sizeof pc);
-        pc.packed = (const void *)0x750000000000ull;
         pc.n_tokens = n_tokens;
         pc.prec = prec;
         pc.group = prec == HA_RAG_PREC_INT8 || prec == HA_RAG_PREC_INT4 ? 128 : 0;
-        pc.part = HA_RAG_PART_KV;
-        for (uint32_t i = 0; i < count; ++i) chunks.push_back(pc);
+        pc.part = part;
+        for (uint32_t i = 0; i < count; ++i) {
+            const size_t n = chunks.size();
+            if (back > n) fail("a document listed before the first");
+            pc.packed = back ? chunks[n - back].packed : (const void *)(0x750000000000ull + apart * n);
+            chunks.push_back(pc);
+        }
         reqs.back().n_chunks += count;
     }
 };
 
-ha_rag_ctx *context(uint32_t H)
+ha_rag_ctx *context(uint32_t H, uint32_t layers = 2)
 {
-    static ha_rag_ctx *ctx[257] = {};
-    if (H == 0 || H > 256) fail("heads");
+    static ha_rag_ctx *all[65][257] = {};
+    if (H == 0 || H > 256 || layers > 64) fail("heads or layers");
+    ha_rag_ctx **ctx = all[layers];
     if (!ctx[H]) {
         ha_rag_config cfg;
         std::memset(&cfg, 0, sizeof cfg);
-        cfg.n_layers = 2;
+        cfg.n_layers = layers;
         cfg.n_kv_heads = H;
         cfg.head_dim = 128;
         cfg.max_chunk_tokens = 4096;
@@ -165,7 +174,7 @@ int attend(Call &c, bool fixed, size_t bytes)
     seen = Seen();
     seen.ws = fixed ? kStaticWorkspace : kWorkspace;
     seen.blocks.assign(c.reqs.size(), 0);
-    ha_rag_ctx *ctx = context(c.H);
+    ha_rag_ctx *ctx = context(c.H, c.layers);
     const uint32_t n = (uint32_t)c.reqs.size();
     const int rc = fixed ? ha_rag_attend_packed_static(ctx, c.chunks.data(), c.reqs.data(), n, 0, c.n_q_heads, 0.1f, nullptr)
                          : ha_rag_attend_packed(ctx, c.chunks.data(), c.reqs.data(), n, 0, c.n_q_heads, 0.1f, (void *)kWorkspace, bytes, nullptr);
@@ -176,7 +185,8 @@ int attend(Call &c, bool fixed, size_t bytes)
     size_t at = 0;
     for (uint32_t r = 0; r < n; ++r) {
         uint64_t blocks = 0;
-        for (uint32_t i = 0; i < c.reqs[r].n_chunks; ++i) blocks += (c.chunks[at++].n_tokens + 15u) / 16u;
+        for (uint32_t i = 0; i < c.reqs[r].n_chunks; ++i, ++at)
+            if (c.chunks[at].part != HA_RAG_PART_V) blocks += (c.chunks[at].n_tokens + 15u) / 16u;
         if (blocks != seen.blocks[r]) fail("a request's runs do not take its blocks once");
     }
     auto by_start = [](const Range &a, const Range &b) { return a.at < b.at || (a.at == b.at && a.end < b.end); };
@@ -237,9 +247,10 @@ void random_call(Call &c)
     }
 }
 
-// One call: "static|workspace|time N HEADS QUERY_HEADS" then per request "/ n_q tokens*count ...".  Prints the return
+// One call: "static|workspace|time N|past LAYERS APART HEADS QUERY_HEADS" then per request "/ n_q tokens*count*format*back*part ..."
+// (APART: bytes between chunks; back: see documents()).  Prints the return
 // code, the workspace asked for, the end of the last record, the shared kernel's form (0: not
-// launched), pieces and runs launched and the blocks of the longest, or the us of a call.
+// launched), pieces and runs launched and the blocks of the longest; or the us of a call; or whether it reads past the cache, and the pieces launched.
 void run_line(char *line)
 {
     Call c = Call();
@@ -248,6 +259,10 @@ void run_line(char *line)
     if (!w) return;
     const std::string how = w;
     const int times = how == "time" ? std::atoi(strtok_r(nullptr, " \n", &save)) : 0;
+    if (how == "past") {
+        c.layers = (uint32_t)std::atoi(strtok_r(nullptr, " \n", &save));
+        c.apart = std::strtoull(strtok_r(nullptr, " \n", &save), nullptr, 10);
+    }
     c.H = (uint32_t)std::atoi(strtok_r(nullptr, " \n", &save));
     c.n_q_heads = (uint32_t)std::atoi(strtok_r(nullptr, " \n", &save));
     bool first = false;
@@ -258,13 +273,13 @@ void run_line(char *line)
         }
         if (first) c.request((uint32_t)std::atoi(w));
         else {
-            unsigned tokens = 0, count = 1, prec = HA_RAG_PREC_INT4;
-            if (std::sscanf(w, "%u*%u*%u", &tokens, &count, &prec) < 1) fail("a call's line");
-            c.documents(tokens, count, prec);
+            unsigned tokens = 0, count = 1, prec = HA_RAG_PREC_INT4, back = 0, part = HA_RAG_PART_KV;
+            if (std::sscanf(w, "%u*%u*%u*%u*%u", &tokens, &count, &prec, &back, &part) < 1) fail("a call's line");
+            c.documents(tokens, count, prec, back, part);
         }
         first = false;
     }
-    ha_rag_ctx *ctx = context(c.H);
+    ha_rag_ctx *ctx = context(c.H, c.layers);
     size_t need = 0;
     const uint32_t n = (uint32_t)c.reqs.size();
     int rc = ha_rag_attend_workspace_bytes(ctx, c.chunks.data(), c.reqs.data(), n, c.n_q_heads, &need);
@@ -283,6 +298,10 @@ void run_line(char *line)
         return;
     }
     if (rc == HA_RAG_OK) rc = attend(c, how == "static", how == "static" ? HA_RAG_ATTEND_STATIC_SCRATCH_BYTES : need);
+    if (how == "past") {
+        std::printf("%d %d %u\n", rc, (int)seen.past, seen.pieces);
+        return;
+    }
     std::printf("%d %zu %llu %u %u %u %u\n", rc, need, (unsigned long long)(rc ? 0 : seen.end), rc ? 0 : seen.form, rc ? 0 : seen.pieces, rc ? 0 : seen.runs, rc ? 0 : seen.longest);
 }
 

@@ -742,6 +742,55 @@ def test_documents_that_the_last_level_cache_does_not_hold(with_16_bit):
     assert torch.equal(results[0][0], results[1][0]) and torch.equal(results[0][1], results[1][1])
 
 
+PAST_LAYERS = 3
+
+
+def _past_call(with_16_bit, many):
+    """Documents of 20 to 23 blocks in every pair of formats: (KV heads, per request (tokens, keys' tag, values' tag))."""
+    tags = ALL if with_16_bit else ALL[1:]
+    pairs = [(320 + (7 * i) % 40, k, v) for i, (k, v) in enumerate((a, b) for a in tags for b in tags)]
+    return (16, [pairs] * 4) if many else (32, [pairs] * 2)
+
+
+PAST_CALLS = [(w, m) + _past_call(w, m) for w in (True, False) for m in (True, False)]
+
+
+@pytest.mark.parametrize("with_16_bit,many,H,reqs", PAST_CALLS, ids=["16-bit-many", "16-bit-few", "narrow-many", "narrow-few"])
+def test_loads_past_the_cache_give_the_same_results(with_16_bit, many, H, reqs):
+    """Calls that read_past_cache takes to nontemporal loads (that it does is checked where launches are seen on the host), with
+    and without 16-bit sides, in a launch of few and of many descriptors: the same bytes, so the same results, to the bit,
+    as through a context of one layer, where ordinary loads read them."""
+    many_layers = B.Context(PAST_LAYERS, H, 128, 512, group_int8=128, group_int4=128)
+    one = B.Context(1, H, 128, 512, group_int8=128, group_int4=128)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(77)
+    call, outs = [], []
+    for r, docs in enumerate(reqs):
+        units = []
+        for i, (T, kp, vp) in enumerate(docs):
+            for part, prec in ((B.PART_K, kp), (B.PART_V, vp)):
+                src = torch.randn((1, H, T, 128), generator=gen, device="cuda").to(torch.bfloat16)
+                buf = torch.zeros(many_layers.chunk_bytes(prec, T, part=part), dtype=torch.uint8, device="cuda")
+                one.quantize_half(src, T, prec, one.group_of(prec), buf)  # layer 0
+                torch.cuda.synchronize()
+                units.append((buf, T, prec, one.group_of(prec), part))
+        q = torch.from_numpy(q_words(1, H, 128, 992 + r).view(np.int16)).cuda()
+        call.append((units, q))
+    results = []
+    for ctx in (one, many_layers):
+        outs = [(torch.full((1, H, 128), float("nan"), dtype=torch.float32, device="cuda"),
+                 torch.full((1, H), float("nan"), dtype=torch.float32, device="cuda")) for _ in call]
+        listed = [(units, q, out, lse, 1) for (units, q), (out, lse) in zip(call, outs)]
+        nb = ctx.attend_workspace_bytes(listed, H)
+        ws = torch.full((nb // 4,), float("nan"), dtype=torch.float32, device="cuda")
+        ctx.attend_packed(listed, 0, H, 0.1, ws, nb)
+        torch.cuda.synchronize()
+        results.append([t.cpu() for pair in outs for t in pair])
+        ctx.destroy()
+    for a, b in zip(*results):
+        assert torch.isfinite(a).all() and torch.equal(a, b)
+
+
 def test_the_most_query_tokens_and_the_widest_head_group_one_call_takes():
     # 4096 query tokens of one head group member (4096 query rows = 256 tiles over one chunk)
     run_case((1, 1, 128), [([48], [B.PREC_INT4], 4096)], 0, 1, 0.1, 810)

@@ -248,3 +248,52 @@ def test_gpu_tests_of_the_forms_take_the_forms_that_they_name(plans_host):
     for n_q, H in ((9, 256), (33, 64)):
         (rc, need, end, _, _, runs, longest), = calls(plans_host, [requests_line(H, 4, gpu.long_lists_call(n_q))])
         assert rc == OK and end == need and (runs, longest) == (8, 128)
+
+
+# ---- loads past the last-level cache ------------------------------------------------------------------------
+BF16, INT8, INT4, E4M3, GSE8 = 0, 1, 2, 3, 5
+MIX = [BF16] * 2 + [INT8] * 3 + [INT4] * 5  # 20 / 30 / 50 %: 10.2 MB a layer for ten documents of 512 tokens
+
+
+def past_line(layers, n_reqs, n_docs, tokens, tags, H=8, n_q=1, apart=1 << 24, back=0):
+    """back: the documents of the last `back[0]` requests are those of `back[1]` requests before."""
+    text = "past %d %d %d %d" % (layers, apart, H, 4 * H)
+    for r in range(n_reqs):
+        again = back[1] * n_docs if back and r >= n_reqs - back[0] else 0
+        text += " / %d" % n_q + "".join(" %d*1*%d*%d" % (tokens, tags[i % len(tags)], again) for i in range(n_docs))
+    return text
+
+
+def reads_past(exe, *shape, **more):
+    (rc, past, _), = calls(exe, [past_line(*shape, **more)])
+    assert rc == OK
+    return bool(past)
+
+
+@pytest.mark.parametrize("shape,past", [
+    # us a pass, ordinary / nontemporal loads
+    ((2, 32, 10, 512, MIX), True),         # 655 MB: 151 / 141
+    ((2, 27, 10, 512, MIX), True),         # 551 MB: 130 / 122
+    ((2, 23, 10, 512, MIX), False),        # 465 MB, 16 blocks: 115 / 116
+    ((1, 29, 10, 512, MIX), False),        # 297 MB in one layer: 60 / 64
+    ((4, 12, 10, 512, MIX), False),        # 491 MB, pieces of eight blocks: 142 / 154
+    ((1, 20, 10, 512, [BF16]), False),     # 419 MB, 16 blocks: 83 / 89
+    ((2, 10, 10, 512, [BF16]), False),     # 419 MB, eight blocks: 101 / 118
+    ((1, 30, 10, 512, [BF16]), True),      # 629 MB, 32 blocks: 118 / 114
+    ((2, 17, 10, 512, [E4M3]), True),      # 357 MB: 80 / 77
+    ((2, 15, 10, 512, [E4M3]), False),     # 315 MB
+    ((8, 5, 9, 512, [GSE8]), True),        # 377 MB, pieces of eight blocks: 166 / 159
+    ((32, 1, 10, 512, MIX), False),        # one request, 327 MB
+    ((32, 2, 10, 512, MIX), False),        # two, 655 MB, four blocks: 450 / 430, within what its runs of one side differ
+    ((32, 2, 10, 512, [INT8]), True)])     # 694 MB
+def test_documents_are_read_past_the_cache_where_that_is_faster(plans_host, shape, past):
+    assert reads_past(plans_host, *shape) == past
+
+
+def test_gpu_tests_of_loads_past_the_cache_take_the_builds_that_they_name(plans_host):
+    import test_gpu_attend as gpu
+    for with_16_bit, many, H, reqs in gpu.PAST_CALLS:
+        text = "".join(" / 1" + "".join(" %d*1*%d*0*1 %d*1*%d*0*2" % (t, k, t, v) for t, k, v in docs) for docs in reqs)
+        (rc, past, pieces), (rc1, past1, _) = calls(plans_host, ["past %d %d %d %d" % (n, 1 << 24, H, H) + text for n in (gpu.PAST_LAYERS, 1)])
+        assert rc == rc1 == OK and past and not past1
+        assert (pieces > 8192 // 72) == many  # the structure of few holds 113 runs
