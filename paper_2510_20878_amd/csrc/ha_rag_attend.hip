@@ -749,8 +749,13 @@ int plan_attend(ha_rag_ctx *c, const ha_rag_packed_chunk *chunks, const ha_rag_a
 // the calls take more than 2 % longer than with ordinary loads: 4-bit ones of eight layers, up to 7 %.
 // Documents that several requests of the call list come out of the cache for the second of them: with more than a
 // quarter such, of the first kLooked, the loads stay as they are.
-bool read_past_cache(const ha_rag_ctx *c, const Plan *plans, uint32_t n_reqs, const Doc *docs)
+// Documents in pinned host memory come over the link and slow a call that has any of them down to its pace; nontemporal
+// loads fetch them in smaller pieces: ten requests of 10 x 512 tokens, two layers, 16 bits 6,274 / 8,729 us, five of eight
+// layers, FP8, 6,347 / 6,753.  Hence ordinary loads for such calls.  in_host: the caller knows of one; those listed by address are
+// looked up in the slabs of that tier.
+bool read_past_cache(const ha_rag_ctx *c, const Plan *plans, uint32_t n_reqs, const Doc *docs, bool in_host)
 {
+    if (in_host) return false;
     uint64_t bytes = 0, blocks = 0, wide = 0, n_runs = 0;  // bytes: of one layer and head
     for (uint32_t r = 0; r < n_reqs; ++r) {
         const Plan &pl = plans[r];
@@ -763,6 +768,16 @@ bool read_past_cache(const ha_rag_ctx *c, const Plan *plans, uint32_t n_reqs, co
     }
     if (bytes * c->cfg.n_kv_heads <= kLastLevelBytes / 4u * 5u / c->cfg.n_layers) return false;
     if (wide && blocks < n_runs * kPastWideRunBlocks) return false;
+    for (const Slab &sl : c->slab[HA_RAG_TIER_PINNED]) {
+        if (!sl.holds_copies()) continue;
+        const uintptr_t base = (uintptr_t)sl.base, size = (uintptr_t)sl.n_slots * sl.slot_bytes;
+        for (uint32_t r = 0; r < n_reqs; ++r) {
+            if (plans[r].shared) continue;
+            const Doc *d = docs + plans[r].first_doc;
+            for (uint32_t i = 0; i < plans[r].n_docs; ++i)
+                if ((uintptr_t)d[i].k - base < size || (uintptr_t)d[i].v - base < size) return false;
+        }
+    }
     constexpr uint32_t kLooked = 1024, kBits = 8 * kLooked;
     uint64_t seen[kBits / 64] = {};  // documents by a hash of where their keys lie
     uint32_t n = 0, repeated = 0;
@@ -810,13 +825,14 @@ struct HeapPlanStore {  // one allocation, not cleared: the lists' entries are w
     PlanStore store() { return ps; }
 };
 
-// checks, workspace layout and launches; the caller holds the context's lock.  *need (nullable)
+// checks, workspace layout and launches; the caller holds the context's lock.  in_host: some chunk is known to lie in
+// pinned host memory.  *need (nullable)
 // receives the workspace bytes the lists ask for, also when the call then fails with ENOSPC; it is given
 // where the workspace's size is fixed and not the one asked for.
 int attend_locked(ha_rag_ctx *c, PlanStore ps, const ha_rag_packed_chunk *chunks,
                   const ha_rag_attend_request *reqs, uint32_t n_reqs, uint32_t layer,
                   uint32_t n_q_heads, float sm_scale, void *workspace, size_t workspace_bytes,
-                  void *stream, uint64_t *need = nullptr)
+                  void *stream, bool in_host = false, uint64_t *need = nullptr)
 {
     uint64_t floats = 0;
     SharedForm form = SharedForm::kShared2;
@@ -851,7 +867,7 @@ int attend_locked(ha_rag_ctx *c, PlanStore ps, const ha_rag_packed_chunk *chunks
     };
     // ---- requests of at most two tiles: every run is a piece of one document
     kq.n_runs = 0;
-    kq.past = read_past_cache(c, plans, n_reqs, docs.data);
+    kq.past = read_past_cache(c, plans, n_reqs, docs.data, in_host);
     kq.heads_first = 0;
     for (uint32_t r = 0; r < n_reqs; ++r)  // the call's longest run
         kq.heads_first |= plans[r].shared && std::min<uint64_t>(plans[r].run_blocks, plans[r].all_blocks) >= kHeadsFirstBlocks;
@@ -1105,7 +1121,7 @@ int ha_rag_attend_packed_static(ha_rag_ctx *c, const ha_rag_packed_chunk *chunks
     }
     uint64_t need = 0;
     int rc = attend_locked(c, ps, chunks, reqs, n_reqs, layer, n_q_heads, sm_scale, ws,
-                           kStaticScratchBytes, stream, &need);
+                           kStaticScratchBytes, stream, false, &need);
     if (rc == HA_RAG_ENOSPC) {
         char msg[192];
         if (need > kStaticScratchBytes)
@@ -1154,15 +1170,17 @@ int ha_rag_attend_chunks(ha_rag_ctx *c, const uint64_t *ids, const ha_rag_attend
     if (rc) return rc;
     hipStream_t s = (hipStream_t)stream;
     // the kernels read the slots where they lie: wait for whoever wrote them on another stream
+    bool in_host = false;
     for (size_t i = 0; i < cis.size(); ++i) {
         const Chunk &ch = c->chunks[cis[i]];
         const int t = ch.fastest();
+        in_host |= t == (int)HA_RAG_TIER_PINNED;
         rc = before_read(c, c->slab[t][ch.prec].use[ch.slot[t]], s);
         if (rc) return rc;
     }
     HeapPlanStore hs(reqs, n_reqs);
     rc = attend_locked(c, hs.store(), chunks.data(), reqs, n_reqs, layer, n_q_heads, sm_scale, workspace,
-                       workspace_bytes, stream);
+                       workspace_bytes, stream, in_host);
     if (rc) return rc;
     if (flags & HA_RAG_ATTEND_COUNT) {  // Algorithm 1's access counts and the LRU order of Algorithm 2
         if (c->cfg.rerank_interval && c->n_loads && (c->n_loads % c->cfg.rerank_interval) == 0)

@@ -6,6 +6,8 @@
 //
 //   plans_host random SEED CALLS   calls of any shape, many of more documents than one run may hold
 //   plans_host calls               one call a line on stdin; prints a line each (see run_line)
+//   plans_host pinned N            the same call of documents in HBM, and of which N lie in pinned memory, through each way to
+//                                  list them; prints for each whether it reads past the last-level cache
 #include <algorithm>
 #include <chrono>
 #include <cstdio>
@@ -305,6 +307,61 @@ void run_line(char *line)
     std::printf("%d %zu %llu %u %u %u %u\n", rc, need, (unsigned long long)(rc ? 0 : seen.end), rc ? 0 : seen.form, rc ? 0 : seen.pieces, rc ? 0 : seen.runs, rc ? 0 : seen.longest);
 }
 
+// 32 requests of ten documents of 512 tokens, two layers, n_pinned of the documents in pinned memory: in the pool's slab there,
+// by id and by address, and at addresses of the caller's, by id.
+void pinned_calls(uint32_t n_pinned)
+{
+    constexpr uint32_t kDocs = 320, kTokens = 512, kPrec = HA_RAG_PREC_FP8_E4M3;
+    for (const bool external : {false, true}) {
+        ha_rag_config cfg;
+        std::memset(&cfg, 0, sizeof cfg);
+        cfg.n_layers = 2;
+        cfg.n_kv_heads = 8;
+        cfg.head_dim = 128;
+        cfg.max_chunk_tokens = kTokens;
+        cfg.group_int8 = cfg.group_int4 = 128;
+        cfg.dry_run = 1;
+        ha_rag_ctx *ctx = nullptr;
+        if (ha_rag_create(&cfg, &ctx) != HA_RAG_OK) fail("ha_rag_create");
+        const size_t slot = 2ull * 2 * 8 * kTokens * 128;
+        const uintptr_t hbm = 0x750000000000ull, pinned = 0x740000000000ull;
+        if (ha_rag_register_slab(ctx, HA_RAG_TIER_HBM, kPrec, (void *)hbm, slot * kDocs) != HA_RAG_OK) fail("the HBM slab");
+        if (external ? ha_rag_register_external(ctx, kPrec) : ha_rag_register_slab(ctx, HA_RAG_TIER_PINNED, kPrec, (void *)pinned, slot * kDocs))
+            fail("the pinned slab");
+        Call c;
+        c.H = 8;
+        c.n_q_heads = 32;
+        std::vector<uint64_t> ids;
+        for (uint32_t i = 0; i < kDocs; ++i) {
+            const bool there = i >= kDocs - n_pinned;
+            if (there && external ? ha_rag_pool_insert_external(ctx, i, HA_RAG_PART_KV, kPrec, kTokens, (const void *)(pinned + slot * i))
+                                  : ha_rag_pool_insert(ctx, i, kPrec, kTokens, nullptr, 0, there ? HA_RAG_TIER_PINNED : HA_RAG_TIER_HBM, nullptr))
+                fail("a chunk of the pool");
+            void *at = nullptr;
+            size_t bytes = 0;
+            if (ha_rag_pool_slot(ctx, i, there ? HA_RAG_TIER_PINNED : HA_RAG_TIER_HBM, &at, &bytes) != HA_RAG_OK) fail("a chunk's place");
+            if (i % 10u == 0) c.request(1);
+            c.documents(kTokens, 1, kPrec);
+            c.chunks.back().packed = at;
+            ids.push_back(i);
+        }
+        const uint32_t n = (uint32_t)c.reqs.size();
+        size_t need = 0;
+        if (ha_rag_attend_workspace_bytes(ctx, c.chunks.data(), c.reqs.data(), n, c.n_q_heads, &need) != HA_RAG_OK) fail("the size of a well-formed call");
+        for (const bool by_id : {true, false}) {
+            seen = Seen();
+            seen.ws = kWorkspace;
+            seen.blocks.assign(n, 0);
+            if (by_id ? ha_rag_attend_chunks(ctx, ids.data(), c.reqs.data(), n, 0, c.n_q_heads, 0.1f, 0, (void *)kWorkspace, need, nullptr)
+                      : ha_rag_attend_packed(ctx, c.chunks.data(), c.reqs.data(), n, 0, c.n_q_heads, 0.1f, (void *)kWorkspace, need, nullptr))
+                fail("a well-formed call");
+            if (by_id || !external) std::printf("%d ", (int)seen.past);
+        }
+        ha_rag_destroy(ctx);
+    }
+    std::printf("\n");
+}
+
 }  // namespace
 
 int main(int argc, char **argv)
@@ -333,5 +390,9 @@ int main(int argc, char **argv)
         while (std::fgets(line.data(), (int)line.size(), stdin)) run_line(line.data());
         return 0;
     }
-    fail("usage: plans_host random SEED CALLS | plans_host calls");
+    if (argc == 3 && !std::strcmp(argv[1], "pinned")) {
+        for (const int n : {0, std::atoi(argv[2])}) pinned_calls((uint32_t)n);
+        return 0;
+    }
+    fail("usage: plans_host random SEED CALLS | plans_host calls | plans_host pinned N");
 }

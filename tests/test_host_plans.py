@@ -297,3 +297,8 @@ def test_gpu_tests_of_loads_past_the_cache_take_the_builds_that_they_name(plans_
         (rc, past, pieces), (rc1, past1, _) = calls(plans_host, ["past %d %d %d %d" % (n, 1 << 24, H, H) + text for n in (gpu.PAST_LAYERS, 1)])
         assert rc == rc1 == OK and past and not past1
         assert (pieces > 8192 // 72) == many  # the structure of few holds 113 runs
+
+
+def test_documents_in_pinned_host_memory_are_read_with_ordinary_loads(plans_host):
+    """In the pool's slab by id and by address, at addresses of the caller's by id; none of them there first."""
+    assert run(plans_host, ["pinned", "1"]).split() == ["1", "1", "1", "0", "0", "0"]
