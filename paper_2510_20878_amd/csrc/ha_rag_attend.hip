@@ -729,6 +729,44 @@ int plan_attend(ha_rag_ctx *c, const ha_rag_packed_chunk *chunks, const ha_rag_a
 }
 
 
+// How many of a call's documents were listed before, of those looked at: all, or if they are more than kMost a part
+// that is chosen by where their keys lie, so that a document is looked at each time that it is listed or never.
+struct RepeatedDocs {
+    uint32_t looked = 0, repeated = 0;
+};
+RepeatedDocs repeated_docs(const Plan *plans, uint32_t n_reqs, const Doc *docs)
+{
+    constexpr uint32_t kMost = 1024, kPlaces = 2 * kMost;
+    const uint8_t *place[kPlaces] = {};
+    auto mixed = [](const uint8_t *at) {  // the finaliser of splitmix64: addresses come evenly spaced
+        uint64_t x = (uint64_t)(uintptr_t)at;
+        x = (x ^ x >> 30) * 0xBF58476D1CE4E5B9ull;
+        x = (x ^ x >> 27) * 0x94D049BB133111EBull;
+        return x ^ x >> 31;
+    };
+    uint32_t all = 0, shift = 0;
+    for (uint32_t r = 0; r < n_reqs; ++r)
+        if (!plans[r].shared) all += plans[r].n_docs;
+    while (all >> shift > kMost) ++shift;
+    RepeatedDocs n;
+    for (uint32_t r = 0; r < n_reqs; ++r) {
+        if (plans[r].shared) continue;
+        const Doc *d = docs + plans[r].first_doc;
+        for (uint32_t i = 0; i < plans[r].n_docs; ++i) {
+            const uint64_t x = mixed(d[i].k);
+            if (x & ((1u << shift) - 1u)) continue;
+            uint32_t at = (uint32_t)(x >> 32) % kPlaces;
+            while (place[at] && place[at] != d[i].k) at = (at + 1u) % kPlaces;
+            if (place[at]) ++n.repeated;
+            else if (n.looked - n.repeated == kPlaces - kMost / 2u) return n;  // more than expected; a place stays empty
+            else place[at] = d[i].k;
+            ++n.looked;
+        }
+    }
+    if (!n.looked) n.looked = 1;
+    return n;
+}
+
 // Whether k6_attend_partial reads its documents past the last-level cache, with nontemporal loads.  A layer's bytes are asked
 // for again by the next query token, after those of all other layers, so what counts is their sum over the layers: up to the
 // cache's size they come out of it, from a quarter more on they do not.  Beyond that it is the work that decides: short
@@ -747,8 +785,11 @@ int plan_attend(ha_rag_ctx *c, const ha_rag_packed_chunk *chunks, const ha_rag_a
 // a request: 32 requests in 20 / 30 / 50 % of 16, 8 and 4 bits, two layers (655 MB) 151 / 141; 12 of them, four layers (507 MB) 153 /
 // 166; FP8, 20 requests, two layers (419 MB) 98 / 93; 16 bits, 10 requests, two layers (419 MB) 101 / 118.  By this rule 1.4 % of
 // the calls take more than 2 % longer than with ordinary loads: 4-bit ones of eight layers, up to 7 %.
-// Documents that several requests of the call list come out of the cache for the second of them: with more than a
-// quarter such, of the first kLooked, the loads stay as they are.
+// Documents that several requests of the call list come out of the cache for the second of them.  They count once, and where
+// they are many ordinary loads are faster: 32 or 48 requests of 10 x 512 tokens, 503 to 1,342 MB, of which this share was listed
+// before (nearby, or after all others), ratio as above: FP8 and GSE-8, a tenth 0.90 to 0.95, a quarter 0.94 to 0.99, a
+// third 0.96 to 1.02, half 1.00 to 1.07; with a fifth of the documents in 16 bits, a twentieth 0.95 to 0.98, a tenth 0.96 to 0.99, a
+// fifth 0.96 to 1.02, a quarter 0.96 to 1.04.
 // Documents in pinned host memory come over the link and slow a call that has any of them down to its pace; nontemporal
 // loads fetch them in smaller pieces: ten requests of 10 x 512 tokens, two layers, 16 bits 6,274 / 8,729 us, five of eight
 // layers, FP8, 6,347 / 6,753.  Hence ordinary loads for such calls.  in_host: the caller knows of one; those listed by address are
@@ -766,7 +807,8 @@ bool read_past_cache(const ha_rag_ctx *c, const Plan *plans, uint32_t n_reqs, co
         wide += pl.wide_blocks;
         n_runs += pl.n_runs;
     }
-    if (bytes * c->cfg.n_kv_heads <= kLastLevelBytes / 4u * 5u / c->cfg.n_layers) return false;
+    auto large = [&](uint64_t n) { return n * c->cfg.n_kv_heads > kLastLevelBytes / 4u * 5u / c->cfg.n_layers; };
+    if (!large(bytes)) return false;
     if (wide && blocks < n_runs * kPastWideRunBlocks) return false;
     for (const Slab &sl : c->slab[HA_RAG_TIER_PINNED]) {
         if (!sl.holds_copies()) continue;
@@ -778,21 +820,9 @@ bool read_past_cache(const ha_rag_ctx *c, const Plan *plans, uint32_t n_reqs, co
                 if ((uintptr_t)d[i].k - base < size || (uintptr_t)d[i].v - base < size) return false;
         }
     }
-    constexpr uint32_t kLooked = 1024, kBits = 8 * kLooked;
-    uint64_t seen[kBits / 64] = {};  // documents by a hash of where their keys lie
-    uint32_t n = 0, repeated = 0;
-    for (uint32_t r = 0; r < n_reqs && n < kLooked; ++r) {
-        if (plans[r].shared) continue;
-        const Doc *d = docs + plans[r].first_doc;
-        for (uint32_t i = 0; i < plans[r].n_docs && n < kLooked; ++i, ++n) {
-            const uint32_t bit = (uint32_t)(((uint64_t)(uintptr_t)d[i].k >> 4) * 0x9E3779B97F4A7C15ull >> 51);
-            static_assert(kBits == 1u << 13, "what the shift leaves");
-            uint64_t &word = seen[bit >> 6];
-            repeated += (uint32_t)(word >> (bit & 63u) & 1u);
-            word |= 1ull << (bit & 63u);
-        }
-    }
-    return repeated * 4u <= n;
+    const RepeatedDocs again = repeated_docs(plans, n_reqs, docs);
+    if (again.repeated * (wide ? 8u : 4u) > again.looked) return false;
+    return large(bytes - bytes / again.looked * again.repeated);
 }
 
 // Storage of one call's plan.  The ordinary entry points size it for the call on the heap; the

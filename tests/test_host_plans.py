@@ -302,3 +302,22 @@ def test_gpu_tests_of_loads_past_the_cache_take_the_builds_that_they_name(plans_
 def test_documents_in_pinned_host_memory_are_read_with_ordinary_loads(plans_host):
     """In the pool's slab by id and by address, at addresses of the caller's by id; none of them there first."""
     assert run(plans_host, ["pinned", "1"]).split() == ["1", "1", "1", "0", "0", "0"]
+
+
+@pytest.mark.parametrize("shape,apart", [((2, 32, 10, 657, [BF16]), 5505024), ((1, 32, 32, 433, [BF16]), 1835008), ((2, 64, 32, 128, [E4M3]), 1 << 20),
+                                         ((2, 64, 64, 64, [E4M3]), 4096)])
+def test_documents_at_even_distances_are_not_taken_for_repeated_ones(plans_host, shape, apart):
+    assert reads_past(plans_host, *shape, apart=apart)
+
+
+@pytest.mark.parametrize("shape,back,past", [
+    ((2, 32, 10, 512, [E4M3]), (8, 8), True),      # a quarter listed before: 114 us with ordinary loads, 109 with nontemporal ones
+    ((2, 32, 10, 512, [E4M3]), (8, 24), True),     # after all others: 128 / 123
+    ((2, 32, 10, 512, [E4M3]), (16, 16), False),   # half: 115 / 121
+    ((2, 32, 10, 512, MIX), (4, 4), True),         # an eighth
+    ((2, 32, 10, 512, MIX), (8, 24), False),       # a quarter: 133 / 138
+    ((2, 18, 10, 512, [E4M3]), (4, 14), False),    # 377 MB listed, 293 MB of documents
+    ((2, 64, 32, 128, [E4M3]), (32, 32), False),   # 2,048 documents, the second half as the first
+    ((1, 128, 32, 128, [E4M3]), (16, 112), True)]) # 4,096, an eighth listed before
+def test_repeated_documents_count_once(plans_host, shape, back, past):
+    assert reads_past(plans_host, *shape, back=back) == past
