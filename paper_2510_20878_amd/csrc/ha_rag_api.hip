@@ -17,29 +17,47 @@ thread_local std::string g_create_err;
 
 namespace ha_rag {
 
-// Where the launch has more workgroups than the chip holds at once (two of 16 waves on a compute unit), a tile of a chunk
-// much shorter than the longest takes only the waves it has blocks for (at most what a wave holds each), and further tiles
-// of the chunk take the workgroup's others.  A tile that would leave less than half of them keeps all, and so does every tile of a
-// launch that leaves places free: its blocks then go round more waves.  share: tiles of a workgroup, waves of a tile, and
+// Where the launch has more workgroups than the chip holds at once (its places: 32 waves a compute unit, 16 where a wave
+// holds four blocks and registers leave room for no more), a tile of a chunk much shorter than the longest takes only the waves it has
+// blocks for (at most what a wave holds each), and further tiles of the chunk take the workgroup's others.  Otherwise it
+// keeps them all: its blocks then go round more waves.
+//   per workgroup: as many tiles as have their waves there, at least two;
+//   up to kFilled blocks in all.  Five of 19 blocks in one (a class of 1,024 and three times 300 tokens) brought 75.7 to 81;
+//   n_tiles / kEngines, so that every row of the grid still has a workgroup for each of the 32 shader engines: the row's
+//     first ones take its tiles, and the chip deals workgroups out in turn.  Without this limit a class of 40 chunks of 30 tokens and one of
+//     1,024 (two layers, 32 tiles: two workgroups a row, both of them on two XCDs only) took 46 us instead of 24;
+//   where a workgroup has a compute unit to itself, no more than leaves one of those that share for every place: 512 tiles of 600
+//     tokens and 512 of 40, 16 of these in one, 32.3, two in one 26.6, each alone 28.0.  (Where two share a compute unit this limit
+//     costs up to 17 %.)
+// share: tiles of a workgroup, waves of a tile, and
 // 256 / those + 1, by which wave / waves is (wave * that) >> 8 (up to 16 waves).  The workgroups that a chunk does not need
-// exit at once.  us a launch, one tile a workgroup / this: eight chunks of 16 to 250 tokens 33.7 / 25.9, twelve of 512 and 17 to 60
-// tokens 80.2 / 67.2, six of 20 to 1,024 (80 layers) 269 / 260; chunks of one length the same.  Left to find their tile by
+// exit at once.  us a launch, one tile a workgroup / this: eight chunks of 16 to 250 tokens 32.6 / 25.0, twelve of 512 and 17 to 60
+// tokens 79.8 / 66.2, six of 20 to 1,024 (80 layers) 273 / 254; 150 classes of 2 to 40 chunks of 8 to 1,024 tokens, 1 to 80
+// layers: 0.93 on average, 0.69 to 1.08, one of them above 1.02.  Left to find their tile by
 // divisions in the kernel, ten chunks of 250 and 201 tokens took 79.5 instead of 74.5, with a search among the chunks 83:
 // what comes before a tile's loads is not hidden by anything.
 void share_gse8_tiles(K2Params &p)
 {
+    constexpr uint32_t kFilled = 32, kEngines = 32;
     auto blocks_of = [&](uint32_t i) { return (uint32_t)(((uint64_t)p.c[i].n_tokens * p.head_dim + 2047u) / 2048u); };
     uint32_t max_blk = 1;
     for (uint32_t i = 0; i < p.n_chunks; ++i) max_blk = std::max(max_blk, blocks_of(i));
     const uint32_t wg = gse8_wg_waves(max_blk), held = gse8_held(max_blk);
-    const bool full = (uint64_t)p.n_tiles * p.n_chunks > 2u * kChipCUs;
+    const uint32_t places = kChipCUs * (held == 4u ? 1u : 32u / wg);
+    const bool full = (uint64_t)p.n_tiles * p.n_chunks > places;
+    uint64_t sharing = 0;  // tiles
     for (uint32_t i = 0; i < p.n_chunks; ++i) {
         uint32_t per_wg = 1;
         if (full && held) {
-            const uint32_t waves = (blocks_of(i) + held - 1u) / held;
-            if (waves * 2u <= wg) per_wg = wg / waves;
+            const uint32_t blocks = std::max(blocks_of(i), 1u), waves = (blocks + held - 1u) / held;
+            if (waves * 2u <= wg) per_wg = std::max(1u, std::min({wg / waves, kFilled / blocks, p.n_tiles / kEngines}));
         }
-        const uint32_t n_waves = wg / per_wg;
+        p.c[i].share = per_wg;
+        if (per_wg > 1u) sharing += p.n_tiles;
+    }
+    const uint32_t most = held == 4u ? (uint32_t)std::min<uint64_t>(16u, std::max<uint64_t>(1u, sharing / places)) : 16u;
+    for (uint32_t i = 0; i < p.n_chunks; ++i) {
+        const uint32_t per_wg = std::min(p.c[i].share, most), n_waves = wg / per_wg;
         p.c[i].share = per_wg | n_waves << 8 | (256u / n_waves + 1u) << 16;
     }
 }

@@ -6,6 +6,7 @@
 //
 //   plans_host random SEED CALLS   calls of any shape, many of more documents than one run may hold
 //   plans_host calls               one call a line on stdin; prints a line each (see run_line)
+//   plans_host share TILES TOKENS ..  tiles to a workgroup of every chunk of a GSE-8 class
 //   plans_host pinned N            the same call of documents in HBM, and of which N lie in pinned memory, through each way to
 //                                  list them; prints for each whether it reads past the last-level cache
 #include <algorithm>
@@ -362,6 +363,30 @@ void pinned_calls(uint32_t n_pinned)
     std::printf("\n");
 }
 
+void share(uint32_t n_tiles, char **tokens, uint32_t n)
+{
+    K2Params p{};
+    p.n_tiles = n_tiles;
+    p.head_dim = 128;
+    if (n > kMaxK2Chunks) fail("chunks");
+    uint32_t max_blk = 1;
+    for (uint32_t i = 0; i < n; ++i) {
+        p.c[p.n_chunks++].n_tokens = (uint32_t)std::atoi(tokens[i]);
+        max_blk = std::max(max_blk, (p.c[i].n_tokens + 15u) / 16u);
+    }
+    share_gse8_tiles(p);
+    const uint32_t wg = gse8_wg_waves(max_blk), held = gse8_held(max_blk);
+    for (uint32_t i = 0; i < n; ++i) {
+        const uint32_t per_wg = p.c[i].share & 0xFFu, waves = (p.c[i].share >> 8) & 0xFFu, mul = p.c[i].share >> 16;
+        if (!per_wg || !waves || per_wg * waves > wg) fail("waves that a workgroup does not have");
+        if (held && held * waves < (p.c[i].n_tokens + 15u) / 16u) fail("a tile's waves do not hold its blocks");
+        for (uint32_t w = 0; w < wg; ++w)
+            if ((w * mul) >> 8 != w / waves) fail("a wave's tile");
+        std::printf("%u ", per_wg);
+    }
+    std::printf("\n");
+}
+
 }  // namespace
 
 int main(int argc, char **argv)
@@ -390,9 +415,13 @@ int main(int argc, char **argv)
         while (std::fgets(line.data(), (int)line.size(), stdin)) run_line(line.data());
         return 0;
     }
+    if (argc > 3 && !std::strcmp(argv[1], "share")) {
+        share((uint32_t)std::atoi(argv[2]), argv + 3, (uint32_t)argc - 3u);
+        return 0;
+    }
     if (argc == 3 && !std::strcmp(argv[1], "pinned")) {
         for (const int n : {0, std::atoi(argv[2])}) pinned_calls((uint32_t)n);
         return 0;
     }
-    fail("usage: plans_host random SEED CALLS | plans_host calls | plans_host pinned N");
+    fail("usage: plans_host random SEED CALLS | plans_host calls | plans_host pinned N | plans_host share TILES TOKENS ..");
 }

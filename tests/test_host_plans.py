@@ -321,3 +321,30 @@ def test_documents_at_even_distances_are_not_taken_for_repeated_ones(plans_host,
     ((1, 128, 32, 128, [E4M3]), (16, 112), True)]) # 4,096, an eighth listed before
 def test_repeated_documents_count_once(plans_host, shape, back, past):
     assert reads_past(plans_host, *shape, back=back) == past
+
+
+# ---- tiles of short GSE-8 chunks that share workgroups -------------------------------------------------------
+
+
+@pytest.mark.parametrize("n_tiles,tokens,per_wg", [
+    (32, [30] * 40 + [1024], [1] * 41),                     # 24 us; 16 in one, on two XCDs, 46
+    (32, [300] * 20 + [40] * 20, [1] * 40),                 # 19 / 25
+    (512, [600, 40], [1, 2]),                               # 28.0 alone, 26.6, 32.3 with 16 in one
+    (256, [16, 44, 64, 1024], [3, 3, 3, 1]),                # 25.8 alone, 23.5, 29.2 with 16
+    (512, [1024, 300, 300, 300], [1] * 4),                  # 75.7, 81 with three
+    (512, [16, 16, 16, 16, 512], [16] * 4 + [1]),           # 29.8 alone, 24.7
+    (128, [16] * 12 + [1024], [4] * 12 + [1]),              # 27 alone, 19.8
+    (128, [33, 17, 60, 512], [1] * 4),                      # as many as there are places
+    (512, [64, 20], [1, 1]),                                # workgroups of four waves, eight to a compute unit
+    (512, [64, 20] * 3, [1, 2] * 3),
+    (512, [2000] + [100] * 6, [1] * 7)])                    # tiles that are read twice
+def test_tiles_share_workgroups_where_that_is_faster(plans_host, n_tiles, tokens, per_wg):
+    assert [int(x) for x in run(plans_host, ["share", str(n_tiles), *map(str, tokens)]).split()] == per_wg
+
+
+def test_shared_workgroups_have_the_waves_that_their_tiles_need(plans_host):
+    import random
+    rnd = random.Random(3)
+    for _ in range(60):
+        tokens = [max(1, int(2 ** rnd.uniform(0, rnd.choice([4, 8, 10, 11])))) for _ in range(rnd.randint(1, 128))]
+        run(plans_host, ["share", str(rnd.choice([2, 8, 33, 64, 264, 1280])), *map(str, tokens)])
