@@ -43,6 +43,7 @@ struct Seen {
     uint32_t form = 0, pieces = 0, runs = 0, longest = 0;
     uint64_t end = 0;                    // of the last record
     bool quiet = false;                  // only timed
+    uint32_t doc_end = 0;                // of the launch with the most descriptors
     bool past = false;                   // k6_attend_partial reads past the last-level cache
 } seen;
 
@@ -81,6 +82,7 @@ hipError_t launch_k6(K6Params &p, hipStream_t, bool)
     if (seen.quiet) return hipSuccess;
     seen.pieces += p.n_runs;
     seen.past = p.past;
+    seen.doc_end = std::max(seen.doc_end, p.doc_end);
     for (uint32_t i = 0; i < p.n_runs; ++i) take_run(p, i, false);
     return hipSuccess;
 }
@@ -92,6 +94,7 @@ hipError_t launch_k6_shared(K6Params &p, SharedForm form, hipStream_t, bool)
     if (seen.form && seen.form != id) fail("two forms of the shared kernel in one call");
     seen.form = id;
     seen.runs += p.n_runs;
+    seen.doc_end = std::max(seen.doc_end, p.doc_end);
     for (uint32_t i = 0; i < p.n_runs; ++i) take_run(p, i, true);
     return hipSuccess;
 }
@@ -250,10 +253,11 @@ void random_call(Call &c)
     }
 }
 
-// One call: "static|workspace|time N|past LAYERS APART HEADS QUERY_HEADS" then per request "/ n_q tokens*count*format*back*part ..."
+// One call: "static|workspace|ends|time N|past LAYERS APART HEADS QUERY_HEADS" then per request "/ n_q tokens*count*format*back*part ..."
 // (APART: bytes between chunks; back: see documents()).  Prints the return
 // code, the workspace asked for, the end of the last record, the shared kernel's form (0: not
-// launched), pieces and runs launched and the blocks of the longest; or the us of a call; or whether it reads past the cache, and the pieces launched.
+// launched), pieces and runs launched and the blocks of the longest; or the us of a call; or whether it reads past the cache, and the pieces
+// launched; or the end of the descriptors of the launch that has the most.
 void run_line(char *line)
 {
     Call c = Call();
@@ -301,6 +305,10 @@ void run_line(char *line)
         return;
     }
     if (rc == HA_RAG_OK) rc = attend(c, how == "static", how == "static" ? HA_RAG_ATTEND_STATIC_SCRATCH_BYTES : need);
+    if (how == "ends") {
+        std::printf("%d %u\n", rc, seen.doc_end);
+        return;
+    }
     if (how == "past") {
         std::printf("%d %d %u\n", rc, (int)seen.past, seen.pieces);
         return;

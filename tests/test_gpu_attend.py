@@ -323,6 +323,20 @@ def test_launches_at_the_edge_of_few_descriptors(n_docs, n_q):
     run_case((1, 1, 128), [([16] * n_docs, [tags[i % 3] for i in range(n_docs)], n_q)], 0, 8, 0.09, 5000 + n_docs)
 
 
+# Documents of one and two blocks; a run takes the room of three short descriptors, and one for each further document.
+EDGE_DOCUMENTS = {340: [16] * 272, 341: [32] * 8 + [16] * 268, 342: [32] * 8 + [16] * 269, 343: [16] * 273}
+
+
+@pytest.mark.parametrize("end", sorted(EDGE_DOCUMENTS))
+@pytest.mark.parametrize("n_q", [12, 80])
+def test_shared_launches_at_the_edge_of_few_descriptors(n_q, end):
+    """The structure of few holds 341 descriptors of further documents: launches that end just before, at and behind it (that
+    they do is checked where launches are seen on the host)."""
+    tags = [B.PREC_INT4, B.PREC_16, B.PREC_GSE8]
+    tokens = EDGE_DOCUMENTS[end]
+    run_case((1, 1, 128), [(tokens, [tags[i % 3] for i in range(len(tokens))], n_q)], 0, 8, 0.09, 5400 + end)
+
+
 def test_requests_of_two_tiles_go_with_those_of_three_and_four():
     """A call with requests of three or four query tiles takes its requests of two tiles to the same
     kernel (runs across documents), those of one tile stay with the other."""

@@ -373,6 +373,22 @@ def test_fp8_decode_every_code(prec):
     ctx.destroy()
 
 
+@pytest.mark.parametrize("prec", [B.PREC_FP8_E4M3, B.PREC_FP8_E5M2])
+def test_fp8_decode_of_codes_that_the_quantizer_never_writes(prec):
+    """Infinities stay infinities, and every NaN code gives the one word that the conversion makes of it."""
+    words = {0x7F: 0xFFC0, 0xFF: 0xFFC0} if prec == B.PREC_FP8_E4M3 else \
+        {0x7C: 0x7F80, 0xFC: 0xFF80, **{s | c: 0xFFC0 for s in (0, 0x80) for c in (0x7D, 0x7E, 0x7F)}}
+    L, H, D, T = 1, 1, 128, 16                                           # one block per tile
+    ctx = B.Context(L, H, D, T)
+    for code, word in words.items():
+        packed = torch.full((ctx.chunk_bytes(prec, T),), code, dtype=torch.uint8, device="cuda")
+        out = torch.zeros((L, 2, H, T, D), dtype=torch.int16, device="cuda")
+        ctx.load_packed([(packed, T, prec, 0)], out, T)
+        torch.cuda.synchronize()
+        assert np.all(host_u16(out) == word), hex(code)
+    ctx.destroy()
+
+
 # ---- GSE-8 (the paper's scheme S4) -------------------------------------------------------
 def _gse_roundtrip(src, T):
     L, _, H, _, D = src.shape

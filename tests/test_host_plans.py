@@ -348,3 +348,11 @@ def test_shared_workgroups_have_the_waves_that_their_tiles_need(plans_host):
     for _ in range(60):
         tokens = [max(1, int(2 ** rnd.uniform(0, rnd.choice([4, 8, 10, 11])))) for _ in range(rnd.randint(1, 128))]
         run(plans_host, ["share", str(rnd.choice([2, 8, 33, 64, 264, 1280])), *map(str, tokens)])
+
+
+@pytest.mark.parametrize("n_q", [12, 80])
+def test_gpu_tests_at_the_edge_of_few_descriptors_end_where_they_say(plans_host, n_q):
+    import test_gpu_attend as gpu
+    lines = ["ends 1 8 / %d" % n_q + "".join(" %d*1*%d" % (t, (INT4, BF16, GSE8)[i % 3]) for i, t in enumerate(tokens))
+             for tokens in gpu.EDGE_DOCUMENTS.values()]
+    assert calls(plans_host, lines) == [[OK, end] for end in gpu.EDGE_DOCUMENTS]
