@@ -838,11 +838,18 @@ __global__ void __launch_bounds__(64 * W, 2) k6_attend_shared(const P p)
 // straight into operands 4 %; the reference lifted above the maximum 3 %; loads issued in the order they are
 // decoded in (before, the compiler waited for all of them at the top of the loop) 2 %.
 // The tile groups of a head read the same blocks.  Numbered one after the other they are dealt to the eight XCDs, each
-// of which fetches the blocks into an L2 of its own; with the heads first (heads_first; 8 KV heads) they meet in one L2.  us for
-// two layers, without / with: two requests of 16 x 1,024 tokens in 16 bits, 256 query tokens, 64 query heads 550 / 516; eight of
-// 10 x 512 and 200 at 90 to 256 486 / 454; three of 16 documents of up to 1,024 at 96 to 201 418 / 404; eight of 4 x 512 at 100
-// 147 / 142.  Short runs lose by it, whose groups all wait for the same lines at their start: one of 10 x 512 at 200 (80 blocks
-// a run) 103.6 / 107.9, two of 4 x 512 at 100 (32 blocks) 66.5 / 72.3; 114 blocks a run 128.5 / 122.8.  Hence kHeadsFirstBlocks.  Scoring with 32x32x16
+// of which fetches the blocks into an L2 of its own, and the last group of a head, which has fewer tiles, falls on the same XCDs
+// each time.  With the heads first (heads_first) the groups of a head meet in one L2 if there are eight heads, and the
+// shorter groups are spread.  us for two layers, without / with, 8 KV heads: two requests of 16 x 1,024 tokens in 16 bits, 256 query
+// tokens, 64 query heads 550 / 516; eight of 10 x 512 and 200 at 90 to 256 486 / 454; three of 16 documents of up to 1,024 at 96 to
+// 201 418 / 404; eight of 4 x 512 at 100 147 / 142.  By KV heads, calls of requests of one kind in runs of 96 blocks and more, mean
+// (least to most) of the ratio: 2 1.00 (0.98-1.02), 3 0.96 (0.94-0.99), 4 0.98 (0.96-1.01), 5 0.97 (0.94-1.01), 6 0.99 (0.96-1.01),
+// 7 0.98 (0.93-1.01), 8 0.95 (0.91-0.99), 10 0.97 (0.95-0.99), 12 0.98 (0.94-1.00), 16 0.96 (0.91-0.99).  Calls of shorter runs only may
+// lose by it, whose groups all wait for the same lines at their start: 16 to 40 blocks a run 0.92 to 1.11.  Next to longer runs
+// shorter ones gain too, so it is the call's longest run that decides: four requests of 1,790 tokens at 100 and 30 of 2 x 512 at 200
+// 367 / 341 (366 with the long ones alone ordered so); 170 random calls of long and short runs 0.98 (0.85-1.05; above 1.02 with two
+// and four heads only).
+// Scoring with 32x32x16
 // MFMAs took 6 % fewer clocks at a clock 5 % lower, 186.5 -> 189.5 us, as at a power limit.
 template <int S, class P>
 __global__ void __launch_bounds__(64 * (S + kRoleDecoders), (S + kRoleDecoders) / 4) k6_attend_roles(const P p)

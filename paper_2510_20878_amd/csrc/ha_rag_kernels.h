@@ -120,7 +120,7 @@ constexpr uint32_t kAttendMinRunBlocks = 8;    // a workgroup takes at least thi
                                                // half as many in a call of very few workgroups),
 constexpr uint32_t kAttendMaxRunBlocks = 128;  // and a piece of one document is at most this long (a power of two)
 constexpr uint32_t kAttendTargetGroups = 2048; // pieces are halved while a launch has fewer workgroups
-constexpr uint32_t kHeadsFirstBlocks = 96;    // runs from this length on have their workgroups ordered by heads (k6_attend_roles)
+constexpr uint32_t kHeadsFirstBlocks = 96;    // calls whose longest run has so many blocks have their workgroups ordered by heads (k6_attend_roles)
 constexpr uint32_t kAttendFewDocs = 32;       // run lengths of the shared kernel: the longest run is looked for in a request of at most this many documents
 constexpr uint32_t kChipCUs = 256;            // compute units of the one GPU this library is built for
 constexpr uint64_t kLastLevelBytes = 256ull << 20;  // its last-level cache
@@ -165,8 +165,9 @@ struct K6Run {
 };
 
 // BYTES: room for descriptors.  A launch of few has a structure of few, since writing the arguments is part of what a
-// launch costs the host, and calls of few documents are bound by that: with 8 instead of 36 KiB at one query token, us a pass, one
-// request of 10 x 512 tokens, 32 layers 392 -> 369, two of them 458 -> 425; one of two of 128, four layers 42.6 -> 39.6.
+// launch costs the host, and calls of few documents are bound by that.  us a pass with 36 / 8 KiB: at one query token, one
+// request of 10 x 512 tokens, 32 layers 379 / 364, two of them 458 / 431; one of two of 128, four layers 40 / 37; in the
+// shared kernels, 32 layers, one request of 2 x 128 at 12 query tokens 357 / 330, of 64 at 40 350 / 306, of 10 x 512 at 32 706 / 705.
 template <uint32_t BYTES>
 struct K6ParamsOf {
     static constexpr uint32_t kMaxRuns = BYTES / sizeof(K6Run), kMaxDocs = BYTES / sizeof(K6Doc);
