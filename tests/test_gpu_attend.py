@@ -721,8 +721,9 @@ def test_every_pair_of_formats_as_documents_of_one_request(with_16_bit):
 
 @pytest.mark.parametrize("with_16_bit", [True, False])
 def test_documents_that_the_last_level_cache_does_not_hold(with_16_bit):
-    """A call whose documents take more than 400 MiB over all layers reads them with other loads
-    (read_past_cache): the same bytes, so the same results, to the bit, as through a context of one layer."""
+    """A call whose documents take more than 400 MiB over all layers, of one to three blocks each: without 16-bit sides it
+    reads them with other loads (read_past_cache), with them as ever.  The same bytes, so the same results, to the bit, as
+    through a context of one layer."""
     L, H, D, g, n_qh, scale = 3000, 1, 128, 64, 4, 0.1
     ORC = [16, 8, 4, 43, 52, 143]
     precs = range(6) if with_16_bit else range(1, 6)
