@@ -3,6 +3,7 @@
 // requests).
 #include "ha_rag_internal.h"
 
+#include <algorithm>
 #include <cstdio>
 #include <memory>
 #include <type_traits>
@@ -736,8 +737,8 @@ struct RepeatedDocs {
 };
 RepeatedDocs repeated_docs(const Plan *plans, uint32_t n_reqs, const Doc *docs)
 {
-    constexpr uint32_t kMost = 1024, kPlaces = 2 * kMost;
-    const uint8_t *place[kPlaces] = {};
+    constexpr uint32_t kMost = 1024;
+    const uint8_t *place[2 * kMost];  // a call of few documents clears and uses few
     auto mixed = [](const uint8_t *at) {  // the finaliser of splitmix64: addresses come evenly spaced
         uint64_t x = (uint64_t)(uintptr_t)at;
         x = (x ^ x >> 30) * 0xBF58476D1CE4E5B9ull;
@@ -748,6 +749,9 @@ RepeatedDocs repeated_docs(const Plan *plans, uint32_t n_reqs, const Doc *docs)
     for (uint32_t r = 0; r < n_reqs; ++r)
         if (!plans[r].shared) all += plans[r].n_docs;
     while (all >> shift > kMost) ++shift;
+    uint32_t places = 16;
+    while (places < 2u * (all >> shift)) places *= 2u;
+    std::fill_n(place, places, nullptr);
     RepeatedDocs n;
     for (uint32_t r = 0; r < n_reqs; ++r) {
         if (plans[r].shared) continue;
@@ -755,10 +759,10 @@ RepeatedDocs repeated_docs(const Plan *plans, uint32_t n_reqs, const Doc *docs)
         for (uint32_t i = 0; i < plans[r].n_docs; ++i) {
             const uint64_t x = mixed(d[i].k);
             if (x & ((1u << shift) - 1u)) continue;
-            uint32_t at = (uint32_t)(x >> 32) % kPlaces;
-            while (place[at] && place[at] != d[i].k) at = (at + 1u) % kPlaces;
+            uint32_t at = (uint32_t)(x >> 32) & (places - 1u);
+            while (place[at] && place[at] != d[i].k) at = (at + 1u) & (places - 1u);
             if (place[at]) ++n.repeated;
-            else if (n.looked - n.repeated == kPlaces - kMost / 2u) return n;  // more than expected; a place stays empty
+            else if (n.looked - n.repeated == places / 4u * 3u) return n;  // more than expected; places stay empty
             else place[at] = d[i].k;
             ++n.looked;
         }
@@ -769,7 +773,7 @@ RepeatedDocs repeated_docs(const Plan *plans, uint32_t n_reqs, const Doc *docs)
 
 // Whether k6_attend_partial reads its documents past the last-level cache, with nontemporal loads.  A layer's bytes are asked
 // for again by the next query token, after those of all other layers, so what counts is their sum over the layers: up to the
-// cache's size they come out of it, from a quarter more on they do not.  Beyond that it is the work that decides: short
+// cache's size they come out of it, from a fifth more on they do not.  Beyond that it is the work that decides: short
 // runs wait for their first loads, which take longer this way, and 16-bit blocks, four times the bytes of 4-bit ones, still find
 // some of them in the cache.  Nontemporal loads / ordinary ones, means of the ratio of a pass at one query token, 4,400 random
 // calls of 1 to 32 layers (up to 1,000 MB, 2 to 16 KV heads, 128 to 2,000 tokens a document), by the MB of all layers:
@@ -781,10 +785,13 @@ RepeatedDocs repeated_docs(const Plan *plans, uint32_t n_reqs, const Doc *docs)
 //   all in 16 bits, 7 to 9                      1.28     1.24     1.18     1.17     1.15     1.12     1.07     1.10
 //   all in 16 bits, 18 to 40                       -        -        -        -     0.97        -     0.97     0.98
 // (13 to 18 blocks, partly or all in 16 bits: 0.98 to 1.05.)  With the cache full of other data, as behind the
-// weights of a layer, the same: 0.99, 0.95, 1.03, 0.96, 1.11 and 0.98.  us a pass, ordinary / nontemporal, 10 x 512 tokens
-// a request: 32 requests in 20 / 30 / 50 % of 16, 8 and 4 bits, two layers (655 MB) 151 / 141; 12 of them, four layers (507 MB) 153 /
-// 166; FP8, 20 requests, two layers (419 MB) 98 / 93; 16 bits, 10 requests, two layers (419 MB) 101 / 118.  By this rule 1.4 % of
-// the calls take more than 2 % longer than with ordinary loads: 4-bit ones of eight layers, up to 7 %.
+// weights of a layer, the same: 0.99, 0.95, 1.03, 0.96, 1.11 and 0.98.  Calls with a fifth to a half in 16 bits whose workgroups are
+// all on the chip at once (four a compute unit) are faster this way with short runs too: 0.96 to 0.99, with the cache full of
+// other data 0.97 to 1.03; all in 16 bits 1.00 to 1.06.  us a pass, ordinary / nontemporal, 10 x 512 tokens
+// a request: 32 requests in 20 / 30 / 50 % of 16, 8 and 4 bits, two layers (655 MB) 151 / 141; 12, four layers (467 MB) 142 /
+// 154; two, 32 layers (655 MB) 439 / 421, six 763 / 768; FP8, 20 requests, two layers (419 MB) 98 / 93; 16 bits, 10 requests, two
+// layers (419 MB) 101 / 118.  By this rule 1.4 % of the calls take more than 2 % longer than with ordinary loads: 4-bit ones of
+// eight layers, up to 7 %.
 // Documents that several requests of the call list come out of the cache for the second of them.  They count once, and where
 // they are many ordinary loads are faster: 32 or 48 requests of 10 x 512 tokens, 503 to 1,342 MB, of which this share was listed
 // before (nearby, or after all others), ratio as above: FP8 and GSE-8, a tenth 0.90 to 0.95, a quarter 0.94 to 0.99, a
@@ -807,9 +814,10 @@ bool read_past_cache(const ha_rag_ctx *c, const Plan *plans, uint32_t n_reqs, co
         wide += pl.wide_blocks;
         n_runs += pl.n_runs;
     }
-    auto large = [&](uint64_t n) { return n * c->cfg.n_kv_heads > kLastLevelBytes / 4u * 5u / c->cfg.n_layers; };
-    if (!large(bytes)) return false;
-    if (wide && blocks < n_runs * kPastWideRunBlocks) return false;
+    const uint64_t H = c->cfg.n_kv_heads, most = (wide ? kLastLevelBytes / 4u * 5u : kLastLevelBytes / 5u * 6u) / c->cfg.n_layers;
+    if (bytes * H <= most) return false;
+    const bool few = n_runs * H <= 4u * kChipCUs && wide * 3u <= blocks;
+    if (wide && blocks < n_runs * kPastWideRunBlocks && !few) return false;
     for (const Slab &sl : c->slab[HA_RAG_TIER_PINNED]) {
         if (!sl.holds_copies()) continue;
         const uintptr_t base = (uintptr_t)sl.base, size = (uintptr_t)sl.n_slots * sl.slot_bytes;
@@ -822,7 +830,7 @@ bool read_past_cache(const ha_rag_ctx *c, const Plan *plans, uint32_t n_reqs, co
     }
     const RepeatedDocs again = repeated_docs(plans, n_reqs, docs);
     if (again.repeated * (wide ? 8u : 4u) > again.looked) return false;
-    return large(bytes - bytes / again.looked * again.repeated);
+    return (bytes - bytes / again.looked * again.repeated) * H > most;
 }
 
 // Storage of one call's plan.  The ordinary entry points size it for the call on the heap; the

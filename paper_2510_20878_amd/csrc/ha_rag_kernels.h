@@ -124,7 +124,7 @@ constexpr uint32_t kHeadsFirstBlocks = 96;    // calls whose longest run has so 
 constexpr uint32_t kAttendFewDocs = 32;       // run lengths of the shared kernel: the longest run is looked for in a request of at most this many documents
 constexpr uint32_t kChipCUs = 256;            // compute units of the one GPU this library is built for
 constexpr uint64_t kLastLevelBytes = 256ull << 20;  // its last-level cache
-constexpr uint32_t kPastWideRunBlocks = 18;   // documents with a 16-bit side are read past it in runs of so many blocks on average
+constexpr uint32_t kPastWideRunBlocks = 18;   // calls with 16-bit sides and more workgroups than the chip holds read past it in runs of so many blocks on average
 constexpr uint32_t kAttendWaves = 2;          // waves of a workgroup; they interleave its blocks
 // Descriptors travel in the kernel argument buffer (36 KiB; launches with arguments of up to
 // 62.5 KiB were checked to work on this runtime).  A workgroup fetches its run's descriptor in one go

@@ -275,16 +275,18 @@ def reads_past(exe, *shape, **more):
     ((2, 32, 10, 512, MIX), True),         # 655 MB: 151 / 141
     ((2, 27, 10, 512, MIX), True),         # 551 MB: 130 / 122
     ((2, 23, 10, 512, MIX), False),        # 465 MB, 16 blocks: 115 / 116
-    ((1, 29, 10, 512, MIX), False),        # 297 MB in one layer: 60 / 64
-    ((4, 12, 10, 512, MIX), False),        # 491 MB, pieces of eight blocks: 142 / 154
+    ((1, 29, 10, 512, MIX), False),        # 297 MB in one layer: 60 / 64 at 302
+    ((4, 12, 10, 512, MIX), False),        # 491 MB, eight blocks, 3,840 workgroups: 142 / 154 at 467 MB
     ((1, 20, 10, 512, [BF16]), False),     # 419 MB, 16 blocks: 83 / 89
     ((2, 10, 10, 512, [BF16]), False),     # 419 MB, eight blocks: 101 / 118
     ((1, 30, 10, 512, [BF16]), True),      # 629 MB, 32 blocks: 118 / 114
-    ((2, 17, 10, 512, [E4M3]), True),      # 357 MB: 80 / 77
+    ((2, 16, 10, 512, [E4M3]), True),      # 336 MB: 80 / 77
     ((2, 15, 10, 512, [E4M3]), False),     # 315 MB
     ((8, 5, 9, 512, [GSE8]), True),        # 377 MB, pieces of eight blocks: 166 / 159
-    ((32, 1, 10, 512, MIX), False),        # one request, 327 MB
-    ((32, 2, 10, 512, MIX), False),        # two, 655 MB, four blocks: 450 / 430, within what its runs of one side differ
+    ((32, 1, 10, 512, MIX), False),        # one request, 327 MB: 369 / 358, with the cache full of other data 14.5 / 14.8 a layer
+    ((32, 2, 10, 512, MIX), True),         # two, 655 MB, eight blocks, 640 workgroups: 439 / 421
+    ((32, 6, 10, 512, MIX), False),        # 1,920 workgroups: 763 / 768
+    ((32, 2, 10, 512, [BF16]), False),     # 492 / 501
     ((32, 2, 10, 512, [INT8]), True)])     # 694 MB
 def test_documents_are_read_past_the_cache_where_that_is_faster(plans_host, shape, past):
     assert reads_past(plans_host, *shape) == past
